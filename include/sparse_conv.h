@@ -220,6 +220,8 @@ int sparse_conv_set_launch(sparse_conv_t h, const int* params, int nparams);
  * the fastest for later forwards of this (N,H,W,stride,pad).
  *   input, output, N..pad, stream   as for sparse_conv_forward (N > 0); output is
  *            overwritten with the layer's result.
+ *            Where an automatic forward would take the matrix kernel (sparse_conv_get_kernel), that is timed as
+ *            well and kept if it is the fastest; sparse_conv_get_launch then reports the fastest tile configuration.
  *   best_us  if not NULL receives the kept configuration's time per launch, in us.
  * Synchronous (it waits for its own measurements) and it allocates plan
  * buffers: call it once, outside timed or captured regions.
@@ -274,7 +276,13 @@ int sparse_conv_set_epilogue(sparse_conv_t h, const float* bias, unsigned flags)
  * when the check ran (whatever it found), else as sparse_conv_get_launch. */
 int sparse_conv_check_plan(sparse_conv_t h, int N, int H, int W, int stride, int pad, int* failed_check);
 
-/* The launch configuration chosen for a geometry: [0] V .. [4] Cc, [5] the LDS
+/* Which kernel sparse_conv_forward takes for a geometry: *kernel receives 0 for the tile kernel (always, if
+ * sparse_conv_set_launch has pinned anything), 1 for the matrix kernel, which multiplies a dense table of the weights,
+ * zeros included, on the matrix cores, and which an automatic choice takes where it is estimated (sparse_conv_autotune:
+ * measured) to be faster.  Returns as sparse_conv_get_launch.  Needs no GPU. */
+int sparse_conv_get_kernel(sparse_conv_t h, int N, int H, int W, int stride, int pad, int* kernel);
+
+/* The tile kernel's launch configuration for a geometry (in force unless sparse_conv_get_kernel says 1): [0] V .. [4] Cc, [5] the LDS
  * budget in force, [6] workgroups launched, [7] LDS bytes
  * per workgroup, [8] threads per workgroup, [9] stored plan entries
  * (including batch padding), [10] LP, [11] channel blocks, [12] kind of output store

@@ -27,7 +27,7 @@ LIB_PATH = os.environ.get("SPARSECONV_LIBRARY") or os.path.join(
 EXPORTS = (
     "sparse_conv_create", "sparse_conv_output_shape", "sparse_conv_forward", "sparse_conv_forward_static",
     "sparse_conv_get_csr", "sparse_conv_set_launch", "sparse_conv_get_launch", "sparse_conv_set_epilogue", "sparse_conv_autotune",
-    "sparse_conv_create_codebook", "sparse_conv_get_codebook", "sparse_conv_check_plan", "sparse_conv_rank_launches",
+    "sparse_conv_create_codebook", "sparse_conv_get_codebook", "sparse_conv_check_plan", "sparse_conv_rank_launches", "sparse_conv_get_kernel",
     "sparse_conv_probe_lds_read", "sparse_conv_probe_copy",
     "sparse_conv_last_hip_error", "sparse_conv_strerror", "sparse_conv_destroy",
 )
@@ -64,6 +64,7 @@ def _load():
     lib.sparse_conv_get_launch.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip]
     lib.sparse_conv_set_epilogue.argtypes = [vp, vp, C.c_uint]
     lib.sparse_conv_check_plan.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip]
+    lib.sparse_conv_get_kernel.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip]
     lib.sparse_conv_rank_launches.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip, ip]
     lib.sparse_conv_autotune.argtypes = [vp, vp, vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, vp, C.c_int,
                                          C.POINTER(C.c_float)]
@@ -211,6 +212,13 @@ def sparse_conv_rank_launches(handle: int, N: int, H: int, W: int, stride: int, 
     return [list(arr[11 * i:11 * i + 11]) for i in range(n.value)]
 
 
+def sparse_conv_get_kernel(handle: int, N: int, H: int, W: int, stride: int, pad: int) -> str:
+    """"matrix" or "tile": the kernel that sparse_conv_forward takes for the geometry."""
+    which = C.c_int(0)
+    _check(_lib.sparse_conv_get_kernel(handle, N, H, W, stride, pad, C.byref(which)), "sparse_conv_get_kernel", handle)
+    return "matrix" if which.value else "tile"
+
+
 def sparse_conv_check_plan(handle: int, N: int, H: int, W: int, stride: int, pad: int) -> int:
     """Host-side consistency check of the geometry's plan: 0, or the number of the first failed check."""
     bad = C.c_int(-1)
@@ -268,6 +276,9 @@ class SparseConv:
 
     def output_shape(self, H: int, W: int, stride: int = 1, pad: int = 0):
         return sparse_conv_output_shape(self.handle, H, W, stride, pad)
+
+    def get_kernel(self, N: int, H: int, W: int, stride: int = 1, pad: int = 0) -> str:
+        return sparse_conv_get_kernel(self.handle, N, H, W, stride, pad)
 
     def check_plan(self, N: int, H: int, W: int, stride: int = 1, pad: int = 0) -> int:
         return sparse_conv_check_plan(self.handle, N, H, W, stride, pad)

@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <atomic>
 #include <mutex>
+#include <cmath>
 #include <cstdint>
 #include <cstring>
 #include <new>
@@ -45,6 +46,80 @@ bool geometry_ok(const sparse_conv_s* h, int H, int W, int stride, int pad)
     return H + 2 * pad >= h->R && W + 2 * pad >= h->S;
 }
 
+int elem_bytes(const sparse_conv_s* h) { return h->dtype == SC_F16 ? 2 : 4; }
+
+std::atomic<unsigned long long> g_next_id{1};
+
+// Nothing about the launch is pinned.
+bool automatic(const Launch& l)
+{
+    return !(l.V || l.WP || l.WK || l.KW || l.Cc || l.lds_budget || l.LP || l.kblocks || l.store || l.lanes || l.csplit);
+}
+
+// The matrix kernel is taken where its estimate lies below this share of the tile kernel's.  Over 168 layers (see
+// estimate_matrix) binary16 loses nowhere up to 1.0; fp32, where the two kernels are closer, loses up to 16 % in three of
+// its 90 layers at 0.9 and nowhere at 0.8.
+constexpr double kMatrixMargin16 = 0.95, kMatrixMargin32 = 0.8;
+
+// The tile kernel's cheapest configuration for the geometry (the search takes most of a first call's time on the host:
+// done once).  A geometry that the tile kernel cannot plan is refused here, whichever kernel would run.
+int find_tile(sparse_conv_s* h, const Geometry& g, Route** out)
+{
+    auto it = h->routes.find(g);
+    if (it == h->routes.end()) {
+        Launch within;
+        within.pool = (h->epilogue & SC_EPILOGUE_MAXPOOL2) ? 1 : 0;
+        Plan none;
+        std::pair<double, Launch> tile;
+        const int rc = build_plan(h->csr, h->C, h->R, h->S, elem_bytes(h), g, within, none, nullptr, &tile);
+        if (rc != SC_OK) return rc;
+        Route r;
+        r.tile = tile.second;
+        r.tile_clocks = tile.first;
+        it = h->routes.emplace(g, r).first;
+    }
+    *out = &it->second;
+    return SC_OK;
+}
+
+// Which kernel an automatic forward of the geometry takes: the one that is estimated cheaper, where the matrix kernel can
+// run.  It multiplies the zeros between the stored weights as well, at 10 to 25 times the tile kernel's rate: for binary16
+// that pays at most sparsities pruning reaches, for fp32 (three binary16 products a weight) below about 85 %, and further
+// up where the tile kernel loses its lanes to padding or to a stride.
+int get_route(sparse_conv_s* h, const Geometry& g, const Route** out)
+{
+    Route* r = nullptr;
+    const int rc = find_tile(h, g, &r);
+    if (rc != SC_OK) return rc;
+    *out = r;
+    if (r->decided) return SC_OK;
+    if (h->finite_weights < 0) {   // an infinite weight would meet the zeros of every output's receptive field
+        h->finite_weights = 1;
+        for (float w : h->csr.val32)
+            if (!(std::fabs(w) <= 3.402823466e38f)) h->finite_weights = 0;
+    }
+    const bool half = h->dtype == SC_F16;
+    double us = 0.0;
+    if (h->finite_weights && choose_matrix(h->csr, h->C, h->R, h->S, elem_bytes(h), g, r->tile.pool != 0, r->tile.csplit, r->plan, &us)) {
+        // stores are not hidden behind short rows: the tile kernel's estimate leaves them out
+        const double terms = (double)h->csr.colidx.size() / h->K;
+        const double mbytes = (double)g.N * ((double)h->C * g.H * g.W + (double)h->K * r->plan.E * r->plan.F) * elem_bytes(h) * 1e-6;
+        const double tile_us = r->tile_clocks / 2400.0 + (terms < 32.0 ? 0.2 * mbytes : 0.0);
+        if (us < (half ? kMatrixMargin16 : kMatrixMargin32) * tile_us) {
+            if (!h->matrix) {
+                std::unique_ptr<MatrixWeights> m(new MatrixWeights());
+                pack_matrix_weights(h->csr, h->C, h->R, h->S, !half, *m);
+                h->matrix = std::move(m);
+                h->matrix_id = g_next_id.fetch_add(1, std::memory_order_relaxed);
+            }
+            // (both forward entry points take the same kernel: the table has to fit the static scratch)
+            r->matrix = h->matrix->bytes() + 1024 <= kStaticScratchBytes;
+        }
+    }
+    r->decided = true;
+    return SC_OK;
+}
+
 int get_plan(sparse_conv_s* h, const Geometry& g, Plan** out)
 {
     auto it = h->plans.find(g);
@@ -54,11 +129,15 @@ int get_plan(sparse_conv_s* h, const Geometry& g, Plan** out)
         // a measured choice was made within the override in force (a new override discards it)
         auto tuned = h->tuned.find(g);
         Launch use = tuned != h->tuned.end() ? tuned->second : h->over;
+        int rc = SC_OK;
+        if (tuned == h->tuned.end() && automatic(h->over)) {
+            Route* r = nullptr;
+            if ((rc = find_tile(h, g, &r)) != SC_OK) return rc;
+            use = r->tile;
+        }
         use.pool = (h->epilogue & SC_EPILOGUE_MAXPOOL2) ? 1 : 0;
-        int rc = build_plan(h->csr, h->C, h->R, h->S, h->dtype == SC_F16 ? 2 : 4, g, use, *p);
-        if (rc != SC_OK) return rc;
-        static std::atomic<unsigned long long> next_id{1};
-        p->id = next_id.fetch_add(1, std::memory_order_relaxed);
+        if ((rc = build_plan(h->csr, h->C, h->R, h->S, elem_bytes(h), g, use, *p)) != SC_OK) return rc;
+        p->id = g_next_id.fetch_add(1, std::memory_order_relaxed);
         it = h->plans.emplace(g, std::move(p)).first;
     }
     *out = it->second.get();
@@ -210,6 +289,81 @@ size_t partial_bytes(const Plan& p)
 }
 size_t counter_bytes(const Plan& p) { return p.J > 1 ? (size_t)p.ntiles * p.kblocks * sizeof(unsigned) : 0; }
 
+// The matrix kernel's part of a forward call (the arguments have been checked).  Its tables are the same for every
+// geometry of the handle: uploaded once, or copied into the static scratch unless they are what it holds.
+int forward_matrix(sparse_conv_s* h, const MatrixPlan& p, const void* input, void* output, const Geometry& g, void* stream,
+                   bool use_static)
+{
+    const MatrixWeights& m = *h->matrix;
+    const size_t b_image = m.image.size() * sizeof(uint16_t), b_exp = m.row_exp.size() * sizeof(int), b_mask = m.mask.size() * sizeof(unsigned);
+    const size_t at_exp = round256(b_image), at_mask = at_exp + round256(b_exp);
+    unsigned char* d = static_cast<unsigned char*>(h->d_matrix);
+    std::unique_lock<std::mutex> hold(g_static_lock, std::defer_lock);
+    hipError_t he = hipSuccess;
+    if (!use_static) {
+        if (!d) {
+            void* fresh = nullptr;
+            he = hipMalloc(&fresh, at_mask + b_mask);
+            d = static_cast<unsigned char*>(fresh);
+            if (he == hipSuccess) he = hipMemcpy(d, m.image.data(), b_image, hipMemcpyHostToDevice);
+            if (he == hipSuccess) he = hipMemcpy(d + at_exp, m.row_exp.data(), b_exp, hipMemcpyHostToDevice);
+            if (he == hipSuccess) he = hipMemcpy(d + at_mask, m.mask.data(), b_mask, hipMemcpyHostToDevice);
+            if (he != hipSuccess) {
+                if (fresh) (void)hipFree(fresh);
+                h->last_hip = (int)he;
+                return he == hipErrorOutOfMemory ? SC_ENOMEM : SC_EHIP;
+            }
+            h->d_matrix = d;
+        }
+    } else {
+        void* base = nullptr;
+        const int e = static_scratch(&base);
+        if (e != 0) {
+            h->last_hip = e;
+            return SC_EHIP;
+        }
+        d = static_cast<unsigned char*>(base);
+        hold.lock();
+        unsigned long long& holds = g_static_holds[h->device & 63];
+        if (holds != h->matrix_id) {
+            holds = 0;
+            hipStream_t s = static_cast<hipStream_t>(stream);
+            he = hipMemcpyAsync(d, m.image.data(), b_image, hipMemcpyHostToDevice, s);
+            if (he == hipSuccess) he = hipMemcpyAsync(d + at_exp, m.row_exp.data(), b_exp, hipMemcpyHostToDevice, s);
+            if (he == hipSuccess) he = hipMemcpyAsync(d + at_mask, m.mask.data(), b_mask, hipMemcpyHostToDevice, s);
+            if (he != hipSuccess) {
+                h->last_hip = (int)he;
+                return SC_EHIP;
+            }
+            holds = h->matrix_id;
+        }
+    }
+    MatrixArgs a;
+    a.x = input;
+    a.y = output;
+    a.weights = d;
+    a.row_exp = reinterpret_cast<const int*>(d + at_exp);
+    a.mask = reinterpret_cast<const unsigned*>(d + at_mask);
+    a.bias = h->d_bias;
+    a.relu = (h->epilogue & SC_EPILOGUE_RELU) ? 1 : 0;
+    a.pool = (h->epilogue & SC_EPILOGUE_MAXPOOL2) ? 1 : 0;
+    fill_matrix_args(m, p, h->K, h->C, h->R, h->S, g, a);
+    const int e = h->dtype == SC_F32 ? launch_matrix_f32(p, a, stream) : launch_matrix_f16(p, a, stream);
+    if (e != 0) {
+        h->last_hip = e;
+        if (use_static) g_static_holds[h->device & 63] = 0;
+        return SC_EHIP;
+    }
+    return SC_OK;
+}
+
+// Bytes of the static scratch that a plan's tables and buffers take.
+size_t static_bytes(const Plan& p)
+{
+    return round256(p.entries.size() * (p.compact ? sizeof(uint32_t) : sizeof(Entry))) + round256(p.seg.size() * sizeof(int)) +
+           round256(p.krow.size() * sizeof(int)) + round256(p.units.size() * sizeof(Plan::Unit)) + round256(counter_bytes(p)) + partial_bytes(p);
+}
+
 // Both forward entry points.  use_static: the plan's tables are read from the GPU's static
 // scratch array (copied there by this call unless the previous call left them) instead of from
 // buffers allocated for the plan, and no device memory is allocated.
@@ -221,14 +375,23 @@ int forward_impl(sparse_conv_s* h, const void* input, void* output, int N, int H
     if (N == 0) return SC_OK;
     if (!input || !output || input == output) return SC_EINVAL;
     try {
+        const Geometry g{N, H, W, stride, pad};
+        int rc = SC_OK;
+        const Route* route = nullptr;
+        const auto tuned = h->tuned.find(g);
+        if (tuned != h->tuned.end() ? tuned->second.matrix != 0 : automatic(h->over))
+            if ((rc = get_route(h, g, &route)) != SC_OK) return rc;
+        const bool matrix = route && route->matrix;
         Plan* p = nullptr;
-        int rc = get_plan(h, Geometry{N, H, W, stride, pad}, &p);
-        if (rc != SC_OK) return rc;
+        // (a call without allocation is refused by what the tile kernel needs, whichever kernel runs)
+        if ((!matrix || use_static) && (rc = get_plan(h, g, &p)) != SC_OK) return rc;
         // the kernels index both tensors with 32-bit element offsets
-        if ((long long)N * h->C * H * W >= (1ll << 31) || (long long)N * h->K * p->E * p->F >= (1ll << 31))
-            return SC_EUNSUPPORTED;
+        const long long E = (H + 2 * pad - h->R) / stride + 1, F = (W + 2 * pad - h->S) / stride + 1;
+        if ((long long)N * h->C * H * W >= (1ll << 31) || (long long)N * h->K * E * F >= (1ll << 31)) return SC_EUNSUPPORTED;
         if (buffers_overlap(h, input, output, N, H, W, stride, pad)) return SC_EINVAL;
         if ((rc = bind_device(h)) != SC_OK) return rc;
+        if (use_static && static_bytes(*p) > kStaticScratchBytes) return SC_ETOOBIG;
+        if (matrix) return forward_matrix(h, route->plan, input, output, g, stream, use_static);
         KernelArgs a;
         fill_args(h, p, input, output, N, H, W, stride, pad, a);
         if (!use_static) {
@@ -272,7 +435,6 @@ int forward_impl(sparse_conv_s* h, const void* input, void* output, int N, int H
             const size_t b_units = p->units.size() * sizeof(Plan::Unit);
             const size_t at_units = at_krow + round256(b_krow), at_counters = at_units + round256(b_units),
                          at_partial = at_counters + round256(counter_bytes(*p));
-            if (at_partial + partial_bytes(*p) > kStaticScratchBytes) return SC_ETOOBIG;
             void* base = nullptr;
             int e = static_scratch(&base);
             if (e != 0) {
@@ -431,6 +593,7 @@ int sparse_conv_set_launch(sparse_conv_t h, const int* params, int nparams)
     l.csplit = v[10];
     h->over = l;
     h->plans.clear();
+    h->routes.clear();
     h->tuned.clear();
     return SC_OK;
 }
@@ -454,6 +617,7 @@ int sparse_conv_set_epilogue(sparse_conv_t h, const float* bias, unsigned flags)
     h->d_bias = d;
     if ((h->epilogue ^ flags) & SC_EPILOGUE_MAXPOOL2) {   // other tiles: plans and measured choices start afresh
         h->plans.clear();
+        h->routes.clear();
         h->tuned.clear();
     }
     h->epilogue = flags;
@@ -598,6 +762,16 @@ int sparse_conv_autotune(sparse_conv_t h, const void* input, void* output,
         }
         if (rc != SC_OK) return rc;
         if (best < 0.f) return SC_EUNSUPPORTED;
+        if (sc::automatic(saved)) {   // and the matrix kernel, where an automatic forward would take it
+            const sc::Route* route = nullptr;
+            if ((rc = sc::get_route(h, g, &route)) != SC_OK) return rc;
+            float ms = -1.f;
+            if (route->matrix && (rc = measure(saved, &ms)) != SC_OK) return rc;
+            if (ms >= 0.f && ms < best) {
+                best = ms;
+                best_launch.matrix = 1;
+            }
+        }
         h->tuned[g] = best_launch;
         restore.replaced = true;
         if (best_us) *best_us = best * 1000.f / 5.f;
@@ -635,6 +809,26 @@ int sparse_conv_rank_launches(sparse_conv_t h, int N, int H, int W, int stride, 
     }
 }
 
+int sparse_conv_get_kernel(sparse_conv_t h, int N, int H, int W, int stride, int pad, int* kernel)
+{
+    if (!h || !kernel || N <= 0) return SC_EINVAL;
+    if (!sc::geometry_ok(h, H, W, stride, pad)) return SC_EINVAL;
+    try {
+        const sc::Geometry g{N, H, W, stride, pad};
+        const auto tuned = h->tuned.find(g);
+        *kernel = 0;
+        if (tuned != h->tuned.end() ? tuned->second.matrix != 0 : sc::automatic(h->over)) {
+            const sc::Route* route = nullptr;
+            const int rc = sc::get_route(h, g, &route);
+            if (rc != SC_OK) return rc;
+            *kernel = route->matrix ? 1 : 0;
+        }
+        return SC_OK;
+    } catch (...) {
+        return SC_ENOMEM;
+    }
+}
+
 int sparse_conv_check_plan(sparse_conv_t h, int N, int H, int W, int stride, int pad, int* failed_check)
 {
     if (!h || N < 0) return SC_EINVAL;
@@ -643,7 +837,10 @@ int sparse_conv_check_plan(sparse_conv_t h, int N, int H, int W, int stride, int
         sc::Plan* p = nullptr;
         int rc = sc::get_plan(h, sc::Geometry{N, H, W, stride, pad}, &p);
         if (rc != SC_OK) return rc;
-        const int bad = sc::check_plan(h->csr, h->C, h->R, h->S, h->dtype == SC_F16 ? 2 : 4, *p);
+        int bad = sc::check_plan(h->csr, h->C, h->R, h->S, h->dtype == SC_F16 ? 2 : 4, *p);
+        const sc::Route* route = nullptr;
+        if (!bad && N > 0 && sc::automatic(h->over) && sc::get_route(h, sc::Geometry{N, H, W, stride, pad}, &route) == SC_OK && route->matrix)
+            bad = sc::check_matrix(h->csr, h->C, h->R, h->S, *h->matrix);
         if (failed_check) *failed_check = bad;
         return SC_OK;
     } catch (...) {
@@ -681,6 +878,7 @@ const char* sparse_conv_strerror(int code)
 void sparse_conv_destroy(sparse_conv_t h)
 {
     if (h && h->d_bias) (void)hipFree(h->d_bias);
+    if (h && h->d_matrix) (void)hipFree(h->d_matrix);
     delete h;
 }
 

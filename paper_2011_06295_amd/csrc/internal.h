@@ -57,6 +57,8 @@ struct Launch {
                       // G image groups interleaved element by element (see Plan)
     int csplit = 0;   // parts the input channels of a (tile, channel block) are dealt over (1, 2, 4, 8), each part a
                       // workgroup of its own; the last one to finish adds the partial sums up
+    int matrix = 0;   // not a launch parameter: set by a measured choice that found the matrix kernel faster (the rest then
+                      // is the fastest of the tile kernel's configurations)
     int pool = 0;     // not a launch parameter: set from the handle's epilogue.  1: the store step takes the maximum over
                       // 2 x 2 windows, so a tile has to hold whole pairs of output rows (output lanes only)
 };
@@ -170,8 +172,10 @@ struct Plan {
 // Chooses the configuration (honouring overrides) and builds the host tables.
 // With `ranked` it only lists the candidate configurations (estimated clocks,
 // full override), cheapest first, and builds nothing.  Returns an SC_* status.
+// With `best` it stops after the search and reports the cheapest configuration and its estimate.
 int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geometry& g,
-               const Launch& over, Plan& plan, std::vector<std::pair<double, Launch>>* ranked = nullptr);
+               const Launch& over, Plan& plan, std::vector<std::pair<double, Launch>>* ranked = nullptr,
+               std::pair<double, Launch>* best = nullptr);
 
 // Checks a built plan against its CSR on the host (every stored weight exactly once, with its
 // tap's LDS offset, inside the tile; every output channel in one slot; table sizes; launch
@@ -230,6 +234,72 @@ struct KernelArgs {
 #endif
 };
 
+// ---------------------------------------------------------------- the matrix kernel (matrix.hip)
+
+// A layer's weights as the matrix kernel reads them, the same for every geometry: dense, with zeros for what is not
+// stored, cut into fragments of 32 output channels x 16 input channels of one tap (a step).  image: [block of 32 output
+// channels][group of 16 input channels][tap][piece][lane][8] binary16, lane l holding output channel l % 32 and input
+// channels 8 * (l / 32) .. + 7; behind it as much again as the last steps of the last block read ahead.  fp32 weights are
+// two binary16 pieces whose sum they are (to 2^-24 of the weight), after multiplication by 2^row_exp.
+struct MatrixWeights {
+    int pieces = 1;        // binary16 numbers a weight is held in: 1, or 2 for fp32 layers
+    int KF = 0;            // blocks of 32 output channels
+    int steps = 0;         // steps of one block: groups of 16 input channels * taps
+    int mask_words = 0;
+    std::vector<uint16_t> image;
+    std::vector<int> row_exp;     // [KF * 32]
+    std::vector<unsigned> mask;   // [K][mask_words], one bit per column (c*R + r)*S + s: stored
+    size_t bytes() const { return image.size() * 2 + row_exp.size() * 4 + mask.size() * 4; }
+};
+void pack_matrix_weights(const Csr& csr, int C, int R, int S, bool split, MatrixWeights& out);
+
+// Tiles of the matrix kernel for one geometry.  A workgroup of four wavefronts owns PT consecutive outputs of the batch
+// (numbered image, row, column) and 32 * MK * WK output channels; a wavefront multiplies MK fragments of weights with NP
+// fragments of 32 outputs.  KS = 1: WK * WP wavefronts share the tile out; KS = 4: each takes the whole tile for a quarter
+// of a chunk's channels.  The lattice (zero-padded rows of all images, one below the other) is the tile kernel's, with 8
+// channels of one image to an element instead of V images.
+struct MatrixPlan {
+    int MK, NP, WK, WP, KS;
+    int CG;          // groups of 8 input channels a chunk holds
+    int EB;          // blocks of 64 lattice elements a tile spans
+    int PT, Wp, Hs, E, F, nout, ntiles, kblocks, nchunks, grid, lds_bytes;
+};
+// Fills p for the given split; false if the kernel cannot run it.
+bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, int MK, int NP, int WK, int KS,
+                 int CG, MatrixPlan& p);
+// The cheapest split by estimate (microseconds in *us); false if there is none.  tile_parts: the channel parts of the tile
+// kernel's plan (they decide how exact its fp32 sums are, and the matrix kernel's must not be less so).
+bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, int tile_parts,
+                   MatrixPlan& p, double* us);
+// Host check of the weight table against the CSR; 0, or the number of the first check that failed.
+int check_matrix(const Csr& csr, int C, int R, int S, const MatrixWeights& m);
+
+struct MatrixArgs {
+    const void* x;
+    void* y;
+    const void* weights;
+    const float* bias;     // [K] or null
+    const int* row_exp;
+    const unsigned* mask;
+    int mask_words;
+    int meet_at;           // LDS byte offset of the word per wavefront they exchange
+    int relu, pool;
+    int N, C, H, W, K, E, F, EF, stride, pad, R, S, RS;
+    int Wp, Hs;
+    int PT, nout, ntiles, kblocks;
+    int WK, logWK;
+    int CG, EB, nchunks;
+    int own_groups;        // groups of 16 input channels of a chunk that a wavefront multiplies
+    int own_steps;         // ... times taps
+    int stream_steps, KF;
+    int block_major;       // order of the (tile, channel block) pairs
+    FastDiv fd_EF, fd_F, fd_Wp, fd_Hs, fd_EB;
+};
+void fill_matrix_args(const MatrixWeights& m, const MatrixPlan& p, int K, int C, int R, int S, const Geometry& g, MatrixArgs& a);
+// Enqueue the matrix kernel.  Return a hipError_t value (0 = success).
+int launch_matrix_f32(const MatrixPlan& p, const MatrixArgs& a, void* stream);
+int launch_matrix_f16(const MatrixPlan& p, const MatrixArgs& a, void* stream);
+
 // Size of the static device array behind sparse_conv_forward_static, and its address on the current
 // device (looked up once per device).  Returns a hipError_t value (0 = success).
 constexpr size_t kStaticScratchBytes = 16u << 20;   // SC_STATIC_SCRATCH_BYTES of the public header
@@ -243,6 +313,16 @@ int launch_tile_kernel(int dtype, int V, int KW, int LP, const KernelArgs& a, in
 int launch_lds_read_probe(void* sink, int workgroups, int iterations, void* stream, long long* bytes_read);
 int launch_copy_probe(void* dst, const void* src, long long bytes, void* stream);
 
+// What is known about an automatic launch of a geometry: the tile kernel's cheapest configuration, and, once a forward call
+// asked, which kernel it takes.
+struct Route {
+    Launch tile;
+    double tile_clocks = 0.0;      // its estimate
+    bool decided = false;
+    bool matrix = false;
+    MatrixPlan plan{};             // matrix: the kernel's tiles
+};
+
 }  // namespace sc
 
 struct sparse_conv_s {
@@ -254,6 +334,11 @@ struct sparse_conv_s {
     unsigned epilogue = 0;
     std::map<sc::Geometry, sc::Launch> tuned;   // per geometry: configuration found by sparse_conv_autotune
     std::map<sc::Geometry, std::unique_ptr<sc::Plan>> plans;
+    std::map<sc::Geometry, sc::Route> routes;   // per geometry: which kernel an automatic forward takes
+    std::unique_ptr<sc::MatrixWeights> matrix;  // made with the first geometry that takes the matrix kernel
+    void* d_matrix = nullptr;                   // its device copy (owned): image, row_exp, mask
+    unsigned long long matrix_id = 0;           // names it in the static device scratch
+    int finite_weights = -1;                    // every stored weight is finite (-1: not looked at yet)
     int last_hip = 0;
     int device = -1;           // HIP device that holds the handle's device buffers; -1 until the first is made
 };

@@ -1,0 +1,575 @@
+// Sparse convolution on the matrix cores of gfx950 (CDNA4).
+//
+// The same result as the tile kernel (kernels.hip), organised as a product: output channels x outputs, summed over
+// (channel, tap).  The stored weights stand in a dense table with zeros between them (MatrixWeights), in the order the
+// matrix instructions take them: v_mfma_f32_32x32x16_f16 multiplies 32 output channels x 16 input channels of one tap with
+// 16 input channels x 32 outputs.  At 90 % sparsity nine tenths of the products are with zeros, yet it is the faster way:
+// the tile kernel is bound by its LDS reads (16 bytes for 4 to 8 multiply-adds a lane) at 30 to 40 TFLOP/s of stored
+// weights, where this kernel does 600 to 1000 TFLOP/s of all weights in binary16 (256 -> 512 channels, 28 x 28, batch 128,
+// 90 %: 569 us by the tile kernel, 229 us here) and 200 to 300 in fp32 (256 -> 256, 14 x 14, batch 256, 70 %: 430 -> 191 us).
+//
+// Tile.  A workgroup of four wavefronts owns consecutive outputs of the batch and keeps, chunk by chunk of channels, the
+// lattice elements they touch in LDS, 8 channels of one position to a 16-byte element: a tap is an LDS offset, so the
+// tile is loaded once for all R * S taps, and a fragment of inputs is one ds_read_b128 a lane, 32 consecutive elements
+// for 32 consecutive outputs (outputs alone: no lane works on padding; a row's end costs a bank conflict, 20 to 40 % of the
+// LDS cycles, which are a quarter of the time).  A wavefront's MK x NP fragments share MK weight and NP input fragments per
+// step: 2 x 4 is what 256 registers hold.  Weight fragments come straight from L2 (each is used by one wavefront of the
+// workgroup, or few), AHEAD steps before their use.
+//
+// Order of the loads.  Vector loads return in order, so a weight fragment that is asked for after the loads of the next
+// chunk's inputs waits for those.  All of a chunk's input loads are therefore issued together at its start, behind the
+// weights of its first AHEAD steps, and those steps stand outside the loop: there the compiler can count exactly which
+// loads are out (in the loop it would have to assume the fewest, and waited for everything at every step: 331 -> 243 us on
+// the layer above).  For the same reason the number of loads does not depend on run-time conditions: FLY blocks of 64
+// elements x 8 channels a wavefront, of which the absent ones are out of the descriptor's range.
+//
+// fp32 layers.  A value is the sum of two binary16 numbers to 2^-23 of it; three of the four products of two such sums are
+// multiplied (the fourth is 2^-22 of the result or less), smallest first.  Range: the weights of an output channel are
+// scaled by a power of two of their own, the inputs by one that the workgroup takes from the largest magnitude of its first
+// chunk; a sum that overflows (a later chunk more than eight times as large) makes the workgroup do its tile once more with
+// the scale of its largest input.  The sum of a chunk is added to that of the chunks before it, which keeps the
+// rounding below that of a sum over all terms: 1.6e-7 of the result (2-norm, against 64 bits) for the layer above, 4.6e-7
+// by the tile kernel.
+//
+// Non-finite inputs.  The table's zeros meet every input of the receptive field, so exactly the outputs with an input that
+// is not finite have a sum that is not: those are summed again over the stored weights alone (a mask says which).
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <atomic>
+#include <type_traits>
+
+#include "internal.h"
+
+namespace sc {
+
+namespace {
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float float16v __attribute__((ext_vector_type(16)));
+
+#define SC_LDS __attribute__((address_space(3)))
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Wold-style-cast"
+__device__ __forceinline__ unsigned lds_address(const unsigned char* in_lds)
+{
+    return (unsigned)(unsigned long long)(const SC_LDS unsigned char*)(in_lds);
+}
+__device__ __forceinline__ half8 lds_read(unsigned address) { return *(const SC_LDS half8*)(address); }
+__device__ __forceinline__ void lds_write(unsigned address, half8 v) { *(SC_LDS half8*)(address) = v; }
+#pragma clang diagnostic pop
+
+// n / d for 0 <= n < 2^31 with the multiplier prepared on the host.
+__device__ __forceinline__ int fdiv(int n, const FastDiv& f)
+{
+    return f.d == 1 ? n : (int)(__umulhi((unsigned)n, f.mul) >> f.shift);
+}
+
+// One input value (as it lies in memory) through a buffer descriptor; out-of-range offsets read as zero.
+template <typename T>
+struct Raw;
+template <>
+struct Raw<_Float16> {
+    typedef unsigned short type;
+    static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t rs, unsigned off, unsigned soff)
+    {
+        return __builtin_amdgcn_raw_buffer_load_b16(rs, (int)off, (int)soff, 0);
+    }
+};
+template <>
+struct Raw<float> {
+    typedef unsigned type;
+    static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t rs, unsigned off, unsigned soff)
+    {
+        return __builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, (int)soff, 0);
+    }
+};
+
+// Eq. 1 for one output over the stored weights of its row alone (the mask says which they are).
+template <typename T>
+__device__ __forceinline__ float stored_sum(const MatrixArgs& a, int u, int k, int i, int j)
+{
+    const T* x = static_cast<const T*>(a.x) + (size_t)u * a.C * a.H * a.W;
+    const _Float16* w = static_cast<const _Float16*>(a.weights);
+    constexpr int kParts = sizeof(T) == 4 ? 2 : 1;
+    const unsigned* mask = a.mask + (size_t)k * a.mask_words;
+    float sum = 0.f;
+    for (int m = 0; m < a.mask_words; ++m) {
+        unsigned bits = mask[m];
+        while (bits) {
+            const int col = m * 32 + __builtin_ctz(bits);
+            bits &= bits - 1;
+            const int c = col / a.RS, tap = col - c * a.RS, r = tap / a.S, s = tap - r * a.S;
+            const int yy = i * a.stride + r - a.pad, xx = j * a.stride + s - a.pad;
+            if (yy < 0 || yy >= a.H || xx < 0 || xx >= a.W) continue;
+            const size_t at = (((size_t)(k >> 5) * a.stream_steps + (size_t)(c >> 4) * a.RS + tap) * kParts) * 512 +
+                              (size_t)(((c & 15) >> 3) * 32 + (k & 31)) * 8 + (c & 7);
+            float weight = (float)w[at];
+            if constexpr (kParts == 2) weight = ldexpf(weight + (float)w[at + 512], -a.row_exp[k]);
+            sum = __builtin_fmaf(weight, (float)x[((size_t)c * a.H + yy) * a.W + xx], sum);
+        }
+    }
+    return sum;
+}
+
+__device__ __forceinline__ bool finite(float v) { return __builtin_fabsf(v) <= 3.402823466e38f; }
+
+}  // namespace
+
+template <typename T, int MK, int NP, int AHEAD, int FLY, int KS>
+__global__ __launch_bounds__(256, 2) void matrix_kernel(const MatrixArgs a)
+{
+    using raw = typename Raw<T>::type;
+    constexpr bool kSplit = sizeof(T) == 4;
+    constexpr int kParts = kSplit ? 2 : 1;      // binary16 pieces a value is held in
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63, half = lane >> 5;
+    const int bid = blockIdx.x;
+    const int item = (bid & 7) * (int)(gridDim.x >> 3) + (bid >> 3);
+    if (item >= a.ntiles * a.kblocks) return;
+    // (tile, channel block) pairs are cut into 8 contiguous ranges, one per XCD, numbered so that the larger of input and
+    // weight table is read by as few XCDs as can be: tile-major, an XCD reads its tiles' input and the whole table,
+    // block-major the other way round
+    const int major = a.block_major ? a.ntiles : a.kblocks;
+    const int outer = item / major, inner = item - outer * major;
+    const int tile = a.block_major ? inner : outer, kb = a.block_major ? outer : inner;
+    // KS = 1: the wavefronts share the tile's output channels and outputs out among them; KS = 4: each works on the
+    // whole tile for a quarter of every chunk's channels
+    const int wk = KS == 1 ? wave & (a.WK - 1) : 0, wp = KS == 1 ? wave >> a.logWK : 0;
+    const int ks = KS == 1 ? 0 : wave;
+    const int kf0 = (kb * a.WK + wk) * MK;      // first block of 32 output channels of this wavefront
+
+    // outputs of the tile and where their receptive fields start in the lattice
+    const int o0 = tile * a.PT;
+    auto lattice = [&](int o) {
+        const int u = fdiv(o, a.fd_EF);
+        const int rem = o - u * a.EF;
+        const int i = fdiv(rem, a.fd_F);
+        return (u * a.Hs + i * a.stride) * a.Wp + (rem - i * a.F) * a.stride;
+    };
+    const int q0 = lattice(o0);
+    const int u0 = fdiv(o0, a.fd_EF);
+    const unsigned lds0 = lds_address(smem);
+    const unsigned plane = (unsigned)a.EB * 64u * 16u;           // bytes of one group of 8 channels
+    const unsigned part = plane * (unsigned)a.CG;                // bytes of one piece of a buffer
+    const unsigned buffer = part * kParts;
+    unsigned at[NP];
+#pragma unroll
+    for (int np = 0; np < NP; ++np) {
+        const int o = o0 + (wp * NP + np) * 32 + (lane & 31);
+        at[np] = lds0 + (unsigned)(lattice(o < a.nout ? o : a.nout - 1) - q0) * 16u + ((unsigned)half + (unsigned)(ks * a.own_groups) * 2u) * plane;
+    }
+
+    // ---- weights: one stream of steps per block of 32 output channels
+    constexpr size_t frag = 64 * 8;                              // halves of one fragment
+    const size_t stream = (size_t)a.stream_steps * kParts * frag;
+    const _Float16* wa[MK];
+#pragma unroll
+    for (int mk = 0; mk < MK; ++mk)                              // blocks past the last repeat it (never stored)
+        wa[mk] = static_cast<const _Float16*>(a.weights) + (size_t)(kf0 + mk < a.KF ? kf0 + mk : a.KF - 1) * stream +
+                 (size_t)(ks * a.own_groups * a.RS) * kParts * frag;
+    // from the end of a chunk's steps of this wavefront to the next chunk's first
+    const size_t skip = KS == 1 ? 0 : (size_t)((a.CG / 2 - a.own_groups) * a.RS) * kParts * frag;
+    const unsigned lane8 = (unsigned)lane * 8u;
+    half8 A[AHEAD][MK][kParts];
+    auto load_a = [&](half8(&dst)[MK][kParts]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int mk = 0; mk < MK; ++mk) {
+#pragma unroll
+            for (int p = 0; p < kParts; ++p) dst[mk][p] = *reinterpret_cast<const half8*>(wa[mk] + p * frag + lane8);
+            wa[mk] += kParts * frag;
+        }
+    };
+
+    // ---- staging: blocks of 64 lattice elements x 8 channels
+    const unsigned chan_bytes = (unsigned)(a.H * a.W) * (unsigned)sizeof(T);
+    const size_t img_bytes = (size_t)a.C * chan_bytes;
+    const size_t base_off = (size_t)u0 * img_bytes;
+    const size_t remain = (size_t)a.N * img_bytes - base_off;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char*>(static_cast<const char*>(a.x)) + base_off, 0, remain > 0x80000000ull ? 0x80000000u : (unsigned)remain, 0x00020000);
+    const int nblk = a.CG * a.EB;               // blocks of a chunk
+    raw st[FLY][8];
+    // the loads of block b of chunk ch; absent blocks (and channels past the last) are out of the descriptor's range
+    // and read as zero, so that nothing here is a branch
+    auto load_block = [&](raw(&dst)[8], int ch, int b) __attribute__((always_inline)) {
+        const int cg = fdiv(b, a.fd_EB), eb = b - cg * a.EB;
+        const int L = q0 + eb * 64 + lane;
+        const int Y = fdiv(L, a.fd_Wp), X = L - Y * a.Wp - a.pad;
+        const int u = fdiv(Y, a.fd_Hs), yy = Y - u * a.Hs - a.pad;
+        const bool ok = (u < a.N) & ((unsigned)yy < (unsigned)a.H) & ((unsigned)X < (unsigned)a.W) & (b < nblk) & (ch < a.nchunks);
+        const unsigned at0 = (unsigned)(u - u0) * (unsigned)img_bytes + (unsigned)(yy * a.W + X) * (unsigned)sizeof(T);
+        const unsigned off = ok ? at0 : 0x80000000u;
+        const int c0 = (ch * a.CG + cg) * 8;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const bool in = c0 + j < a.C;
+            dst[j] = Raw<T>::load(rs, in ? off : 0x80000000u, in ? (unsigned)(c0 + j) * chan_bytes : 0u);
+        }
+    };
+    int xexp = 0;   // kSplit: inputs are multiplied by 2^xexp before they are cut in two
+    float xscale = 1.f;
+    auto store_block = [&](const raw(&src)[8], int buf, int b) __attribute__((always_inline)) {
+        const int cg = fdiv(b, a.fd_EB), eb = b - cg * a.EB;
+        const unsigned to = lds0 + (unsigned)buf * buffer + (unsigned)cg * plane + (unsigned)(eb * 64 + lane) * 16u;
+        half8 hi, lo;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if constexpr (kSplit) {
+                const float v = __uint_as_float(src[j]) * xscale;
+                hi[j] = (_Float16)v;
+                lo[j] = (_Float16)(v - (float)hi[j]);
+            } else {
+                __builtin_memcpy(reinterpret_cast<char*>(&hi) + 2 * j, &src[j], 2);
+            }
+        }
+        lds_write(to, hi);
+        if constexpr (kSplit) lds_write(to + part, lo);
+    };
+    auto fetch = [&](int ch) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < FLY; ++i) load_block(st[i], ch, wave + 4 * i);
+    };
+    auto deposit = [&](int ch, int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < FLY; ++i)
+            if (wave + 4 * i < nblk) store_block(st[i], buf, wave + 4 * i);
+        for (int b = wave + 4 * FLY; b < nblk; b += 4) {        // what does not fit in flight
+            raw more[8];
+            load_block(more, ch, b);
+            store_block(more, buf, b);
+        }
+    };
+
+    // kSplit: the largest finite magnitude any thread of the workgroup holds, as an exponent e: 2^14 <= it * 2^e < 2^15
+    unsigned* meet = reinterpret_cast<unsigned*>(smem + a.meet_at);
+    auto top_of_block = [&](const raw(&src)[8], unsigned top) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const unsigned m = (unsigned)src[j] & 0x7fffffffu;
+            top = (m < 0x7f800000u) & (m > top) ? m : top;
+        }
+        return top;
+    };
+    auto workgroup_exponent = [&](unsigned top) __attribute__((always_inline)) -> int {
+#pragma unroll
+        for (int d = 32; d; d >>= 1) {
+            const unsigned other = (unsigned)__shfl_xor((int)top, d);
+            top = other > top ? other : top;
+        }
+        if (lane == 0) meet[wave] = top;
+        __syncthreads();
+        unsigned all = meet[0];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) all = meet[w] > all ? meet[w] : all;
+        all = (unsigned)__builtin_amdgcn_readfirstlane((int)all);
+        __syncthreads();
+        const int e = 14 + 127 - (int)(all >> 23);
+        return e > 120 ? 120 : e < -120 ? -120 : e;
+    };
+
+    auto for_steps = [&](auto& step, int t, bool more) __attribute__((always_inline)) {
+        if constexpr (KS > 1) {   // the weights asked for during a chunk's last steps are the next chunk's
+            const size_t jump = more && t + AHEAD >= a.own_steps ? skip : 0;
+#pragma unroll
+            for (int mk = 0; mk < MK; ++mk) wa[mk] += jump;
+        }
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) step(A[i]);
+    };
+
+    float16v acc[MK][NP];
+    float16v sum[kSplit ? MK : 1][kSplit ? NP : 1];   // kSplit: the chunks before this one
+    half8 B[NP][kParts];
+    constexpr int kMK = KS > 1 ? 1 : MK, kNP = KS > 1 ? 1 : NP;   // pairs a wavefront finishes
+    unsigned bad;   // one bit per np: some sum of the lane's output np is not finite
+    for (int attempt = 0;; ++attempt) {
+#pragma unroll
+        for (int mk = 0; mk < MK; ++mk)
+#pragma unroll
+            for (int np = 0; np < NP; ++np)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    acc[mk][np][i] = 0.f;
+                    if constexpr (kSplit) sum[mk][np][i] = 0.f;
+                }
+        fetch(0);
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) load_a(A[i]);
+        if constexpr (kSplit) {
+            if (attempt == 0) {
+                unsigned top = 0;
+#pragma unroll
+                for (int i = 0; i < FLY; ++i) top = top_of_block(st[i], top);
+                xexp = workgroup_exponent(top) - 3;     // other chunks may hold values up to eight times as large
+                xscale = __uint_as_float((unsigned)(xexp + 127) << 23);
+            }
+        }
+        deposit(0, 0);
+        __syncthreads();
+
+        auto chunk = [&](int ch, auto more) __attribute__((always_inline)) {
+            constexpr bool kMore = decltype(more)::value;
+            if constexpr (kMore) fetch(ch + 1);
+            const unsigned here = (unsigned)(ch & 1) * buffer;
+            auto read_b = [&](int np, unsigned o) __attribute__((always_inline)) {
+#pragma unroll
+                for (int p = 0; p < kParts; ++p) B[np][p] = lds_read(at[np] + o + (unsigned)p * part);
+            };
+#pragma unroll
+            for (int np = 0; np < NP; ++np) read_b(np, here);
+            int r = 0, s = 0;
+            unsigned group = here;                               // the 16 channels the step is at
+            const unsigned end = here + (unsigned)(2 * a.own_groups) * plane;
+            auto step = [&](half8(&W)[MK][kParts]) __attribute__((always_inline)) {
+                // where the next step reads (after the chunk's last one: somewhere in the chunk, unused)
+                ++s;
+                const bool row_done = s == a.S;
+                s = row_done ? 0 : s;
+                r += row_done ? 1 : 0;
+                const bool group_done = r == a.R;
+                r = group_done ? 0 : r;
+                group += group_done ? 2 * plane : 0u;
+                group = group >= end ? here : group;
+                const unsigned off = group + (unsigned)(r * a.Wp + s) * 16u;
+#pragma unroll
+                for (int np = 0; np < NP; ++np) {
+#pragma unroll
+                    for (int mk = 0; mk < MK; ++mk) {
+                        if constexpr (kSplit) {
+                            acc[mk][np] = __builtin_amdgcn_mfma_f32_32x32x16_f16(W[mk][1], B[np][0], acc[mk][np], 0, 0, 0);
+                            acc[mk][np] = __builtin_amdgcn_mfma_f32_32x32x16_f16(W[mk][0], B[np][1], acc[mk][np], 0, 0, 0);
+                        }
+                        acc[mk][np] = __builtin_amdgcn_mfma_f32_32x32x16_f16(W[mk][0], B[np][0], acc[mk][np], 0, 0, 0);
+                    }
+                    read_b(np, off);
+                }
+                load_a(W);
+            };
+            // the first steps stand by themselves: their weights were asked for before the loads of the next chunk
+            for_steps(step, 0, kMore);
+            for (int t = AHEAD; t < a.own_steps; t += AHEAD) for_steps(step, t, kMore);
+            if constexpr (kSplit) {
+#pragma unroll
+                for (int mk = 0; mk < MK; ++mk)
+#pragma unroll
+                    for (int np = 0; np < NP; ++np) {
+                        sum[mk][np] += acc[mk][np];
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) acc[mk][np][i] = 0.f;
+                    }
+            }
+            if constexpr (kMore) deposit(ch + 1, (ch + 1) & 1);
+            __syncthreads();
+        };
+        for (int ch = 0; ch + 1 < a.nchunks; ++ch) chunk(ch, std::true_type{});
+        chunk(a.nchunks - 1, std::false_type{});
+        if constexpr (kSplit) {
+#pragma unroll
+            for (int mk = 0; mk < MK; ++mk)
+#pragma unroll
+                for (int np = 0; np < NP; ++np) acc[mk][np] = sum[mk][np];
+        }
+        if constexpr (KS > 1) {
+            // the four wavefronts' sums of a (mk, np) pair meet at the wavefront with the pair's number, always added in
+            // the same order (nobody reads the tile any more: its place is free)
+            static_assert(MK * NP == KS, "one pair a wavefront");
+            float* meeting = reinterpret_cast<float*>(smem);
+#pragma unroll
+            for (int mk = 0; mk < MK; ++mk)
+#pragma unroll
+                for (int np = 0; np < NP; ++np)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) meeting[(((ks * MK + mk) * NP + np) * 16 + i) * 64 + lane] = acc[mk][np][i];
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                float v = meeting[((size_t)wave * 16 + i) * 64 + lane];
+#pragma unroll
+                for (int q = 1; q < KS; ++q) v += meeting[(((size_t)q * KS + wave) * 16 + i) * 64 + lane];
+                acc[0][0][i] = v;
+            }
+            __syncthreads();
+        }
+        bad = 0;
+#pragma unroll
+        for (int np = 0; np < kNP; ++np) {
+            bool ok = true;
+#pragma unroll
+            for (int mk = 0; mk < kMK; ++mk)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) ok = ok & finite(acc[mk][np][i]);
+            bad |= ok ? 0u : 1u << np;
+        }
+        bad |= (unsigned)__shfl_xor((int)bad, 32);       // the lane that holds the other rows of the same outputs
+        if constexpr (!kSplit) break;
+        // a sum that is not finite: a value too large for the scale the first chunk gave (once more with the right one),
+        // or an input that is not finite itself
+        const bool any = __ballot(bad != 0) != 0;
+        if (lane == 0) meet[wave] = any ? 1u : 0u;
+        __syncthreads();
+        const unsigned votes = meet[0] | meet[1] | meet[2] | meet[3];
+        __syncthreads();
+        if (!__builtin_amdgcn_readfirstlane((int)votes) || attempt) break;
+        unsigned top = 0;
+        for (int c = 0; c < a.nchunks; ++c)
+            for (int b = wave; b < nblk; b += 4) {
+                raw more[8];
+                load_block(more, c, b);
+                top = top_of_block(more, top);
+            }
+        const int e = workgroup_exponent(top);
+        if (e >= xexp) break;
+        xexp = e;
+        xscale = __uint_as_float((unsigned)(xexp + 127) << 23);
+#pragma unroll
+        for (int mk = 0; mk < MK; ++mk)
+            wa[mk] -= (size_t)(a.nchunks * a.own_steps + AHEAD) * kParts * frag + (size_t)(a.nchunks - 1) * skip;
+    }
+
+    // ---- store
+    T* __restrict__ y = static_cast<T*>(a.y);
+    const int kfirst = (kf0 + (KS > 1 ? wave / NP : 0)) * 32;                  // first output channel and
+    const int ofirst = o0 + (wp * NP + (KS > 1 ? wave % NP : 0)) * 32;         // first output of the wavefront's sums
+    const int krow0 = kfirst + half * 4;
+    auto finish = [&](float v, int k) __attribute__((always_inline)) {         // section 3: bias, then activation
+        if (a.bias) v += a.bias[k];
+        if (a.relu) v = v > 0.f ? v : 0.f;
+        return v;
+    };
+    if (!a.pool) {
+#pragma unroll
+        for (int np = 0; np < kNP; ++np) {
+            const int o = ofirst + np * 32 + (lane & 31);
+            const int u = fdiv(o, a.fd_EF);
+            const bool valid = o < a.nout && !((bad >> np) & 1u);
+            T* to = y + ((size_t)u * a.K + krow0) * a.EF + (o - u * a.EF);
+#pragma unroll
+            for (int mk = 0; mk < kMK; ++mk)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int kr = mk * 32 + (i >> 2) * 8 + (i & 3);
+                    const int k = krow0 + kr;
+                    if (k < a.K && valid) {
+                        float v = acc[mk][np][i];
+                        if constexpr (kSplit) v = ldexpf(v, -xexp - a.row_exp[k]);
+                        to[(size_t)kr * a.EF] = (T)finish(v, k);
+                    }
+                }
+        }
+    } else {
+        // 2 x 2 maximum: the wavefront's outputs hold whole pairs of rows of F outputs (the planner's condition).  The
+        // value below is F / 32 registers or F lanes away, the one to the right one lane.  (Scale, bias and activation
+        // are monotonic: they are applied to the largest of the four sums.)
+        const int F = a.F, apart = F >> 5;
+        const size_t plane_out = (size_t)(a.E >> 1) * (F >> 1);
+#pragma unroll
+        for (int np = 0; np < kNP; ++np) {
+            if (apart && ((np / apart) & 1)) continue;
+            unsigned wrong = bad >> np;
+            if (apart == 1 && np + 1 < kNP) wrong |= bad >> (np + 1 < kNP ? np + 1 : 0);
+            if (apart == 2 && np + 2 < kNP) wrong |= bad >> (np + 2 < kNP ? np + 2 : 0);
+            wrong &= 1u;
+            if (!apart) wrong |= (unsigned)__shfl_xor((int)wrong, F);
+            wrong |= (unsigned)__shfl_xor((int)wrong, 1);
+            const int o = ofirst + np * 32 + (lane & 31);
+            const int u = fdiv(o, a.fd_EF);
+            const int rem = o - u * a.EF, i0 = fdiv(rem, a.fd_F), j0 = rem - i0 * F;
+            const bool valid = o < a.nout && !wrong && !((i0 | j0) & 1);
+            T* to = y + ((size_t)u * a.K + krow0) * plane_out + (size_t)(i0 >> 1) * (F >> 1) + (j0 >> 1);
+#pragma unroll
+            for (int mk = 0; mk < kMK; ++mk)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int kr = mk * 32 + (i >> 2) * 8 + (i & 3);
+                    const int k = krow0 + kr;
+                    float v = acc[mk][np][i];
+                    float below = v;
+                    if (apart == 1) below = acc[mk][np + 1 < kNP ? np + 1 : np][i];
+                    if (apart == 2) below = acc[mk][np + 2 < kNP ? np + 2 : np][i];
+                    if (!apart) below = __shfl_xor(v, F);
+                    v = below > v ? below : v;
+                    const float right = __shfl_xor(v, 1);
+                    v = right > v ? right : v;
+                    if (k < a.K && valid) {
+                        if constexpr (kSplit) v = ldexpf(v, -xexp - a.row_exp[k]);
+                        to[(size_t)kr * plane_out] = (T)finish(v, k);
+                    }
+                }
+        }
+    }
+    // ---- outputs whose receptive field holds a value that is not finite: the zeros of the dense table met it as well.
+    // Summed once more over the stored weights alone, a lane a row.
+    if (__builtin_expect(__ballot(bad != 0) != 0, 0)) {
+#pragma unroll 1
+        for (int np = 0; np < kNP; ++np) {
+            unsigned todo = (unsigned)__ballot((bad >> np) & 1u);      // the upper half repeats the lower
+#pragma unroll 1
+            while (todo) {
+                const int o = ofirst + np * 32 + __builtin_ctz(todo);
+                todo &= todo - 1;
+                if (o >= a.nout) continue;
+                const int u = fdiv(o, a.fd_EF);
+                const int rem = o - u * a.EF, i0 = fdiv(rem, a.fd_F), j0 = rem - i0 * a.F;
+#pragma unroll 1
+                for (int k = kfirst + lane; k < kfirst + kMK * 32 && k < a.K; k += 64) {
+                    float v = 0.f;
+#pragma unroll 1
+                    for (int q = 0; q < (a.pool ? 4 : 1); ++q) {
+                        const float w = stored_sum<T>(a, u, k, a.pool ? (i0 & ~1) + (q >> 1) : i0, a.pool ? (j0 & ~1) + (q & 1) : j0);
+                        v = q == 0 || w > v ? w : v;
+                    }
+                    T* to = a.pool ? y + ((size_t)u * a.K + k) * ((size_t)(a.E >> 1) * (a.F >> 1)) + (size_t)(i0 >> 1) * (a.F >> 1) + (j0 >> 1)
+                                   : y + ((size_t)u * a.K + k) * a.EF + rem;
+                    *to = (T)finish(v, k);
+                }
+            }
+        }
+    }
+}
+
+namespace {
+
+template <typename T, int MK, int NP, int AHEAD, int FLY, int KS>
+int launch_one(const MatrixArgs& a, int grid, int lds, hipStream_t s)
+{
+    auto fn = matrix_kernel<T, MK, NP, AHEAD, FLY, KS>;
+    if (lds > 64 * 1024) {
+        // more than 64 KB of dynamic LDS has to be allowed per kernel and device: once, for the whole 160 KB
+        static std::atomic<unsigned long long> allowed{0};   // one bit per device ordinal
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return (int)e;
+        const unsigned long long bit = dev < 64 ? 1ull << dev : 0ull;
+        if (!(allowed.load(std::memory_order_relaxed) & bit)) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            if (e != hipSuccess) return (int)e;
+            allowed.fetch_or(bit, std::memory_order_relaxed);
+        }
+    }
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(256), lds, s, a);
+    return (int)hipGetLastError();
+}
+
+template <typename T, int MK, int NP, int KS>
+int launch_fly(const MatrixArgs& a, int fly, int grid, int lds, hipStream_t s)
+{
+    constexpr int low = sizeof(T) == 4 ? 1 : 2, high = sizeof(T) == 4 ? 3 : 6;
+    // (two binary16 pieces: three steps of weights ahead are more registers than there are)
+    if (a.own_steps % 3 == 0 && !(sizeof(T) == 4 && a.own_steps % 2 == 0)) {
+        if (fly <= low) return launch_one<T, MK, NP, 3, low, KS>(a, grid, lds, s);
+        if (fly < high) return launch_one<T, MK, NP, 3, 2 * low, KS>(a, grid, lds, s);
+        return launch_one<T, MK, NP, 3, high, KS>(a, grid, lds, s);
+    }
+    if (a.own_steps % 2) return (int)hipErrorInvalidValue;
+    if (fly <= low) return launch_one<T, MK, NP, 2, low, KS>(a, grid, lds, s);
+    if (fly < high) return launch_one<T, MK, NP, 2, 2 * low, KS>(a, grid, lds, s);
+    return launch_one<T, MK, NP, 2, high, KS>(a, grid, lds, s);
+}
+
+}  // namespace
+
+}  // namespace sc

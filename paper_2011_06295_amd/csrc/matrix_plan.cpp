@@ -1,0 +1,232 @@
+// Host side of the matrix kernel (matrix.hip): the weight table, the tiles of a geometry and which split of them to take.
+#include <algorithm>
+#include <climits>
+#include <cmath>
+#include <cstring>
+
+#include "internal.h"
+
+namespace sc {
+
+namespace {
+
+constexpr int kMatrixGroups = 8;      // groups of 16 channels a chunk holds at most
+constexpr int kMaxLds = 160 * 1024;   // LDS per CU
+constexpr int kCUs = 256;
+
+// Place of weight (k, col) in the image, first piece.
+size_t image_at(const MatrixWeights& m, int RS, int k, int col)
+{
+    const int c = col / RS, tap = col % RS;
+    const size_t step = (size_t)(c / 16) * RS + tap, lane = (size_t)((c % 16) / 8) * 32 + k % 32;
+    return (((size_t)(k / 32) * m.steps + step) * m.pieces) * 512 + lane * 8 + c % 8;
+}
+
+}  // namespace
+
+void pack_matrix_weights(const Csr& csr, int C, int R, int S, bool split, MatrixWeights& m)
+{
+    const int K = csr.K, RS = R * S;
+    m.pieces = split ? 2 : 1;
+    m.KF = (K + 31) / 32;
+    m.steps = (C + 15) / 16 * RS;
+    // behind the last stream: the groups of its last chunk that are not there (they meet zeros of the input) and what its
+    // last steps ask for ahead
+    m.image.assign(((size_t)m.KF * m.steps + (size_t)kMatrixGroups * RS + 3) * m.pieces * 512, 0);
+    m.mask_words = (C * RS + 31) / 32;
+    m.mask.assign((size_t)K * m.mask_words, 0u);
+    m.row_exp.assign((size_t)m.KF * 32, 0);
+    for (int k = 0; k < K; ++k) {
+        if (split) {   // the largest weight of the row lands in [2^14, 2^15)
+            float top = 0.f;
+            for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) top = std::max(top, std::fabs(csr.val32[i]));
+            int ex = 0;
+            if (top > 0.f) (void)std::frexp(top, &ex), ex = 15 - ex;
+            m.row_exp[k] = ex;
+        }
+        for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) {
+            const int col = csr.colidx[i];
+            m.mask[(size_t)k * m.mask_words + col / 32] |= 1u << (col % 32);
+            uint16_t* to = &m.image[image_at(m, RS, k, col)];
+            const float w = split ? std::ldexp(csr.val32[i], m.row_exp[k]) : csr.val32[i];
+            to[0] = float_to_half_rne(w);
+            if (split) to[512] = float_to_half_rne(w - half_to_float(to[0]));
+        }
+    }
+}
+
+int check_matrix(const Csr& csr, int C, int R, int S, const MatrixWeights& m)
+{
+    const int RS = R * S;
+    if (m.KF != (csr.K + 31) / 32 || m.steps != (C + 15) / 16 * RS || m.mask_words != (C * RS + 31) / 32) return 10;
+    if (m.image.size() != ((size_t)m.KF * m.steps + (size_t)kMatrixGroups * RS + 3) * m.pieces * 512) return 10;
+    // 11: every stored weight is in its place; 12: and nothing else is in the table or the mask
+    size_t marked = 0;
+    std::vector<uint16_t> rest = m.image;
+    for (int k = 0; k < csr.K; ++k)
+        for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) {
+            const int col = csr.colidx[i];
+            const size_t at = image_at(m, RS, k, col);
+            if (!(m.mask[(size_t)k * m.mask_words + col / 32] >> (col % 32) & 1u)) return 11;
+            const float w = std::ldexp(csr.val32[i], m.pieces == 2 ? m.row_exp[k] : 0);
+            const float is = half_to_float(m.image[at]) + (m.pieces == 2 ? half_to_float(m.image[at + 512]) : 0.f);
+            // two pieces: 2^-23 of the weight (22 bits and a sign), or half of binary16's smallest number
+            const float may = m.pieces == 2 ? std::max(std::fabs(w) * 0x1p-23f, 0x1p-25f) : 0.f;
+            if (!(std::fabs(is - w) <= may)) return 11;
+            rest[at] = 0;
+            if (m.pieces == 2) rest[at + 512] = 0;
+        }
+    for (uint16_t h : rest)
+        if (h) return 12;
+    for (unsigned w : m.mask) marked += (size_t)__builtin_popcount(w);
+    return marked == csr.colidx.size() ? 0 : 12;
+}
+
+bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, int MK, int NP, int WK, int KS,
+                 int CG, MatrixPlan& p)
+{
+    p = MatrixPlan{};
+    p.MK = MK; p.NP = NP; p.WK = WK; p.KS = KS; p.WP = 4 / (WK * KS);
+    p.E = (g.H + 2 * g.pad - R) / g.stride + 1;
+    p.F = (g.W + 2 * g.pad - S) / g.stride + 1;
+    const long long EF = (long long)p.E * p.F, nout = g.N * EF;
+    p.PT = 32 * NP * p.WP;
+    // 2 x 2 maximum in the store step: a wavefront's outputs hold whole pairs of rows, a pair in 2, 4 ... 32 lanes of one
+    // fragment or in the same lanes of fragments 1 or 2 apart
+    if (pool) {
+        if (((p.E | p.F) & 1) || (p.F & (p.F - 1)) || g.stride != 1) return false;
+        if ((KS == 1 ? 32 * NP : 32) % (2 * p.F) != 0 || p.F > 64) return false;
+    }
+    p.Wp = std::max(g.W + g.pad, (p.F - 1) * g.stride + 1);
+    p.Hs = std::max(g.H + g.pad, (p.E - 1) * g.stride + 1);
+    if (nout >= (1ll << 31) - 4096 || (long long)g.N * p.Hs * p.Wp + (long long)(R + 1) * p.Wp + 4096 >= (1ll << 31)) return false;
+    p.nout = (int)nout;
+    p.ntiles = (int)((nout + p.PT - 1) / p.PT);
+    // the lattice elements a tile spans depend only on its first output's place in its image, of which there are EF
+    auto lattice = [&](long long o) { return (o / EF * p.Hs + o % EF / p.F * g.stride) * (long long)p.Wp + o % p.F * g.stride; };
+    long long span = 0;
+    for (long long t = 0; t < std::min<long long>(p.ntiles, EF + 1); ++t) {
+        const long long a = t * p.PT, b = std::min<long long>(nout, a + p.PT) - 1;
+        span = std::max(span, lattice(b) - lattice(a));
+    }
+    const long long elems = span + (long long)(R - 1) * p.Wp + S;
+    if (elems > kMaxLds / 16) return false;
+    p.EB = (int)((elems + 63) / 64);
+    // source offsets are 31-bit byte offsets from the tile's first image
+    const long long images = ((long long)p.EB * 64 / p.Wp + 1) / p.Hs + 2;
+    if (images * C * g.H * g.W * elem_bytes >= (1ll << 31)) return false;
+    if (CG / 2 > kMatrixGroups || CG / 2 % KS) return false;
+    p.CG = CG;
+    const int own = CG / 2 / KS * R * S;
+    if (own % 3 && own % 2) return false;           // the kernel walks a chunk two or three steps at a time
+    const int pieces = elem_bytes == 4 ? 2 : 1, groups = 2 * ((C + 15) / 16);
+    p.nchunks = (groups + CG - 1) / CG;
+    long long lds = (long long)(p.nchunks > 1 ? 2 : 1) * CG * p.EB * 64 * 16 * pieces;
+    if (KS > 1) lds = std::max(lds, (long long)KS * MK * NP * 16 * 64 * 4);   // where the four sums of a pair meet
+    lds += 64;
+    if (lds > kMaxLds) return false;
+    p.lds_bytes = (int)lds;
+    p.kblocks = (K + 32 * MK * WK - 1) / (32 * MK * WK);
+    const long long grid = ((long long)p.ntiles * p.kblocks + 7) / 8 * 8;   // a multiple of the XCD count
+    if (grid > INT_MAX - 8) return false;
+    p.grid = (int)grid;
+    return true;
+}
+
+namespace {
+
+// Rough time of one launch in microseconds.  Structure and constants are fitted to the measured times of every split of
+// 168 layers (the 32-pixel VGG-16's, those of larger networks, and random ones: 1 x 1, 1-D, 3 x 3, 5 x 5, stride 2, first
+// layers, batches of 1 to 256): 13 % rms of the logarithm, the cheapest by estimate 3 % (fp32: 4 %) slower than the fastest
+// measured in the mean.  In clocks of 2.1 GHz:
+//  * A step costs its matrix instructions (48 clocks each over the workgroups resident on the CU, fp32 61; 32 at the nominal
+//    rate), but never less than a wavefront's own chain of loads and instructions.
+//  * A chunk's staging blocks (64 lattice elements x 8 channels) cost 180 (247) clocks each; a third of the shorter of
+//    multiplying and staging is not hidden behind the longer.
+//  * Workgroups run in rounds of what is resident; a partly filled last round after full ones is a little shorter.
+double estimate_matrix(const MatrixPlan& p, int RS, bool split)
+{
+    struct Clocks { double fixed, chain, chain_mf, mf, chunk, stage_chunk, stage, pair, tail; };
+    static const Clocks k16 = {10960, 221, 30.7, 47.7, 472, 180, 180, 790, 0.83}, k32 = {13940, 414, 8.9, 61.1, 94, 124, 247, 2650, 0.98};
+    const Clocks& k = split ? k32 : k16;
+    const int conc_max = std::min(2, kMaxLds / p.lds_bytes);      // registers allow two workgroups a CU
+    const double mf = p.MK * p.NP * (split ? 3 : 1), own = (double)(p.CG / 2 / p.KS) * RS;
+    auto round = [&](double conc) {
+        const double multiply = own * std::max(k.chain + k.chain_mf * mf, conc * mf * k.mf), stage = conc * p.CG * p.EB * k.stage;
+        return p.nchunks * (std::max(multiply, stage + k.stage_chunk) + 0.35 * std::min(multiply, stage) + k.chunk) + 0.6 * stage +
+               k.stage_chunk + conc * k.pair * p.MK * p.NP / (p.KS > 1 ? 4 : 1);
+    };
+    const long long slots = (long long)kCUs * conc_max, wgs = (long long)p.ntiles * p.kblocks;
+    const long long full = wgs / slots, rest = wgs % slots;
+    double t = k.fixed + (double)full * round(conc_max);
+    if (rest) t += round((double)((rest + kCUs - 1) / kCUs)) * (full ? k.tail : 1.0);
+    return t / 2100.0;
+}
+
+}  // namespace
+
+bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, int tile_parts,
+                   MatrixPlan& best, double* us)
+{
+    const bool split = elem_bytes == 4;
+    const int RS = R * S;
+    const int E = (g.H + 2 * g.pad - R) / g.stride + 1, F = (g.W + 2 * g.pad - S) / g.stride + 1;
+    // fp32 sums: terms of an output that do not fall on padding, in the mean
+    double terms = 0.0;
+    if (split) {
+        double rows = 0, cols = 0;
+        for (int i = 0; i < E; ++i)
+            for (int r = 0; r < R; ++r) rows += (unsigned)(i * g.stride + r - g.pad) < (unsigned)g.H;
+        for (int j = 0; j < F; ++j)
+            for (int s = 0; s < S; ++s) cols += (unsigned)(j * g.stride + s - g.pad) < (unsigned)g.W;
+        terms = (double)csr.colidx.size() / csr.K * rows * cols / ((double)E * F * RS);
+    }
+    static const int shapes16[][4] = {{2, 4, 1, 1}, {2, 4, 2, 1}, {2, 4, 4, 1}, {2, 2, 1, 1}, {2, 2, 2, 1}, {2, 2, 4, 1}, {2, 2, 1, 4}};
+    static const int shapes32[][4] = {{2, 2, 1, 1}, {2, 2, 2, 1}, {2, 2, 4, 1}, {1, 2, 1, 1}, {1, 2, 2, 1}, {1, 2, 4, 1}, {2, 2, 1, 4}};
+    double best_us = -1.0;
+    for (const auto& sh : split ? shapes32 : shapes16)
+        for (int CG = 2; CG <= 2 * kMatrixGroups; CG *= 2) {
+            MatrixPlan p;
+            if (CG > 2 && CG / 2 >= 2 * ((C + 15) / 16)) break;   // a smaller chunk holds them all
+            if (!plan_matrix(csr.K, C, R, S, elem_bytes, g, pool, sh[0], sh[1], sh[2], sh[3], CG, p)) continue;
+            if (split) {
+                // Squared relative error of an output, in units of 1e-14, fitted to the measured ones: the tile kernel rounds
+                // its sum at every term (1.8e-7 at 100); here the pieces' own error, three roundings a step of a chunk's
+                // sum, one a chunk.  What is as exact by this measure, with 15 % to spare, may run.
+                const double here = 0.81 + 0.047 * 3 * RS * (CG / 2 / sh[3]) + 0.04 * p.nchunks;
+                if (here * 1.3 > 0.0335 * terms / std::max(1, tile_parts)) continue;
+            }
+            const double t = estimate_matrix(p, RS, split);
+            if (best_us < 0 || t < best_us) {
+                best_us = t;
+                best = p;
+            }
+        }
+    if (best_us < 0) return false;
+    *us = best_us;
+    return true;
+}
+
+void fill_matrix_args(const MatrixWeights& m, const MatrixPlan& p, int K, int C, int R, int S, const Geometry& g, MatrixArgs& a)
+{
+    a.N = g.N; a.C = C; a.H = g.H; a.W = g.W; a.K = K; a.E = p.E; a.F = p.F; a.EF = p.E * p.F;
+    a.stride = g.stride; a.pad = g.pad; a.R = R; a.S = S; a.RS = R * S;
+    a.Wp = p.Wp; a.Hs = p.Hs;
+    a.PT = p.PT; a.nout = p.nout; a.ntiles = p.ntiles; a.kblocks = p.kblocks;
+    a.WK = p.WK;
+    a.logWK = p.WK == 4 ? 2 : p.WK == 2 ? 1 : 0;
+    a.mask_words = m.mask_words;
+    a.meet_at = p.lds_bytes - 64;
+    a.CG = p.CG; a.EB = p.EB; a.nchunks = p.nchunks;
+    a.own_groups = p.CG / 2 / p.KS;
+    a.own_steps = a.own_groups * a.RS;
+    a.stream_steps = m.steps; a.KF = m.KF;
+    a.block_major = m.image.size() * 2 > (size_t)g.N * C * g.H * g.W * (m.pieces == 2 ? 4 : 2);
+    a.fd_EF = make_fastdiv(a.EF);
+    a.fd_F = make_fastdiv(p.F);
+    a.fd_Wp = make_fastdiv(p.Wp);
+    a.fd_Hs = make_fastdiv(p.Hs);
+    a.fd_EB = make_fastdiv(p.EB);
+}
+
+}  // namespace sc

@@ -8,6 +8,8 @@ namespace sc {
 
 int static_scratch(void**) { return (int)hipErrorNotSupported; }
 int launch_tile_kernel(int, int, int, int, const KernelArgs&, int, int, int, void*) { return (int)hipErrorNotSupported; }
+int launch_matrix_f32(const MatrixPlan&, const MatrixArgs&, void*) { return (int)hipErrorNotSupported; }
+int launch_matrix_f16(const MatrixPlan&, const MatrixArgs&, void*) { return (int)hipErrorNotSupported; }
 int launch_lds_read_probe(void*, int, int, void*, long long*) { return (int)hipErrorNotSupported; }
 int launch_copy_probe(void*, const void*, long long, void*) { return (int)hipErrorNotSupported; }
 

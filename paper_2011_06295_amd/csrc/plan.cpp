@@ -200,7 +200,7 @@ FastDiv make_fastdiv(int d)
 }
 
 int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geometry& g,
-               const Launch& over, Plan& p, std::vector<std::pair<double, Launch>>* ranked)
+               const Launch& over, Plan& p, std::vector<std::pair<double, Launch>>* ranked, std::pair<double, Launch>* cheapest)
 {
     const int K = csr.K;
     const int st = g.stride, pad = g.pad;
@@ -459,6 +459,14 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
 
     const Shape& s = bs;
     const int V = best.V;
+    if (cheapest) {
+        Launch l = over;
+        l.V = best.V; l.WP = best.WP; l.WK = best.WK; l.KW = best.KW; l.Cc = best.Cc; l.LP = best.LP; l.kblocks = best.kblocks;
+        l.lanes = 1 + s.G;
+        l.csplit = best.J;
+        *cheapest = {best_t, l};
+        return SC_OK;
+    }
     const int ngroups = std::max(1, cdiv(g.N, V));
     p.V = V; p.WP = best.WP; p.WK = best.WK; p.KW = best.KW; p.Cc = best.Cc; p.LP = best.LP;
     p.store = over.store ? over.store : 1;   // which kind is faster depends on what else lives in L2: only a measurement tells

@@ -1,0 +1,134 @@
+"""The matrix kernel (sparse_conv_get_kernel says "matrix") against the CPU oracle at the edges of its tiles: channels off
+its groups of 16, rows off its blocks of 32, outputs off its tiles, every way of sharing a tile out, pooled stores, inputs
+that are not finite, and fp32 inputs of every magnitude (they are cut into two scaled binary16 pieces)."""
+import numpy as np
+import pytest
+
+from helpers import TOL, assert_close, rand_layer
+from test_gpu_parity import oracle_ref, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+# N, C, K, R, S, H, W, stride, pad: weights 90 or 100 % dense, so that these sizes take the kernel
+SHAPES = [(40, 64, 65, 3, 3, 14, 14, 1, 1), (40, 33, 130, 3, 3, 9, 13, 1, 1), (100, 17, 96, 5, 5, 8, 7, 1, 2), (64, 200, 31, 3, 3, 15, 15, 1, 0),
+          (24, 48, 64, 3, 3, 29, 31, 2, 1), (60, 240, 250, 1, 1, 15, 14, 1, 0), (200, 600, 100, 1, 1, 7, 7, 1, 0), (150, 300, 100, 1, 3, 1, 64, 1, 0),
+          (600, 512, 128, 3, 3, 2, 2, 1, 1), (64, 256, 256, 3, 3, 4, 4, 1, 1), (4, 16, 64, 3, 3, 65, 120, 1, 1), (100, 80, 48, 2, 2, 18, 18, 2, 3)]
+
+
+def _layer(dtype, shape, seed, density):
+    from paper_2011_06295_amd import binding as B
+    N, C, K, R, S, H, W, st, p = shape
+    w, m, x = rand_layer(np.random.default_rng(seed), N, C, K, R, S, H, W, density=density)
+    return B.SparseConv(w, m, dtype=dtype), w, m, x
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_matrix_kernel_against_the_oracle(dtype, shape):
+    layer, w, m, x = _layer(dtype, shape, 91, 0.9)
+    N, C, K, R, S, H, W, st, p = shape
+    # (the fp32 sums of a 5 x 5 filter's chunk are not exact enough for so few channels: the tile kernel's)
+    assert layer.get_kernel(N, H, W, st, p) == ("tile" if dtype == "f32" and R == 5 else "matrix"), "the sizes no longer take the kernel under test"
+    assert layer.check_plan(N, H, W, st, p) == 0
+    ref = oracle_ref(w, m, x, st, p, dtype)
+    bias = np.random.default_rng(5).standard_normal(K).astype(np.float32)
+    assert_close(run_gpu(layer, x, st, p, dtype), ref, TOL[dtype], f"{dtype} {shape}")
+    layer.set_epilogue(bias, relu=True)
+    assert_close(run_gpu(layer, x, st, p, dtype), np.maximum(ref + bias[None, :, None, None], 0.0), TOL[dtype], f"bias, ReLU {dtype} {shape}")
+    layer.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("H,N,C,K", [(2, 1200, 256, 64), (4, 400, 256, 40), (8, 64, 128, 64), (16, 33, 64, 96), (32, 9, 48, 64), (64, 5, 40, 64)])
+def test_matrix_kernel_pooled_store(dtype, H, N, C, K):
+    import oracle
+    import torch
+    shape = (N, C, K, 3, 3, H, H, 1, 1)
+    layer, w, m, x = _layer(dtype, shape, 92, 1.0)
+    bias = np.random.default_rng(6).standard_normal(K).astype(np.float32)
+    layer.set_epilogue(bias, relu=True, maxpool=True)
+    # (fp32 wavefronts own 64 outputs: no pair of rows of 64)
+    assert layer.get_kernel(N, H, H, 1, 1) == ("tile" if dtype == "f32" and H == 64 else "matrix")
+    ref = oracle.maxpool2(oracle.relu((oracle_ref(w, m, x, 1, 1, dtype) + bias[None, :, None, None]).astype(np.float32)))
+    assert_close(run_gpu(layer, x, 1, 1, dtype), ref, TOL[dtype], f"pooled {dtype} {H}")
+    if H <= 8:   # (larger maps: the tile kernel's partial sums are more than the static scratch holds, the call is refused)
+        xt = torch.from_numpy(x).cuda().to(torch.float16 if dtype == "f16" else torch.float32)
+        assert torch.equal(layer.forward_static(xt, 1, 1), layer.forward(xt, 1, 1))
+    layer.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[5], SHAPES[8]], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("pool", [False, True])
+def test_matrix_kernel_inputs_that_are_not_finite(dtype, shape, pool):
+    """The dense table's zeros meet every input of a receptive field: an Inf or NaN must count under stored weights only."""
+    import torch
+    N, C, K, R, S, H, W, st, p = shape
+    if pool and (H, W) != (2, 2):
+        pytest.skip("pooled: the 2 x 2 map")
+    layer, w, m, x = _layer(dtype, shape, 93, 0.9)
+    rng = np.random.default_rng(7)
+    flat = x.reshape(-1)
+    where = rng.choice(flat.size, size=40, replace=False)
+    flat[where[:15]], flat[where[15:30]], flat[where[30:]] = np.inf, -np.inf, np.nan
+    layer.set_epilogue(None, maxpool=pool)
+    assert layer.get_kernel(N, H, W, st, p) == "matrix"
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref = oracle_ref(w, m, x, st, p, dtype)
+    xt = torch.from_numpy(x).cuda().to(torch.float16 if dtype == "f16" else torch.float32)
+    got = layer.forward(xt, st, p).float().cpu().numpy().astype(np.float64)
+    if pool:   # windows without a NaN (one with a NaN gives any of its values)
+        win = ref.reshape(N, K, H // 2, 2, W // 2, 2).transpose(0, 1, 2, 4, 3, 5).reshape(N, K, H // 2, W // 2, 4)
+        keep = ~np.isnan(win).any(-1)
+        got, ref = got[keep], np.where(np.isnan(win), -np.inf, win).max(-1)[keep]
+    assert not np.isfinite(ref).all()
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref))
+    assert np.array_equal(np.isneginf(got), np.isneginf(ref))
+    fin = np.isfinite(ref)
+    assert_close(got[fin], ref[fin], TOL[dtype], f"not finite {dtype} {shape}")
+    layer.close()
+
+
+@pytest.mark.parametrize("how", ["tiny", "huge", "late", "early", "zeros first", "rows apart"])
+def test_matrix_kernel_fp32_magnitudes(how):
+    """A workgroup takes the scale of its two binary16 pieces from its first chunk of channels; a later chunk that does not
+    fit it (late, zeros first) is done again.  "early": the first chunk is the largest by far, the error is relative to it.
+    Each output channel's weights have a scale of their own ("rows apart"): compared row by row."""
+    shape = (24, 64, 64, 3, 3, 14, 14, 1, 1)
+    layer, w, m, x = _layer("f32", shape, 94, 0.9)
+    if how == "tiny":
+        x *= np.float32(1e-25)
+    elif how == "huge":
+        x *= np.float32(1e25)
+    elif how == "late":
+        x[:, 40:] *= np.float32(1e6)
+    elif how == "early":
+        x[:, :16] *= np.float32(1e4)
+    elif how == "zeros first":
+        x[:, :48] = 0.0
+        x[:, 48:] *= np.float32(1e-6)
+    elif how == "rows apart":
+        from paper_2011_06295_amd import binding as B
+        w *= np.logspace(-12, 12, 64, dtype=np.float32)[:, None, None, None]
+        layer.close()
+        layer = B.SparseConv(w, m, dtype="f32")
+    assert layer.get_kernel(24, 14, 14, 1, 1) == "matrix"
+    ref = oracle_ref(w, m, x, 1, 1, "f32")
+    got = run_gpu(layer, x, 1, 1, "f32")
+    for k in range(64):
+        assert_close(got[:, k], ref[:, k], 2e-6, f"{how} row {k}")   # four times the largest error of an fp32 sum of this length
+    layer.close()
+
+
+def test_matrix_kernel_binary16_subnormals():
+    """Inputs and weights below binary16's normal range take part with their value."""
+    from paper_2011_06295_amd import binding as B
+    rng = np.random.default_rng(95)
+    shape = (40, 64, 65, 3, 3, 14, 14, 1, 1)
+    for xs, ws in ((2e-6, 1000.0), (1000.0, 2e-6)):
+        w, m, x = rand_layer(rng, *shape[:7], density=0.8)
+        w, x = w * np.float32(ws), x * np.float32(xs)
+        layer = B.SparseConv(w, m, dtype="f16")
+        assert layer.get_kernel(40, 14, 14, 1, 1) == "matrix"
+        assert_close(run_gpu(layer, x, 1, 1, "f16"), oracle_ref(w, m, x, 1, 1, "f16"), TOL["f16"], f"subnormal {xs} {ws}")
+        layer.close()
