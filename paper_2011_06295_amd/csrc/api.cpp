@@ -605,8 +605,16 @@ int sparse_conv_set_epilogue(sparse_conv_t h, const float* bias, unsigned flags)
     if (bias) {
         const int rc = sc::bind_device(h);
         if (rc != SC_OK) return rc;
-        hipError_t e = hipMalloc(reinterpret_cast<void**>(&d), sizeof(float) * (size_t)h->K);
-        if (e == hipSuccess) e = hipMemcpy(d, bias, sizeof(float) * (size_t)h->K, hipMemcpyHostToDevice);
+        // whole blocks of 32 channels, zeros behind the last: the matrix kernel reads them four at a time
+        std::vector<float> padded;
+        try {
+            padded.assign((size_t)(h->K + 31) / 32 * 32, 0.f);
+        } catch (...) {
+            return SC_ENOMEM;
+        }
+        std::copy(bias, bias + h->K, padded.begin());
+        hipError_t e = hipMalloc(reinterpret_cast<void**>(&d), sizeof(float) * padded.size());
+        if (e == hipSuccess) e = hipMemcpy(d, padded.data(), sizeof(float) * padded.size(), hipMemcpyHostToDevice);
         if (e != hipSuccess) {
             h->last_hip = (int)e;
             if (d) (void)hipFree(d);

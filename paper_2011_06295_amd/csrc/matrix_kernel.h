@@ -435,29 +435,76 @@ __global__ __launch_bounds__(256, 2) void matrix_kernel(const MatrixArgs a)
     const int kfirst = (kf0 + (KS > 1 ? wave / NP : 0)) * 32;                  // first output channel and
     const int ofirst = o0 + (wp * NP + (KS > 1 ? wave % NP : 0)) * 32;         // first output of the wavefront's sums
     const int krow0 = kfirst + half * 4;
-    auto finish = [&](float v, int k) __attribute__((always_inline)) {         // section 3: bias, then activation
-        if (a.bias) v += a.bias[k];
-        if (a.relu) v = v > 0.f ? v : 0.f;
-        return v;
+    // Bias and scale of the lane's 16 rows a fragment, before the first store: asked for at each row, a load would wait for
+    // all stores before it (loads and stores share one counter: 47 -> 33 us on a 256 -> 256 layer of 8 x 8 maps).
+    float4 bias[kMK][4];
+    int4 rexp[kSplit ? kMK : 1][4];
+#pragma unroll
+    for (int mk = 0; mk < kMK; ++mk)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int k = (kfirst + mk * 32 < a.KF * 32 ? kfirst + mk * 32 : 0) + q * 8 + half * 4;   // (the arrays hold whole blocks of 32)
+            bias[mk][q] = a.bias ? *reinterpret_cast<const float4*>(a.bias + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+            if constexpr (kSplit) rexp[mk][q] = *reinterpret_cast<const int4*>(a.row_exp + k);
+        }
+    auto at4 = [](const auto& v, int i) __attribute__((always_inline)) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; };
+    auto finish = [&](float v, float b) __attribute__((always_inline)) {       // section 3: bias, then activation
+        v += b;
+        return a.relu ? (v > 0.f ? v : 0.f) : v;
+    };
+    auto scaled = [&](float v, int mk, int i) __attribute__((always_inline)) {
+        if constexpr (kSplit) v = ldexpf(v, -xexp - at4(rexp[mk][i >> 2], i & 3));
+        return finish(v, at4(bias[mk][i >> 2], i & 3));
     };
     if (!a.pool) {
+        // binary16: four neighbouring lanes exchange their values of four rows, so that each stores four outputs of one row
+        // (8 bytes; wherever four outputs never straddle images and the output starts at a multiple of 8 bytes)
+        const bool wide = sizeof(T) == 2 && (a.EF & 3) == 0 && (reinterpret_cast<unsigned long long>(y) & 7) == 0;
 #pragma unroll
         for (int np = 0; np < kNP; ++np) {
             const int o = ofirst + np * 32 + (lane & 31);
             const int u = fdiv(o, a.fd_EF);
             const bool valid = o < a.nout && !((bad >> np) & 1u);
             T* to = y + ((size_t)u * a.K + krow0) * a.EF + (o - u * a.EF);
+            if (sizeof(T) == 2 && wide && __ballot((bad >> np) & 1u) == 0) {
+                const int r = lane & 3;
+                T* row = to - r + (size_t)r * a.EF;              // row r of the four, first output of the four
+#pragma unroll
+                for (int mk = 0; mk < kMK; ++mk)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        unsigned pair[2];                        // rows 0 and 1, rows 2 and 3 of the lane's own output
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            const _Float16 v0 = (_Float16)scaled(acc[mk][np][q * 4 + 2 * h], mk, q * 4 + 2 * h);
+                            const _Float16 v1 = (_Float16)scaled(acc[mk][np][q * 4 + 2 * h + 1], mk, q * 4 + 2 * h + 1);
+                            unsigned short b0, b1;
+                            __builtin_memcpy(&b0, &v0, 2);
+                            __builtin_memcpy(&b1, &v1, 2);
+                            pair[h] = (unsigned)b0 | ((unsigned)b1 << 16);
+                        }
+                        unsigned of[4];                          // row r of output p
+#define SC_OF(p)                                                                                                         \
+    {                                                                                                                    \
+        const unsigned lo_ = (unsigned)__builtin_amdgcn_mov_dpp((int)pair[0], (p) * 0x55, 0xf, 0xf, true);               \
+        const unsigned hi_ = (unsigned)__builtin_amdgcn_mov_dpp((int)pair[1], (p) * 0x55, 0xf, 0xf, true);               \
+        const unsigned both_ = r & 2 ? hi_ : lo_;                                                                        \
+        of[p] = r & 1 ? both_ >> 16 : both_ & 0xffffu;                                                                   \
+    }
+                        SC_OF(0) SC_OF(1) SC_OF(2) SC_OF(3)
+#undef SC_OF
+                        const int kr = mk * 32 + q * 8;
+                        if (krow0 + kr + r < a.K && valid)
+                            *reinterpret_cast<uint2*>(row + (size_t)kr * a.EF) = make_uint2(of[0] | (of[1] << 16), of[2] | (of[3] << 16));
+                    }
+                continue;
+            }
 #pragma unroll
             for (int mk = 0; mk < kMK; ++mk)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const int kr = mk * 32 + (i >> 2) * 8 + (i & 3);
-                    const int k = krow0 + kr;
-                    if (k < a.K && valid) {
-                        float v = acc[mk][np][i];
-                        if constexpr (kSplit) v = ldexpf(v, -xexp - a.row_exp[k]);
-                        to[(size_t)kr * a.EF] = (T)finish(v, k);
-                    }
+                    if (krow0 + kr < a.K && valid) to[(size_t)kr * a.EF] = (T)scaled(acc[mk][np][i], mk, i);
                 }
         }
     } else {
@@ -485,19 +532,15 @@ __global__ __launch_bounds__(256, 2) void matrix_kernel(const MatrixArgs a)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const int kr = mk * 32 + (i >> 2) * 8 + (i & 3);
-                    const int k = krow0 + kr;
                     float v = acc[mk][np][i];
                     float below = v;
                     if (apart == 1) below = acc[mk][np + 1 < kNP ? np + 1 : np][i];
                     if (apart == 2) below = acc[mk][np + 2 < kNP ? np + 2 : np][i];
                     if (!apart) below = __shfl_xor(v, F);
                     v = below > v ? below : v;
-                    const float right = __shfl_xor(v, 1);
+                    const float right = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xf, 0xf, true));   // lane ^ 1
                     v = right > v ? right : v;
-                    if (k < a.K && valid) {
-                        if constexpr (kSplit) v = ldexpf(v, -xexp - a.row_exp[k]);
-                        to[(size_t)kr * plane_out] = (T)finish(v, k);
-                    }
+                    if (krow0 + kr < a.K && valid) to[(size_t)kr * plane_out] = (T)scaled(v, mk, i);
                 }
         }
     }
@@ -524,7 +567,7 @@ __global__ __launch_bounds__(256, 2) void matrix_kernel(const MatrixArgs a)
                     }
                     T* to = a.pool ? y + ((size_t)u * a.K + k) * ((size_t)(a.E >> 1) * (a.F >> 1)) + (size_t)(i0 >> 1) * (a.F >> 1) + (j0 >> 1)
                                    : y + ((size_t)u * a.K + k) * a.EF + rem;
-                    *to = (T)finish(v, k);
+                    *to = (T)finish(v, a.bias ? a.bias[k] : 0.f);
                 }
             }
         }

@@ -25,6 +25,7 @@ def _layer(dtype, shape, seed, density):
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
 def test_matrix_kernel_against_the_oracle(dtype, shape):
+    import torch
     layer, w, m, x = _layer(dtype, shape, 91, 0.9)
     N, C, K, R, S, H, W, st, p = shape
     # (the fp32 sums of a 5 x 5 filter's chunk are not exact enough for so few channels: the tile kernel's)
@@ -33,6 +34,12 @@ def test_matrix_kernel_against_the_oracle(dtype, shape):
     ref = oracle_ref(w, m, x, st, p, dtype)
     bias = np.random.default_rng(5).standard_normal(K).astype(np.float32)
     assert_close(run_gpu(layer, x, st, p, dtype), ref, TOL[dtype], f"{dtype} {shape}")
+    # an output that starts off the alignment of the wide stores: the same bits
+    xt = torch.from_numpy(x).cuda().to(torch.float16 if dtype == "f16" else torch.float32)
+    y = layer.forward(xt, st, p)
+    odd = torch.full((y.numel() + 2,), float("nan"), dtype=y.dtype, device="cuda")
+    layer.forward(xt, st, p, out=odd[1:-1].view(y.shape))
+    assert torch.equal(odd[1:-1].view(y.shape), y) and torch.isnan(odd[[0, -1]]).all()
     layer.set_epilogue(bias, relu=True)
     assert_close(run_gpu(layer, x, st, p, dtype), np.maximum(ref + bias[None, :, None, None], 0.0), TOL[dtype], f"bias, ReLU {dtype} {shape}")
     layer.close()
