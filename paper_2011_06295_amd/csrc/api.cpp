@@ -56,10 +56,10 @@ bool automatic(const Launch& l)
     return !(l.V || l.WP || l.WK || l.KW || l.Cc || l.lds_budget || l.LP || l.kblocks || l.store || l.lanes || l.csplit);
 }
 
-// The matrix kernel is taken where its estimate lies below this share of the tile kernel's.  Over 168 layers (see
-// estimate_matrix) binary16 loses nowhere up to 1.0; fp32, where the two kernels are closer, loses up to 16 % in three of
-// its 90 layers at 0.9 and nowhere at 0.8.
-constexpr double kMatrixMargin16 = 0.95, kMatrixMargin32 = 0.8;
+// The matrix kernel is taken where its estimate lies below this share of the tile kernel's.  Over 208 layers (see
+// estimate_matrix) binary16 loses nowhere up to 1.0; fp32, where the two kernels are closer, loses up to 25 % in five layers
+// at 0.9 and nowhere at 0.7 (1.07 times faster in the mean at either).
+constexpr double kMatrixMargin16 = 0.95, kMatrixMargin32 = 0.75;
 
 // The tile kernel's cheapest configuration for the geometry (the search takes most of a first call's time on the host:
 // done once).  A geometry that the tile kernel cannot plan is refused here, whichever kernel would run.
@@ -605,16 +605,8 @@ int sparse_conv_set_epilogue(sparse_conv_t h, const float* bias, unsigned flags)
     if (bias) {
         const int rc = sc::bind_device(h);
         if (rc != SC_OK) return rc;
-        // whole blocks of 32 channels, zeros behind the last: the matrix kernel reads them four at a time
-        std::vector<float> padded;
-        try {
-            padded.assign((size_t)(h->K + 31) / 32 * 32, 0.f);
-        } catch (...) {
-            return SC_ENOMEM;
-        }
-        std::copy(bias, bias + h->K, padded.begin());
-        hipError_t e = hipMalloc(reinterpret_cast<void**>(&d), sizeof(float) * padded.size());
-        if (e == hipSuccess) e = hipMemcpy(d, padded.data(), sizeof(float) * padded.size(), hipMemcpyHostToDevice);
+        hipError_t e = hipMalloc(reinterpret_cast<void**>(&d), sizeof(float) * (size_t)h->K);
+        if (e == hipSuccess) e = hipMemcpy(d, bias, sizeof(float) * (size_t)h->K, hipMemcpyHostToDevice);
         if (e != hipSuccess) {
             h->last_hip = (int)e;
             if (d) (void)hipFree(d);

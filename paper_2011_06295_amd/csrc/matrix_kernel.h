@@ -6,7 +6,7 @@
 // 16 input channels x 32 outputs.  At 90 % sparsity nine tenths of the products are with zeros, yet it is the faster way:
 // the tile kernel is bound by its LDS reads (16 bytes for 4 to 8 multiply-adds a lane) at 30 to 40 TFLOP/s of stored
 // weights, where this kernel does 600 to 1000 TFLOP/s of all weights in binary16 (256 -> 512 channels, 28 x 28, batch 128,
-// 90 %: 569 us by the tile kernel, 229 us here) and 200 to 300 in fp32 (256 -> 256, 14 x 14, batch 256, 70 %: 430 -> 191 us).
+// 90 %: 569 us by the tile kernel, 225 us here) and 200 to 330 in fp32 (256 -> 256, 14 x 14, batch 256, 70 %: 431 -> 181 us).
 //
 // Tile.  A workgroup of four wavefronts owns consecutive outputs of the batch and keeps, chunk by chunk of channels, the
 // lattice elements they touch in LDS, 8 channels of one position to a 16-byte element: a tap is an LDS offset, so the
@@ -116,8 +116,13 @@ __device__ __forceinline__ bool finite(float v) { return __builtin_fabsf(v) <= 3
 
 }  // namespace
 
+// Wavefronts a SIMD holds at least: the smallest variant (1 x 1 layers mostly, which load and store more than they multiply)
+// fits 128 registers but for one, and four of it are faster than three (64 -> 256 channels, 56 x 56, binary16: 71 and 79 us).
 template <typename T, int MK, int NP, int AHEAD, int FLY, int KS>
-__global__ __launch_bounds__(256, 2) void matrix_kernel(const MatrixArgs a)
+constexpr int kResident = sizeof(T) == 2 && MK * NP == 4 && AHEAD == 2 && FLY <= 2 && KS == 1 ? 4 : 2;
+
+template <typename T, int MK, int NP, int AHEAD, int FLY, int KS>
+__global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void matrix_kernel(const MatrixArgs a)
 {
     using raw = typename Raw<T>::type;
     constexpr bool kSplit = sizeof(T) == 4;
@@ -141,6 +146,19 @@ __global__ __launch_bounds__(256, 2) void matrix_kernel(const MatrixArgs a)
     const int wk = KS == 1 ? wave & (a.WK - 1) : 0, wp = KS == 1 ? wave >> a.logWK : 0;
     const int ks = KS == 1 ? 0 : wave;
     const int kf0 = (kb * a.WK + wk) * MK;      // first block of 32 output channels of this wavefront
+
+    // Bias and scale of the workgroup's rows, in LDS for the store step: loaded from memory there they would cost a latency
+    // each workgroup, and at each row wait for the stores before it (loads and stores share one counter).
+    const int rows = (KS == 1 ? a.WK : 1) * MK * 32;
+    float* row_bias = reinterpret_cast<float*>(smem + a.meet_at + 64);
+    int* row_exp = reinterpret_cast<int*>(smem + a.meet_at + 64) + rows;
+    float my_bias = 0.f;      // (a row a thread; on their way while the first chunk's inputs are)
+    if (tid < rows && kb * rows + tid < a.K) {
+        if (a.bias) my_bias = a.bias[kb * rows + tid];
+        if constexpr (kSplit) row_exp[tid] = a.row_exp[kb * rows + tid];
+    }
+    if constexpr (kSplit)     // (no register to spare for it there)
+        if (tid < rows) row_bias[tid] = my_bias;
 
     // outputs of the tile and where their receptive fields start in the lattice
     const int o0 = tile * a.PT;
@@ -309,6 +327,8 @@ __global__ __launch_bounds__(256, 2) void matrix_kernel(const MatrixArgs a)
             }
         }
         deposit(0, 0);
+        if constexpr (!kSplit)
+            if (tid < rows) row_bias[tid] = my_bias;
         __syncthreads();
 
         auto chunk = [&](int ch, auto more) __attribute__((always_inline)) {
@@ -435,100 +455,67 @@ __global__ __launch_bounds__(256, 2) void matrix_kernel(const MatrixArgs a)
     const int kfirst = (kf0 + (KS > 1 ? wave / NP : 0)) * 32;                  // first output channel and
     const int ofirst = o0 + (wp * NP + (KS > 1 ? wave % NP : 0)) * 32;         // first output of the wavefront's sums
     const int krow0 = kfirst + half * 4;
-    // Bias and scale of the lane's 16 rows a fragment, before the first store: asked for at each row, a load would wait for
-    // all stores before it (loads and stores share one counter: 47 -> 33 us on a 256 -> 256 layer of 8 x 8 maps).
-    float4 bias[kMK][4];
-    int4 rexp[kSplit ? kMK : 1][4];
-#pragma unroll
-    for (int mk = 0; mk < kMK; ++mk)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int k = (kfirst + mk * 32 < a.KF * 32 ? kfirst + mk * 32 : 0) + q * 8 + half * 4;   // (the arrays hold whole blocks of 32)
-            bias[mk][q] = a.bias ? *reinterpret_cast<const float4*>(a.bias + k) : make_float4(0.f, 0.f, 0.f, 0.f);
-            if constexpr (kSplit) rexp[mk][q] = *reinterpret_cast<const int4*>(a.row_exp + k);
-        }
-    auto at4 = [](const auto& v, int i) __attribute__((always_inline)) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; };
     auto finish = [&](float v, float b) __attribute__((always_inline)) {       // section 3: bias, then activation
         v += b;
         return a.relu ? (v > 0.f ? v : 0.f) : v;
     };
-    auto scaled = [&](float v, int mk, int i) __attribute__((always_inline)) {
-        if constexpr (kSplit) v = ldexpf(v, -xexp - at4(rexp[mk][i >> 2], i & 3));
-        return finish(v, at4(bias[mk][i >> 2], i & 3));
-    };
-    if (!a.pool) {
-        // binary16: four neighbouring lanes exchange their values of four rows, so that each stores four outputs of one row
-        // (8 bytes; wherever four outputs never straddle images and the output starts at a multiple of 8 bytes)
-        const bool wide = sizeof(T) == 2 && (a.EF & 3) == 0 && (reinterpret_cast<unsigned long long>(y) & 7) == 0;
+    // What the table holds for the lane's 16 rows of a fragment, in registers before the fragment's first store (read
+    // inside the branches below, each of them would wait for its own).
+    const int table_row = kfirst - kb * rows + half * 4;
+    float4 bias[4];
+    int4 rexp[4];
+    auto take_rows = [&](int mk) __attribute__((always_inline)) {
 #pragma unroll
-        for (int np = 0; np < kNP; ++np) {
-            const int o = ofirst + np * 32 + (lane & 31);
-            const int u = fdiv(o, a.fd_EF);
-            const bool valid = o < a.nout && !((bad >> np) & 1u);
-            T* to = y + ((size_t)u * a.K + krow0) * a.EF + (o - u * a.EF);
-            if (sizeof(T) == 2 && wide && __ballot((bad >> np) & 1u) == 0) {
-                const int r = lane & 3;
-                T* row = to - r + (size_t)r * a.EF;              // row r of the four, first output of the four
-#pragma unroll
-                for (int mk = 0; mk < kMK; ++mk)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        unsigned pair[2];                        // rows 0 and 1, rows 2 and 3 of the lane's own output
-#pragma unroll
-                        for (int h = 0; h < 2; ++h) {
-                            const _Float16 v0 = (_Float16)scaled(acc[mk][np][q * 4 + 2 * h], mk, q * 4 + 2 * h);
-                            const _Float16 v1 = (_Float16)scaled(acc[mk][np][q * 4 + 2 * h + 1], mk, q * 4 + 2 * h + 1);
-                            unsigned short b0, b1;
-                            __builtin_memcpy(&b0, &v0, 2);
-                            __builtin_memcpy(&b1, &v1, 2);
-                            pair[h] = (unsigned)b0 | ((unsigned)b1 << 16);
-                        }
-                        unsigned of[4];                          // row r of output p
-#define SC_OF(p)                                                                                                         \
-    {                                                                                                                    \
-        const unsigned lo_ = (unsigned)__builtin_amdgcn_mov_dpp((int)pair[0], (p) * 0x55, 0xf, 0xf, true);               \
-        const unsigned hi_ = (unsigned)__builtin_amdgcn_mov_dpp((int)pair[1], (p) * 0x55, 0xf, 0xf, true);               \
-        const unsigned both_ = r & 2 ? hi_ : lo_;                                                                        \
-        of[p] = r & 1 ? both_ >> 16 : both_ & 0xffffu;                                                                   \
-    }
-                        SC_OF(0) SC_OF(1) SC_OF(2) SC_OF(3)
-#undef SC_OF
-                        const int kr = mk * 32 + q * 8;
-                        if (krow0 + kr + r < a.K && valid)
-                            *reinterpret_cast<uint2*>(row + (size_t)kr * a.EF) = make_uint2(of[0] | (of[1] << 16), of[2] | (of[3] << 16));
-                    }
-                continue;
+        for (int q = 0; q < 4; ++q) {
+            bias[q] = *reinterpret_cast<const float4*>(row_bias + table_row + mk * 32 + q * 8);
+            asm volatile("" : "+v"(bias[q].x), "+v"(bias[q].y), "+v"(bias[q].z), "+v"(bias[q].w));
+            if constexpr (kSplit) {
+                rexp[q] = *reinterpret_cast<const int4*>(row_exp + table_row + mk * 32 + q * 8);
+                asm volatile("" : "+v"(rexp[q].x), "+v"(rexp[q].y), "+v"(rexp[q].z), "+v"(rexp[q].w));
             }
+        }
+    };
+    auto at4 = [](const auto& v, int i) __attribute__((always_inline)) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; };
+    auto scaled = [&](float v, int i) __attribute__((always_inline)) {
+        if constexpr (kSplit) v = ldexpf(v, -xexp - at4(rexp[i >> 2], i & 3));
+        return finish(v, at4(bias[i >> 2], i & 3));
+    };
 #pragma unroll
-            for (int mk = 0; mk < kMK; ++mk)
+    for (int mk = 0; mk < kMK; ++mk) {
+        take_rows(mk);
+        if (!a.pool) {
+#pragma unroll
+            for (int np = 0; np < kNP; ++np) {
+                const int o = ofirst + np * 32 + (lane & 31);
+                const int u = fdiv(o, a.fd_EF);
+                const bool valid = o < a.nout && !((bad >> np) & 1u);
+                T* to = y + ((size_t)u * a.K + krow0) * a.EF + (o - u * a.EF);
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const int kr = mk * 32 + (i >> 2) * 8 + (i & 3);
-                    if (krow0 + kr < a.K && valid) to[(size_t)kr * a.EF] = (T)scaled(acc[mk][np][i], mk, i);
+                    if (krow0 + kr < a.K && valid) to[(size_t)kr * a.EF] = (T)scaled(acc[mk][np][i], i);
                 }
-        }
-    } else {
-        // 2 x 2 maximum: the wavefront's outputs hold whole pairs of rows of F outputs (the planner's condition).  The
-        // value below is F / 32 registers or F lanes away, the one to the right one lane.  (Scale, bias and activation
-        // are monotonic: they are applied to the largest of the four sums.)
-        const int F = a.F, apart = F >> 5;
-        const size_t plane_out = (size_t)(a.E >> 1) * (F >> 1);
+            }
+        } else {
+            // 2 x 2 maximum: the wavefront's outputs hold whole pairs of rows of F outputs (the planner's condition).  The
+            // value below is F / 32 registers or F lanes away, the one to the right one lane.  (Scale, bias and activation
+            // are monotonic: they are applied to the largest of the four sums.)
+            const int F = a.F, apart = F >> 5;
+            const size_t plane_out = (size_t)(a.E >> 1) * (F >> 1);
 #pragma unroll
-        for (int np = 0; np < kNP; ++np) {
-            if (apart && ((np / apart) & 1)) continue;
-            unsigned wrong = bad >> np;
-            if (apart == 1 && np + 1 < kNP) wrong |= bad >> (np + 1 < kNP ? np + 1 : 0);
-            if (apart == 2 && np + 2 < kNP) wrong |= bad >> (np + 2 < kNP ? np + 2 : 0);
-            wrong &= 1u;
-            if (!apart) wrong |= (unsigned)__shfl_xor((int)wrong, F);
-            wrong |= (unsigned)__shfl_xor((int)wrong, 1);
-            const int o = ofirst + np * 32 + (lane & 31);
-            const int u = fdiv(o, a.fd_EF);
-            const int rem = o - u * a.EF, i0 = fdiv(rem, a.fd_F), j0 = rem - i0 * F;
-            const bool valid = o < a.nout && !wrong && !((i0 | j0) & 1);
-            T* to = y + ((size_t)u * a.K + krow0) * plane_out + (size_t)(i0 >> 1) * (F >> 1) + (j0 >> 1);
-#pragma unroll
-            for (int mk = 0; mk < kMK; ++mk)
+            for (int np = 0; np < kNP; ++np) {
+                if (apart && ((np / apart) & 1)) continue;
+                unsigned wrong = bad >> np;
+                if (apart == 1 && np + 1 < kNP) wrong |= bad >> (np + 1 < kNP ? np + 1 : 0);
+                if (apart == 2 && np + 2 < kNP) wrong |= bad >> (np + 2 < kNP ? np + 2 : 0);
+                wrong &= 1u;
+                if (!apart) wrong |= (unsigned)__shfl_xor((int)wrong, F);
+                wrong |= (unsigned)__shfl_xor((int)wrong, 1);
+                const int o = ofirst + np * 32 + (lane & 31);
+                const int u = fdiv(o, a.fd_EF);
+                const int rem = o - u * a.EF, i0 = fdiv(rem, a.fd_F), j0 = rem - i0 * F;
+                const bool valid = o < a.nout && !wrong && !((i0 | j0) & 1);
+                T* to = y + ((size_t)u * a.K + krow0) * plane_out + (size_t)(i0 >> 1) * (F >> 1) + (j0 >> 1);
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const int kr = mk * 32 + (i >> 2) * 8 + (i & 3);
@@ -540,8 +527,9 @@ __global__ __launch_bounds__(256, 2) void matrix_kernel(const MatrixArgs a)
                     v = below > v ? below : v;
                     const float right = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xf, 0xf, true));   // lane ^ 1
                     v = right > v ? right : v;
-                    if (krow0 + kr < a.K && valid) to[(size_t)kr * plane_out] = (T)scaled(v, mk, i);
+                    if (krow0 + kr < a.K && valid) to[(size_t)kr * plane_out] = (T)scaled(v, i);
                 }
+            }
         }
     }
     // ---- outputs whose receptive field holds a value that is not finite: the zeros of the dense table met it as well.

@@ -123,7 +123,7 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     p.nchunks = (groups + CG - 1) / CG;
     long long lds = (long long)(p.nchunks > 1 ? 2 : 1) * CG * p.EB * 64 * 16 * pieces;
     if (KS > 1) lds = std::max(lds, (long long)KS * MK * NP * 16 * 64 * 4);   // where the four sums of a pair meet
-    lds += 64;
+    lds += 64 + 8 * 32 * MK * WK;             // what the wavefronts tell each other, bias and scale of the rows
     if (lds > kMaxLds) return false;
     p.lds_bytes = (int)lds;
     p.kblocks = (K + 32 * MK * WK - 1) / (32 * MK * WK);
@@ -136,18 +136,17 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
 namespace {
 
 // Rough time of one launch in microseconds.  Structure and constants are fitted to the measured times of every split of
-// 168 layers (the 32-pixel VGG-16's, those of larger networks, and random ones: 1 x 1, 1-D, 3 x 3, 5 x 5, stride 2, first
-// layers, batches of 1 to 256): 13 % rms of the logarithm, the cheapest by estimate 3 % (fp32: 4 %) slower than the fastest
+// 208 layers (the 32-pixel VGG-16's, those of larger networks, and random ones: 1 x 1, 1-D, 3 x 3, 5 x 5, stride 2, first
+// layers, batches of 1 to 256): 13 % rms of the logarithm, the cheapest by estimate 3 % slower than the fastest
 // measured in the mean.  In clocks of 2.1 GHz:
-//  * A step costs its matrix instructions (48 clocks each over the workgroups resident on the CU, fp32 61; 32 at the nominal
-//    rate), but never less than a wavefront's own chain of loads and instructions.
-//  * A chunk's staging blocks (64 lattice elements x 8 channels) cost 180 (247) clocks each; a third of the shorter of
+//  * A step costs its matrix instructions (51 to 53 clocks each over the workgroups resident on the CU; 32 at the nominal rate), but never less than a wavefront's own chain of loads and instructions.
+//  * A chunk's staging blocks (64 lattice elements x 8 channels) cost 169 (fp32: 242) clocks each; a third of the shorter of
 //    multiplying and staging is not hidden behind the longer.
 //  * Workgroups run in rounds of what is resident; a partly filled last round after full ones is a little shorter.
 double estimate_matrix(const MatrixPlan& p, int RS, bool split)
 {
     struct Clocks { double fixed, chain, chain_mf, mf, chunk, stage_chunk, stage, pair, tail; };
-    static const Clocks k16 = {10960, 221, 30.7, 47.7, 472, 180, 180, 790, 0.83}, k32 = {13940, 414, 8.9, 61.1, 94, 124, 247, 2650, 0.98};
+    static const Clocks k16 = {10570, 267, 21.0, 51.4, 556, 169, 169, 845, 0.83}, k32 = {9630, 235, 44.9, 52.9, 42, 10, 242, 1756, 0.88};
     const Clocks& k = split ? k32 : k16;
     const int conc_max = std::min(2, kMaxLds / p.lds_bytes);      // registers allow two workgroups a CU
     const double mf = p.MK * p.NP * (split ? 3 : 1), own = (double)(p.CG / 2 / p.KS) * RS;
@@ -216,7 +215,7 @@ void fill_matrix_args(const MatrixWeights& m, const MatrixPlan& p, int K, int C,
     a.WK = p.WK;
     a.logWK = p.WK == 4 ? 2 : p.WK == 2 ? 1 : 0;
     a.mask_words = m.mask_words;
-    a.meet_at = p.lds_bytes - 64;
+    a.meet_at = p.lds_bytes - 64 - 8 * 32 * p.MK * p.WK;
     a.CG = p.CG; a.EB = p.EB; a.nchunks = p.nchunks;
     a.own_groups = p.CG / 2 / p.KS;
     a.own_steps = a.own_groups * a.RS;
