@@ -102,10 +102,13 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     if (nout >= (1ll << 31) - 4096 || (long long)g.N * p.Hs * p.Wp + (long long)(R + 1) * p.Wp + 4096 >= (1ll << 31)) return false;
     p.nout = (int)nout;
     p.ntiles = (int)((nout + p.PT - 1) / p.PT);
-    // the lattice elements a tile spans depend only on its first output's place in its image, of which there are EF
+    // the lattice elements a tile spans depend only on its first output's place in its image, which repeats after
+    // EF / gcd(PT, EF) tiles
+    long long gcd = EF;
+    for (long long r = p.PT % EF; r;) { const long long t = gcd % r; gcd = r; r = t; }
     auto lattice = [&](long long o) { return (o / EF * p.Hs + o % EF / p.F * g.stride) * (long long)p.Wp + o % p.F * g.stride; };
     long long span = 0;
-    for (long long t = 0; t < std::min<long long>(p.ntiles, EF + 1); ++t) {
+    for (long long t = 0; t < std::min<long long>(p.ntiles, EF / gcd); ++t) {
         const long long a = t * p.PT, b = std::min<long long>(nout, a + p.PT) - 1;
         span = std::max(span, lattice(b) - lattice(a));
     }
