@@ -356,6 +356,8 @@ def run_workload(name, args, steps, warmup, brief):
             "gflops": round(2 * roofs["macs"] / t / 1e9, 1),
             "bound": bound[0], "roof_frac": round(bound[1] / t, 4),
             "hbm_GBs": round(roofs["hbm_bytes"] / t / 1e9, 1), "lds_GBs": round(roofs["lds_bytes"] / t / 1e9, 1),
+            # "matrix": the layer runs on the matrix cores (roof_frac and the rates stay those of the stored weights' work)
+            "kernel": r.layer.get_kernel(N, r.spec.H, r.spec.W, r.spec.stride, r.spec.pad),
             "launch": {k: v for k, v in r.layer.get_launch(N, r.spec.H, r.spec.W, r.spec.stride, r.spec.pad).items()
                        if k in ("V", "WP", "WK", "KW", "Cc", "LP", "kblocks", "store", "lanes", "csplit", "grid", "lds_bytes", "threads")},
         })
@@ -398,7 +400,7 @@ def run_workload(name, args, steps, warmup, brief):
     if measured:
         roofline["traffic_source"] = measured[1]
         roofline["traffic_over_algorithmic"] = measured[0] / (sums["hbm_bytes"] / nl)
-    roofline["kernel"] = "sc::tile_kernel"
+    roofline["kernel"] = ", ".join(f"sc::{k}_kernel" for k in sorted({l["kernel"] for l in layers}, reverse=True))
     roofline["avg_launch_us"] = avg_launch_s * 1e6
     roofline["launches_per_step"] = nl
     roofline["hbm_frac"] = sums["hbm_bytes"] / nl / avg_launch_s / HBM_PEAK

@@ -124,7 +124,8 @@ class Network:
             s = run.spec
             d = run.layer.get_launch(self.work.N, s.H, s.W, s.stride, s.pad)
             entry = {"route": self.route[li],
-                     "launch": [d["V"], d["WP"], d["WK"], d["KW"], d["Cc"], 0, d["LP"], d["kblocks"], d["store"], d["lanes"],
+                     "launch": [] if getattr(run, "automatic", False) else
+                               [d["V"], d["WP"], d["WK"], d["KW"], d["Cc"], 0, d["LP"], d["kblocks"], d["store"], d["lanes"],
                                 d["csplit"]]}
             entry.update(self.timings.get(li, {}))
             table[self.table_key(li)] = entry
@@ -217,6 +218,8 @@ class Network:
             tuned = [d["V"], d["WP"], d["WK"], d["KW"], d["Cc"], 0, d["LP"], d["kblocks"], d["store"], d["lanes"], d["csplit"]]
             run.layer.set_launch([])                 # back to the estimate (this discards the measured choice)
             cands = [tuned]
+            if run.layer.get_kernel(*geom(run)) == "matrix":   # nothing pinned: the kernel an automatic forward takes
+                cands.append([])
             for c in run.layer.rank_launches(*geom(run), max_candidates=top):
                 if c[:8] + c[9:] not in [k[:8] + k[9:] for k in cands]:
                     cands.append(c)
@@ -225,9 +228,13 @@ class Network:
                 cands = [cands[i] for _, i in brief[:3]]
             timed = sorted(((time_layer(li, c, steps), i, c) for i, c in enumerate(cands)), key=lambda e: e[:2])
             for t, i, c in list(timed[:2]):
+                if not c:
+                    continue
                 other = c[:8] + [3 - c[8]] + c[9:]
                 timed.append((time_layer(li, other, steps), len(timed), other))
-            run.layer.set_launch(min(timed, key=lambda e: e[:2])[2])
+            chosen = min(timed, key=lambda e: e[:2])[2]
+            run.layer.set_launch(chosen)
+            run.automatic = not chosen
         return [run.layer.get_launch(*geom(run)) for run in self.runs]
 
     def make_buffer_sets(self, min_bytes: int = 512 << 20, max_sets: int = 16) -> int:
