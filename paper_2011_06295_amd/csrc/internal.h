@@ -246,6 +246,7 @@ struct MatrixWeights {
     int KF = 0;            // blocks of 32 output channels
     int steps = 0;         // steps of one block: groups of 16 input channels * taps
     int mask_words = 0;
+    int longest = 0;       // stored weights of the fullest output channel
     std::vector<uint16_t> image;
     std::vector<int> row_exp;     // [KF * 32]
     std::vector<unsigned> mask;   // [K][mask_words], one bit per column (c*R + r)*S + s: stored
@@ -263,7 +264,9 @@ struct MatrixPlan {
     int CG;          // groups of 8 input channels a chunk holds
     int EB;          // blocks of 64 lattice elements a tile spans
     int PT, Wp, Hs, E, F, nout, ntiles, kblocks, nchunks, grid, lds_bytes;
+    int images;      // images the lattice elements of a tile belong to, at most
 };
+constexpr int kImageWindowBytes = 24;   // fp32: LDS bytes for each of them
 // Fills p for the given split; false if the kernel cannot run it.
 bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, int MK, int NP, int WK, int KS,
                  int CG, MatrixPlan& p);
@@ -282,7 +285,10 @@ struct MatrixArgs {
     const int* row_exp;
     const unsigned* mask;
     int mask_words;
-    int meet_at;           // LDS byte offset of the word per wavefront they exchange
+    int meet_at;           // LDS byte offset of what the wavefronts exchange, then the rows' bias and scale, then
+                           // (fp32) the images' windows and a bit per lattice element
+    int images;            // images a tile's lattice elements belong to, at most
+    float sum_floor;       // fp32: sums below this may be short of what inputs below their image's window lack
     int relu, pool;
     int N, C, H, W, K, E, F, EF, stride, pad, R, S, RS;
     int Wp, Hs;

@@ -37,6 +37,7 @@ void pack_matrix_weights(const Csr& csr, int C, int R, int S, bool split, Matrix
     m.mask.assign((size_t)K * m.mask_words, 0u);
     m.row_exp.assign((size_t)m.KF * 32, 0);
     for (int k = 0; k < K; ++k) {
+        m.longest = std::max(m.longest, csr.rowptr[k + 1] - csr.rowptr[k]);
         if (split) {   // the largest weight of the row lands in [2^14, 2^15)
             float top = 0.f;
             for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) top = std::max(top, std::fabs(csr.val32[i]));
@@ -117,6 +118,7 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     p.EB = (int)((elems + 63) / 64);
     // source offsets are 31-bit byte offsets from the tile's first image
     const long long images = ((long long)p.EB * 64 / p.Wp + 1) / p.Hs + 2;
+    p.images = (int)images;
     if (images * C * g.H * g.W * elem_bytes >= (1ll << 31)) return false;
     if (CG / 2 > kMatrixGroups || CG / 2 % KS) return false;
     p.CG = CG;
@@ -127,6 +129,7 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     long long lds = (long long)(p.nchunks > 1 ? 2 : 1) * CG * p.EB * 64 * 16 * pieces;
     if (KS > 1) lds = std::max(lds, (long long)KS * MK * NP * 16 * 64 * 4);   // where the four sums of a pair meet
     lds += 64 + 8 * 32 * MK * WK;             // what the wavefronts tell each other, bias and scale of the rows
+    if (pieces == 2) lds += images * kImageWindowBytes + p.EB * 8;
     if (lds > kMaxLds) return false;
     p.lds_bytes = (int)lds;
     p.kblocks = (K + 32 * MK * WK - 1) / (32 * MK * WK);
@@ -218,7 +221,11 @@ void fill_matrix_args(const MatrixWeights& m, const MatrixPlan& p, int K, int C,
     a.WK = p.WK;
     a.logWK = p.WK == 4 ? 2 : p.WK == 2 ? 1 : 0;
     a.mask_words = m.mask_words;
-    a.meet_at = p.lds_bytes - 64 - 8 * 32 * p.MK * p.WK;
+    a.meet_at = p.lds_bytes - 64 - 8 * 32 * p.MK * p.WK - (m.pieces == 2 ? p.images * kImageWindowBytes + p.EB * 8 : 0);
+    a.images = p.images;
+    // an input below its window is cut to multiples of 2^-36, and its low piece (up to 2^-25) misses the weight's low piece
+    // (2^-11 of it): 2^-37 + 2^-36 of each weight, which is below 2^15, and all that times 2^23
+    a.sum_floor = 6.f * (float)m.longest;
     a.CG = p.CG; a.EB = p.EB; a.nchunks = p.nchunks;
     a.own_groups = p.CG / 2 / p.KS;
     a.own_steps = a.own_groups * a.RS;

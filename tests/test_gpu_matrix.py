@@ -4,6 +4,7 @@ that are not finite, and fp32 inputs of every magnitude (they are cut into two s
 import numpy as np
 import pytest
 
+import oracle
 from helpers import TOL, assert_close, rand_layer
 from test_gpu_parity import oracle_ref, run_gpu
 
@@ -48,7 +49,6 @@ def test_matrix_kernel_against_the_oracle(dtype, shape):
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
 @pytest.mark.parametrize("H,N,C,K", [(2, 1200, 256, 64), (4, 400, 256, 40), (8, 64, 128, 64), (16, 33, 64, 96), (32, 9, 48, 64), (64, 5, 40, 64)])
 def test_matrix_kernel_pooled_store(dtype, H, N, C, K):
-    import oracle
     import torch
     shape = (N, C, K, 3, 3, H, H, 1, 1)
     layer, w, m, x = _layer(dtype, shape, 92, 1.0)
@@ -124,6 +124,81 @@ def test_matrix_kernel_fp32_magnitudes(how):
     got = run_gpu(layer, x, 1, 1, "f32")
     for k in range(64):
         assert_close(got[:, k], ref[:, k], 2e-6, f"{how} row {k}")   # four times the largest error of an fp32 sum of this length
+    layer.close()
+
+
+# channels in one chunk for each of four wavefronts; in four; in several chunks of wavefronts that share the tile out
+RANGES = [(24, 64, 64, 3, 3, 14, 14, 1, 1), (64, 256, 256, 3, 3, 4, 4, 1, 1), (60, 240, 250, 1, 1, 15, 14, 1, 0)]
+
+
+def _each_output(layer, w, m, x, st, p, what):
+    """Every output against the sum of its own terms' magnitudes: what a sum of fp32 numbers in any order keeps, 2^-24 for
+    each term (and 2^-21 for the pieces a value is held in)."""
+    K, _, R, S = w.shape
+    csr = oracle.csr_encode(w, m)
+    ref, size = (v.astype(np.float64) for v in oracle.sparse_conv(csr, x, K, R, S, st, p, want_abs=True))
+    got = run_gpu(layer, x, st, p, "f32")
+    terms = int(np.diff(csr[0]).max())
+    bad = ~(np.abs(got - ref) <= size * (terms + 8) * 2.0 ** -24 + terms * 2.0 ** -149)
+    assert not bad.any(), (what, int(bad.sum()), float((np.abs(got - ref) / np.maximum(size, 1e-300)).max()))
+    return got, ref
+
+
+@pytest.mark.parametrize("ratio", [1e4, 1e6, 1e8, 1e12, 1e25])
+@pytest.mark.parametrize("shape", RANGES, ids=lambda s: "x".join(map(str, s)))
+def test_matrix_kernel_fp32_images_do_not_depend_on_their_neighbours(shape, ratio):
+    """Tiles reach over several images: a loud one takes nothing from the others, not even a bit."""
+    N, C, K, R, S, H, W, st, p = shape
+    layer, w, m, x = _layer("f32", shape, 96, 0.9)
+    assert layer.get_kernel(N, H, W, st, p) == "matrix"
+    x[::3] *= np.float32(ratio)
+    got, ref = _each_output(layer, w, m, x, st, p, ratio)
+    quiet = np.arange(N) % 3 != 0
+    assert np.linalg.norm(got[quiet] - ref[quiet]) <= 1e-6 * np.linalg.norm(ref[quiet])   # (an fp32 sum in order: 4e-7)
+    x[::3] = 0.0
+    assert np.array_equal(run_gpu(layer, x, st, p, "f32")[quiet], got[quiet])
+    layer.close()
+
+
+@pytest.mark.parametrize("how", ["corner", "channel", "spread", "far apart", "tiny", "subnormal", "late", "late and quiet", "dead first", "one pixel"])
+@pytest.mark.parametrize("shape", RANGES, ids=lambda s: "x".join(map(str, s)))
+def test_matrix_kernel_fp32_inputs_of_every_size(shape, how):
+    """Finite inputs of any range within one image, output by output: those that do not see the loud inputs keep fp32's
+    precision, those under which a row has no stored weight count for nothing in it."""
+    N, C, K, R, S, H, W, st, p = shape
+    rng = np.random.default_rng(97)
+    w, m, x = rand_layer(rng, N, C, K, R, S, H, W, density=0.9)
+    if how == "corner":
+        x[:, :, :2, :2] *= np.float32(1e10)
+    elif how == "channel":
+        x[:, 5] *= np.float32(1e10)
+        m[::2, 5] = 0
+    elif how == "spread":        # fifty binary orders of magnitude
+        x *= np.exp2(rng.uniform(-25, 25, x.shape)).astype(np.float32)
+    elif how == "far apart":     # more than one sum holds
+        x *= np.where(rng.random(x.shape) < 0.02, 1e20, 1e-15).astype(np.float32)
+    elif how == "tiny":
+        x *= np.float32(2.0 ** -119)
+        w *= np.float32(2.0 ** 12)
+    elif how == "subnormal":
+        x *= np.exp2(rng.uniform(-149, -120, x.shape)).astype(np.float32)
+        w *= np.float32(2.0 ** 60)
+    elif how == "late":
+        x[:, C // 2:] *= np.float32(1e7)
+    elif how == "late and quiet":
+        x[:, C // 2:] *= np.float32(1e-9)
+        m[::2, :C // 2] = 0
+    elif how == "dead first":
+        x[:, :3 * C // 4] = 0.0
+        x[:, 3 * C // 4:] *= np.float32(1e-12)
+    elif how == "one pixel":
+        keep = x[:, C - 1, H - 1, W - 1].copy()
+        x[:] = 0.0
+        x[:, C - 1, H - 1, W - 1] = keep
+    from paper_2011_06295_amd import binding as B
+    layer = B.SparseConv(w, m, dtype="f32")
+    assert layer.get_kernel(N, H, W, st, p) == "matrix"
+    _each_output(layer, w, m, x, st, p, how)
     layer.close()
 
 
