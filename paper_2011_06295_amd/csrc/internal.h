@@ -288,7 +288,7 @@ struct MatrixArgs {
     int meet_at;           // LDS byte offset of what the wavefronts exchange, then the rows' bias and scale, then
                            // (fp32) the images' windows and a bit per lattice element
     int images;            // images a tile's lattice elements belong to, at most
-    float sum_floor;       // fp32: sums below this may be short of what inputs below their image's window lack
+    int longest;           // stored weights of the fullest output channel
     int relu, pool;
     int N, C, H, W, K, E, F, EF, stride, pad, R, S, RS;
     int Wp, Hs;

@@ -27,13 +27,13 @@
 // multiplied (the fourth is 2^-22 of the result or less), smallest first.  binary16 has few exponents, so the weights of an
 // output channel are scaled by a power of two of their own, and the inputs by one for each image of the tile, taken from the
 // image's largest magnitude in the first chunk.  The low piece of an input is kept times 2^12 and meets the high piece of the
-// weight times 2^-12: so 28 binary orders of magnitude hold every bit of both pieces (kWindow; without that factor 16).
+// weight times 2^-12: so 29 binary orders of magnitude hold every value to 2^-23 (kWindow; without that factor 17).
 //  * An input above its image's window is left out, and its chunk is multiplied once more with only what was left out, under
 //    a scale that fits it, as often as something is left.
-//  * The product with an input below the window is good to 2^-35.4 of the weight.  The input's place is marked, and if an
-//    output that sees a marked place has a sum so small that this could be more than 2^-23 of its terms, those inputs are taken
-//    out of the sums again and multiplied in the same way.  (Normally distributed inputs: one tile in a thousand has such an
-//    input, and next to none repeats a chunk for it.)
+//  * An input below the window takes part with 11 bits.  Its place is marked, and if an output that sees a marked place has a
+//    sum so small that what such inputs lack could be more than 2^-23 of its terms, they are taken out of the sums again and
+//    multiplied in the same way.  (Normally distributed inputs: one tile in two thousand has such an input, and one in some
+//    ten thousand repeats a chunk for it.)
 // So every output has fp32's precision whatever else is in its tile, and no image's sums depend on another image.  Measured
 // (256 -> 256, 14 x 14, batch 256, 70 %): 172 us with one scale for the tile and no such care, 177 with it; 779 us for inputs
 // spread evenly over 50 binary orders of magnitude, 320 if the second half of the channels is a million times the first.
@@ -57,6 +57,7 @@ namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float float16v __attribute__((ext_vector_type(16)));
+typedef unsigned uint4v __attribute__((ext_vector_type(4)));
 
 #define SC_LDS __attribute__((address_space(3)))
 #pragma clang diagnostic push
@@ -131,25 +132,45 @@ __device__ __forceinline__ float stored_sum(const MatrixArgs& a, int u, int k, i
 }
 
 // fp32 inputs.  A window of binary orders of magnitude [base, base + kWindow) (biased exponents) whose values, scaled to
-// 2^-13 .. 2^15, are held by the two pieces to 2^-23 of them, the low one times kLowScale: its last bit then stands at 2^-36,
-// which is the last bit of any fp32 number from 2^-13 up, so the pieces are the same whatever the window.  The first window
-// leaves room for chunks kRoom orders above the first.
-constexpr int kWindow = 28, kRoom = 2;
+// 2^-14 .. 2^15, are held by the two pieces to 2^-23 of them, the low one times kLowScale.  In it the high piece is a normal
+// number: the matrix instruction takes subnormal ones as what they are, but aligns their products as if they were 2^-14, and
+// drops what then lies below fp32 (2^-38 of the other factor).  The first window leaves room for chunks kRoom orders above the
+// first.
+constexpr int kWindow = 29, kRoom = 2;
 constexpr float kLowScale = 4096.f;
 constexpr int kDefaultTop = 134;      // nothing seen to take a window from: values below 2^7
 constexpr int kMaxApart = 64;         // windows further apart than this share no sum: the image's outputs are summed by themselves
 
-__device__ __forceinline__ float window_scale(int base) { return __uint_as_float((unsigned)(241 - base) << 23); }
-__device__ __forceinline__ int window_base(float scale) { return 241 - (int)(__float_as_uint(scale) >> 23); }
-// magnitudes (as bits) [low, high) of a window; the lowest one holds the subnormals too
-__device__ __forceinline__ unsigned window_low(int base) { return base <= 1 ? 1u : (unsigned)base << 23; }
+__device__ __forceinline__ float window_scale(int base) { return __uint_as_float((unsigned)(240 - base) << 23); }
+__device__ __forceinline__ int window_base(float scale) { return 240 - (int)(__float_as_uint(scale) >> 23); }
+// the lowest window that ends with the biased exponent `last`; subnormal inputs are below any
+__device__ __forceinline__ int window_ending(int last) { return last + 1 - kWindow > 1 ? last + 1 - kWindow : 1; }
+// magnitudes (as bits) [low, high) of a window
+__device__ __forceinline__ unsigned window_low(int base) { return (unsigned)base << 23; }
 __device__ __forceinline__ unsigned window_high(int base) { return (unsigned)(base + kWindow < 255 ? base + kWindow : 255) << 23; }
 
-// An input in two pieces under a window's scale.
-__device__ __forceinline__ void cut(float x, float scale, _Float16& hi, _Float16& lo)
+// Eight inputs in two pieces each under a window's scale.  (By hand: the compiler takes half as many instructions again.)
+__device__ __forceinline__ void cut(const float (&x)[8], float scale, half8& hi, half8& lo)
 {
-    hi = (_Float16)__builtin_fmaf(x, scale, 0.f);        // (an instruction each: the product of a power of two is exact)
-    lo = (_Float16)__builtin_fmaf((float)hi, -kLowScale, x * (scale * kLowScale));
+    uint4v high, low;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        unsigned h, l;
+        float t0, t1;
+        asm("v_fma_mixlo_f16 %0, %4, %6, 0\n\t"
+            "v_fma_mixhi_f16 %0, %5, %6, 0\n\t"
+            "v_mul_f32 %2, %4, %7\n\t"
+            "v_mul_f32 %3, %5, %7\n\t"
+            "v_fma_mixlo_f16 %1, %0, %8, %2 op_sel_hi:[1,0,0]\n\t"
+            "v_fma_mixhi_f16 %1, %0, %8, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\t"
+            "s_nop 0"
+            : "=&v"(h), "=&v"(l), "=&v"(t0), "=&v"(t1)
+            : "v"(x[2 * j]), "v"(x[2 * j + 1]), "v"(scale), "v"(scale * kLowScale), "s"(-kLowScale));
+        high[j] = h;
+        low[j] = l;
+    }
+    hi = __builtin_bit_cast(half8, high);
+    lo = __builtin_bit_cast(half8, low);
 }
 
 // The windows of one image of the tile, in LDS.
@@ -164,18 +185,28 @@ static_assert(sizeof(ImageWindow) == kImageWindowBytes, "what the plan reserves 
 // The window of the next round: from the largest magnitude that is left, those above the first window before those below.
 __device__ __forceinline__ void next_window(ImageWindow& w)
 {
-    const unsigned edge = window_high(window_base(w.first));
+    const int first = window_base(w.first);
     const unsigned top = w.above ? w.above : w.below;
-    if (!top) {
-        w.low = w.high = 0u;
-        return;
-    }
-    const int base = (int)(top >> 23) + 1 - kWindow > 1 ? (int)(top >> 23) + 1 - kWindow : 1;
+    w.low = w.high = 0u;
+    if (!top) return;
+    const int base = window_ending((int)(top >> 23));
+    const unsigned low = window_low(base), high = window_high(base);
     w.scale = window_scale(base);
-    w.low = w.above && window_low(base) < edge ? edge : window_low(base);
-    w.high = w.above ? window_high(base) : window_low(window_base(w.first)) < window_high(base) ? window_low(window_base(w.first)) : window_high(base);
-    if (w.above) w.above = 0u;
-    else w.below = 0u;
+    if (w.above) {
+        w.low = low < window_high(first) ? window_high(first) : low;
+        w.high = high;
+        w.above = 0u;
+    } else {
+        w.low = top < low ? 1u : low;                       // (subnormal ones: a window by themselves)
+        w.high = top < low ? low : high < window_low(first) ? high : window_low(first);
+        w.below = 0u;
+    }
+}
+// The window's values can be added to the sums: it is near enough to the first one, and its values are normal numbers.
+__device__ __forceinline__ bool summable(const ImageWindow& w)
+{
+    const int by = window_base(w.scale) - window_base(w.first);
+    return by >= -kMaxApart && by <= kMaxApart && w.high > window_low(1);
 }
 
 __device__ __forceinline__ bool finite(float v) { return __builtin_fabsf(v) <= 3.402823466e38f; }
@@ -221,7 +252,8 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
     ImageWindow* images = reinterpret_cast<ImageWindow*>(smem + a.meet_at + 64 + 8 * rows);   // kSplit
     unsigned* marks = reinterpret_cast<unsigned*>(images + a.images);                          // kSplit: a bit per lattice element
     unsigned* meet = reinterpret_cast<unsigned*>(smem + a.meet_at);   // kSplit: [0..1] chunks (modulo 64) with values that the
-                                                                      // first windows do not hold, [2] some sum is short of them
+                                                                      // first windows do not hold, [2] some sum is short of them,
+                                                                      // [3] how many values are below them
     float my_bias = 0.f;      // (a row a thread; on their way while the first chunk's inputs are)
     if (tid < rows && kb * rows + tid < a.K) {
         if (a.bias) my_bias = a.bias[kb * rows + tid];
@@ -232,7 +264,7 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
         if (tid < rows) row_bias[tid] = my_bias;
         for (int i = tid; i < a.images; i += 256) images[i].above = 0u;
         for (int i = tid; i < a.EB * 2; i += 256) marks[i] = 0u;
-        if (tid < 3) meet[tid] = 0u;
+        if (tid < 4) meet[tid] = 0u;
     }
 
     // outputs of the tile and where their receptive fields start in the lattice
@@ -319,19 +351,17 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
         half8 hi, lo;
         if constexpr (kSplit) {
             unsigned least = ~0u;               // of twice the magnitude bits, less one: zeros are the largest
-            float most = 0.f;
+            float most = 0.f, x[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                _Float16 h, l;
-                cut(__uint_as_float(src[j]), scale, h, l);
-                hi[j] = h;
-                lo[j] = l;
+                x[j] = __uint_as_float(src[j]);
                 const unsigned twice = ((unsigned)src[j] << 1) - 1u;
                 least = twice < least ? twice : least;
             }
 #pragma unroll
             for (int j = 0; j < 8; j += 2)      // (fmaxf would first make every operand a quiet number)
-                asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(most) : "v"(src[j]), "v"(src[j + 1]));
+                asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(most) : "v"(x[j]), "v"(x[j + 1]));
+            cut(x, scale, hi, lo);
             const int base = window_base(scale);
             outside = outside | (most >= __uint_as_float(window_high(base))) | (least < ((unsigned)base << 24) - 1u);
             lds_write(to + part, lo);
@@ -342,9 +372,10 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
         lds_write(to, hi);
     };
     // kSplit: this wavefront's blocks of a chunk once more, value by value.  First round: without what is above its image's
-    // window.  Later rounds: of the values above the first window, or of those below it, only what is in the present window;
-    // between the two, under an empty window, those below it with their signs turned, which takes them out of the sums.  The
-    // largest of what is left is remembered, and in the first round the places of those below the windows.  (Values that are not finite belong to the first round.)
+    // window, and with 11 bits of what is below it, which is marked and counted.  Later rounds: of the values above the first
+    // window, or of those below it, only what is in the present window; between the two, under an empty window, those below it
+    // as they were first but with their signs turned, which takes them out of the sums (11 bits by 11: exactly).  The largest
+    // of what is left is remembered.  (Values that are not finite belong to the first round.)
     auto restage = [&](int ch, int buf, bool first) __attribute__((always_inline)) {
         const MatrixArgs& a = late_arguments();
 #pragma unroll 1
@@ -358,27 +389,34 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
             const unsigned low = w.low, high = w.high, bottom = window_low(base), top = window_high(base);
             const bool lows = !first & (low < top), out = lows & (low == high) & (low != 0u);
             unsigned left = 0u;
-            bool low_one = false;
-            half8 hi, lo;
+            int strays = 0;
+            float x[8];
+            half8 hi, lo, eleven;                                 // eleven: values below the window, low pieces only
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const unsigned bits = (unsigned)src[j], m = bits & 0x7fffffffu;
-                const bool mine = first | (lows ? m < bottom : (m >= top) & (m < 0x7f800000u));
-                const bool in = first ? (m < top) | (m >= 0x7f800000u) : mine & (out | (m - low < high - low));
-                const bool rest = first ? !in : mine & (m < low);
-                _Float16 h, l;
-                cut(in ? __uint_as_float(out ? bits ^ 0x80000000u : bits) : 0.f, w.scale, h, l);
-                hi[j] = h;
-                lo[j] = l;
+                const float v = __uint_as_float(out ? bits ^ 0x80000000u : bits);
+                const bool stray = (m < bottom) & (m != 0u), high_one = (m >= top) & (m < 0x7f800000u);
+                const bool in = first ? !stray & !high_one : (lows ? stray & !out : high_one) & (m - low < high - low);
+                x[j] = in ? v : 0.f;
+                const float y = ((first | out) & stray) ? v * (w.scale * kLowScale) : 0.f;
+                eleven[j] = (_Float16)(__builtin_fabsf(y) >= 0x1p-14f ? y : 0.f);
+                const bool rest = first ? high_one : (lows ? stray : high_one) & (m < low);
                 left = (rest & (m > left)) ? m : left;
-                low_one = low_one | ((m < bottom) & (m != 0u));
+                strays += stray;
             }
+            cut(x, w.scale, hi, lo);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) lo[j] += eleven[j];       // (one of the two is zero)
             lds_write(to, hi);
             lds_write(to + part, lo);
             if (left) atomicMax(lows ? &w.below : &w.above, left);
             if (first) {
-                if (low_one) atomicOr(&marks[eb * 2 + (lane >> 5)], 1u << (lane & 31));
-                if (low_one | (left != 0u)) atomicOr(&meet[ch >> 5 & 1], 1u << (ch & 31));
+                if (strays) {
+                    atomicOr(&marks[eb * 2 + (lane >> 5)], 1u << (lane & 31));
+                    atomicAdd(&meet[3], (unsigned)strays);
+                }
+                if (strays | (int)left) atomicOr(&meet[ch >> 5 & 1], 1u << (ch & 31));
             }
         }
     };
@@ -427,8 +465,8 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
         __syncthreads();
         for (int i = tid; i < a.images; i += 256) {
             const unsigned top = images[i].above;
-            const int ends = top ? (int)(top >> 23) + 1 + kRoom : kDefaultTop;
-            const int base = (ends < 255 ? ends : 255) - kWindow > 1 ? (ends < 255 ? ends : 255) - kWindow : 1;
+            const int last = top ? (int)(top >> 23) + kRoom : kDefaultTop - 1;
+            const int base = window_ending(last < 254 ? last : 254);
             images[i] = ImageWindow{window_scale(base), window_scale(base), window_low(base), window_high(base), 0u, 0u};
         }
         __syncthreads();
@@ -536,7 +574,8 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
         return __builtin_amdgcn_readfirstlane((int)some) != 0;
     };
     // kSplit: an output of the lane sees a marked input, and a sum of it is so small that what the products with such inputs
-    // lack may be more than 2^-23 of its terms' magnitudes, which are no less than the sum
+    // lack may be more than 2^-23 of its terms' magnitudes, which are no less than the sum: of each, 2^-11 for the low piece's
+    // rounding and as much for the weight's low piece, of less than 2^-14 times a weight of less than 2^15
     auto short_sums = [&](const MatrixArgs& a) __attribute__((always_inline)) {
         unsigned sees = 0;
 #pragma unroll
@@ -546,6 +585,8 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
                 const int e = (int)((at[np] - lds0) % plane >> 4) + t / a.S * a.Wp + t % a.S;
                 sees |= (marks[e >> 5] >> (e & 31) & 1u) << np;
             }
+        const unsigned strays = meet[3];
+        const float floor = 16384.f * (float)(strays < (unsigned)a.longest ? strays : (unsigned)a.longest);
         bool yes = false;
 #pragma unroll
         for (int np = 0; np < NP; ++np)
@@ -553,7 +594,7 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
             for (int mk = 0; mk < MK; ++mk)
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
-                    yes |= (sees >> np & 1u) & !(__builtin_fabsf(sum[mk][np][i]) >= a.sum_floor) &
+                    yes |= (sees >> np & 1u) & !(__builtin_fabsf(sum[mk][np][i]) >= floor) &
                            ((kf0 + mk) * 32 + half * 4 + (i >> 2) * 8 + (i & 3) < a.K);
         return yes;
     };
@@ -598,10 +639,8 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
 #pragma unroll
                 for (int np = 0; np < NP; ++np) {
                     const ImageWindow& w = images[image_of(o0 + (wp * NP + np) * 32 + (lane & 31), a)];
-                    const int by = window_base(w.scale) - window_base(w.first);
-                    const bool far = by > kMaxApart || by < -kMaxApart;
-                    apart[np] = far ? 0.f : __uint_as_float((unsigned)(127 + by) << 23);
-                    if (far && w.high) bad |= 1u << np;
+                    apart[np] = summable(w) ? __uint_as_float((unsigned)(127 + window_base(w.scale) - window_base(w.first)) << 23) : 0.f;
+                    if (w.high && !summable(w)) bad |= 1u << np;
                 }
                 last = 0;
                 while (!(again >> (last & 63) & 1u)) ++last;
@@ -684,7 +723,7 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
     };
     auto at4 = [](const auto& v, int i) __attribute__((always_inline)) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; };
     auto unscale = [&](int o) __attribute__((always_inline)) {                 // kSplit: the exponent its sums lack, but for the row's
-        if constexpr (kSplit) return window_base(images[image_of(o, la)].first) - 114;
+        if constexpr (kSplit) return window_base(images[image_of(o, la)].first) - 113;
         return 0;
     };
     auto scaled = [&](float v, int i, int exponent) __attribute__((always_inline)) {

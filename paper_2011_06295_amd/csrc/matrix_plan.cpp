@@ -223,9 +223,7 @@ void fill_matrix_args(const MatrixWeights& m, const MatrixPlan& p, int K, int C,
     a.mask_words = m.mask_words;
     a.meet_at = p.lds_bytes - 64 - 8 * 32 * p.MK * p.WK - (m.pieces == 2 ? p.images * kImageWindowBytes + p.EB * 8 : 0);
     a.images = p.images;
-    // an input below its window is cut to multiples of 2^-36, and its low piece (up to 2^-25) misses the weight's low piece
-    // (2^-11 of it): 2^-37 + 2^-36 of each weight, which is below 2^15, and all that times 2^23
-    a.sum_floor = 6.f * (float)m.longest;
+    a.longest = m.longest;
     a.CG = p.CG; a.EB = p.EB; a.nchunks = p.nchunks;
     a.own_groups = p.CG / 2 / p.KS;
     a.own_steps = a.own_groups * a.RS;
