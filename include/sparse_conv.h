@@ -279,7 +279,9 @@ int sparse_conv_check_plan(sparse_conv_t h, int N, int H, int W, int stride, int
 /* Which kernel sparse_conv_forward takes for a geometry: *kernel receives 0 for the tile kernel (always, if
  * sparse_conv_set_launch has pinned anything), 1 for the matrix kernel, which multiplies a dense table of the weights,
  * zeros included, on the matrix cores, and which an automatic choice takes where it is estimated (sparse_conv_autotune:
- * measured) to be faster.  Returns as sparse_conv_get_launch.  Needs no GPU. */
+ * measured) to be faster.  There fp32 numbers are sums of two binary16 numbers under scales that fit them: each product of
+ * a stored weight with a finite input of any size is within 2^-21 of itself, and they are summed in fp32.  Returns as
+ * sparse_conv_get_launch.  Needs no GPU. */
 int sparse_conv_get_kernel(sparse_conv_t h, int N, int H, int W, int stride, int pad, int* kernel);
 
 /* The tile kernel's launch configuration for a geometry (in force unless sparse_conv_get_kernel says 1): [0] V .. [4] Cc, [5] the LDS

@@ -4,7 +4,6 @@
 #include <algorithm>
 #include <atomic>
 #include <mutex>
-#include <cmath>
 #include <cstdint>
 #include <cstring>
 #include <new>
@@ -93,14 +92,10 @@ int get_route(sparse_conv_s* h, const Geometry& g, const Route** out)
     if (rc != SC_OK) return rc;
     *out = r;
     if (r->decided) return SC_OK;
-    if (h->finite_weights < 0) {   // an infinite weight would meet the zeros of every output's receptive field
-        h->finite_weights = 1;
-        for (float w : h->csr.val32)
-            if (!(std::fabs(w) <= 3.402823466e38f)) h->finite_weights = 0;
-    }
     const bool half = h->dtype == SC_F16;
+    if (h->matrix_holds < 0) h->matrix_holds = matrix_holds(h->csr, !half) ? 1 : 0;
     double us = 0.0;
-    if (h->finite_weights && choose_matrix(h->csr, h->C, h->R, h->S, elem_bytes(h), g, r->tile.pool != 0, r->tile.csplit, r->plan, &us)) {
+    if (h->matrix_holds && choose_matrix(h->csr, h->C, h->R, h->S, elem_bytes(h), g, r->tile.pool != 0, r->tile.csplit, r->plan, &us)) {
         // stores are not hidden behind short rows: the tile kernel's estimate leaves them out
         const double terms = (double)h->csr.colidx.size() / h->K;
         const double mbytes = (double)g.N * ((double)h->C * g.H * g.W + (double)h->K * r->plan.E * r->plan.F) * elem_bytes(h) * 1e-6;
@@ -113,7 +108,7 @@ int get_route(sparse_conv_s* h, const Geometry& g, const Route** out)
                 h->matrix_id = g_next_id.fetch_add(1, std::memory_order_relaxed);
             }
             // (both forward entry points take the same kernel: the table has to fit the static scratch)
-            r->matrix = h->matrix->bytes() + 1024 <= kStaticScratchBytes;
+            r->matrix = h->matrix->bytes() + 6 * 256 <= kStaticScratchBytes;
         }
     }
     r->decided = true;
@@ -295,19 +290,25 @@ int forward_matrix(sparse_conv_s* h, const MatrixPlan& p, const void* input, voi
                    bool use_static)
 {
     const MatrixWeights& m = *h->matrix;
-    const size_t b_image = m.image.size() * sizeof(uint16_t), b_exp = m.row_exp.size() * sizeof(int), b_mask = m.mask.size() * sizeof(unsigned);
-    const size_t at_exp = round256(b_image), at_mask = at_exp + round256(b_exp);
+    struct { const void* from; size_t bytes, at; } parts[] = {
+        {m.image.data(), m.image.size() * sizeof(uint16_t), 0}, {m.row_exp.data(), m.row_exp.size() * sizeof(int), 0},
+        {m.mask.data(), m.mask.size() * sizeof(unsigned), 0}, {m.slots.data(), m.slots.size() * sizeof(MatrixWeights::Small), 0},
+        {m.small.data(), m.small.size() * sizeof(MatrixWeights::Small), 0}, {m.small_first.data(), m.small_first.size() * sizeof(int), 0}};
+    size_t total = 0;
+    for (auto& part : parts) {
+        part.at = total;
+        total += round256(part.bytes);
+    }
     unsigned char* d = static_cast<unsigned char*>(h->d_matrix);
     std::unique_lock<std::mutex> hold(g_static_lock, std::defer_lock);
     hipError_t he = hipSuccess;
     if (!use_static) {
         if (!d) {
             void* fresh = nullptr;
-            he = hipMalloc(&fresh, at_mask + b_mask);
+            he = hipMalloc(&fresh, total);
             d = static_cast<unsigned char*>(fresh);
-            if (he == hipSuccess) he = hipMemcpy(d, m.image.data(), b_image, hipMemcpyHostToDevice);
-            if (he == hipSuccess) he = hipMemcpy(d + at_exp, m.row_exp.data(), b_exp, hipMemcpyHostToDevice);
-            if (he == hipSuccess) he = hipMemcpy(d + at_mask, m.mask.data(), b_mask, hipMemcpyHostToDevice);
+            for (const auto& part : parts)
+                if (he == hipSuccess && part.bytes) he = hipMemcpy(d + part.at, part.from, part.bytes, hipMemcpyHostToDevice);
             if (he != hipSuccess) {
                 if (fresh) (void)hipFree(fresh);
                 h->last_hip = (int)he;
@@ -328,9 +329,8 @@ int forward_matrix(sparse_conv_s* h, const MatrixPlan& p, const void* input, voi
         if (holds != h->matrix_id) {
             holds = 0;
             hipStream_t s = static_cast<hipStream_t>(stream);
-            he = hipMemcpyAsync(d, m.image.data(), b_image, hipMemcpyHostToDevice, s);
-            if (he == hipSuccess) he = hipMemcpyAsync(d + at_exp, m.row_exp.data(), b_exp, hipMemcpyHostToDevice, s);
-            if (he == hipSuccess) he = hipMemcpyAsync(d + at_mask, m.mask.data(), b_mask, hipMemcpyHostToDevice, s);
+            for (const auto& part : parts)
+                if (he == hipSuccess && part.bytes) he = hipMemcpyAsync(d + part.at, part.from, part.bytes, hipMemcpyHostToDevice, s);
             if (he != hipSuccess) {
                 h->last_hip = (int)he;
                 return SC_EHIP;
@@ -342,8 +342,11 @@ int forward_matrix(sparse_conv_s* h, const MatrixPlan& p, const void* input, voi
     a.x = input;
     a.y = output;
     a.weights = d;
-    a.row_exp = reinterpret_cast<const int*>(d + at_exp);
-    a.mask = reinterpret_cast<const unsigned*>(d + at_mask);
+    a.row_exp = reinterpret_cast<const int*>(d + parts[1].at);
+    a.mask = reinterpret_cast<const unsigned*>(d + parts[2].at);
+    a.slots = reinterpret_cast<const MatrixWeights::Small*>(d + parts[3].at);
+    a.small = reinterpret_cast<const MatrixWeights::Small*>(d + parts[4].at);
+    a.small_first = reinterpret_cast<const int*>(d + parts[5].at);
     a.bias = h->d_bias;
     a.relu = (h->epilogue & SC_EPILOGUE_RELU) ? 1 : 0;
     a.pool = (h->epilogue & SC_EPILOGUE_MAXPOOL2) ? 1 : 0;

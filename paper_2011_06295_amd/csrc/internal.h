@@ -240,8 +240,15 @@ struct KernelArgs {
 // stored, cut into fragments of 32 output channels x 16 input channels of one tap (a step).  image: [block of 32 output
 // channels][group of 16 input channels][tap][piece][lane][8] binary16, lane l holding output channel l % 32 and input
 // channels 8 * (l / 32) .. + 7; behind it as much again as the last steps of the last block read ahead.  fp32 weights are
-// two binary16 pieces whose sum they are (to 2^-24 of the weight), after multiplication by 2^row_exp.
+// two binary16 pieces whose sum they are (to 2^-23 of the weight), after multiplication by 2^row_exp; those that pieces of
+// that scale do not hold (below 2^-2 after it, 2^-16 of their row's largest) stand in a list instead.
 struct MatrixWeights {
+    struct Small {
+        int row;           // in its block of 32 output channels; -1: none
+        int c, tap;
+        float weight;      // times 2^row_exp
+    };
+    static constexpr int kSlots = 4;
     int pieces = 1;        // binary16 numbers a weight is held in: 1, or 2 for fp32 layers
     int KF = 0;            // blocks of 32 output channels
     int steps = 0;         // steps of one block: groups of 16 input channels * taps
@@ -249,9 +256,18 @@ struct MatrixWeights {
     int longest = 0;       // stored weights of the fullest output channel
     std::vector<uint16_t> image;
     std::vector<int> row_exp;     // [KF * 32]
-    std::vector<unsigned> mask;   // [K][mask_words], one bit per column (c*R + r)*S + s: stored
-    size_t bytes() const { return image.size() * 2 + row_exp.size() * 4 + mask.size() * 4; }
+    std::vector<unsigned> mask;   // [K][mask_words], one bit per column (c*R + r)*S + s: stored in the image
+    std::vector<Small> slots;     // [KF][kSlots]: a block's first small weights
+    std::vector<Small> small;     // and the rest, in the order of their blocks
+    std::vector<int> small_first; // [KF + 1]: a block's first of the rest
+    size_t bytes() const
+    {
+        return image.size() * 2 + row_exp.size() * 4 + mask.size() * 4 + (slots.size() + small.size()) * sizeof(Small) + small_first.size() * 4;
+    }
 };
+// Whether the matrix kernel can multiply these weights: they are finite (an infinite one would meet the zeros of every
+// output's receptive field), and few are in the list of small ones.
+bool matrix_holds(const Csr& csr, bool split);
 void pack_matrix_weights(const Csr& csr, int C, int R, int S, bool split, MatrixWeights& out);
 
 // Tiles of the matrix kernel for one geometry.  A workgroup of four wavefronts owns PT consecutive outputs of the batch
@@ -284,9 +300,12 @@ struct MatrixArgs {
     const float* bias;     // [K] or null
     const int* row_exp;
     const unsigned* mask;
+    const MatrixWeights::Small* slots;   // fp32, like the next two
+    const MatrixWeights::Small* small;
+    const int* small_first;
     int mask_words;
     int meet_at;           // LDS byte offset of what the wavefronts exchange, then the rows' bias and scale, then
-                           // (fp32) the images' windows and a bit per lattice element
+                           // (fp32) the blocks' first small weights, the images' windows and a bit per lattice element
     int images;            // images a tile's lattice elements belong to, at most
     int longest;           // stored weights of the fullest output channel
     int relu, pool;
@@ -344,7 +363,7 @@ struct sparse_conv_s {
     std::unique_ptr<sc::MatrixWeights> matrix;  // made with the first geometry that takes the matrix kernel
     void* d_matrix = nullptr;                   // its device copy (owned): image, row_exp, mask
     unsigned long long matrix_id = 0;           // names it in the static device scratch
-    int finite_weights = -1;                    // every stored weight is finite (-1: not looked at yet)
+    int matrix_holds = -1;                      // the matrix kernel can multiply the weights (-1: not looked at yet)
     int last_hip = 0;
     int device = -1;           // HIP device that holds the handle's device buffers; -1 until the first is made
 };

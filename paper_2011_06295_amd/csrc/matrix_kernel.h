@@ -25,7 +25,8 @@
 //
 // fp32 layers.  A value is the sum of two binary16 numbers to 2^-23 of it; three of the four products of two such sums are
 // multiplied (the fourth is 2^-22 of the result or less), smallest first.  binary16 has few exponents, so the weights of an
-// output channel are scaled by a power of two of their own, and the inputs by one for each image of the tile, taken from the
+// output channel are scaled by a power of two of their own (those below 2^-16 of the largest, which two pieces do not hold, are
+// few: they stand in a list and are multiplied as fp32), and the inputs by one for each image of the tile, taken from the
 // image's largest magnitude in the first chunk.  The low piece of an input is kept times 2^12 and meets the high piece of the
 // weight times 2^-12: so 29 binary orders of magnitude hold every value to 2^-23 (kWindow; without that factor 17).
 //  * An input above its image's window is left out, and its chunk is multiplied once more with only what was left out, under
@@ -127,6 +128,17 @@ __device__ __forceinline__ float stored_sum(const MatrixArgs& a, int u, int k, i
             if constexpr (kParts == 2) weight = ldexpf(weight + (float)w[at + 512], -a.row_exp[k]);
             sum = __builtin_fmaf(weight, (float)x[((size_t)c * a.H + yy) * a.W + xx], sum);
         }
+    }
+    if constexpr (kParts == 2) {
+        auto add = [&](const MatrixWeights::Small& w1) {
+            const int r = w1.tap / a.S, yy = i * a.stride + r - a.pad, xx = j * a.stride + w1.tap - r * a.S - a.pad;
+            if (w1.row == (k & 31) && yy >= 0 && yy < a.H && xx >= 0 && xx < a.W)
+                sum = __builtin_fmaf(ldexpf(w1.weight, -a.row_exp[k]), (float)x[((size_t)w1.c * a.H + yy) * a.W + xx], sum);
+        };
+#pragma unroll 1
+        for (int e = 0; e < MatrixWeights::kSlots; ++e) add(a.slots[(k >> 5) * MatrixWeights::kSlots + e]);
+#pragma unroll 1
+        for (int e = a.small_first[k >> 5]; e < a.small_first[(k >> 5) + 1]; ++e) add(a.small[e]);
     }
     return sum;
 }
@@ -249,7 +261,9 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
     const int rows = (KS == 1 ? a.WK : 1) * MK * 32;
     float* row_bias = reinterpret_cast<float*>(smem + a.meet_at + 64);
     int* row_exp = reinterpret_cast<int*>(smem + a.meet_at + 64) + rows;
-    ImageWindow* images = reinterpret_cast<ImageWindow*>(smem + a.meet_at + 64 + 8 * rows);   // kSplit
+    // kSplit: the first small weights of the workgroup's blocks, the windows of its images
+    MatrixWeights::Small* slots = reinterpret_cast<MatrixWeights::Small*>(smem + a.meet_at + 64 + 8 * rows);
+    ImageWindow* images = reinterpret_cast<ImageWindow*>(slots + rows / 32 * MatrixWeights::kSlots);
     unsigned* marks = reinterpret_cast<unsigned*>(images + a.images);                          // kSplit: a bit per lattice element
     unsigned* meet = reinterpret_cast<unsigned*>(smem + a.meet_at);   // kSplit: [0..1] chunks (modulo 64) with values that the
                                                                       // first windows do not hold, [2] some sum is short of them,
@@ -262,6 +276,10 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
     if constexpr (kSplit)     // (no register to spare for it there)
     {
         if (tid < rows) row_bias[tid] = my_bias;
+        if (tid < rows / 32 * MatrixWeights::kSlots) {
+            const int at = kb * rows / 32 * MatrixWeights::kSlots + tid;
+            slots[tid] = at < a.KF * MatrixWeights::kSlots ? a.slots[at] : MatrixWeights::Small{-1, 0, 0, 0.f};
+        }
         for (int i = tid; i < a.images; i += 256) images[i].above = 0u;
         for (int i = tid; i < a.EB * 2; i += 256) marks[i] = 0u;
         if (tid < 4) meet[tid] = 0u;
@@ -606,6 +624,32 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
     if constexpr (kSplit)                             // (all chunks have been staged)
         again = ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)meet[1]) << 32) |
                 (unsigned)__builtin_amdgcn_readfirstlane((int)meet[0]);
+    // kSplit: the small weights are multiplied as fp32, two columns a product.  The inputs of the first ones are on their way
+    // during the last chunk.
+    bool few[MK];
+    float few_w[MK][2], few_x[MK][2][NP];
+    auto small_input = [&](const MatrixWeights::Small& w, int np, const MatrixArgs& a) __attribute__((always_inline)) {
+        const int o = o0 + (wp * NP + np) * 32 + (lane & 31), oo = o < a.nout ? o : a.nout - 1;
+        const int u = fdiv(oo, a.fd_EF), rem = oo - u * a.EF, i = fdiv(rem, a.fd_F), r = w.tap / a.S;
+        const int yy = i * a.stride + r - a.pad, xx = (rem - i * a.F) * a.stride + w.tap - r * a.S - a.pad;
+        const bool in = (w.row >= 0) & ((unsigned)yy < (unsigned)a.H) & ((unsigned)xx < (unsigned)a.W);
+        return in ? (float)static_cast<const T*>(a.x)[(((size_t)u * a.C + w.c) * a.H + yy) * a.W + xx] : 0.f;
+    };
+    if constexpr (kSplit) {
+#pragma unroll
+        for (int mk = 0; mk < MK; ++mk) {
+            const MatrixWeights::Small* mine = slots + (wk * MK + mk) * MatrixWeights::kSlots;
+            few[mk] = ks == 0 && __builtin_amdgcn_readfirstlane(mine->row) >= 0;
+            if (!few[mk]) continue;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const MatrixWeights::Small w = mine[q * 2 + half];
+                few_w[mk][q] = w.row == (lane & 31) ? w.weight : 0.f;
+#pragma unroll
+                for (int np = 0; np < NP; ++np) few_x[mk][q][np] = small_input(w, np, late_arguments());
+            }
+        }
+    }
     bool begun = false, short_of = false;             // short_of: the values below the windows are needed in full, and not yet looked for
     for (;;) {
         chunk(last, std::false_type{});
@@ -653,6 +697,38 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
         }
     }
     if constexpr (kSplit) {
+#pragma unroll
+        for (int mk = 0; mk < MK; ++mk) {
+            if (!few[mk]) continue;
+            const MatrixArgs& a = late_arguments();
+            float scale[NP];
+#pragma unroll
+            for (int np = 0; np < NP; ++np) scale[np] = images[image_of(o0 + (wp * NP + np) * 32 + (lane & 31), a)].first;
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int np = 0; np < NP; ++np)
+                    sum[mk][np] = __builtin_amdgcn_mfma_f32_32x32x2f32(few_w[mk][q], few_x[mk][q][np] * scale[np], sum[mk][np], 0, 0, 0);
+            const int end = a.small_first[kf0 + mk + 1];
+#pragma unroll 1
+            for (int e = a.small_first[kf0 + mk]; e < end; e += 8) {
+                float weight[4], x[4][NP];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int mine = e + q * 2 + half;
+                    MatrixWeights::Small w = a.small[mine < end ? mine : e];
+                    if (mine >= end) w.row = -1;
+                    weight[q] = w.row == (lane & 31) ? w.weight : 0.f;
+#pragma unroll
+                    for (int np = 0; np < NP; ++np) x[q][np] = small_input(w, np, a) * scale[np];
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int np = 0; np < NP; ++np)
+                        sum[mk][np] = __builtin_amdgcn_mfma_f32_32x32x2f32(weight[q], x[q][np], sum[mk][np], 0, 0, 0);
+            }
+        }
 #pragma unroll
         for (int mk = 0; mk < MK; ++mk)
 #pragma unroll

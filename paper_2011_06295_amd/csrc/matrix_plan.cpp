@@ -22,7 +22,40 @@ size_t image_at(const MatrixWeights& m, int RS, int k, int col)
     return (((size_t)(k / 32) * m.steps + step) * m.pieces) * 512 + lane * 8 + c % 8;
 }
 
+// The exponent that puts a row's largest weight in [2^14, 2^15).
+int row_exponent(const Csr& csr, int k)
+{
+    float top = 0.f;
+    for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) top = std::max(top, std::fabs(csr.val32[i]));
+    int ex = 0;
+    if (top > 0.f) (void)std::frexp(top, &ex), ex = 15 - ex;
+    return ex;
+}
+
+// A weight, scaled, of which two binary16 pieces keep less than 2^-23 of it, or the high one 2^-12 times as large less than
+// all its bits.
+bool small_weight(float scaled) { return scaled != 0.f && std::fabs(scaled) < 0.25f; }
+// Small weights a block of 32 rows may have: the first four are added at no cost that shows, eight more in about 2 us a tile.
+// Normally distributed weights have 4 in a block of 147456.
+constexpr int kMaxSmall = 32;
+
 }  // namespace
+
+bool matrix_holds(const Csr& csr, bool split)
+{
+    for (int k0 = 0; k0 < csr.K; k0 += 32) {
+        int small = 0;
+        for (int k = k0; k < std::min(csr.K, k0 + 32); ++k) {
+            for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i)
+                if (!std::isfinite(csr.val32[i])) return false;
+            if (!split) continue;
+            const int ex = row_exponent(csr, k);
+            for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) small += small_weight(std::ldexp(csr.val32[i], ex));
+        }
+        if (small > kMaxSmall) return false;
+    }
+    return true;
+}
 
 void pack_matrix_weights(const Csr& csr, int C, int R, int S, bool split, MatrixWeights& m)
 {
@@ -36,24 +69,33 @@ void pack_matrix_weights(const Csr& csr, int C, int R, int S, bool split, Matrix
     m.mask_words = (C * RS + 31) / 32;
     m.mask.assign((size_t)K * m.mask_words, 0u);
     m.row_exp.assign((size_t)m.KF * 32, 0);
+    m.small_first.assign(split ? (size_t)m.KF + 1 : 0, 0);
+    m.slots.assign(split ? (size_t)m.KF * m.kSlots : 0, {-1, 0, 0, 0.f});
     for (int k = 0; k < K; ++k) {
         m.longest = std::max(m.longest, csr.rowptr[k + 1] - csr.rowptr[k]);
-        if (split) {   // the largest weight of the row lands in [2^14, 2^15)
-            float top = 0.f;
-            for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) top = std::max(top, std::fabs(csr.val32[i]));
-            int ex = 0;
-            if (top > 0.f) (void)std::frexp(top, &ex), ex = 15 - ex;
-            m.row_exp[k] = ex;
-        }
+        if (split) m.row_exp[k] = row_exponent(csr, k);
         for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) {
             const int col = csr.colidx[i];
+            const float w = split ? std::ldexp(csr.val32[i], m.row_exp[k]) : csr.val32[i];
+            if (split && small_weight(w)) {
+                const MatrixWeights::Small s{k % 32, col / RS, col % RS, w};
+                MatrixWeights::Small *slot = &m.slots[(size_t)(k / 32) * m.kSlots], *end = slot + m.kSlots;
+                while (slot < end && slot->row >= 0) ++slot;
+                if (slot < end) {
+                    *slot = s;
+                } else {
+                    m.small.push_back(s);
+                    ++m.small_first[k / 32 + 1];
+                }
+                continue;
+            }
             m.mask[(size_t)k * m.mask_words + col / 32] |= 1u << (col % 32);
             uint16_t* to = &m.image[image_at(m, RS, k, col)];
-            const float w = split ? std::ldexp(csr.val32[i], m.row_exp[k]) : csr.val32[i];
             to[0] = float_to_half_rne(w);
             if (split) to[512] = float_to_half_rne(w - half_to_float(to[0]));
         }
     }
+    for (int b = 0; split && b < m.KF; ++b) m.small_first[b + 1] += m.small_first[b];
 }
 
 int check_matrix(const Csr& csr, int C, int R, int S, const MatrixWeights& m)
@@ -62,25 +104,40 @@ int check_matrix(const Csr& csr, int C, int R, int S, const MatrixWeights& m)
     if (m.KF != (csr.K + 31) / 32 || m.steps != (C + 15) / 16 * RS || m.mask_words != (C * RS + 31) / 32) return 10;
     if (m.image.size() != ((size_t)m.KF * m.steps + (size_t)kMatrixGroups * RS + 3) * m.pieces * 512) return 10;
     // 11: every stored weight is in its place; 12: and nothing else is in the table or the mask
-    size_t marked = 0;
+    size_t marked = 0, small = 0, listed = m.small.size();
+    for (const auto& s : m.slots) listed += s.row >= 0;
+    std::vector<int> used(m.KF, 0);
     std::vector<uint16_t> rest = m.image;
     for (int k = 0; k < csr.K; ++k)
         for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) {
             const int col = csr.colidx[i];
             const size_t at = image_at(m, RS, k, col);
+            const float scaled = std::ldexp(csr.val32[i], m.pieces == 2 ? m.row_exp[k] : 0);
+            if (m.pieces == 2 && small_weight(scaled)) {   // 13: every small weight is in a slot or in its block's part of the list
+                const int n = used[k / 32]++, at = m.small_first[k / 32] + n - m.kSlots;
+                if (n >= m.kSlots && at >= m.small_first[k / 32 + 1]) return 13;
+                const MatrixWeights::Small& s = n < m.kSlots ? m.slots[(size_t)(k / 32) * m.kSlots + n] : m.small[at];
+                ++small;
+                if (s.row != k % 32 || s.c * RS + s.tap != col || s.weight != scaled) return 13;
+                continue;
+            }
             if (!(m.mask[(size_t)k * m.mask_words + col / 32] >> (col % 32) & 1u)) return 11;
-            const float w = std::ldexp(csr.val32[i], m.pieces == 2 ? m.row_exp[k] : 0);
             const float is = half_to_float(m.image[at]) + (m.pieces == 2 ? half_to_float(m.image[at + 512]) : 0.f);
-            // two pieces: 2^-23 of the weight (22 bits and a sign), or half of binary16's smallest number
-            const float may = m.pieces == 2 ? std::max(std::fabs(w) * 0x1p-23f, 0x1p-25f) : 0.f;
-            if (!(std::fabs(is - w) <= may)) return 11;
+            // two pieces: 22 bits and a sign
+            if (!(std::fabs(is - scaled) <= (m.pieces == 2 ? std::fabs(scaled) * 0x1p-23f : 0.f))) return 11;
             rest[at] = 0;
             if (m.pieces == 2) rest[at + 512] = 0;
         }
     for (uint16_t h : rest)
         if (h) return 12;
     for (unsigned w : m.mask) marked += (size_t)__builtin_popcount(w);
-    return marked == csr.colidx.size() ? 0 : 12;
+    return marked + small == csr.colidx.size() && small == listed ? 0 : 12;
+}
+
+// fp32: the blocks' first small weights, the images' windows, a bit per lattice element
+int matrix_extra_lds(const MatrixPlan& p)
+{
+    return p.MK * p.WK * MatrixWeights::kSlots * (int)sizeof(MatrixWeights::Small) + p.images * kImageWindowBytes + p.EB * 8;
 }
 
 bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, int MK, int NP, int WK, int KS,
@@ -129,7 +186,7 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     long long lds = (long long)(p.nchunks > 1 ? 2 : 1) * CG * p.EB * 64 * 16 * pieces;
     if (KS > 1) lds = std::max(lds, (long long)KS * MK * NP * 16 * 64 * 4);   // where the four sums of a pair meet
     lds += 64 + 8 * 32 * MK * WK;             // what the wavefronts tell each other, bias and scale of the rows
-    if (pieces == 2) lds += images * kImageWindowBytes + p.EB * 8;
+    if (pieces == 2) lds += matrix_extra_lds(p);
     if (lds > kMaxLds) return false;
     p.lds_bytes = (int)lds;
     p.kblocks = (K + 32 * MK * WK - 1) / (32 * MK * WK);
@@ -221,7 +278,7 @@ void fill_matrix_args(const MatrixWeights& m, const MatrixPlan& p, int K, int C,
     a.WK = p.WK;
     a.logWK = p.WK == 4 ? 2 : p.WK == 2 ? 1 : 0;
     a.mask_words = m.mask_words;
-    a.meet_at = p.lds_bytes - 64 - 8 * 32 * p.MK * p.WK - (m.pieces == 2 ? p.images * kImageWindowBytes + p.EB * 8 : 0);
+    a.meet_at = p.lds_bytes - 64 - 8 * 32 * p.MK * p.WK - (m.pieces == 2 ? matrix_extra_lds(p) : 0);
     a.images = p.images;
     a.longest = m.longest;
     a.CG = p.CG; a.EB = p.EB; a.nchunks = p.nchunks;

@@ -207,6 +207,33 @@ def test_matrix_kernel_fp32_inputs_of_every_size(shape, how):
     layer.close()
 
 
+@pytest.mark.parametrize("shape", RANGES, ids=lambda s: "x".join(map(str, s)))
+def test_matrix_kernel_fp32_weights_of_every_size(shape):
+    """Weights far below their row's largest count in full where they meet the only inputs that are not zero."""
+    from paper_2011_06295_amd import binding as B
+    N, C, K, R, S, H, W, st, p = shape
+    rng = np.random.default_rng(98)
+    w, m, x = rand_layer(rng, N, C, K, R, S, H, W, density=0.9)
+    for k0 in range(0, K, 32):                               # 1, 2 ... of 32 rows
+        flat = w[k0:k0 + 32].reshape(-1)
+        flat[rng.choice(flat.size, size=1 + k0 // 32 * 3, replace=False)] *= np.float32(2.0 ** -20)
+    small = np.abs(w) < 2.0 ** -19
+    m[small] = 1
+    alone = x * (rng.random(x.shape) < 0.5 / (C * R * S))    # most outputs see one input or none
+    k, c, r, s = np.argwhere(small)[0]
+    alone[0], alone[0, c, min(r, H - 1), min(s, W - 1)] = 0.0, 3.0
+    layer = B.SparseConv(w, m, dtype="f32")
+    assert layer.get_kernel(N, H, W, st, p) == "matrix" and layer.check_plan(N, H, W, st, p) == 0
+    for data in (x, alone, alone * np.float32(1e-30)):
+        _each_output(layer, w, m, data, st, p, "small weights")
+    layer.close()
+    w.reshape(-1)[::50] *= np.float32(1e-7)                  # many: not this kernel's
+    layer = B.SparseConv(w, m, dtype="f32")
+    assert layer.get_kernel(N, H, W, st, p) == "tile"
+    _each_output(layer, w, m, x, st, p, "many small weights")
+    layer.close()
+
+
 def test_matrix_kernel_binary16_subnormals():
     """Inputs and weights below binary16's normal range take part with their value."""
     from paper_2011_06295_amd import binding as B
