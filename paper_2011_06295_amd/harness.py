@@ -124,7 +124,8 @@ class Network:
             s = run.spec
             d = run.layer.get_launch(self.work.N, s.H, s.W, s.stride, s.pad)
             entry = {"route": self.route[li],
-                     "launch": [] if getattr(run, "automatic", False) else
+                     # (the matrix kernel is what an automatic launch takes: nothing to pin)
+                     "launch": [] if run.layer.get_kernel(self.work.N, s.H, s.W, s.stride, s.pad) == "matrix" else
                                [d["V"], d["WP"], d["WK"], d["KW"], d["Cc"], 0, d["LP"], d["kblocks"], d["store"], d["lanes"],
                                 d["csplit"]]}
             entry.update(self.timings.get(li, {}))
@@ -234,7 +235,6 @@ class Network:
                 timed.append((time_layer(li, other, steps), len(timed), other))
             chosen = min(timed, key=lambda e: e[:2])[2]
             run.layer.set_launch(chosen)
-            run.automatic = not chosen
         return [run.layer.get_launch(*geom(run)) for run in self.runs]
 
     def make_buffer_sets(self, min_bytes: int = 512 << 20, max_sets: int = 16) -> int:
