@@ -96,6 +96,37 @@ def test_matrix_kernel_inputs_that_are_not_finite(dtype, shape, pool):
     layer.close()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_matrix_kernel_inputs_that_are_not_finite_do_not_stop_it(dtype):
+    """Outputs that see such an input are summed one by one.  Measured against the tile kernel, which they do not slow down
+    (one NaN: 10 times its time, all NaN: 80 times, when each lane followed a row's mask by itself; 2 and 8 now)."""
+    import torch
+    layer, w, m, x = _layer(dtype, (128, 256, 256, 3, 3, 14, 14, 1, 1), 99, 0.3)
+    assert layer.get_kernel(128, 14, 14, 1, 1) == "matrix"
+    xt = torch.from_numpy(x).cuda().to(torch.float16 if dtype == "f16" else torch.float32)
+    y = layer.forward(xt, 1, 1)
+
+    def best(data):
+        times = []
+        for _ in range(5):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            layer.forward(data, 1, 1, out=y)
+            e[1].record()
+            torch.cuda.synchronize()
+            times.append(e[0].elapsed_time(e[1]))
+        return min(times)
+
+    one = xt.clone()
+    one[5, 3, 4, 4] = float("nan")
+    plain, t_one, t_all = best(xt), best(one), best(torch.full_like(xt, float("nan")))
+    layer.set_launch(layer.rank_launches(128, 14, 14, 1, 1, 1)[0])
+    tile = best(xt)
+    print(f"{dtype}: {plain * 1e3:.0f} us, one NaN {t_one * 1e3:.0f} us, all NaN {t_all * 1e3:.0f} us; tile kernel {tile * 1e3:.0f} us", flush=True)
+    assert t_one < 5 * tile and t_all < 25 * tile
+    layer.close()
+
+
 @pytest.mark.parametrize("how", ["tiny", "huge", "late", "early", "zeros first", "rows apart"])
 def test_matrix_kernel_fp32_magnitudes(how):
     """A workgroup takes the scale of its two binary16 pieces from its first chunk of channels; a later chunk that does not
