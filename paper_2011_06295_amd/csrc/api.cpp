@@ -93,7 +93,9 @@ int get_route(sparse_conv_s* h, const Geometry& g, const Route** out)
     *out = r;
     if (r->decided) return SC_OK;
     const bool half = h->dtype == SC_F16;
-    if (h->matrix_holds < 0) h->matrix_holds = matrix_holds(h->csr, !half) ? 1 : 0;
+    // (both forward entry points take the same kernel: the table has to fit the static scratch)
+    if (h->matrix_holds < 0)
+        h->matrix_holds = matrix_bytes_at_least(h->K, h->C, h->R, h->S, !half) <= kStaticScratchBytes && matrix_holds(h->csr, !half) ? 1 : 0;
     double us = 0.0;
     if (h->matrix_holds && choose_matrix(h->csr, h->C, h->R, h->S, elem_bytes(h), g, r->tile.pool != 0, r->tile.csplit, r->plan, &us)) {
         // stores are not hidden behind short rows: the tile kernel's estimate leaves them out
@@ -107,7 +109,6 @@ int get_route(sparse_conv_s* h, const Geometry& g, const Route** out)
                 h->matrix = std::move(m);
                 h->matrix_id = g_next_id.fetch_add(1, std::memory_order_relaxed);
             }
-            // (both forward entry points take the same kernel: the table has to fit the static scratch)
             r->matrix = h->matrix->bytes() + 6 * 256 <= kStaticScratchBytes;
         }
     }

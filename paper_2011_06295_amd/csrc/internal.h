@@ -268,6 +268,8 @@ struct MatrixWeights {
 // Whether the matrix kernel can multiply these weights: they are finite (an infinite one would meet the zeros of every
 // output's receptive field), and few are in the list of small ones.
 bool matrix_holds(const Csr& csr, bool split);
+// Bytes of such a table, but for what depends on the weights.
+size_t matrix_bytes_at_least(int K, int C, int R, int S, bool split);
 void pack_matrix_weights(const Csr& csr, int C, int R, int S, bool split, MatrixWeights& out);
 
 // Tiles of the matrix kernel for one geometry.  A workgroup of four wavefronts owns PT consecutive outputs of the batch

@@ -41,6 +41,22 @@ constexpr int kMaxSmall = 32;
 
 }  // namespace
 
+namespace {
+
+// Halves of the image: behind the last stream, the groups of its last chunk that are not there (they meet zeros of the input)
+// and what its last steps ask for ahead.
+size_t image_halves(int K, int C, int RS, int pieces)
+{
+    return ((size_t)((K + 31) / 32) * ((C + 15) / 16 * RS) + (size_t)kMatrixGroups * RS + 3) * pieces * 512;
+}
+
+}  // namespace
+
+size_t matrix_bytes_at_least(int K, int C, int R, int S, bool split)
+{
+    return image_halves(K, C, R * S, split ? 2 : 1) * sizeof(uint16_t) + (size_t)K * ((C * R * S + 31) / 32) * sizeof(unsigned);
+}
+
 bool matrix_holds(const Csr& csr, bool split)
 {
     for (int k0 = 0; k0 < csr.K; k0 += 32) {
@@ -63,9 +79,7 @@ void pack_matrix_weights(const Csr& csr, int C, int R, int S, bool split, Matrix
     m.pieces = split ? 2 : 1;
     m.KF = (K + 31) / 32;
     m.steps = (C + 15) / 16 * RS;
-    // behind the last stream: the groups of its last chunk that are not there (they meet zeros of the input) and what its
-    // last steps ask for ahead
-    m.image.assign(((size_t)m.KF * m.steps + (size_t)kMatrixGroups * RS + 3) * m.pieces * 512, 0);
+    m.image.assign(image_halves(K, C, RS, m.pieces), 0);
     m.mask_words = (C * RS + 31) / 32;
     m.mask.assign((size_t)K * m.mask_words, 0u);
     m.row_exp.assign((size_t)m.KF * 32, 0);
@@ -102,7 +116,7 @@ int check_matrix(const Csr& csr, int C, int R, int S, const MatrixWeights& m)
 {
     const int RS = R * S;
     if (m.KF != (csr.K + 31) / 32 || m.steps != (C + 15) / 16 * RS || m.mask_words != (C * RS + 31) / 32) return 10;
-    if (m.image.size() != ((size_t)m.KF * m.steps + (size_t)kMatrixGroups * RS + 3) * m.pieces * 512) return 10;
+    if (m.image.size() != image_halves(csr.K, C, RS, m.pieces)) return 10;
     // 11: every stored weight is in its place; 12: and nothing else is in the table or the mask
     size_t marked = 0, small = 0, listed = m.small.size();
     for (const auto& s : m.slots) listed += s.row >= 0;

@@ -330,3 +330,24 @@ def test_every_pooled_layer_of_the_benchmark_vgg_can_pool_in_its_store_step():
             layer.close()
             pooled += 1
         assert pooled == 5
+
+
+def test_a_table_too_large_for_the_matrix_kernel_is_not_made():
+    """1024 -> 1024 channels, 3 x 3, fp32: the dense table (38 MB) is more than the kernel's entry points hold, and asking
+    which kernel runs must not leave one in memory."""
+    import os
+    from paper_2011_06295_amd import binding as B
+
+    def resident():
+        with open("/proc/self/statm") as f:
+            return int(f.read().split()[1]) * os.sysconf("SC_PAGE_SIZE")
+
+    rng = np.random.default_rng(12)
+    w = rng.standard_normal((1024, 1024, 3, 3), dtype=np.float32)
+    m = (rng.random(w.shape, dtype=np.float32) < 0.3).astype(np.uint8)
+    layer = B.SparseConv(w, m, dtype="f32")
+    assert layer.get_launch(64, 14, 14, 1, 1)["V"] > 0      # (its plan and what the search needs)
+    before = resident()
+    assert layer.get_kernel(64, 14, 14, 1, 1) == "tile"
+    assert resident() - before < 16 << 20
+    layer.close()
