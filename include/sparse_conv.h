@@ -271,7 +271,8 @@ int sparse_conv_set_epilogue(sparse_conv_t h, const float* bias, unsigned flags)
  * host against the CSR: every stored weight appears exactly once, with the LDS
  * offset of its tap (section 7's pre-computed input offsets) inside the staged
  * tile, every output channel has one accumulator slot, the tables have the sizes
- * the kernel walks, and the launch fits the hardware.  *failed_check receives 0,
+ * the kernel walks, and the launch fits the hardware; and, with nothing pinned, every way the matrix kernel could share the
+ * geometry out, and its weight table where it is taken.  *failed_check receives 0,
  * or the number of the first check that failed.  Needs no GPU.  Returns SC_OK
  * when the check ran (whatever it found), else as sparse_conv_get_launch. */
 int sparse_conv_check_plan(sparse_conv_t h, int N, int H, int W, int stride, int pad, int* failed_check);
@@ -283,6 +284,14 @@ int sparse_conv_check_plan(sparse_conv_t h, int N, int H, int W, int stride, int
  * a stored weight with a finite input of any size is within 2^-21 of itself, and they are summed in fp32.  Returns as
  * sparse_conv_get_launch.  Needs no GPU. */
 int sparse_conv_get_kernel(sparse_conv_t h, int N, int H, int W, int stride, int pad, int* kernel);
+
+/* How the matrix kernel shares the geometry out, where sparse_conv_get_kernel says 1 (else SC_EUNSUPPORTED): [0] blocks of 32
+ * output channels and [1] blocks of 32 outputs a wavefront multiplies, [2] wavefronts side by side over output channels,
+ * [3] wavefronts that share the input channels (1 or 4), [4] groups of 8 input channels a chunk holds, [5] blocks of 64 input
+ * positions a tile spans, [6] chunks, [7] steps the weights are loaded ahead, [8] staging blocks a wavefront has in flight,
+ * [9] workgroups, [10] LDS bytes per workgroup, [11] images a tile reaches over, at most.  Needs no GPU.  params must have room
+ * for 12 ints. */
+int sparse_conv_get_matrix_plan(sparse_conv_t h, int N, int H, int W, int stride, int pad, int* params);
 
 /* The tile kernel's launch configuration for a geometry (in force unless sparse_conv_get_kernel says 1): [0] V .. [4] Cc, [5] the LDS
  * budget in force, [6] workgroups launched, [7] LDS bytes

@@ -28,6 +28,7 @@ EXPORTS = (
     "sparse_conv_create", "sparse_conv_output_shape", "sparse_conv_forward", "sparse_conv_forward_static",
     "sparse_conv_get_csr", "sparse_conv_set_launch", "sparse_conv_get_launch", "sparse_conv_set_epilogue", "sparse_conv_autotune",
     "sparse_conv_create_codebook", "sparse_conv_get_codebook", "sparse_conv_check_plan", "sparse_conv_rank_launches", "sparse_conv_get_kernel",
+    "sparse_conv_get_matrix_plan",
     "sparse_conv_probe_lds_read", "sparse_conv_probe_copy",
     "sparse_conv_last_hip_error", "sparse_conv_strerror", "sparse_conv_destroy",
 )
@@ -65,6 +66,7 @@ def _load():
     lib.sparse_conv_set_epilogue.argtypes = [vp, vp, C.c_uint]
     lib.sparse_conv_check_plan.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip]
     lib.sparse_conv_get_kernel.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip]
+    lib.sparse_conv_get_matrix_plan.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip]
     lib.sparse_conv_rank_launches.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip, ip]
     lib.sparse_conv_autotune.argtypes = [vp, vp, vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, vp, C.c_int,
                                          C.POINTER(C.c_float)]
@@ -219,6 +221,16 @@ def sparse_conv_get_kernel(handle: int, N: int, H: int, W: int, stride: int, pad
     return "matrix" if which.value else "tile"
 
 
+MATRIX_PLAN_KEYS = ("MK", "NP", "WK", "KS", "CG", "EB", "nchunks", "ahead", "fly", "grid", "lds_bytes", "images")
+
+
+def sparse_conv_get_matrix_plan(handle: int, N: int, H: int, W: int, stride: int, pad: int) -> dict:
+    """The matrix kernel's share-out of the geometry (an error where the tile kernel is taken)."""
+    arr = (C.c_int * 12)()
+    _check(_lib.sparse_conv_get_matrix_plan(handle, N, H, W, stride, pad, arr), "sparse_conv_get_matrix_plan", handle)
+    return dict(zip(MATRIX_PLAN_KEYS, arr))
+
+
 def sparse_conv_check_plan(handle: int, N: int, H: int, W: int, stride: int, pad: int) -> int:
     """Host-side consistency check of the geometry's plan: 0, or the number of the first failed check."""
     bad = C.c_int(-1)
@@ -279,6 +291,9 @@ class SparseConv:
 
     def get_kernel(self, N: int, H: int, W: int, stride: int = 1, pad: int = 0) -> str:
         return sparse_conv_get_kernel(self.handle, N, H, W, stride, pad)
+
+    def get_matrix_plan(self, N: int, H: int, W: int, stride: int = 1, pad: int = 0) -> dict:
+        return sparse_conv_get_matrix_plan(self.handle, N, H, W, stride, pad)
 
     def check_plan(self, N: int, H: int, W: int, stride: int = 1, pad: int = 0) -> int:
         return sparse_conv_check_plan(self.handle, N, H, W, stride, pad)

@@ -833,6 +833,19 @@ int sparse_conv_get_kernel(sparse_conv_t h, int N, int H, int W, int stride, int
     }
 }
 
+int sparse_conv_get_matrix_plan(sparse_conv_t h, int N, int H, int W, int stride, int pad, int* params)
+{
+    if (!params) return SC_EINVAL;
+    int kernel = 0;
+    const int rc = sparse_conv_get_kernel(h, N, H, W, stride, pad, &kernel);
+    if (rc != SC_OK) return rc;
+    if (!kernel) return SC_EUNSUPPORTED;
+    const sc::MatrixPlan& p = h->routes.at(sc::Geometry{N, H, W, stride, pad}).plan;
+    const int v[12] = {p.MK, p.NP, p.WK, p.KS, p.CG, p.EB, p.nchunks, p.ahead, p.fly, p.grid, p.lds_bytes, p.images};
+    std::memcpy(params, v, sizeof v);
+    return SC_OK;
+}
+
 int sparse_conv_check_plan(sparse_conv_t h, int N, int H, int W, int stride, int pad, int* failed_check)
 {
     if (!h || N < 0) return SC_EINVAL;
@@ -842,9 +855,12 @@ int sparse_conv_check_plan(sparse_conv_t h, int N, int H, int W, int stride, int
         int rc = sc::get_plan(h, sc::Geometry{N, H, W, stride, pad}, &p);
         if (rc != SC_OK) return rc;
         int bad = sc::check_plan(h->csr, h->C, h->R, h->S, h->dtype == SC_F16 ? 2 : 4, *p);
+        const sc::Geometry g{N, H, W, stride, pad};
         const sc::Route* route = nullptr;
-        if (!bad && N > 0 && sc::automatic(h->over) && sc::get_route(h, sc::Geometry{N, H, W, stride, pad}, &route) == SC_OK && route->matrix)
-            bad = sc::check_matrix(h->csr, h->C, h->R, h->S, *h->matrix);
+        if (!bad && N > 0 && sc::automatic(h->over) && sc::get_route(h, g, &route) == SC_OK) {
+            bad = sc::check_matrix_plans(h->K, h->C, h->R, h->S, sc::elem_bytes(h), g, (h->epilogue & SC_EPILOGUE_MAXPOOL2) != 0);
+            if (!bad && route->matrix) bad = sc::check_matrix(h->csr, h->C, h->R, h->S, *h->matrix);
+        }
         if (failed_check) *failed_check = bad;
         return SC_OK;
     } catch (...) {

@@ -283,6 +283,8 @@ struct MatrixPlan {
     int EB;          // blocks of 64 lattice elements a tile spans
     int PT, Wp, Hs, E, F, nout, ntiles, kblocks, nchunks, grid, lds_bytes;
     int images;      // images the lattice elements of a tile belong to, at most
+    int ahead;       // steps the weights are asked for ahead: 2 or 3, the chunk's steps of a wavefront being a multiple
+    int fly;         // staging blocks a wavefront has in flight: fp32 1, 2 or 3, binary16 2, 4 or 6
 };
 constexpr int kImageWindowBytes = 24;   // fp32: LDS bytes for each of them
 // Fills p for the given split; false if the kernel cannot run it.
@@ -294,6 +296,9 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
                    MatrixPlan& p, double* us);
 // Host check of the weight table against the CSR; 0, or the number of the first check that failed.
 int check_matrix(const Csr& csr, int C, int R, int S, const MatrixWeights& m);
+// Host check of every split that plan_matrix accepts for the geometry, as the kernel walks it: each tap of each output in the
+// tile, at the input it stands for; LDS, table and index ranges.  0, or the number of the first check that failed.
+int check_matrix_plans(int K, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool);
 
 struct MatrixArgs {
     const void* x;

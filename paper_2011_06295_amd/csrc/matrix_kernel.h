@@ -944,19 +944,22 @@ int launch_one(const MatrixArgs& a, int grid, int lds, hipStream_t s)
 }
 
 template <typename T, int MK, int NP, int KS>
-int launch_fly(const MatrixArgs& a, int fly, int grid, int lds, hipStream_t s)
+int launch_fly(const MatrixArgs& a, const MatrixPlan& p, hipStream_t s)
 {
-    constexpr int low = sizeof(T) == 4 ? 1 : 2, high = sizeof(T) == 4 ? 3 : 6;
-    // (two binary16 pieces: three steps of weights ahead are more registers than there are)
-    if (a.own_steps % 3 == 0 && !(sizeof(T) == 4 && a.own_steps % 2 == 0)) {
-        if (fly <= low) return launch_one<T, MK, NP, 3, low, KS>(a, grid, lds, s);
-        if (fly < high) return launch_one<T, MK, NP, 3, 2 * low, KS>(a, grid, lds, s);
-        return launch_one<T, MK, NP, 3, high, KS>(a, grid, lds, s);
+    constexpr int unit = sizeof(T) == 4 ? 1 : 2;
+    if (a.own_steps % p.ahead) return (int)hipErrorInvalidValue;
+    const int kind = p.ahead * 10 + p.fly / unit;
+    if constexpr (unit == 2 || KS == 1) {     // (four wavefronts that share the channels have two fp32 blocks in flight at least)
+        if (kind == 31) return launch_one<T, MK, NP, 3, unit, KS>(a, p.grid, p.lds_bytes, s);
+        if (kind == 21) return launch_one<T, MK, NP, 2, unit, KS>(a, p.grid, p.lds_bytes, s);
     }
-    if (a.own_steps % 2) return (int)hipErrorInvalidValue;
-    if (fly <= low) return launch_one<T, MK, NP, 2, low, KS>(a, grid, lds, s);
-    if (fly < high) return launch_one<T, MK, NP, 2, 2 * low, KS>(a, grid, lds, s);
-    return launch_one<T, MK, NP, 2, high, KS>(a, grid, lds, s);
+    switch (kind) {
+        case 32: return launch_one<T, MK, NP, 3, 2 * unit, KS>(a, p.grid, p.lds_bytes, s);
+        case 33: return launch_one<T, MK, NP, 3, 3 * unit, KS>(a, p.grid, p.lds_bytes, s);
+        case 22: return launch_one<T, MK, NP, 2, 2 * unit, KS>(a, p.grid, p.lds_bytes, s);
+        case 23: return launch_one<T, MK, NP, 2, 3 * unit, KS>(a, p.grid, p.lds_bytes, s);
+    }
+    return (int)hipErrorInvalidValue;
 }
 
 }  // namespace

@@ -1,4 +1,4 @@
-// Host side of the matrix kernel (matrix.hip): the weight table, the tiles of a geometry and which split of them to take.
+// Host side of the matrix kernel (matrix_kernel.h): the weight table, the tiles of a geometry and which split of them to take.
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -197,6 +197,10 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     if (own % 3 && own % 2) return false;           // the kernel walks a chunk two or three steps at a time
     const int pieces = elem_bytes == 4 ? 2 : 1, groups = 2 * ((C + 15) / 16);
     p.nchunks = (groups + CG - 1) / CG;
+    // (two binary16 pieces: three steps of weights ahead are more registers than there are, unless it has to be three)
+    p.ahead = own % 3 == 0 && !(pieces == 2 && own % 2 == 0) ? 3 : 2;
+    const int unit = pieces == 2 ? 1 : 2, blocks = (CG * p.EB + 3) / 4;   // a chunk's staging blocks of a wavefront
+    p.fly = blocks <= unit ? unit : blocks < 3 * unit ? 2 * unit : 3 * unit;
     long long lds = (long long)(p.nchunks > 1 ? 2 : 1) * CG * p.EB * 64 * 16 * pieces;
     if (KS > 1) lds = std::max(lds, (long long)KS * MK * NP * 16 * 64 * 4);   // where the four sums of a pair meet
     lds += 64 + 8 * 32 * MK * WK;             // what the wavefronts tell each other, bias and scale of the rows
@@ -241,6 +245,59 @@ double estimate_matrix(const MatrixPlan& p, int RS, bool split)
 
 }  // namespace
 
+namespace {
+
+// The splits an automatic choice looks at: MK, NP, WK, KS.
+constexpr int kShapes16[][4] = {{2, 4, 1, 1}, {2, 4, 2, 1}, {2, 4, 4, 1}, {2, 2, 1, 1}, {2, 2, 2, 1}, {2, 2, 4, 1}, {2, 2, 1, 4}};
+constexpr int kShapes32[][4] = {{2, 2, 1, 1}, {2, 2, 2, 1}, {2, 2, 4, 1}, {1, 2, 1, 1}, {1, 2, 2, 1}, {1, 2, 4, 1}, {2, 2, 1, 4}};
+
+int check_matrix_plan(int K, int C, int R, int S, int elem_bytes, const Geometry& g, const MatrixPlan& p)
+{
+    const int pieces = elem_bytes == 4 ? 2 : 1, RS = R * S, own = p.CG / 2 / p.KS * RS;
+    // 14: the channels are covered, the steps come out, the table holds what the last block asks for (last steps' weights ahead)
+    const long long steps = (C + 15) / 16 * RS, last = (long long)p.nchunks * (p.CG / 2) * RS + p.ahead;
+    if ((long long)p.nchunks * p.CG * 8 < C || own % p.ahead || p.CG / 2 % p.KS) return 14;
+    if (((long long)(K + 31) / 32 - 1) * steps + last > (long long)image_halves(K, C, RS, 1) / 512) return 14;
+    // 15: LDS holds the buffers (and the sums that meet there) and what lies behind them; every block of rows and outputs is there
+    const long long buffers = (long long)(p.nchunks > 1 ? 2 : 1) * p.CG * p.EB * 1024 * pieces, rows = 32ll * p.MK * p.WK;
+    const long long behind = 64 + 8 * rows + (pieces == 2 ? matrix_extra_lds(p) : 0);
+    if (p.lds_bytes > kMaxLds || buffers + behind > p.lds_bytes || (p.KS > 1 && p.KS * p.MK * p.NP * 4096ll + behind > p.lds_bytes)) return 15;
+    if (p.kblocks * rows < K || (long long)p.ntiles * p.PT < p.nout || p.WK * p.WP * p.KS != 4 || p.PT != 32 * p.NP * p.WP) return 15;
+    if (p.grid % 8 || p.grid < (long long)p.ntiles * p.kblocks) return 15;
+    // 16: each tap of each output of a tile is inside the tile, at the element of its input or at one that reads as zero
+    const int EF = p.E * p.F, look = std::min(p.ntiles, 48);
+    auto lattice = [&](int o) { return (o / EF * p.Hs + o % EF / p.F * g.stride) * p.Wp + o % p.F * g.stride; };
+    for (int t = 0; t < look; ++t) {
+        const int tile = t == look - 1 ? p.ntiles - 1 : t, o0 = tile * p.PT, q0 = lattice(o0), u0 = o0 / EF;
+        if ((q0 + p.EB * 64 - 1) / p.Wp / p.Hs - u0 >= p.images) return 16;
+        for (int o = o0; o < std::min(p.nout, o0 + p.PT); ++o)
+            for (int r = 0; r < R; ++r)
+                for (int s = 0; s < S; ++s) {
+                    const int L = lattice(o) + r * p.Wp + s, Y = L / p.Wp, X = L % p.Wp - g.pad, u = Y / p.Hs, y = Y % p.Hs - g.pad;
+                    const int yy = o % EF / p.F * g.stride + r - g.pad, xx = o % p.F * g.stride + s - g.pad;
+                    if (L - q0 >= p.EB * 64) return 16;
+                    const bool reads = u < g.N && y >= 0 && y < g.H && X >= 0 && X < g.W;
+                    const bool wants = yy >= 0 && yy < g.H && xx >= 0 && xx < g.W;
+                    if (reads != wants || (wants && (u != o / EF || y != yy || X != xx))) return 16;
+                }
+    }
+    return 0;
+}
+
+}  // namespace
+
+int check_matrix_plans(int K, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool)
+{
+    for (const auto& sh : elem_bytes == 4 ? kShapes32 : kShapes16)
+        for (int CG = 2; CG <= 2 * kMatrixGroups; CG *= 2) {
+            MatrixPlan p;
+            if (!plan_matrix(K, C, R, S, elem_bytes, g, pool, sh[0], sh[1], sh[2], sh[3], CG, p)) continue;
+            const int bad = check_matrix_plan(K, C, R, S, elem_bytes, g, p);
+            if (bad) return bad;
+        }
+    return 0;
+}
+
 bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, int tile_parts,
                    MatrixPlan& best, double* us)
 {
@@ -257,10 +314,8 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
             for (int s = 0; s < S; ++s) cols += (unsigned)(j * g.stride + s - g.pad) < (unsigned)g.W;
         terms = (double)csr.colidx.size() / csr.K * rows * cols / ((double)E * F * RS);
     }
-    static const int shapes16[][4] = {{2, 4, 1, 1}, {2, 4, 2, 1}, {2, 4, 4, 1}, {2, 2, 1, 1}, {2, 2, 2, 1}, {2, 2, 4, 1}, {2, 2, 1, 4}};
-    static const int shapes32[][4] = {{2, 2, 1, 1}, {2, 2, 2, 1}, {2, 2, 4, 1}, {1, 2, 1, 1}, {1, 2, 2, 1}, {1, 2, 4, 1}, {2, 2, 1, 4}};
     double best_us = -1.0;
-    for (const auto& sh : split ? shapes32 : shapes16)
+    for (const auto& sh : split ? kShapes32 : kShapes16)
         for (int CG = 2; CG <= 2 * kMatrixGroups; CG *= 2) {
             MatrixPlan p;
             if (CG > 2 && CG / 2 >= 2 * ((C + 15) / 16)) break;   // a smaller chunk holds them all

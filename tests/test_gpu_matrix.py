@@ -1,6 +1,6 @@
 """The matrix kernel (sparse_conv_get_kernel says "matrix") against the CPU oracle at the edges of its tiles: channels off
-its groups of 16, rows off its blocks of 32, outputs off its tiles, every way of sharing a tile out, pooled stores, inputs
-that are not finite, and fp32 inputs of every magnitude (they are cut into two scaled binary16 pieces)."""
+its groups of 16, rows off its blocks of 32, outputs off its tiles, every variant that is built, pooled stores, inputs that are
+not finite, and fp32 inputs and weights of every magnitude (they are cut into two scaled binary16 pieces)."""
 import numpy as np
 import pytest
 
@@ -46,6 +46,42 @@ def test_matrix_kernel_against_the_oracle(dtype, shape):
     layer.close()
 
 
+# Every kernel that is built, and every way of sharing output channels out: MK, NP, WK, KS, steps ahead, blocks in flight, and a
+# small layer that takes it (N, C, K, R, S, H, W, stride, pad).
+VARIANTS = [
+    ("f16", (2, 2, 1, 1, 2, 2), (1, 16, 34, 2, 2, 1, 1, 2, 1)), ("f16", (2, 2, 4, 1, 2, 4), (11, 30, 26, 1, 2, 54, 54, 2, 0)),
+    ("f16", (2, 2, 2, 1, 2, 6), (110, 30, 23, 1, 1, 17, 52, 2, 0)), ("f16", (2, 2, 1, 1, 3, 2), (1, 16, 28, 3, 1, 1, 1, 1, 1)),
+    ("f16", (2, 2, 4, 1, 3, 4), (1, 16, 33, 3, 3, 5, 82, 2, 1)), ("f16", (2, 2, 1, 1, 3, 6), (150, 18, 37, 1, 3, 17, 51, 2, 0)),
+    ("f16", (2, 2, 1, 4, 2, 2), (1, 35, 21, 1, 2, 1, 6, 2, 0)), ("f16", (2, 2, 1, 4, 2, 4), (1, 103, 21, 1, 1, 1, 1, 1, 0)),
+    ("f16", (2, 2, 1, 4, 2, 6), (4, 41, 19, 2, 2, 1, 21, 2, 1)), ("f16", (2, 2, 1, 4, 3, 2), (1, 35, 34, 3, 1, 1, 1, 2, 1)),
+    ("f16", (2, 2, 1, 4, 3, 4), (1, 209, 73, 3, 3, 1, 1, 2, 1)), ("f16", (2, 2, 1, 4, 3, 6), (14, 44, 16, 3, 3, 4, 1, 2, 1)),
+    ("f16", (2, 4, 4, 1, 2, 2), (15, 36, 159, 1, 2, 42, 42, 1, 0)), ("f16", (2, 4, 4, 1, 2, 4), (10, 24, 142, 1, 2, 50, 50, 1, 0)),
+    ("f16", (2, 4, 1, 1, 2, 6), (136, 19, 16, 2, 2, 54, 54, 2, 0)), ("f16", (2, 4, 4, 1, 3, 2), (101, 18, 194, 1, 3, 15, 15, 1, 0)),
+    ("f16", (2, 4, 2, 1, 3, 4), (146, 17, 88, 3, 1, 57, 2, 1, 1)), ("f16", (2, 4, 1, 1, 3, 6), (137, 19, 26, 3, 1, 14, 54, 1, 1)),
+    ("f16", (2, 4, 2, 1, 2, 4), (132, 36, 86, 1, 2, 21, 21, 1, 0)), ("f16", (2, 4, 1, 1, 3, 4), (128, 29, 24, 1, 3, 24, 24, 1, 0)),
+    ("f32", (1, 2, 4, 1, 2, 1), (1, 90, 295, 1, 1, 60, 28, 1, 0)), ("f32", (1, 2, 4, 1, 2, 2), (115, 26, 70, 2, 2, 5, 31, 2, 1)),
+    ("f32", (1, 2, 4, 1, 2, 3), (10, 25, 47, 2, 2, 49, 49, 2, 1)), ("f32", (1, 2, 4, 1, 3, 1), (21, 20, 279, 1, 3, 12, 20, 1, 0)),
+    ("f32", (1, 2, 4, 1, 3, 2), (188, 26, 254, 3, 1, 44, 1, 2, 0)), ("f32", (1, 2, 4, 1, 3, 3), (12, 16, 53, 3, 3, 32, 32, 2, 1)),
+    ("f32", (2, 2, 4, 1, 2, 1), (113, 28, 166, 1, 2, 12, 12, 1, 0)), ("f32", (2, 2, 2, 1, 2, 2), (101, 27, 71, 1, 2, 18, 18, 1, 0)),
+    ("f32", (2, 2, 4, 1, 2, 3), (113, 60, 137, 1, 1, 48, 10, 2, 0)), ("f32", (2, 2, 4, 1, 3, 1), (140, 21, 136, 1, 3, 6, 21, 1, 0)),
+    ("f32", (2, 2, 4, 1, 3, 2), (12, 31, 223, 3, 1, 36, 36, 1, 0)), ("f32", (2, 2, 4, 1, 3, 3), (10, 26, 135, 3, 1, 58, 58, 2, 1)),
+    ("f32", (2, 2, 1, 4, 2, 2), (1, 47, 61, 1, 2, 1, 2, 2, 0)), ("f32", (2, 2, 1, 4, 2, 3), (15, 54, 244, 2, 2, 62, 3, 2, 1)),
+    ("f32", (2, 2, 1, 4, 3, 3), (13, 60, 141, 3, 1, 26, 5, 1, 1)), ("f32", (1, 2, 2, 1, 3, 2), (102, 22, 47, 1, 3, 5, 56, 1, 0)),
+    ("f32", (1, 2, 1, 1, 2, 3), (100, 27, 22, 2, 2, 23, 17, 1, 0)), ("f32", (2, 2, 1, 1, 3, 3), (140, 25, 42, 1, 3, 7, 66, 1, 0)),
+]
+
+
+@pytest.mark.parametrize("dtype,split,shape", VARIANTS, ids=lambda v: v if isinstance(v, str) else "x".join(map(str, v)))
+def test_every_variant_against_the_oracle(dtype, split, shape):
+    layer, w, m, x = _layer(dtype, shape, 90, 0.9)
+    N, C, K, R, S, H, W, st, p = shape
+    plan = layer.get_matrix_plan(N, H, W, st, p)
+    assert tuple(plan[k] for k in ("MK", "NP", "WK", "KS", "ahead", "fly")) == split, "the sizes no longer take the variant under test"
+    assert layer.check_plan(N, H, W, st, p) == 0
+    assert_close(run_gpu(layer, x, st, p, dtype), oracle_ref(w, m, x, st, p, dtype), TOL[dtype], f"{dtype} {split} {shape}")
+    layer.close()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
 @pytest.mark.parametrize("H,N,C,K", [(2, 1200, 256, 64), (4, 400, 256, 40), (8, 64, 128, 64), (16, 33, 64, 96), (32, 9, 48, 64), (64, 5, 40, 64)])
 def test_matrix_kernel_pooled_store(dtype, H, N, C, K):
@@ -65,14 +101,12 @@ def test_matrix_kernel_pooled_store(dtype, H, N, C, K):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
-@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[5], SHAPES[8]], ids=lambda s: "x".join(map(str, s)))
-@pytest.mark.parametrize("pool", [False, True])
+@pytest.mark.parametrize("shape,pool", [(SHAPES[0], False), (SHAPES[5], False), (SHAPES[8], False), (SHAPES[8], True)],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
 def test_matrix_kernel_inputs_that_are_not_finite(dtype, shape, pool):
     """The dense table's zeros meet every input of a receptive field: an Inf or NaN must count under stored weights only."""
     import torch
     N, C, K, R, S, H, W, st, p = shape
-    if pool and (H, W) != (2, 2):
-        pytest.skip("pooled: the 2 x 2 map")
     layer, w, m, x = _layer(dtype, shape, 93, 0.9)
     rng = np.random.default_rng(7)
     flat = x.reshape(-1)
@@ -127,39 +161,47 @@ def test_matrix_kernel_inputs_that_are_not_finite_do_not_stop_it(dtype):
     layer.close()
 
 
+# four wavefronts that share the channels, in one chunk and in three; wavefronts that share the tile out, eight chunks
+RANGES = [(24, 64, 64, 3, 3, 14, 14, 1, 1), (48, 192, 100, 3, 3, 5, 5, 1, 1), (40, 240, 130, 1, 1, 15, 14, 1, 0)]
+CHUNKS = {RANGES[0]: (4, 1), RANGES[1]: (4, 3), RANGES[2]: (1, 8)}
+
+
+def _takes_the_kernel(layer, shape):
+    N, C, K, R, S, H, W, st, p = shape
+    plan = layer.get_matrix_plan(N, H, W, st, p)
+    assert (plan["KS"], plan["nchunks"]) == CHUNKS[shape], "the sizes no longer take the split under test"
+
+
 @pytest.mark.parametrize("how", ["tiny", "huge", "late", "early", "zeros first", "rows apart"])
-def test_matrix_kernel_fp32_magnitudes(how):
-    """A workgroup takes the scale of its two binary16 pieces from its first chunk of channels; a later chunk that does not
-    fit it (late, zeros first) is done again.  "early": the first chunk is the largest by far, the error is relative to it.
-    Each output channel's weights have a scale of their own ("rows apart"): compared row by row."""
-    shape = (24, 64, 64, 3, 3, 14, 14, 1, 1)
+@pytest.mark.parametrize("shape", RANGES, ids=lambda s: "x".join(map(str, s)))
+def test_matrix_kernel_fp32_magnitudes(shape, how):
+    """The scales of an image's two binary16 pieces come from its first chunk of channels; what a later chunk has above them
+    (late; in the one-chunk split what is staged last) is multiplied in a round of its own.  Each output channel's weights have
+    a scale of their own ("rows apart"): compared row by row."""
+    N, C, K, R, S, H, W, st, p = shape
     layer, w, m, x = _layer("f32", shape, 94, 0.9)
     if how == "tiny":
         x *= np.float32(1e-25)
     elif how == "huge":
         x *= np.float32(1e25)
     elif how == "late":
-        x[:, 40:] *= np.float32(1e6)
+        x[:, C - 12:] *= np.float32(1e6)
     elif how == "early":
         x[:, :16] *= np.float32(1e4)
     elif how == "zeros first":
-        x[:, :48] = 0.0
-        x[:, 48:] *= np.float32(1e-6)
+        x[:, :C - 16] = 0.0
+        x[:, C - 16:] *= np.float32(1e-6)
     elif how == "rows apart":
         from paper_2011_06295_amd import binding as B
-        w *= np.logspace(-12, 12, 64, dtype=np.float32)[:, None, None, None]
+        w *= np.logspace(-12, 12, K, dtype=np.float32)[:, None, None, None]
         layer.close()
         layer = B.SparseConv(w, m, dtype="f32")
-    assert layer.get_kernel(24, 14, 14, 1, 1) == "matrix"
-    ref = oracle_ref(w, m, x, 1, 1, "f32")
-    got = run_gpu(layer, x, 1, 1, "f32")
-    for k in range(64):
+    _takes_the_kernel(layer, shape)
+    ref = oracle_ref(w, m, x, st, p, "f32")
+    got = run_gpu(layer, x, st, p, "f32")
+    for k in range(K):
         assert_close(got[:, k], ref[:, k], 2e-6, f"{how} row {k}")   # four times the largest error of an fp32 sum of this length
     layer.close()
-
-
-# channels in one chunk for each of four wavefronts; in four; in several chunks of wavefronts that share the tile out
-RANGES = [(24, 64, 64, 3, 3, 14, 14, 1, 1), (64, 256, 256, 3, 3, 4, 4, 1, 1), (60, 240, 250, 1, 1, 15, 14, 1, 0)]
 
 
 def _each_output(layer, w, m, x, st, p, what):
@@ -182,7 +224,7 @@ def test_matrix_kernel_fp32_images_do_not_depend_on_their_neighbours(shape, rati
     """Tiles reach over several images: a loud one takes nothing from the others, not even a bit."""
     N, C, K, R, S, H, W, st, p = shape
     layer, w, m, x = _layer("f32", shape, 96, 0.9)
-    assert layer.get_kernel(N, H, W, st, p) == "matrix"
+    _takes_the_kernel(layer, shape)
     x[::3] *= np.float32(ratio)
     got, ref = _each_output(layer, w, m, x, st, p, ratio)
     quiet = np.arange(N) % 3 != 0
@@ -220,7 +262,7 @@ def test_matrix_kernel_fp32_inputs_of_every_size(shape, how):
         x[:, C // 2:] *= np.float32(1e7)
     elif how == "late and quiet":
         x[:, C // 2:] *= np.float32(1e-9)
-        m[::2, :C // 2] = 0
+        m[::K - 1, :C // 2] = 0        # (two rows that see nothing else)
     elif how == "dead first":
         x[:, :3 * C // 4] = 0.0
         x[:, 3 * C // 4:] *= np.float32(1e-12)
@@ -233,7 +275,7 @@ def test_matrix_kernel_fp32_inputs_of_every_size(shape, how):
         w = np.copysign(np.maximum(np.abs(w), np.float32(0.01)), w)
     from paper_2011_06295_amd import binding as B
     layer = B.SparseConv(w, m, dtype="f32")
-    assert layer.get_kernel(N, H, W, st, p) == "matrix"
+    _takes_the_kernel(layer, shape)
     _each_output(layer, w, m, x, st, p, how)
     layer.close()
 
@@ -254,7 +296,8 @@ def test_matrix_kernel_fp32_weights_of_every_size(shape):
     k, c, r, s = np.argwhere(small)[0]
     alone[0], alone[0, c, min(r, H - 1), min(s, W - 1)] = 0.0, 3.0
     layer = B.SparseConv(w, m, dtype="f32")
-    assert layer.get_kernel(N, H, W, st, p) == "matrix" and layer.check_plan(N, H, W, st, p) == 0
+    _takes_the_kernel(layer, shape)
+    assert layer.check_plan(N, H, W, st, p) == 0
     for data in (x, alone, alone * np.float32(1e-30)):
         _each_output(layer, w, m, data, st, p, "small weights")
     layer.close()
