@@ -396,6 +396,8 @@ def run_workload(name, args, steps, warmup, brief):
     # HBM-side bytes per launch come from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs (profiles/); a bench run
     # does not count them, it quotes the profile of the same workload in its default configuration
     measured = MEASURED_TRAFFIC_BYTES_PER_LAUNCH.get(name) if not (args.launch or args.unify or args.codebook or args.fused) else None
+    if any(l["kernel"] == "matrix" for l in layers):   # the profiled traffic is that of the tile kernel's pass
+        measured = None
     roofline["traffic"] = measured[0] if measured else None
     if measured:
         roofline["traffic_source"] = measured[1]

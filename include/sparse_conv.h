@@ -117,8 +117,10 @@ int sparse_conv_forward(sparse_conv_t h, const void* input, void* output,
  * copied, on `stream`, into a static device array of SC_STATIC_SCRATCH_BYTES that is part of the
  * library's code object (every GPU the library runs on holds its own copy until the process
  * ends), and the kernel reads them there.
- *   - SC_ETOOBIG if the tables of this layer and geometry need more than that (about 8.2 bytes
- *     per stored weight); nothing is enqueued then.
+ *   - SC_ETOOBIG if the tile kernel's tables of this layer and geometry need more than that (about
+ *     8.2 bytes per stored weight, and its partial sums), whichever kernel runs; nothing is enqueued
+ *     then.  (The matrix kernel is taken only where its table fits too: 2 bytes per weight, stored or
+ *     not, 4 in fp32.)
  *   - All handles of the process share the array of a GPU, and it keeps what the last call
  *     left there: a call whose tables are already in place (same handle, geometry and launch
  *     configuration as the call before it on that GPU) copies nothing, any other call

@@ -55,9 +55,11 @@ bool automatic(const Launch& l)
     return !(l.V || l.WP || l.WK || l.KW || l.Cc || l.lds_budget || l.LP || l.kblocks || l.store || l.lanes || l.csplit);
 }
 
-// The matrix kernel is taken where its estimate lies below this share of the tile kernel's.  Over 208 layers (see
-// estimate_matrix) binary16 loses nowhere up to 1.0; fp32, where the two kernels are closer, loses up to 25 % in five layers
-// at 0.9 and nowhere at 0.7 (1.07 times faster in the mean at either).
+// The matrix kernel is taken where its estimate lies below this share of the tile kernel's.  Of 208 layers (see
+// estimate_matrix) the 91 in binary16 lose nowhere up to 1.0.  Of the 117 in fp32, ten take it at 0.75, in half the tile
+// kernel's time in the mean, and one of them is 16 % slower; at 0.9 fifteen do, one 28 % slower; at 0.7 nine, none slower, but
+// VGG-16's second to fourth layer at batches of 32 to 200 then lose what 0.75 gives them (0.58 to 1.06 of the tile kernel's
+// time, 0.84 in the mean).
 constexpr double kMatrixMargin16 = 0.95, kMatrixMargin32 = 0.75;
 
 // The tile kernel's cheapest configuration for the geometry (the search takes most of a first call's time on the host:

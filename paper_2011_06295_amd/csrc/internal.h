@@ -172,10 +172,10 @@ struct Plan {
 // Chooses the configuration (honouring overrides) and builds the host tables.
 // With `ranked` it only lists the candidate configurations (estimated clocks,
 // full override), cheapest first, and builds nothing.  Returns an SC_* status.
-// With `best` it stops after the search and reports the cheapest configuration and its estimate.
+// With `cheapest` it stops after the search and reports the cheapest configuration and its estimate.
 int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geometry& g,
                const Launch& over, Plan& plan, std::vector<std::pair<double, Launch>>* ranked = nullptr,
-               std::pair<double, Launch>* best = nullptr);
+               std::pair<double, Launch>* cheapest = nullptr);
 
 // Checks a built plan against its CSR on the host (every stored weight exactly once, with its
 // tap's LDS offset, inside the tile; every output channel in one slot; table sizes; launch
@@ -234,7 +234,7 @@ struct KernelArgs {
 #endif
 };
 
-// ---------------------------------------------------------------- the matrix kernel (matrix.hip)
+// ---------------------------------------------------------------- the matrix kernel (matrix_kernel.h)
 
 // A layer's weights as the matrix kernel reads them, the same for every geometry: dense, with zeros for what is not
 // stored, cut into fragments of 32 output channels x 16 input channels of one tap (a step).  image: [block of 32 output
