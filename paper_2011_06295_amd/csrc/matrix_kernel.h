@@ -799,7 +799,7 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
     bad |= (unsigned)__shfl_xor((int)bad, 32);           // the lane that holds the other rows of the same outputs
 
     // ---- store
-    // (binary16 layers are faster without: 64 -> 256 channels, 56 x 56, batch 128: 95 us, and 102 with the arguments read late)
+    // (binary16 layers store faster without: 64 -> 256 channels, 56 x 56, batch 128: 95 us, and 102 with the arguments read late here)
     const MatrixArgs& la = [&]() -> const MatrixArgs& {
         if constexpr (kSplit) return late_arguments();
         return a;
@@ -894,6 +894,7 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
     // ---- outputs whose receptive field holds a value that is not finite: the zeros of the dense table met it as well.
     // Summed once more over the stored weights alone, one output after the other, a lane a row.
     if (__builtin_expect(__ballot(bad != 0) != 0, 0)) {
+        const MatrixArgs& la = late_arguments();
 #pragma unroll 1
         for (int np = 0; np < kNP; ++np) {
             unsigned todo = (unsigned)__ballot((bad >> np) & 1u);      // the upper half repeats the lower
