@@ -285,6 +285,9 @@ struct MatrixPlan {
     int images;      // images the lattice elements of a tile belong to, at most
     int ahead;       // steps the weights are asked for ahead: 2 or 3, the chunk's steps of a wavefront being a multiple
     int fly;         // staging blocks a wavefront has in flight: fp32 1, 2 or 3, binary16 2, 4 or 6
+    // Wide staging: a lane takes 8 bytes of each of 8 channels, four (fp32: two) consecutive pixels of one plane.
+    int quads;       // such runs of pixels of one channel group a tile holds at most; 0: the planes are not whole runs
+    int wide_fly;    // blocks of 64 of them a wavefront has in flight: 1 or 2
 };
 constexpr int kImageWindowBytes = 24;   // fp32: LDS bytes for each of them
 // Fills p for the given split; false if the kernel cannot run it.
@@ -325,7 +328,9 @@ struct MatrixArgs {
     int own_steps;         // ... times taps
     int stream_steps, KF;
     int block_major;       // order of the (tile, channel block) pairs
-    FastDiv fd_EF, fd_F, fd_Wp, fd_Hs, fd_EB;
+    int quads, plane_quads;   // wide staging: runs of pixels of a tile (at most) and of a plane
+    int padded;               // ... the lattice has elements that are no pixel
+    FastDiv fd_EF, fd_F, fd_Wp, fd_Hs, fd_EB, fd_W, fd_quads, fd_plane_quads;
 };
 void fill_matrix_args(const MatrixWeights& m, const MatrixPlan& p, int K, int C, int R, int S, const Geometry& g, MatrixArgs& a);
 // Enqueue the matrix kernel.  Return a hipError_t value (0 = success).

@@ -60,6 +60,7 @@ namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float float16v __attribute__((ext_vector_type(16)));
+typedef unsigned uint2v __attribute__((ext_vector_type(2)));
 typedef unsigned uint4v __attribute__((ext_vector_type(4)));
 
 #define SC_LDS __attribute__((address_space(3)))
@@ -258,13 +259,15 @@ __device__ __forceinline__ bool finite(float v) { return __builtin_fabsf(v) <= 3
 
 // Wavefronts a SIMD holds at least: the smallest variant (1 x 1 layers mostly, which load and store more than they multiply)
 // fits 128 registers but for one, and four of it are faster than three (64 -> 256 channels, 56 x 56, binary16: 71 and 79 us).
-template <typename T, int MK, int NP, int AHEAD, int FLY, int KS>
-constexpr int kResident = sizeof(T) == 2 && MK * NP == 4 && AHEAD == 2 && FLY <= 2 && KS == 1 ? 4 : 2;
+template <typename T, int MK, int NP, int AHEAD, int FLY, int KS, bool WIDE>
+constexpr int kResident = sizeof(T) == 2 && MK * NP == 4 && AHEAD == 2 && FLY <= 2 && KS == 1 && !WIDE ? 4 : 2;
 
-template <typename T, int MK, int NP, int AHEAD, int FLY, int KS>
-__global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void matrix_kernel(const MatrixArgs a)
+template <typename T, int MK, int NP, int AHEAD, int FLY, int KS, bool WIDE>
+__global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) void matrix_kernel(const MatrixArgs a)
 {
     using raw = typename Raw<T>::type;
+    constexpr int kPx = WIDE ? 8 / (int)sizeof(T) : 1;          // pixels of a channel a lane stages
+    using staged = std::conditional_t<WIDE, uint2v, raw>;
     constexpr bool kSplit = sizeof(T) == 4;
     constexpr int kParts = kSplit ? 2 : 1;      // binary16 pieces a value is held in
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -370,7 +373,43 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<char*>(static_cast<const char*>(a.x)) + base_off, 0, remain > 0x80000000ull ? 0x80000000u : (unsigned)remain, 0x00020000);
     const int nblk = a.CG * a.EB;               // blocks of a chunk
-    raw st[FLY][8];
+    // Wide staging.  The address unit takes some 20 clocks for a load of 64 lanes, 2 bytes each or 8 (512 -> 512 channels, 4 x 4,
+    // binary16, batch 256: of 37.6 us, 13 were these loads).  So where planes are whole runs of kPx pixels, a lane takes runs: all
+    // pixels of the tile's lattice elements are consecutive, images one behind the other, and the padding between them, which no
+    // run holds, is cleared once.  (That layer's best split: 37.5 -> 26.4 us; in fp32, batch 128: 51.3 -> 37.1.)  A block is 64 runs, those of all channel groups one behind the other.
+    const int nwide = WIDE ? (a.CG * a.quads + 63) >> 6 : 0;
+    int quad0 = 0;                              // the tile's first run
+    if constexpr (WIDE) {
+        const int Y = fdiv(q0, a.fd_Wp), X = q0 - Y * a.Wp - a.pad, y = Y - fdiv(Y, a.fd_Hs) * a.Hs - a.pad;
+        const int inside = y < 0 ? 0 : y * a.W + (X < 0 ? 0 : X < a.W ? X : a.W);
+        quad0 = u0 * a.plane_quads + (inside < a.H * a.W ? inside : a.H * a.W) / kPx;
+        const half8 zero = {};
+        const unsigned all = a.padded ? (a.nchunks > 1 ? 2u : 1u) * buffer : 0u;
+        for (unsigned i = (unsigned)tid * 16u; i < all; i += 256u * 16u) lds_write(lds0 + i, zero);
+    }
+    const int blocks = WIDE ? nwide : nblk;     // what the wavefronts share
+    staged st[FLY][8];
+    // run b * 64 + lane: its channel group, image and place in the plane
+    auto run_of = [&](int b, int& cg, int& u, int& at, const MatrixArgs& a) __attribute__((always_inline)) {
+        const int n = b * 64 + lane;
+        cg = fdiv(n, a.fd_quads);
+        const int quad = quad0 + n - cg * a.quads;
+        u = fdiv(quad, a.fd_plane_quads);
+        at = quad - u * a.plane_quads;
+    };
+    auto load_runs = [&](uint2v(&dst)[8], int ch, int b, const MatrixArgs& a) __attribute__((always_inline)) {
+        int cg, u, at;
+        run_of(b, cg, u, at, a);
+        const bool ok = (u < a.N) & (cg < a.CG) & (ch < a.nchunks);
+        const unsigned off = (unsigned)(u - u0) * (unsigned)img_bytes + (unsigned)(cg * 8) * chan_bytes + (unsigned)at * 8u;
+        const int left = ok ? a.C - (ch * a.CG + cg) * 8 : 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int c = ch * a.CG * 8 + j;                     // (the descriptor's range is what lies behind this channel: it has to be there)
+            const unsigned from = c < a.C ? (unsigned)c * chan_bytes : 0u;
+            dst[j] = __builtin_bit_cast(uint2v, __builtin_amdgcn_raw_buffer_load_b64(rs, j < left ? (int)off : (int)0x80000000u, (int)from, 0));
+        }
+    };
     // the loads of block b of chunk ch; absent blocks (and channels past the last) are out of the descriptor's range
     // and read as zero, so that nothing here is a branch
     auto load_block = [&](raw(&dst)[8], int ch, int b, const MatrixArgs& a) __attribute__((always_inline)) {
@@ -394,9 +433,7 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
         return fdiv(fdiv(q0 + eb * 64 + lane, a.fd_Wp), a.fd_Hs) - u0;
     };
     bool outside = false;                       // kSplit: some value is not in its image's window
-    auto store_block = [&](const raw(&src)[8], float scale, int buf, int b) __attribute__((always_inline)) {
-        const int cg = fdiv(b, a.fd_EB), eb = b - cg * a.EB;
-        const unsigned to = lds0 + (unsigned)buf * buffer + (unsigned)cg * plane + (unsigned)(eb * 64 + lane) * 16u;
+    auto store_element = [&](const raw(&src)[8], float scale, unsigned to) __attribute__((always_inline)) {
         half8 hi, lo;
         if constexpr (kSplit) {
             unsigned least = ~0u;               // of twice the magnitude bits, less one: zeros are the largest
@@ -420,6 +457,28 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
         }
         lds_write(to, hi);
     };
+    auto store_block = [&](const raw(&src)[8], float scale, int buf, int b) __attribute__((always_inline)) {
+        const int cg = fdiv(b, a.fd_EB), eb = b - cg * a.EB;
+        store_element(src, scale, lds0 + (unsigned)buf * buffer + (unsigned)cg * plane + (unsigned)(eb * 64 + lane) * 16u);
+    };
+    auto store_runs = [&](const uint2v(&src)[8], float scale, int buf, int b) __attribute__((always_inline)) {
+        int cg, u, at;
+        run_of(b, cg, u, at, a);
+        const int y = fdiv(at * kPx, a.fd_W), x = at * kPx - y * a.W;
+        const int e0 = (u * a.Hs + a.pad + y) * a.Wp + a.pad + x - q0;
+        const unsigned to = lds0 + (unsigned)buf * buffer + (unsigned)cg * plane;
+#pragma unroll
+        for (int p = 0; p < kPx; ++p) {
+            const int e = e0 + p + (x + p >= a.W ? a.Wp - a.W : 0);            // (a run goes over a row's end once at most)
+            raw one[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if constexpr (kSplit) one[j] = src[j][p];
+                else one[j] = (raw)(src[j][p / 2] >> (p % 2 * 16));
+            }
+            if ((cg < a.CG) & ((unsigned)e < (unsigned)(a.EB * 64))) store_element(one, scale, to + (unsigned)e * 16u);
+        }
+    };
     // kSplit: this wavefront's blocks of a chunk once more, value by value.  First round: without what is above its image's
     // window, and with 11 bits of what is below it, which is marked and counted.  Later rounds: of the values above the first
     // window, or of those below it, only what is in the present window; between the two, under an empty window, those below it
@@ -427,13 +486,8 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
     // of what is left is remembered.  (Values that are not finite belong to the first round.)
     auto restage = [&](int ch, int buf, bool first) __attribute__((always_inline)) {
         const MatrixArgs& a = late_arguments();
-#pragma unroll 1
-        for (int b = wave; b < nblk; b += 4) {
-            raw src[8];
-            load_block(src, ch, b, a);
-            const int cg = fdiv(b, a.fd_EB), eb = b - cg * a.EB;
-            const unsigned to = lds0 + (unsigned)buf * buffer + (unsigned)cg * plane + (unsigned)(eb * 64 + lane) * 16u;
-            ImageWindow& w = images[image_of_block(b, a)];
+        auto again_element = [&](const raw(&src)[8], int cg, int e, ImageWindow& w) __attribute__((always_inline)) {
+            const unsigned to = lds0 + (unsigned)buf * buffer + (unsigned)cg * plane + (unsigned)e * 16u;
             const int base = window_base(w.first);
             const unsigned low = w.low, high = w.high, bottom = window_low(base), top = window_high(base);
             const bool lows = !first & (low < top), out = lows & (low == high) & (low != 0u);
@@ -462,33 +516,79 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
             if (left) atomicMax(lows ? &w.below : &w.above, left);
             if (first) {
                 if (strays) {
-                    atomicOr(&marks[eb * 2 + (lane >> 5)], 1u << (lane & 31));
+                    atomicOr(&marks[e >> 5], 1u << (e & 31));
                     atomicAdd(&meet[3], (unsigned)strays);
                 }
                 if (strays | (int)left) atomicOr(&meet[ch >> 5 & 1], 1u << (ch & 31));
             }
+        };
+#pragma unroll 1
+        for (int b = wave; b < blocks; b += 4) {
+            if constexpr (WIDE) {
+                uint2v src[8];
+                load_runs(src, ch, b, a);
+                int cg, u, at;
+                run_of(b, cg, u, at, a);
+                const int y = fdiv(at * kPx, a.fd_W), x = at * kPx - y * a.W;
+                const int e0 = (u * a.Hs + a.pad + y) * a.Wp + a.pad + x - q0;
+#pragma unroll 1
+                for (int p = 0; p < kPx; ++p) {
+                    const int e = e0 + p + (x + p >= a.W ? a.Wp - a.W : 0);
+                    raw one[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) one[j] = p ? src[j][1] : src[j][0];
+                    if ((cg < a.CG) & ((unsigned)e < (unsigned)(a.EB * 64))) again_element(one, cg, e, images[u - u0]);
+                }
+            } else {
+                raw src[8];
+                load_block(src, ch, b, a);
+                const int cg = fdiv(b, a.fd_EB), eb = b - cg * a.EB;
+                again_element(src, cg, eb * 64 + lane, images[image_of_block(b, a)]);
+            }
         }
+    };
+    auto load = [&](staged(&dst)[8], int ch, int b) __attribute__((always_inline)) {
+        if constexpr (WIDE) load_runs(dst, ch, b, a);
+        else load_block(dst, ch, b, a);
+    };
+    // kSplit: the image of what the lane stages in block b, counted from the tile's first (past its last: not stored)
+    auto staged_image = [&](int b) __attribute__((always_inline)) {
+        if constexpr (WIDE) {
+            int cg, u, at;
+            run_of(b, cg, u, at, a);
+            return u - u0;
+        } else {
+            return image_of_block(b, a);
+        }
+    };
+    auto staged_scale = [&](int b) __attribute__((always_inline)) {
+        const int image = staged_image(b);
+        return images[!WIDE || image < a.images ? image : 0].first;
     };
     auto fetch = [&](int ch) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < FLY; ++i) load_block(st[i], ch, wave + 4 * i, a);
+        for (int i = 0; i < FLY; ++i) load(st[i], ch, wave + 4 * i);
     };
     float scale[kSplit ? FLY : 1];              // kSplit: of the blocks in flight
     auto take_scales = [&]() __attribute__((always_inline)) {
         if constexpr (kSplit) {
 #pragma unroll
             for (int i = 0; i < FLY; ++i)
-                if (wave + 4 * i < nblk) scale[i] = images[image_of_block(wave + 4 * i, a)].first;
+                if (wave + 4 * i < blocks) scale[i] = staged_scale(wave + 4 * i);
         }
     };
     auto deposit = [&](int ch, int buf) __attribute__((always_inline)) {
+        auto store = [&](const staged(&src)[8], float scale, int b) __attribute__((always_inline)) {
+            if constexpr (WIDE) store_runs(src, scale, buf, b);
+            else store_block(src, scale, buf, b);
+        };
 #pragma unroll
         for (int i = 0; i < FLY; ++i)
-            if (wave + 4 * i < nblk) store_block(st[i], scale[kSplit ? i : 0], buf, wave + 4 * i);
-        for (int b = wave + 4 * FLY; b < nblk; b += 4) {        // what does not fit in flight
-            raw more[8];
-            load_block(more, ch, b, a);
-            store_block(more, kSplit ? images[image_of_block(b, a)].first : 0.f, buf, b);
+            if (wave + 4 * i < blocks) store(st[i], scale[kSplit ? i : 0], wave + 4 * i);
+        for (int b = wave + 4 * FLY; b < blocks; b += 4) {      // what does not fit in flight
+            staged more[8];
+            load(more, ch, b);
+            store(more, kSplit ? staged_scale(b) : 0.f, b);
         }
         if constexpr (kSplit) {
             if (__builtin_expect(__ballot(outside) != 0, 0)) {
@@ -504,12 +604,17 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
 #pragma unroll
         for (int i = 0; i < FLY; ++i) {
             unsigned top = 0;
+            auto see = [&](unsigned bits) __attribute__((always_inline)) {
+                const unsigned m = bits & 0x7fffffffu;
+                top = ((m < 0x7f800000u) & (m > top)) ? m : top;
+            };
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const unsigned m = (unsigned)st[i][j] & 0x7fffffffu;
-                top = ((m < 0x7f800000u) & (m > top)) ? m : top;
+                if constexpr (WIDE) see(st[i][j][0]), see(st[i][j][1]);
+                else see((unsigned)st[i][j]);
             }
-            if (top) atomicMax(&images[image_of_block(wave + 4 * i, a)].above, top);     // (absent blocks hold zeros)
+            const int image = staged_image(wave + 4 * i);
+            if (top && (!WIDE || image < a.images)) atomicMax(&images[image].above, top);           // (absent blocks hold zeros)
         }
         __syncthreads();
         for (int i = tid; i < a.images; i += 256) {
@@ -553,6 +658,8 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
     for (int i = 0; i < AHEAD; ++i) load_a(A[i]);
     if constexpr (kSplit) first_windows();
     take_scales();
+    if constexpr (WIDE && !kSplit)
+        if (a.padded) __syncthreads();                   // the padding is cleared (kSplit: behind the windows' barriers)
     deposit(0, 0);
     if constexpr (!kSplit)
         if (tid < rows) row_bias[tid] = my_bias;
@@ -929,10 +1036,10 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS>)) void m
 
 namespace {
 
-template <typename T, int MK, int NP, int AHEAD, int FLY, int KS>
+template <typename T, int MK, int NP, int AHEAD, int FLY, int KS, bool WIDE>
 int launch_one(const MatrixArgs& a, int grid, int lds, hipStream_t s)
 {
-    auto fn = matrix_kernel<T, MK, NP, AHEAD, FLY, KS>;
+    auto fn = matrix_kernel<T, MK, NP, AHEAD, FLY, KS, WIDE>;
     if (lds > 64 * 1024) {
         // more than 64 KB of dynamic LDS has to be allowed per kernel and device: once, for the whole 160 KB
         static std::atomic<unsigned long long> allowed{0};   // one bit per device ordinal
@@ -955,16 +1062,30 @@ int launch_fly(const MatrixArgs& a, const MatrixPlan& p, hipStream_t s)
 {
     constexpr int unit = sizeof(T) == 4 ? 1 : 2;
     if (a.own_steps % p.ahead) return (int)hipErrorInvalidValue;
+    // Wide staging: the planes are whole runs, and the input lies on a run's boundary.  Where a wavefront has but one block of
+    // single pixels to stage (binary16: two), runs would leave wavefronts without one: of 506 splits of 27 layers those with one
+    // are 2 to 4 % slower with runs in the mean, up to 24 % (64 -> 256, 56 x 56, binary16: 65 -> 80 us); with two (three) and
+    // more, 6 to 40 % faster, two in a hundred of them slower, by 5 % at most.
+    if (p.quads && p.fly > unit && reinterpret_cast<uintptr_t>(a.x) % 8 == 0) {
+        const int kind = p.ahead * 10 + p.wide_fly;
+        if (kind == 21) return launch_one<T, MK, NP, 2, 1, KS, true>(a, p.grid, p.lds_bytes, s);
+        if (kind == 31) return launch_one<T, MK, NP, 3, 1, KS, true>(a, p.grid, p.lds_bytes, s);
+        if constexpr (MK * NP * (unit == 1 ? 2 : 1) < 8) {           // (registers)
+            if (kind == 22) return launch_one<T, MK, NP, 2, 2, KS, true>(a, p.grid, p.lds_bytes, s);
+            if (kind == 32) return launch_one<T, MK, NP, 3, 2, KS, true>(a, p.grid, p.lds_bytes, s);
+        }
+        return (int)hipErrorInvalidValue;
+    }
     const int kind = p.ahead * 10 + p.fly / unit;
     if constexpr (unit == 2 || KS == 1) {     // (four wavefronts that share the channels have two fp32 blocks in flight at least)
-        if (kind == 31) return launch_one<T, MK, NP, 3, unit, KS>(a, p.grid, p.lds_bytes, s);
-        if (kind == 21) return launch_one<T, MK, NP, 2, unit, KS>(a, p.grid, p.lds_bytes, s);
+        if (kind == 31) return launch_one<T, MK, NP, 3, unit, KS, false>(a, p.grid, p.lds_bytes, s);
+        if (kind == 21) return launch_one<T, MK, NP, 2, unit, KS, false>(a, p.grid, p.lds_bytes, s);
     }
     switch (kind) {
-        case 32: return launch_one<T, MK, NP, 3, 2 * unit, KS>(a, p.grid, p.lds_bytes, s);
-        case 33: return launch_one<T, MK, NP, 3, 3 * unit, KS>(a, p.grid, p.lds_bytes, s);
-        case 22: return launch_one<T, MK, NP, 2, 2 * unit, KS>(a, p.grid, p.lds_bytes, s);
-        case 23: return launch_one<T, MK, NP, 2, 3 * unit, KS>(a, p.grid, p.lds_bytes, s);
+        case 32: return launch_one<T, MK, NP, 3, 2 * unit, KS, false>(a, p.grid, p.lds_bytes, s);
+        case 33: return launch_one<T, MK, NP, 3, 3 * unit, KS, false>(a, p.grid, p.lds_bytes, s);
+        case 22: return launch_one<T, MK, NP, 2, 2 * unit, KS, false>(a, p.grid, p.lds_bytes, s);
+        case 23: return launch_one<T, MK, NP, 2, 3 * unit, KS, false>(a, p.grid, p.lds_bytes, s);
     }
     return (int)hipErrorInvalidValue;
 }

@@ -320,3 +320,31 @@ def test_matrix_kernel_binary16_subnormals():
         assert layer.get_kernel(40, 14, 14, 1, 1) == "matrix"
         assert_close(run_gpu(layer, x, 1, 1, "f16"), oracle_ref(w, m, x, 1, 1, "f16"), TOL["f16"], f"subnormal {xs} {ws}")
         layer.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("shape", [(40, 64, 65, 3, 3, 14, 14, 1, 1), (516, 45, 70, 3, 3, 4, 4, 1, 1), (1692, 130, 66, 3, 3, 2, 2, 1, 1), (228, 61, 40, 3, 3, 2, 30, 1, 1),
+                                   (24, 48, 64, 3, 3, 29, 32, 2, 1), (134, 200, 80, 1, 3, 1, 36, 1, 0), (60, 240, 252, 1, 1, 16, 14, 1, 0), (52, 40, 64, 3, 3, 3, 44, 1, 3)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_matrix_kernel_stages_runs_and_single_pixels(dtype, shape):
+    """Where planes are whole runs of 8 bytes the kernel stages runs, else, and from an input that does not start on a run's
+    boundary, pixel by pixel: both against the oracle, with an input that is not finite and (fp32) one far above the others."""
+    import torch
+    layer, w, m, x = _layer(dtype, shape, 101, 0.9)
+    N, C, K, R, S, H, W, st, p = shape
+    x[N // 2, C // 2, H // 2, W // 2] *= np.float32(1e6 if dtype == "f32" else 8)
+    x[N - 1, C - 1, H - 1, W - 1] = np.inf
+    tdtype = torch.float16 if dtype == "f16" else torch.float32
+    aligned = torch.from_numpy(x).cuda().to(tdtype)
+    shifted = torch.empty(aligned.numel() + 1, dtype=tdtype, device="cuda")[1:].view(aligned.shape)
+    shifted.copy_(aligned)
+    assert layer.get_kernel(N, H, W, st, p) == "matrix" and layer.check_plan(N, H, W, st, p) == 0
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref = oracle_ref(w, m, x, st, p, dtype)
+    fin = np.isfinite(ref)
+    assert not fin.all()
+    for data in (aligned, shifted):
+        got = layer.forward(data, st, p).float().cpu().numpy().astype(np.float64)
+        assert np.array_equal(np.isposinf(got), np.isposinf(ref)) and np.array_equal(np.isneginf(got), np.isneginf(ref))
+        assert_close(got[fin], ref[fin], TOL[dtype], f"{dtype} {shape}")
+    layer.close()
