@@ -55,13 +55,6 @@ bool automatic(const Launch& l)
     return !(l.V || l.WP || l.WK || l.KW || l.Cc || l.lds_budget || l.LP || l.kblocks || l.store || l.lanes || l.csplit);
 }
 
-// The matrix kernel is taken where its estimate lies below this share of the tile kernel's.  Of 208 layers (see
-// estimate_matrix) the 91 in binary16 lose nowhere up to 1.0.  Of the 117 in fp32, ten take it at 0.75, in half the tile
-// kernel's time in the mean, and one of them is 16 % slower; at 0.9 fifteen do, one 28 % slower; at 0.7 nine, none slower, but
-// VGG-16's second to fourth layer at batches of 32 to 200 then lose what 0.75 gives them (0.58 to 1.06 of the tile kernel's
-// time, 0.84 in the mean).
-constexpr double kMatrixMargin16 = 0.95, kMatrixMargin32 = 0.75;
-
 // The tile kernel's cheapest configuration for the geometry (the search takes most of a first call's time on the host:
 // done once).  A geometry that the tile kernel cannot plan is refused here, whichever kernel would run.
 int find_tile(sparse_conv_s* h, const Geometry& g, Route** out)
@@ -85,7 +78,7 @@ int find_tile(sparse_conv_s* h, const Geometry& g, Route** out)
 
 // Which kernel an automatic forward of the geometry takes: the one that is estimated cheaper, where the matrix kernel can
 // run.  It multiplies the zeros between the stored weights as well, at 10 to 25 times the tile kernel's rate: for binary16
-// that pays at most sparsities pruning reaches, for fp32 (three binary16 products a weight) below about 85 %, and further
+// that pays at most sparsities pruning reaches, for fp32 (three binary16 products a weight) below about 89 %, and further
 // up where the tile kernel loses its lanes to padding or to a stride.
 int get_route(sparse_conv_s* h, const Geometry& g, const Route** out)
 {
@@ -98,13 +91,13 @@ int get_route(sparse_conv_s* h, const Geometry& g, const Route** out)
     // (both forward entry points take the same kernel: the table has to fit the static scratch)
     if (h->matrix_holds < 0)
         h->matrix_holds = matrix_bytes_at_least(h->K, h->C, h->R, h->S, !half) <= kStaticScratchBytes && matrix_holds(h->csr, !half) ? 1 : 0;
-    double us = 0.0;
-    if (h->matrix_holds && choose_matrix(h->csr, h->C, h->R, h->S, elem_bytes(h), g, r->tile.pool != 0, r->tile.csplit, r->plan, &us)) {
+    double us = 0.0, share = 0.0;
+    if (h->matrix_holds && choose_matrix(h->csr, h->C, h->R, h->S, elem_bytes(h), g, r->tile.pool != 0, r->tile.csplit, r->plan, &us, &share)) {
         // stores are not hidden behind short rows: the tile kernel's estimate leaves them out
         const double terms = (double)h->csr.colidx.size() / h->K;
         const double mbytes = (double)g.N * ((double)h->C * g.H * g.W + (double)h->K * r->plan.E * r->plan.F) * elem_bytes(h) * 1e-6;
         const double tile_us = r->tile_clocks / 2400.0 + (terms < 32.0 ? 0.2 * mbytes : 0.0);
-        if (us < (half ? kMatrixMargin16 : kMatrixMargin32) * tile_us) {
+        if (us < share * tile_us) {
             if (!h->matrix) {
                 std::unique_ptr<MatrixWeights> m(new MatrixWeights());
                 pack_matrix_weights(h->csr, h->C, h->R, h->S, !half, *m);

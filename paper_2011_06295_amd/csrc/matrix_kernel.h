@@ -1062,11 +1062,7 @@ int launch_fly(const MatrixArgs& a, const MatrixPlan& p, hipStream_t s)
 {
     constexpr int unit = sizeof(T) == 4 ? 1 : 2;
     if (a.own_steps % p.ahead) return (int)hipErrorInvalidValue;
-    // Wide staging: the planes are whole runs, and the input lies on a run's boundary.  Where a wavefront has but one block of
-    // single pixels to stage (binary16: two), runs would leave wavefronts without one: of 506 splits of 27 layers those with one
-    // are 2 to 4 % slower with runs in the mean, up to 24 % (64 -> 256, 56 x 56, binary16: 65 -> 80 us); with two (three) and
-    // more, 6 to 40 % faster, two in a hundred of them slower, by 5 % at most.
-    if (p.quads && p.fly > unit && reinterpret_cast<uintptr_t>(a.x) % 8 == 0) {
+    if (stages_runs(p, sizeof(T)) && reinterpret_cast<uintptr_t>(a.x) % 8 == 0) {
         const int kind = p.ahead * 10 + p.wide_fly;
         if (kind == 21) return launch_one<T, MK, NP, 2, 1, KS, true>(a, p.grid, p.lds_bytes, s);
         if (kind == 31) return launch_one<T, MK, NP, 3, 1, KS, true>(a, p.grid, p.lds_bytes, s);

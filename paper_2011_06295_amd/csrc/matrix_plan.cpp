@@ -154,6 +154,12 @@ int matrix_extra_lds(const MatrixPlan& p)
     return p.MK * p.WK * MatrixWeights::kSlots * (int)sizeof(MatrixWeights::Small) + p.images * kImageWindowBytes + p.EB * 8;
 }
 
+// Whether the kernel stages runs (where the input lies on a run's boundary).  Where a wavefront has but one block of single
+// pixels to stage (binary16: two), runs would leave wavefronts without one: of 506 splits of 27 layers those with one are 2 to
+// 4 % slower with runs in the mean, up to 24 % (64 -> 256, 56 x 56, binary16: 65 -> 80 us); with two (three) and more, 6 to 40 %
+// faster, two in a hundred of them slower, by 5 % at most.
+bool stages_runs(const MatrixPlan& p, int elem_bytes) { return p.quads && p.fly > (elem_bytes == 4 ? 1 : 2); }
+
 bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, int MK, int NP, int WK, int KS,
                  int CG, MatrixPlan& p)
 {
@@ -226,25 +232,41 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
 
 namespace {
 
-// Rough time of one launch in microseconds.  Structure and constants are fitted to the measured times of every split of
-// 208 layers (the 32-pixel VGG-16's, those of larger networks, and random ones: 1 x 1, 1-D, 3 x 3, 5 x 5, stride 2, first
-// layers, batches of 1 to 256): 13 % rms of the logarithm, the cheapest by estimate 3 % slower than the fastest
-// measured in the mean.  In clocks of 2.1 GHz:
-//  * A step costs its matrix instructions (51 to 53 clocks each over the workgroups resident on the CU; 32 at the nominal rate), but never less than a wavefront's own chain of loads and instructions.
-//  * A chunk's staging blocks (64 lattice elements x 8 channels) cost 169 (fp32: 242) clocks each; a third of the shorter of
-//    multiplying and staging is not hidden behind the longer.
-//  * Workgroups run in rounds of what is resident; a partly filled last round after full ones is a little shorter.
-double estimate_matrix(const MatrixPlan& p, int RS, bool split)
+// Rough time of one launch in microseconds.  Structure and constants are fitted to the measured times of every split (3278 of
+// them) of 187 layers (the 32-pixel VGG-16's, those of larger networks, and random ones: 1 x 1, 1-D, 3 x 3, 5 x 5, stride 2,
+// batches of 1 to 256): 10 % rms of the logarithm, the cheapest by estimate 2 % slower than the fastest measured in the mean.
+// In clocks of 2.1 GHz:
+//  * A step costs its matrix instructions (39 to 41 clocks each over the workgroups resident on the CU; 32 at the nominal rate)
+//    and its reads, but never less than a wavefront's own chain of loads and instructions.
+//  * A chunk's staging blocks cost 59 to 299 clocks each by kind (single pixels or runs, half or two pieces); multiplying and
+//    staging hide each other little.  What a wavefront does not have in flight costs most of a memory latency a block.
+//  * Workgroups run in rounds of what is resident.
+// Layers of fewer than 4e8 products, zeros counted, take 9 to 35 us, most of it what every launch costs: an earlier fit to 208
+// layers chooses as well among their splits (1.0 to 2.5 % above the fastest in the mean, this one 1.4 to 2.4 %) and is kept for
+// them.  Above, this one is 1 to 3 % above the fastest and the earlier one 3 to 6 %.
+constexpr double kSmallLayer = 4e8;
+double estimate_matrix(const MatrixPlan& p, int RS, bool split, bool small)
 {
-    struct Clocks { double fixed, chain, chain_mf, mf, chunk, stage_chunk, stage, pair, tail; };
-    static const Clocks k16 = {10570, 267, 21.0, 51.4, 556, 169, 169, 845, 0.83}, k32 = {9630, 235, 44.9, 52.9, 42, 10, 242, 1756, 0.88};
-    const Clocks& k = split ? k32 : k16;
-    const int conc_max = std::min(2, kMaxLds / p.lds_bytes);      // registers allow two workgroups a CU
+    struct Clocks { double fixed, chain, chain_mf, mf, read, chunk, stage_chunk, stage, run_chunk, run, both, late, pair, tail; };
+    static const Clocks k16 = {11300, 172, 17.2, 40.9, 9.2, 482, 13, 58.5, 2, 197, 1.24, 659, 993, 1.0},
+                        k32 = {11800, 7, 49.0, 38.9, 1.5, 306, 45, 139, 6, 290, 1.19, 676, 2110, 1.09};
+    static const Clocks small16 = {10570, 267, 21.0, 51.4, 0, 556, 169, 169, 169, 169, 0.35, 0, 845, 0.83},
+                        small32 = {9630, 235, 44.9, 52.9, 0, 42, 10, 242, 10, 242, 0.35, 0, 1756, 0.88};
+    const Clocks& k = small ? (split ? small32 : small16) : split ? k32 : k16;
+    const int unit = split ? 1 : 2, pieces = split ? 2 : 1;
+    const bool runs = !small && stages_runs(p, split ? 4 : 2);
+    const int blocks = runs ? (p.CG * p.quads + 63) / 64 : p.CG * p.EB, fly = runs ? p.wide_fly : p.fly;
+    // workgroups a CU holds: registers allow two, three of the small variants, four of the smallest
+    const int room = small || p.MK * p.NP * pieces > 4 ? 2 : !split && p.ahead == 2 && p.fly == unit && p.KS == 1 && !runs ? 4 :
+                     fly == (runs ? (split ? 2 : 0) : 3 * unit) ? 2 : 3;
+    const int conc_max = std::min(room, kMaxLds / p.lds_bytes);
     const double mf = p.MK * p.NP * (split ? 3 : 1), own = (double)(p.CG / 2 / p.KS) * RS;
+    const double late = std::max(0, (blocks + 3) / 4 - fly) * k.late, begin = runs ? k.run_chunk : k.stage_chunk;
     auto round = [&](double conc) {
-        const double multiply = own * std::max(k.chain + k.chain_mf * mf, conc * mf * k.mf), stage = conc * p.CG * p.EB * k.stage;
-        return p.nchunks * (std::max(multiply, stage + k.stage_chunk) + 0.35 * std::min(multiply, stage) + k.chunk) + 0.6 * stage +
-               k.stage_chunk + conc * k.pair * p.MK * p.NP / (p.KS > 1 ? 4 : 1);
+        const double multiply = own * std::max(k.chain + k.chain_mf * mf, conc * (mf * k.mf + p.NP * pieces * k.read));
+        const double stage = conc * blocks * (runs ? k.run : k.stage);
+        return p.nchunks * (std::max(multiply, stage + begin) + k.both * std::min(multiply, stage) + k.chunk + late) + 0.6 * stage + begin +
+               conc * k.pair * p.MK * p.NP / (p.KS > 1 ? 4 : 1);
     };
     const long long slots = (long long)kCUs * conc_max, wgs = (long long)p.ntiles * p.kblocks;
     const long long full = wgs / slots, rest = wgs % slots;
@@ -316,7 +338,7 @@ int check_matrix_plans(int K, int C, int R, int S, int elem_bytes, const Geometr
 }
 
 bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, int tile_parts,
-                   MatrixPlan& best, double* us)
+                   MatrixPlan& best, double* us, double* share)
 {
     const bool split = elem_bytes == 4;
     const int RS = R * S;
@@ -331,6 +353,9 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
             for (int s = 0; s < S; ++s) cols += (unsigned)(j * g.stride + s - g.pad) < (unsigned)g.W;
         terms = (double)csr.colidx.size() / csr.K * rows * cols / ((double)E * F * RS);
     }
+    // Taken below these shares of the tile kernel's estimate.  Of the 43 larger layers in binary16 none is slower at 0.95 or 1.0 (the
+    // mean of all is 1 % shorter at 1.0), one by 5 % at 1.05; of the 18 in fp32 none up to 0.88, one by 1 % at 0.9.  Of the 208 layers of the earlier fit those in binary16 lose nowhere up to 1.0, and one of ten in fp32 at 0.75, two more at 0.9.
+    const bool small = (double)g.N * E * F * csr.K * C * RS < kSmallLayer;
     double best_us = -1.0;
     for (const auto& sh : split ? kShapes32 : kShapes16)
         for (int CG = 2; CG <= 2 * kMatrixGroups; CG *= 2) {
@@ -344,7 +369,7 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
                 const double here = 0.81 + 0.047 * 3 * RS * (CG / 2 / sh[3]) + 0.04 * p.nchunks;
                 if (here * 1.3 > 0.0335 * terms / std::max(1, tile_parts)) continue;
             }
-            const double t = estimate_matrix(p, RS, split);
+            const double t = estimate_matrix(p, RS, split, small);
             if (best_us < 0 || t < best_us) {
                 best_us = t;
                 best = p;
@@ -352,6 +377,7 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
         }
     if (best_us < 0) return false;
     *us = best_us;
+    *share = small ? (split ? 0.75 : 0.95) : (split ? 0.88 : 0.95);
     return true;
 }
 
