@@ -6,7 +6,7 @@
 // 16 input channels x 32 outputs.  At 90 % sparsity nine tenths of the products are with zeros, yet it is the faster way:
 // the tile kernel is bound by its LDS reads (16 bytes for 4 to 8 multiply-adds a lane) at 30 to 40 TFLOP/s of stored
 // weights, where this kernel does 600 to 1000 TFLOP/s of all weights in binary16 (256 -> 512 channels, 28 x 28, batch 128,
-// 90 %: 569 us by the tile kernel, 225 us here) and 200 to 330 in fp32 (256 -> 256, 14 x 14, batch 256, 70 %: 431 -> 181 us).
+// 90 %: 555 us by the tile kernel, 219 us here) and 200 to 340 in fp32 (256 -> 256, 14 x 14, batch 256, 70 %: 440 -> 178 us).
 //
 // Tile.  A workgroup of four wavefronts owns consecutive outputs of the batch and keeps, chunk by chunk of channels, the
 // lattice elements they touch in LDS, 8 channels of one position to a 16-byte element: a tap is an LDS offset, so the
@@ -21,7 +21,8 @@
 // weights of its first AHEAD steps, and those steps stand outside the loop: there the compiler can count exactly which
 // loads are out (in the loop it would have to assume the fewest, and waited for everything at every step: 331 -> 243 us on
 // the layer above).  For the same reason the number of loads does not depend on run-time conditions: FLY blocks of 64
-// elements x 8 channels a wavefront, of which the absent ones are out of the descriptor's range.
+// elements x 8 channels a wavefront (or of 64 runs of pixels x 8 channels: "Wide staging" below), of which the absent ones are
+// out of the descriptor's range.
 //
 // fp32 layers.  A value is the sum of two binary16 numbers to 2^-23 of it; three of the four products of two such sums are
 // multiplied (the fourth is 2^-22 of the result or less), smallest first.  binary16 has few exponents, so the weights of an
