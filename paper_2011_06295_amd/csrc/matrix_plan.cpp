@@ -343,16 +343,47 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
     const bool split = elem_bytes == 4;
     const int RS = R * S;
     const int E = (g.H + 2 * g.pad - R) / g.stride + 1, F = (g.W + 2 * g.pad - S) / g.stride + 1;
-    // fp32 sums: terms of an output that do not fall on padding, in the mean
-    double terms = 0.0;
+    // fp32 sums: the share of an output's terms that do not fall on padding, and the terms, both in the mean
+    double inside = 0.0, terms = 0.0;
+    std::vector<int> before;       // [K][C + 1]: a row's weights (but zeros, which add no rounding) before a channel
     if (split) {
         double rows = 0, cols = 0;
         for (int i = 0; i < E; ++i)
             for (int r = 0; r < R; ++r) rows += (unsigned)(i * g.stride + r - g.pad) < (unsigned)g.H;
         for (int j = 0; j < F; ++j)
             for (int s = 0; s < S; ++s) cols += (unsigned)(j * g.stride + s - g.pad) < (unsigned)g.W;
-        terms = (double)csr.colidx.size() / csr.K * rows * cols / ((double)E * F * RS);
+        inside = rows * cols / ((double)E * F * RS);
+        terms = (double)csr.colidx.size() / csr.K * inside;
+        before.assign((size_t)csr.K * (C + 1), 0);
+        for (int k = 0; k < csr.K; ++k) {
+            int* n = &before[(size_t)k * (C + 1)];
+            for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) n[csr.colidx[i] / RS + 1] += csr.val32[i] != 0.f;
+            for (int c = 0; c < C; ++c) n[c + 1] += n[c];
+        }
     }
+    // Terms that a term of row k is summed with, in the mean, itself included, where every `width` channels have a sum.
+    auto company = [&](int k, int width) {
+        const int* n = &before[(size_t)k * (C + 1)];
+        double squares = 0.0;
+        for (int c = 0; c < C; c += width) {
+            const double here = n[std::min(C, c + width)] - n[c];
+            squares += here * here;
+        }
+        return squares / n[C] * inside;
+    };
+    // Whether no row is less exact under the split than in the tile kernel.  Units and numbers as below, but a row of few weights
+    // has no term in some steps and chunks: then the pieces' own error is most of it (10 terms: 9e-8 to 1.0e-7, the tile kernel
+    // 5e-8 to 6e-8).  Of 1568 pairs of plans with rows of 2 to 448 terms, 183 pass; their error here is 0.95 of that there or less.
+    auto rows_as_exact = [&](const MatrixPlan& p, double steps) {
+        const int own = p.CG / 2 / p.KS * 16, part = (C + std::max(1, tile_parts) - 1) / std::max(1, tile_parts);
+        for (int k = 0; k < csr.K; ++k) {
+            const int n = before[(size_t)(k + 1) * (C + 1) - 1];
+            if (!n) continue;
+            const double met = steps * (1.0 - std::exp(-company(k, own) / steps)), chunks = p.nchunks * (1.0 - std::exp(-n * inside / p.nchunks));
+            if ((0.81 + 0.047 * 3 * met + 0.04 * chunks) * 1.1 > 0.0335 * company(k, part)) return false;
+        }
+        return true;
+    };
     // Taken below these shares of the tile kernel's estimate.  Of the 43 larger layers in binary16 none is slower at 0.95 or 1.0 (the
     // mean of all is 1 % shorter at 1.0), one by 5 % at 1.05; of the 18 in fp32 none up to 0.88, one by 1 % at 0.9.  Of the 208 layers of the earlier fit those in binary16 lose nowhere up to 1.0, and one of ten in fp32 at 0.75, two more at 0.9.
     const bool small = (double)g.N * E * F * csr.K * C * RS < kSmallLayer;
@@ -366,11 +397,11 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
                 // Squared relative error of an output, in units of 1e-14, fitted to the measured ones: the tile kernel rounds
                 // its sum at every term (1.8e-7 at 100); here the pieces' own error, three roundings a step of a chunk's
                 // sum, one a chunk.  What is as exact by this measure, with 15 % to spare, may run.
-                const double here = 0.81 + 0.047 * 3 * RS * (CG / 2 / sh[3]) + 0.04 * p.nchunks;
-                if (here * 1.3 > 0.0335 * terms / std::max(1, tile_parts)) continue;
+                const double steps = RS * (CG / 2.0 / sh[3]);
+                if ((0.81 + 0.047 * 3 * steps + 0.04 * p.nchunks) * 1.3 > 0.0335 * terms / std::max(1, tile_parts)) continue;
             }
             const double t = estimate_matrix(p, RS, split, small);
-            if (best_us < 0 || t < best_us) {
+            if ((best_us < 0 || t < best_us) && (!split || rows_as_exact(p, RS * (CG / 2.0 / sh[3])))) {
                 best_us = t;
                 best = p;
             }

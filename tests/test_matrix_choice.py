@@ -1,0 +1,26 @@
+"""Which kernel an automatic forward takes, where the choice carries more than speed.  Needs no GPU."""
+import numpy as np
+import pytest
+
+from paper_2011_06295_amd import binding as B
+
+
+def _fp32_layer(kept, K=256, C=256, R=3, unify=False):
+    """A layer whose output channels keep these counts of weights in turn."""
+    rng = np.random.default_rng(21)
+    m = np.zeros((K, C * R * R), dtype=np.uint8)
+    for k in range(K):
+        m[k, rng.permutation(C * R * R)[:kept[k % len(kept)]]] = 1
+    w = rng.standard_normal((K, C, R, R)).astype(np.float32)
+    return B.SparseConv(w, m.reshape(w.shape), dtype="f32", unify=unify)
+
+
+@pytest.mark.parametrize("unify", [False, True])
+@pytest.mark.parametrize("short,kernel", [(9, "tile"), (1, "tile"), (40, "tile"), (200, "matrix"), (0, "matrix")])
+def test_short_rows_keep_the_precision_of_fp32_products(short, kernel, unify):
+    """256 -> 256, 14 x 14, 80 %: the matrix kernel holds a weight and an input in two binary16 pieces each, 1.0e-7 of a sum of
+    10 terms, where fp32 products leave 0.6e-7 (0.9e-7 and 0.5e-7 of 5 terms; from some 60 terms on it is the more exact one).
+    One such row keeps the layer on the tile kernel, with or without zero weights that fill it up; an empty row has no error."""
+    layer = _fp32_layer([460] * 255 + [short], unify=unify)
+    assert layer.get_kernel(256, 14, 14, 1, 1) == kernel
+    layer.close()
