@@ -78,7 +78,7 @@ int find_tile(sparse_conv_s* h, const Geometry& g, Route** out)
 
 // Which kernel an automatic forward of the geometry takes: the one that is estimated cheaper, where the matrix kernel can
 // run.  It multiplies the zeros between the stored weights as well, at 10 to 25 times the tile kernel's rate: for binary16
-// that pays at most sparsities pruning reaches, for fp32 (three binary16 products a weight) below about 89 %, and further
+// that pays at most sparsities pruning reaches, for fp32 (three binary16 products a weight) below 90 %, and further
 // up where the tile kernel loses its lanes to padding or to a stride.
 int get_route(sparse_conv_s* h, const Geometry& g, const Route** out)
 {
