@@ -346,6 +346,7 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
     // fp32 sums: the share of an output's terms that do not fall on padding, and the terms, both in the mean
     double inside = 0.0, terms = 0.0;
     std::vector<int> before;       // [K][C + 1]: a row's weights (but zeros, which add no rounding) before a channel
+    int shortest = INT_MAX;        // weights of the shortest row that has any
     if (split) {
         double rows = 0, cols = 0;
         for (int i = 0; i < E; ++i)
@@ -354,13 +355,13 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
             for (int s = 0; s < S; ++s) cols += (unsigned)(j * g.stride + s - g.pad) < (unsigned)g.W;
         inside = rows * cols / ((double)E * F * RS);
         terms = (double)csr.colidx.size() / csr.K * inside;
-        before.assign((size_t)csr.K * (C + 1), 0);
         for (int k = 0; k < csr.K; ++k) {
-            int* n = &before[(size_t)k * (C + 1)];
-            for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) n[csr.colidx[i] / RS + 1] += csr.val32[i] != 0.f;
-            for (int c = 0; c < C; ++c) n[c + 1] += n[c];
+            int n = 0;
+            for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) n += csr.val32[i] != 0.f;
+            if (n) shortest = std::min(shortest, n);
         }
     }
+    const int parts = std::max(1, tile_parts);
     // Terms that a term of row k is summed with, in the mean, itself included, where every `width` channels have a sum.
     auto company = [&](int k, int width) {
         const int* n = &before[(size_t)k * (C + 1)];
@@ -375,7 +376,16 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
     // has no term in some steps and chunks: then the pieces' own error is most of it (10 terms: 9e-8 to 1.0e-7, the tile kernel
     // 5e-8 to 6e-8).  Of 1568 pairs of plans with rows of 2 to 448 terms, 183 pass; their error here is 0.95 of that there or less.
     auto rows_as_exact = [&](const MatrixPlan& p, double steps) {
-        const int own = p.CG / 2 / p.KS * 16, part = (C + std::max(1, tile_parts) - 1) / std::max(1, tile_parts);
+        if ((0.81 + 0.047 * 3 * steps + 0.04 * p.nchunks) * 1.1 <= 0.0335 * shortest * inside / parts) return true;   // the least they can be
+        if (before.empty()) {
+            before.assign((size_t)csr.K * (C + 1), 0);
+            for (int k = 0; k < csr.K; ++k) {
+                int* n = &before[(size_t)k * (C + 1)];
+                for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) n[csr.colidx[i] / RS + 1] += csr.val32[i] != 0.f;
+                for (int c = 0; c < C; ++c) n[c + 1] += n[c];
+            }
+        }
+        const int own = p.CG / 2 / p.KS * 16, part = (C + parts - 1) / parts;
         for (int k = 0; k < csr.K; ++k) {
             const int n = before[(size_t)(k + 1) * (C + 1) - 1];
             if (!n) continue;
@@ -401,7 +411,7 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
                 // its sum at every term (1.8e-7 at 100); here the pieces' own error, three roundings a step of a chunk's
                 // sum, one a chunk.  What is as exact by this measure, with 15 % to spare, may run.
                 const double steps = RS * (CG / 2.0 / sh[3]);
-                if ((0.81 + 0.047 * 3 * steps + 0.04 * p.nchunks) * 1.3 > 0.0335 * terms / std::max(1, tile_parts)) continue;
+                if ((0.81 + 0.047 * 3 * steps + 0.04 * p.nchunks) * 1.3 > 0.0335 * terms / parts) continue;
             }
             const double t = estimate_matrix(p, RS, split, small);
             if ((best_us < 0 || t < best_us) && (!split || rows_as_exact(p, RS * (CG / 2.0 / sh[3])))) {
