@@ -91,13 +91,13 @@ int get_route(sparse_conv_s* h, const Geometry& g, const Route** out)
     // (both forward entry points take the same kernel: the table has to fit the static scratch)
     if (h->matrix_holds < 0)
         h->matrix_holds = matrix_bytes_at_least(h->K, h->C, h->R, h->S, !half) <= kStaticScratchBytes && matrix_holds(h->csr, !half) ? 1 : 0;
-    double us = 0.0, share = 0.0;
-    if (h->matrix_holds && choose_matrix(h->csr, h->C, h->R, h->S, elem_bytes(h), g, r->tile.pool != 0, r->tile.csplit, r->plan, &us, &share)) {
+    double us = 0.0;
+    if (h->matrix_holds && choose_matrix(h->csr, h->C, h->R, h->S, elem_bytes(h), g, r->tile.pool != 0, r->tile.csplit, r->plan, &us)) {
         // stores are not hidden behind short rows: the tile kernel's estimate leaves them out
         const double terms = (double)h->csr.colidx.size() / h->K;
         const double mbytes = (double)g.N * ((double)h->C * g.H * g.W + (double)h->K * r->plan.E * r->plan.F) * elem_bytes(h) * 1e-6;
         const double tile_us = r->tile_clocks / 2400.0 + (terms < 32.0 ? 0.2 * mbytes : 0.0);
-        if (us < share * tile_us) {
+        if (matrix_pays(us, tile_us, !half)) {
             if (!h->matrix) {
                 std::unique_ptr<MatrixWeights> m(new MatrixWeights());
                 pack_matrix_weights(h->csr, h->C, h->R, h->S, !half, *m);

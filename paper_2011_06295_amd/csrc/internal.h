@@ -294,11 +294,12 @@ bool stages_runs(const MatrixPlan& p, int elem_bytes);
 // Fills p for the given split; false if the kernel cannot run it.
 bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, int MK, int NP, int WK, int KS,
                  int CG, MatrixPlan& p);
-// The cheapest split by estimate (microseconds in *us; *share: of the tile kernel's estimate, below which it is taken); false if
-// there is none.  tile_parts: the channel parts of the tile
+// The cheapest split by estimate (microseconds in *us); false if there is none.  tile_parts: the channel parts of the tile
 // kernel's plan (they decide how exact its fp32 sums are, and the matrix kernel's must not be less so).
 bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, int tile_parts,
-                   MatrixPlan& p, double* us, double* share);
+                   MatrixPlan& p, double* us);
+// Whether that is worth taking beside the tile kernel's estimate.
+bool matrix_pays(double us, double tile_us, bool split);
 // Host check of the weight table against the CSR; 0, or the number of the first check that failed.
 int check_matrix(const Csr& csr, int C, int R, int S, const MatrixWeights& m);
 // Host check of every split that plan_matrix accepts for the geometry, as the kernel walks it: each tap of each output in the

@@ -241,23 +241,19 @@ namespace {
 //  * A chunk's staging blocks cost 59 to 299 clocks each by kind (single pixels or runs, half or two pieces); multiplying and
 //    staging hide each other little.  What a wavefront does not have in flight costs most of a memory latency a block.
 //  * Workgroups run in rounds of what is resident.
-// Layers of fewer than 4e8 products, zeros counted, take 9 to 35 us, most of it what every launch costs: an earlier fit to 208
-// layers chooses as well among their splits (1.0 to 2.5 % above the fastest in the mean, this one 1.4 to 2.4 %) and is kept for
-// them.  Above, this one is 1 to 3 % above the fastest and the earlier one 3 to 6 %.
-constexpr double kSmallLayer = 4e8;
-double estimate_matrix(const MatrixPlan& p, int RS, bool split, bool small)
+// (A launch of few products is mostly the fixed part: 51 fp32 and 44 binary16 layers of fewer than 4e8, zeros counted, are
+// within 2.4 and 1.4 % of their fastest split in the mean as well.)
+double estimate_matrix(const MatrixPlan& p, int RS, bool split)
 {
     struct Clocks { double fixed, chain, chain_mf, mf, read, chunk, stage_chunk, stage, run_chunk, run, both, late, pair, tail; };
     static const Clocks k16 = {11300, 172, 17.2, 40.9, 9.2, 482, 13, 58.5, 2, 197, 1.24, 659, 993, 1.0},
                         k32 = {11800, 7, 49.0, 38.9, 1.5, 306, 45, 139, 6, 290, 1.19, 676, 2110, 1.09};
-    static const Clocks small16 = {10570, 267, 21.0, 51.4, 0, 556, 169, 169, 169, 169, 0.35, 0, 845, 0.83},
-                        small32 = {9630, 235, 44.9, 52.9, 0, 42, 10, 242, 10, 242, 0.35, 0, 1756, 0.88};
-    const Clocks& k = small ? (split ? small32 : small16) : split ? k32 : k16;
+    const Clocks& k = split ? k32 : k16;
     const int unit = split ? 1 : 2, pieces = split ? 2 : 1;
-    const bool runs = !small && stages_runs(p, split ? 4 : 2);
+    const bool runs = stages_runs(p, split ? 4 : 2);
     const int blocks = runs ? (p.CG * p.quads + 63) / 64 : p.CG * p.EB, fly = runs ? p.wide_fly : p.fly;
     // workgroups a CU holds: registers allow two, three of the small variants, four of the smallest
-    const int room = small || p.MK * p.NP * pieces > 4 ? 2 : !split && p.ahead == 2 && p.fly == unit && p.KS == 1 && !runs ? 4 :
+    const int room = p.MK * p.NP * pieces > 4 ? 2 : !split && p.ahead == 2 && p.fly == unit && p.KS == 1 && !runs ? 4 :
                      fly == (runs ? (split ? 2 : 0) : 3 * unit) ? 2 : 3;
     const int conc_max = std::min(room, kMaxLds / p.lds_bytes);
     const double mf = p.MK * p.NP * (split ? 3 : 1), own = (double)(p.CG / 2 / p.KS) * RS;
@@ -338,7 +334,7 @@ int check_matrix_plans(int K, int C, int R, int S, int elem_bytes, const Geometr
 }
 
 bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, int tile_parts,
-                   MatrixPlan& best, double* us, double* share)
+                   MatrixPlan& best, double* us)
 {
     const bool split = elem_bytes == 4;
     const int RS = R * S;
@@ -394,12 +390,6 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
         }
         return true;
     };
-    // Taken below these shares of the tile kernel's estimate.  Of the 43 larger layers in binary16 none is slower at 0.95 or 1.0,
-    // one by 5 % at 1.05.  fp32, 71 layers timed in turn over blocks of a tenth of a second, which heat the chip as a pass does:
-    // up to 0.85 all gain 6 % or more; between 0.85 and 0.9 lie 256 -> 256, 14 x 14, batch 256 at 90 % (169 us, tile kernel 167)
-    // and its like, and from 0.9 to 1.0 six of twelve lose 5 to 19 %.  Of the 208 layers of the earlier fit those in binary16 lose nowhere
-    // up to 1.0, and one of ten in fp32 at 0.75, two more at 0.9.
-    const bool small = (double)g.N * E * F * csr.K * C * RS < kSmallLayer;
     double best_us = -1.0;
     for (const auto& sh : split ? kShapes32 : kShapes16)
         for (int CG = 2; CG <= 2 * kMatrixGroups; CG *= 2) {
@@ -413,7 +403,7 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
                 const double steps = RS * (CG / 2.0 / sh[3]);
                 if ((0.81 + 0.047 * 3 * steps + 0.04 * p.nchunks) * 1.3 > 0.0335 * terms / parts) continue;
             }
-            const double t = estimate_matrix(p, RS, split, small);
+            const double t = estimate_matrix(p, RS, split);
             if ((best_us < 0 || t < best_us) && (!split || rows_as_exact(p, RS * (CG / 2.0 / sh[3])))) {
                 best_us = t;
                 best = p;
@@ -421,9 +411,15 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
         }
     if (best_us < 0) return false;
     *us = best_us;
-    *share = small ? (split ? 0.75 : 0.95) : (split ? 0.85 : 0.95);
     return true;
 }
+
+// Taken below these shares of the tile kernel's estimate.  binary16: of 504 layers of every size timed in turn, where
+// 0.95 or less is estimated six are 4 to 14 % slower, all of 8 to 10 us, and the mean loses 2 % to the better kernel of each
+// (4 % at 0.9).  fp32, 71 layers, timed over blocks of a tenth of a second, which heat the chip as a pass does: up to 0.85 all
+// gain 6 % or more; between 0.85 and 0.9 lie 256 -> 256, 14 x 14, batch 256 at 90 % (169 us, tile kernel 167) and its like,
+// and from 0.9 to 1.0 six of twelve lose 5 to 19 %.
+bool matrix_pays(double us, double tile_us, bool split) { return us < (split ? 0.85 : 0.95) * tile_us; }
 
 void fill_matrix_args(const MatrixWeights& m, const MatrixPlan& p, int K, int C, int R, int S, const Geometry& g, MatrixArgs& a)
 {
