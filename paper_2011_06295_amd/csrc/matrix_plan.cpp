@@ -414,12 +414,14 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
     return true;
 }
 
-// Taken below these shares of the tile kernel's estimate.  binary16: of 504 layers of every size timed in turn, where
-// 0.95 or less is estimated six are 4 to 14 % slower, all of 8 to 10 us, and the mean loses 2 % to the better kernel of each
-// (4 % at 0.9).  fp32, 71 layers, timed over blocks of a tenth of a second, which heat the chip as a pass does: up to 0.85 all
-// gain 6 % or more; between 0.85 and 0.9 lie 256 -> 256, 14 x 14, batch 256 at 90 % (169 us, tile kernel 167) and its like,
-// and from 0.9 to 1.0 six of twelve lose 5 to 19 %.
-bool matrix_pays(double us, double tile_us, bool split) { return us < (split ? 0.85 : 0.95) * tile_us; }
+// binary16: taken where it is estimated 0.7 us faster.  Of 504 layers of every size timed in turn, four that take it so are 4 to
+// 8 % slower, and the mean loses 2.2 % to the better kernel of each.  (The 0.7 us are for launches of 8 to 10 us, most of which
+// both kernels have alike: without, 16 are slower, by up to 20 %.  Below 0.95 of the tile kernel's estimate instead: six, by up
+// to 14 %, the mean loses 2.3 %, and VGG-16's last layer takes 26 us by the tile kernel for 18.7.)
+// fp32: taken below 0.85 of the tile kernel's estimate.  Of 71 layers, timed over blocks of a tenth of a second, which heat the
+// chip as a pass does, all below gain 6 % or more; between 0.85 and 0.9 lie 256 -> 256, 14 x 14, batch 256 at 90 % (169 us, tile
+// kernel 167) and its like, and from 0.9 to 1.0 six of twelve lose 5 to 19 %.
+bool matrix_pays(double us, double tile_us, bool split) { return us < (split ? 0.85 * tile_us : tile_us - 0.7); }
 
 void fill_matrix_args(const MatrixWeights& m, const MatrixPlan& p, int K, int C, int R, int S, const Geometry& g, MatrixArgs& a)
 {

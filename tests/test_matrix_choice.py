@@ -15,6 +15,12 @@ def _fp32_layer(kept, K=256, C=256, R=3, unify=False):
     return B.SparseConv(w, m.reshape(w.shape), dtype="f32", unify=unify)
 
 
+def _masked(K, C, density):
+    rng = np.random.default_rng(22)
+    w = rng.standard_normal((K, C, 3, 3), dtype=np.float32)
+    return w, (rng.random(w.shape, dtype=np.float32) < density).astype(np.uint8)
+
+
 @pytest.mark.parametrize("unify", [False, True])
 @pytest.mark.parametrize("short,kernel", [(9, "tile"), (1, "tile"), (40, "tile"), (200, "matrix"), (0, "matrix")])
 def test_short_rows_keep_the_precision_of_fp32_products(short, kernel, unify):
@@ -39,9 +45,13 @@ def test_fp32_layers_take_the_matrix_kernel_where_it_was_measured_faster(sparsit
 def test_small_layers_are_priced_as_they_run(N):
     """512 -> 512, 2 x 2, 80 %, binary16 takes 18 us by the matrix kernel and 23 to 32 by the tile kernel from 30 images to 60; an
     estimate of single pixels, which the kernel does not stage there, had it at the tile kernel up to 42."""
-    rng = np.random.default_rng(22)
-    w = rng.standard_normal((512, 512, 3, 3), dtype=np.float32)
-    m = (rng.random(w.shape, dtype=np.float32) < 0.2).astype(np.uint8)
-    layer = B.SparseConv(w, m, dtype="f16")
+    layer = B.SparseConv(*_masked(512, 512, 0.2), dtype="f16")
     assert layer.get_kernel(N, 2, 2, 1, 1) == "matrix"
+    layer.close()
+
+
+def test_binary16_layers_take_the_kernel_that_was_measured_faster():
+    """VGG-16's last layer, batch 256 (512 -> 512, 2 x 2, 95 %): 18.7 us by the matrix kernel, 26 by the tile kernel."""
+    layer = B.SparseConv(*_masked(512, 512, 0.05), dtype="f16")
+    assert layer.get_kernel(256, 2, 2, 1, 1) == "matrix"
     layer.close()
