@@ -377,7 +377,9 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
     // Wide staging.  The address unit takes some 20 clocks for a load of 64 lanes, 2 bytes each or 8 (512 -> 512 channels, 4 x 4,
     // binary16, batch 256: of 37.6 us, 13 were these loads).  So where planes are whole runs of kPx pixels, a lane takes runs: all
     // pixels of the tile's lattice elements are consecutive, images one behind the other, and the padding between them, which no
-    // run holds, is cleared once.  (That layer's best split: 37.5 -> 26.4 us; in fp32, batch 128: 51.3 -> 37.1.)  A block is 64 runs, those of all channel groups one behind the other.
+    // run holds, is cleared once.  (That layer's best split: 37.5 -> 26.4 us; in fp32, batch 128: 51.3 -> 37.1.)  A block is 64
+    // runs, those of all channel groups one behind the other.  Inputs start at any element, as vector memory loads 8 bytes from
+    // any address: 2 bytes off a word that layer takes 24.8 us for 23.6 (single pixels: 33.3), 2 x 2 maps 21.4 for 18.0.
     const int nwide = WIDE ? (a.CG * a.quads + 63) >> 6 : 0;
     int quad0 = 0;                              // the tile's first run
     if constexpr (WIDE) {
@@ -1063,7 +1065,7 @@ int launch_fly(const MatrixArgs& a, const MatrixPlan& p, hipStream_t s)
 {
     constexpr int unit = sizeof(T) == 4 ? 1 : 2;
     if (a.own_steps % p.ahead) return (int)hipErrorInvalidValue;
-    if (stages_runs(p, sizeof(T)) && reinterpret_cast<uintptr_t>(a.x) % 8 == 0) {
+    if (stages_runs(p, sizeof(T))) {      // (from any element on: vector memory takes 8 bytes at any address)
         const int kind = p.ahead * 10 + p.wide_fly;
         if (kind == 21) return launch_one<T, MK, NP, 2, 1, KS, true>(a, p.grid, p.lds_bytes, s);
         if (kind == 31) return launch_one<T, MK, NP, 3, 1, KS, true>(a, p.grid, p.lds_bytes, s);

@@ -154,7 +154,7 @@ int matrix_extra_lds(const MatrixPlan& p)
     return p.MK * p.WK * MatrixWeights::kSlots * (int)sizeof(MatrixWeights::Small) + p.images * kImageWindowBytes + p.EB * 8;
 }
 
-// Whether the kernel stages runs (where the input lies on a run's boundary).  Where a wavefront has but one block of single
+// Whether the kernel stages runs.  Where a wavefront has but one block of single
 // pixels to stage (binary16: two), runs would leave wavefronts without one: of 506 splits of 27 layers those with one are 2 to
 // 4 % slower with runs in the mean, up to 24 % (64 -> 256, 56 x 56, binary16: 65 -> 80 us); with two (three) and more, 6 to 40 %
 // faster, two in a hundred of them slower, by 5 % at most.

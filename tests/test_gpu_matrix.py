@@ -340,8 +340,8 @@ def test_matrix_kernel_binary16_subnormals():
                                    (24, 48, 64, 3, 3, 29, 32, 2, 1), (134, 200, 80, 1, 3, 1, 36, 1, 0), (60, 240, 252, 1, 1, 16, 14, 1, 0), (52, 40, 64, 3, 3, 3, 44, 1, 3)],
                          ids=lambda s: "x".join(map(str, s)))
 def test_matrix_kernel_stages_runs_and_single_pixels(dtype, shape):
-    """Where planes are whole runs of 8 bytes the kernel stages runs, else, and from an input that does not start on a run's
-    boundary, pixel by pixel: both against the oracle, with an input that is not finite and (fp32) one far above the others."""
+    """Where planes are whole runs of 8 bytes the kernel stages runs, else pixel by pixel: against the oracle, from an input that
+    starts on a run's boundary and one that does not, with a value that is not finite and (fp32) one far above the others."""
     import torch
     layer, w, m, x = _layer(dtype, shape, 101, 0.9)
     N, C, K, R, S, H, W, st, p = shape
@@ -360,4 +360,25 @@ def test_matrix_kernel_stages_runs_and_single_pixels(dtype, shape):
         got = layer.forward(data, st, p).float().cpu().numpy().astype(np.float64)
         assert np.array_equal(np.isposinf(got), np.isposinf(ref)) and np.array_equal(np.isneginf(got), np.isneginf(ref))
         assert_close(got[fin], ref[fin], TOL[dtype], f"{dtype} {shape}")
+    layer.close()
+
+
+@pytest.mark.parametrize("dtype,shape", [("f32", (516, 64, 70, 3, 3, 4, 4, 1, 1)), ("f32", (40, 64, 65, 3, 3, 14, 14, 1, 1)), ("f32", (60, 240, 252, 1, 1, 16, 14, 1, 0)),
+                                         ("f16", (1692, 130, 66, 3, 3, 2, 2, 1, 1)), ("f16", (40, 64, 65, 3, 3, 14, 14, 1, 1)), ("f16", (60, 240, 252, 1, 1, 16, 14, 1, 0))],
+                         ids=lambda v: v if isinstance(v, str) else "x".join(map(str, v)))
+def test_matrix_kernel_results_do_not_depend_on_the_inputs_address(dtype, shape):
+    """An input that starts one element off a run's boundary gives the same bits, also where fp32 values within an image are so
+    far apart that the scale its first chunk gives them shows."""
+    import torch
+    layer, w, m, x = _layer(dtype, shape, 103, 0.9)
+    N, C, K, R, S, H, W, st, p = shape
+    if dtype == "f32":
+        x *= np.exp2(np.random.default_rng(104).uniform(-20, 20, x.shape)).astype(np.float32)
+    assert layer.get_kernel(N, H, W, st, p) == "matrix"
+    aligned = torch.from_numpy(x).cuda().to(torch.float16 if dtype == "f16" else torch.float32)
+    want = layer.forward(aligned, st, p)
+    for off in (1, 2, 3):
+        shifted = torch.empty(aligned.numel() + off, dtype=aligned.dtype, device="cuda")[off:].view(aligned.shape)
+        shifted.copy_(aligned)
+        assert torch.equal(layer.forward(shifted, st, p), want), off
     layer.close()
