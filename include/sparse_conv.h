@@ -296,6 +296,10 @@ int sparse_conv_get_kernel(sparse_conv_t h, int N, int H, int W, int stride, int
  * for 12 ints. */
 int sparse_conv_get_matrix_plan(sparse_conv_t h, int N, int H, int W, int stride, int pad, int* params);
 
+/* How it stages its input there: *in_flight receives the blocks of 64 runs of 8 bytes that a wavefront has in flight, 0 where
+ * it stages single pixels ([8] above).  Returns as sparse_conv_get_matrix_plan.  Needs no GPU. */
+int sparse_conv_get_matrix_runs(sparse_conv_t h, int N, int H, int W, int stride, int pad, int* in_flight);
+
 /* The tile kernel's launch configuration for a geometry (in force unless sparse_conv_get_kernel says 1): [0] V .. [4] Cc, [5] the LDS
  * budget in force, [6] workgroups launched, [7] LDS bytes
  * per workgroup, [8] threads per workgroup, [9] stored plan entries

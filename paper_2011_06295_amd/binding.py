@@ -28,7 +28,7 @@ EXPORTS = (
     "sparse_conv_create", "sparse_conv_output_shape", "sparse_conv_forward", "sparse_conv_forward_static",
     "sparse_conv_get_csr", "sparse_conv_set_launch", "sparse_conv_get_launch", "sparse_conv_set_epilogue", "sparse_conv_autotune",
     "sparse_conv_create_codebook", "sparse_conv_get_codebook", "sparse_conv_check_plan", "sparse_conv_rank_launches", "sparse_conv_get_kernel",
-    "sparse_conv_get_matrix_plan",
+    "sparse_conv_get_matrix_plan", "sparse_conv_get_matrix_runs",
     "sparse_conv_probe_lds_read", "sparse_conv_probe_copy",
     "sparse_conv_last_hip_error", "sparse_conv_strerror", "sparse_conv_destroy",
 )
@@ -67,6 +67,7 @@ def _load():
     lib.sparse_conv_check_plan.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip]
     lib.sparse_conv_get_kernel.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip]
     lib.sparse_conv_get_matrix_plan.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip]
+    lib.sparse_conv_get_matrix_runs.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip]
     lib.sparse_conv_rank_launches.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip, ip]
     lib.sparse_conv_autotune.argtypes = [vp, vp, vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, vp, C.c_int,
                                          C.POINTER(C.c_float)]
@@ -225,10 +226,12 @@ MATRIX_PLAN_KEYS = ("MK", "NP", "WK", "KS", "CG", "EB", "nchunks", "ahead", "fly
 
 
 def sparse_conv_get_matrix_plan(handle: int, N: int, H: int, W: int, stride: int, pad: int) -> dict:
-    """The matrix kernel's share-out of the geometry (an error where the tile kernel is taken)."""
-    arr = (C.c_int * 12)()
+    """The matrix kernel's share-out of the geometry and how it stages its input ("runs": blocks of runs in flight, 0 for single
+    pixels); an error where the tile kernel is taken."""
+    arr, runs = (C.c_int * 12)(), C.c_int(0)
     _check(_lib.sparse_conv_get_matrix_plan(handle, N, H, W, stride, pad, arr), "sparse_conv_get_matrix_plan", handle)
-    return dict(zip(MATRIX_PLAN_KEYS, arr))
+    _check(_lib.sparse_conv_get_matrix_runs(handle, N, H, W, stride, pad, C.byref(runs)), "sparse_conv_get_matrix_runs", handle)
+    return dict(zip(MATRIX_PLAN_KEYS, arr), runs=runs.value)
 
 
 def sparse_conv_check_plan(handle: int, N: int, H: int, W: int, stride: int, pad: int) -> int:
