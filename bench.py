@@ -4,8 +4,8 @@
 A step is one pass of the hot path over one batch: the sparse convolution of
 every layer of the workload on its resident (already in HBM) input.  Prints one
 JSON line: effective GFLOP/s = 2 * stored weights * E * F * N / time, the
-roofline position of the tile kernel, per-layer figures and the CPU oracle
-timed on a bounded sample of the same workload.
+roofline position of the pass, per-layer figures of the kernel that each layer
+takes and the CPU oracle timed on a bounded sample of the same workload.
 """
 from __future__ import annotations
 
@@ -20,7 +20,7 @@ import numpy as np
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-from paper_2011_06295_amd.roofs import (HBM_PEAK, LDS_PEAK, VALU_PEAK_FMA, MEASURED_LDS_B_PER_CLK_PER_CU,  # noqa: E402
+from paper_2011_06295_amd.roofs import (HBM_PEAK, LDS_PEAK, MFMA_PEAK_FLOPS, VALU_PEAK_FMA, MEASURED_LDS_B_PER_CLK_PER_CU,  # noqa: E402
                                         MEASURED_TRAFFIC_BYTES_PER_LAUNCH,
                                         MEASURED_COPY_BYTES_PER_S, CUS, CLOCK_HZ, PROFILE as ROOF_PROFILE)
 
@@ -50,17 +50,21 @@ def make_workload(name: str):
 
 
 def layer_roofs(run, N, b):
+    """Work of a layer and the times it takes at the peaks of the kernel it runs on.  tile: a multiply-add and b bytes from LDS
+    per stored weight and output; matrix: binary16 products of all weights, zeros included, three to an fp32 one."""
     s = run.spec
     macs = run.macs(N)
     hbm_bytes = N * s.C * s.H * s.W * b + N * s.K * s.E * s.F * b + run.nnz * (b + 4) + (s.K + 1) * 4
-    return {
-        "macs": macs,
-        "hbm_bytes": hbm_bytes,
-        "lds_bytes": macs * b,
-        "t_hbm": hbm_bytes / HBM_PEAK,
-        "t_lds": macs * b / LDS_PEAK,
-        "t_valu": macs / VALU_PEAK_FMA,
-    }
+    kernel = run.layer.get_kernel(N, s.H, s.W, s.stride, s.pad)
+    lds_bytes, fmas, flops = macs * b, macs, 0
+    if kernel == "matrix":
+        lds_bytes, fmas, flops = 0, 0, 2 * N * s.E * s.F * s.K * s.L * (3 if b == 4 else 1)
+    roofs = {"kernel": kernel, "macs": macs, "hbm_bytes": hbm_bytes, "lds_bytes": lds_bytes, "mfma_flops": flops,
+             "t_hbm": hbm_bytes / HBM_PEAK, "t_lds": lds_bytes / LDS_PEAK, "t_valu": fmas / VALU_PEAK_FMA,
+             "t_mfma": flops / MFMA_PEAK_FLOPS}
+    roofs["bound"], roofs["t_roof"] = max((("hbm", roofs["t_hbm"]), ("lds", roofs["t_lds"]), ("alu", roofs["t_valu"]),
+                                           ("mfma", roofs["t_mfma"])), key=lambda kv: kv[1])
+    return roofs
 
 
 def oracle_leg(net, work, budget_s=12.0, npts=2000, time_it=True):
@@ -349,18 +353,22 @@ def run_workload(name, args, steps, warmup, brief):
         t_raw = raw[i]
         t = max(t_raw - event_gap, 0.25 * t_raw)
         roofs = layer_roofs(r, N, b)
-        bound = max(("hbm", roofs["t_hbm"]), ("lds", roofs["t_lds"]), ("alu", roofs["t_valu"]), key=lambda kv: kv[1])
-        layers.append({
+        geom = (N, r.spec.H, r.spec.W, r.spec.stride, r.spec.pad)
+        entry = {
             "name": r.spec.name, "shape": f"{r.spec.C}x{r.spec.H}x{r.spec.W}->{r.spec.K}",
             "nnz": r.nnz, "us": round(t * 1e6, 2), "us_between_events": round(t_raw * 1e6, 2),
             "gflops": round(2 * roofs["macs"] / t / 1e9, 1),
-            "bound": bound[0], "roof_frac": round(bound[1] / t, 4),
-            "hbm_GBs": round(roofs["hbm_bytes"] / t / 1e9, 1), "lds_GBs": round(roofs["lds_bytes"] / t / 1e9, 1),
-            # "matrix": the layer runs on the matrix cores (roof_frac and the rates stay those of the stored weights' work)
-            "kernel": r.layer.get_kernel(N, r.spec.H, r.spec.W, r.spec.stride, r.spec.pad),
-            "launch": {k: v for k, v in r.layer.get_launch(N, r.spec.H, r.spec.W, r.spec.stride, r.spec.pad).items()
-                       if k in ("V", "WP", "WK", "KW", "Cc", "LP", "kblocks", "store", "lanes", "csplit", "grid", "lds_bytes", "threads")},
-        })
+            "bound": roofs["bound"], "roof_frac": round(roofs["t_roof"] / t, 4),
+            "hbm_GBs": round(roofs["hbm_bytes"] / t / 1e9, 1), "kernel": roofs["kernel"],
+        }
+        if roofs["kernel"] == "matrix":
+            entry["mfma_TFLOPs"] = round(roofs["mfma_flops"] / t / 1e12, 1)
+            entry["launch"] = r.layer.get_matrix_plan(*geom)
+        else:
+            entry["lds_GBs"] = round(roofs["lds_bytes"] / t / 1e9, 1)
+            entry["launch"] = {k: v for k, v in r.layer.get_launch(*geom).items()
+                               if k in ("V", "WP", "WK", "KW", "Cc", "LP", "kblocks", "store", "lanes", "csplit", "grid", "lds_bytes", "threads")}
+        layers.append(entry)
 
     if args.copy_probe_mib > 0:
         src = torch.empty(args.copy_probe_mib << 20, dtype=torch.uint8, device="cuda").random_(0, 255)
@@ -374,10 +382,19 @@ def run_workload(name, args, steps, warmup, brief):
     roofs = [layer_roofs(r, N, b) for r in net.runs]
     nl = len(net.runs)
     avg_launch_s = gpu_ms * 1e-3 / (steps * nl)
-    sums = {k: sum(rf[k] for rf in roofs) for k in ("t_hbm", "t_lds", "t_valu", "lds_bytes", "hbm_bytes")}
+    sums = {k: sum(rf[k] for rf in roofs) for k in ("t_hbm", "t_lds", "t_valu", "t_roof", "lds_bytes", "hbm_bytes")}
+    kernels = sorted({rf["kernel"] for rf in roofs}, reverse=True)
     # the binding roof is the largest of the three times (fp32: the LDS read rate and the non-packed multiply-add
     # rate tie, reported as LDS; fp16: half the LDS bytes per multiply-add, so the multiply-add rate binds)
-    if sums["t_valu"] > sums["t_lds"] and sums["t_valu"] >= sums["t_hbm"]:
+    if "matrix" in kernels:
+        # layers on either kernel have roofs of their own: the pass is held against the sum of their times, in the unit of
+        # the roof that most of it belongs to
+        share = {k: sum(rf["t_roof"] for rf in roofs if rf["bound"] == k) for k in ("hbm", "lds", "alu", "mfma")}
+        bound = max(share, key=share.get)
+        peak, unit = {"hbm": (HBM_PEAK / 1e9, "GB/s"), "lds": (LDS_PEAK / 1e9, "GB/s"), "alu": (2.0 * VALU_PEAK_FMA / 1e12, "TFLOP/s"),
+                      "mfma": (MFMA_PEAK_FLOPS / 1e12, "TFLOP/s")}[bound]
+        roofline = {"bound": bound, "achieved": peak * sums["t_roof"] / nl / avg_launch_s, "peak": peak, "unit": unit}
+    elif sums["t_valu"] > sums["t_lds"] and sums["t_valu"] >= sums["t_hbm"]:
         roofline = {"bound": "alu", "achieved": 2.0 * total_macs / nl / avg_launch_s / 1e12,
                     "peak": 2.0 * VALU_PEAK_FMA / 1e12, "unit": "TFLOP/s"}
     elif sums["t_lds"] >= sums["t_hbm"]:
@@ -387,7 +404,7 @@ def run_workload(name, args, steps, warmup, brief):
         roofline = {"bound": "hbm", "achieved": sums["hbm_bytes"] / nl / avg_launch_s / 1e9, "peak": HBM_PEAK / 1e9,
                     "unit": "GB/s"}
     roofline["frac"] = roofline["achieved"] / roofline["peak"]
-    # the LDS fraction whatever binds, and the same against the read rate measured on this machine (bench.py --probe)
+    # the LDS fraction whatever binds (of what tile kernel layers read), and the same against the read rate measured on this machine (bench.py --probe)
     roofline["lds_frac"] = sums["lds_bytes"] / nl / avg_launch_s / LDS_PEAK
     roofline["lds_frac_of_measured_read_rate"] = (sums["lds_bytes"] / nl / avg_launch_s /
                                                   (MEASURED_LDS_B_PER_CLK_PER_CU * CUS * CLOCK_HZ))
@@ -396,17 +413,17 @@ def run_workload(name, args, steps, warmup, brief):
     # HBM-side bytes per launch come from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs (profiles/); a bench run
     # does not count them, it quotes the profile of the same workload in its default configuration
     measured = MEASURED_TRAFFIC_BYTES_PER_LAUNCH.get(name) if not (args.launch or args.unify or args.codebook or args.fused) else None
-    if any(l["kernel"] == "matrix" for l in layers):   # the profiled traffic is that of the tile kernel's pass
+    if "matrix" in kernels:   # the profiled traffic is that of the tile kernel's pass
         measured = None
     roofline["traffic"] = measured[0] if measured else None
     if measured:
         roofline["traffic_source"] = measured[1]
         roofline["traffic_over_algorithmic"] = measured[0] / (sums["hbm_bytes"] / nl)
-    roofline["kernel"] = ", ".join(f"sc::{k}_kernel" for k in sorted({l["kernel"] for l in layers}, reverse=True))
+    roofline["kernel"] = ", ".join(f"sc::{k}_kernel" for k in kernels)
     roofline["avg_launch_us"] = avg_launch_s * 1e6
     roofline["launches_per_step"] = nl
     roofline["hbm_frac"] = sums["hbm_bytes"] / nl / avg_launch_s / HBM_PEAK
-    roofline["alu_frac"] = total_macs / nl / avg_launch_s / VALU_PEAK_FMA
+    roofline["alu_frac"] = sums["t_valu"] / nl / avg_launch_s
 
     out = {
         "metric": "effective GFLOP/s (2*nnz*E*F*N over the sparse conv layers of the workload)",

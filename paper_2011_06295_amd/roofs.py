@@ -12,6 +12,7 @@ VALU_PEAK_FMA = CUS * 64 * CLOCK_HZ            # non-packed fp32 multiply-adds p
                                                # (78.6 TFLOP/s; the 157.3 TFLOP/s datasheet figure is the packed form,
                                                # which this build does not use)
 VALU_PEAK_FMA_PACKED = 2 * VALU_PEAK_FMA
+MFMA_PEAK_FLOPS = 2.5e15                       # dense binary16 products on the matrix cores
 
 # measured with `bench.py --probe` (profiles/roof_probes.md)
 MEASURED_LDS_B_PER_CLK_PER_CU = 229.4          # ds_read_b128, 64 consecutive elements per wavefront, 16 wavefronts per CU
