@@ -284,7 +284,7 @@ int sparse_conv_check_plan(sparse_conv_t h, int N, int H, int W, int stride, int
  * zeros included, on the matrix cores, and which an automatic choice takes where it is estimated (sparse_conv_autotune:
  * measured) to be faster.  There fp32 numbers are sums of two binary16 numbers under scales that fit them: each product of
  * a stored weight with a finite input of any size is within 2^-21 of itself, and they are summed in fp32.  (An output channel
- * of few weights is the more exact in fp32 products: a layer that has one takes the tile kernel.)  Returns as
+ * of few weights is the more exact in fp32 products and is summed in them; a layer with many of them takes the tile kernel.)  Returns as
  * sparse_conv_get_launch.  Needs no GPU. */
 int sparse_conv_get_kernel(sparse_conv_t h, int N, int H, int W, int stride, int pad, int* kernel);
 

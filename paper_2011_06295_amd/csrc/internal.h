@@ -241,7 +241,7 @@ struct KernelArgs {
 // channels][group of 16 input channels][tap][piece][lane][8] binary16, lane l holding output channel l % 32 and input
 // channels 8 * (l / 32) .. + 7; behind it as much again as the last steps of the last block read ahead.  fp32 weights are
 // two binary16 pieces whose sum they are (to 2^-23 of the weight), after multiplication by 2^row_exp; those that pieces of
-// that scale do not hold (below 2^-2 after it, 2^-16 of their row's largest) stand in a list instead.
+// that scale do not hold (below 2^-2 after it, 2^-16 of their row's largest), and all of a row of few, stand in a list instead.
 struct MatrixWeights {
     struct Small {
         int row;           // in its block of 32 output channels; -1: none

@@ -27,8 +27,8 @@
 // fp32 layers.  A value is the sum of two binary16 numbers to 2^-23 of it; three of the four products of two such sums are
 // multiplied (the fourth is 2^-22 of the result or less), smallest first.  binary16 has few exponents, so the weights of an
 // output channel are scaled by a power of two of their own (those below 2^-16 of the largest, which two pieces do not hold, are
-// few: they stand in a list and are multiplied as fp32), and the inputs by one for each image of the tile, taken from the
-// image's largest magnitude in the first chunk.  The low piece of an input is kept times 2^12 and meets the high piece of the
+// few: they stand in a list and are multiplied as fp32; so are all weights of rows of few, which are more exact so), and the
+// inputs by one for each image of the tile, taken from the image's largest magnitude in the first chunk.  The low piece of an input is kept times 2^12 and meets the high piece of the
 // weight times 2^-12: so 29 binary orders of magnitude hold every value to 2^-23 (kWindow; without that factor 17).
 //  * An input above its image's window is left out, and its chunk is multiplied once more with only what was left out, under
 //    a scale that fits it, as often as something is left.

@@ -39,9 +39,39 @@ bool small_weight(float scaled) { return scaled != 0.f && std::fabs(scaled) < 0.
 // Normally distributed weights have 4 in a block of 147456.
 constexpr int kMaxSmall = 32;
 
-}  // namespace
+// Weights of a row but zeros, which add no rounding.
+int row_weights(const Csr& csr, int k)
+{
+    int n = 0;
+    for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) n += csr.val32[i] != 0.f;
+    return n;
+}
 
-namespace {
+// fp32 rows of few weights are the less exact in two pieces: all of their weights stand in the list, where they are multiplied as
+// fp32, each row a sum of its own as in the tile kernel (33 rows of 3 to 54 weights: the tile kernel's error to the digit).  A sum
+// of two pieces' products is rounded with every tap, so the two meet at some 35, 65 and 130 weights under 1 x 1, 3 x 3 and 5 x 5
+// taps: a layer that has a row below that and not in the list takes the tile kernel.
+int short_row(int RS) { return 32 + 4 * RS; }
+// Weights of short rows a block of 32 rows may have, at 2.2 us a tile for eight (estimate_matrix counts them).  A layer with more
+// has none in the list: one whose rows are mostly short is the tile kernel's.
+constexpr int kMaxShort = 160;
+
+// [K] whether the row's weights stand in the list.
+std::vector<char> listed_rows(const Csr& csr, int RS)
+{
+    std::vector<char> listed(csr.K, 0);
+    for (int k0 = 0; k0 < csr.K; k0 += 32) {
+        int weights = 0;
+        for (int k = k0; k < std::min(csr.K, k0 + 32); ++k) {
+            const int n = row_weights(csr, k);
+            if (n > short_row(RS)) continue;
+            listed[k] = 1;
+            weights += n;
+        }
+        if (weights > kMaxShort) return std::vector<char>(csr.K, 0);
+    }
+    return listed;
+}
 
 // Halves of the image: behind the last stream, the groups of its last chunk that are not there (they meet zeros of the input)
 // and what its last steps ask for ahead.
@@ -85,13 +115,14 @@ void pack_matrix_weights(const Csr& csr, int C, int R, int S, bool split, Matrix
     m.row_exp.assign((size_t)m.KF * 32, 0);
     m.small_first.assign(split ? (size_t)m.KF + 1 : 0, 0);
     m.slots.assign(split ? (size_t)m.KF * m.kSlots : 0, {-1, 0, 0, 0.f});
+    const std::vector<char> listed = split ? listed_rows(csr, RS) : std::vector<char>();
     for (int k = 0; k < K; ++k) {
         m.longest = std::max(m.longest, csr.rowptr[k + 1] - csr.rowptr[k]);
         if (split) m.row_exp[k] = row_exponent(csr, k);
         for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) {
             const int col = csr.colidx[i];
             const float w = split ? std::ldexp(csr.val32[i], m.row_exp[k]) : csr.val32[i];
-            if (split && small_weight(w)) {
+            if (split && (small_weight(w) || (listed[k] && w != 0.f))) {
                 const MatrixWeights::Small s{k % 32, col / RS, col % RS, w};
                 MatrixWeights::Small *slot = &m.slots[(size_t)(k / 32) * m.kSlots], *end = slot + m.kSlots;
                 while (slot < end && slot->row >= 0) ++slot;
@@ -122,12 +153,14 @@ int check_matrix(const Csr& csr, int C, int R, int S, const MatrixWeights& m)
     for (const auto& s : m.slots) listed += s.row >= 0;
     std::vector<int> used(m.KF, 0);
     std::vector<uint16_t> rest = m.image;
+    const std::vector<char> in_list = m.pieces == 2 ? listed_rows(csr, RS) : std::vector<char>();
     for (int k = 0; k < csr.K; ++k)
         for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) {
             const int col = csr.colidx[i];
             const size_t at = image_at(m, RS, k, col);
             const float scaled = std::ldexp(csr.val32[i], m.pieces == 2 ? m.row_exp[k] : 0);
-            if (m.pieces == 2 && small_weight(scaled)) {   // 13: every small weight is in a slot or in its block's part of the list
+            // 13: every small weight and those of short rows are in a slot or in their block's part of the list
+            if (m.pieces == 2 && (small_weight(scaled) || (in_list[k] && scaled != 0.f))) {
                 const int n = used[k / 32]++, at = m.small_first[k / 32] + n - m.kSlots;
                 if (n >= m.kSlots && at >= m.small_first[k / 32 + 1]) return 13;
                 const MatrixWeights::Small& s = n < m.kSlots ? m.slots[(size_t)(k / 32) * m.kSlots + n] : m.small[at];
@@ -243,7 +276,8 @@ namespace {
 //  * Workgroups run in rounds of what is resident.
 // (A launch of few products is mostly the fixed part: 51 fp32 and 44 binary16 layers of fewer than 4e8, zeros counted, are
 // within 2.4 and 1.4 % of their fastest split in the mean as well.)
-double estimate_matrix(const MatrixPlan& p, int RS, bool split)
+//  * Weights in the list (but for a block's first ones) take 4700 clocks for eight, in a wavefront's own chain: `listed`.
+double estimate_matrix(const MatrixPlan& p, int RS, bool split, double listed)
 {
     struct Clocks { double fixed, chain, chain_mf, mf, read, chunk, stage_chunk, stage, run_chunk, run, both, late, pair, tail; };
     static const Clocks k16 = {11300, 172, 17.2, 40.9, 9.2, 482, 13, 58.5, 2, 197, 1.24, 659, 993, 1.0},
@@ -262,7 +296,7 @@ double estimate_matrix(const MatrixPlan& p, int RS, bool split)
         const double multiply = own * std::max(k.chain + k.chain_mf * mf, conc * (mf * k.mf + p.NP * pieces * k.read));
         const double stage = conc * blocks * (runs ? k.run : k.stage);
         return p.nchunks * (std::max(multiply, stage + begin) + k.both * std::min(multiply, stage) + k.chunk + late) + 0.6 * stage + begin +
-               conc * k.pair * p.MK * p.NP / (p.KS > 1 ? 4 : 1);
+               conc * k.pair * p.MK * p.NP / (p.KS > 1 ? 4 : 1) + listed;
     };
     const long long slots = (long long)kCUs * conc_max, wgs = (long long)p.ntiles * p.kblocks;
     const long long full = wgs / slots, rest = wgs % slots;
@@ -342,7 +376,10 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
     // fp32 sums: the share of an output's terms that do not fall on padding, and the terms, both in the mean
     double inside = 0.0, terms = 0.0;
     std::vector<int> before;       // [K][C + 1]: a row's weights (but zeros, which add no rounding) before a channel
-    int shortest = INT_MAX;        // weights of the shortest row that has any
+    int shortest = INT_MAX;        // weights of the shortest row that has any, but for those in the list
+    std::vector<char> in_list;     // [K]
+    bool lists = false;            // it has rows with weights
+    std::vector<int> trips;        // [blocks of 32 rows]: turns of eight weights in the list, behind the first ones
     if (split) {
         double rows = 0, cols = 0;
         for (int i = 0; i < E; ++i)
@@ -351,11 +388,14 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
             for (int s = 0; s < S; ++s) cols += (unsigned)(j * g.stride + s - g.pad) < (unsigned)g.W;
         inside = rows * cols / ((double)E * F * RS);
         terms = (double)csr.colidx.size() / csr.K * inside;
+        in_list = listed_rows(csr, RS);
         for (int k = 0; k < csr.K; ++k) {
-            int n = 0;
-            for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) n += csr.val32[i] != 0.f;
-            if (n) shortest = std::min(shortest, n);
+            if (k % 32 == 0) trips.push_back(0);
+            const int n = row_weights(csr, k);
+            if (in_list[k]) trips.back() += n, lists |= n > 0;
+            else if (n) shortest = std::min(shortest, n);
         }
+        for (int& t : trips) t = (std::max(0, t - MatrixWeights::kSlots) + 7) / 8;
     }
     const int parts = std::max(1, tile_parts);
     // Terms that a term of row k is summed with, in the mean, itself included, where every `width` channels have a sum.
@@ -370,9 +410,10 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
     };
     // Whether no row is less exact under the split than in the tile kernel.  Units and numbers as below, but a row of few weights
     // has no term in some steps and chunks: then the pieces' own error is most of it (10 terms: 9e-8 to 1.0e-7, the tile kernel
-    // 5e-8 to 6e-8).  Of 1568 pairs of plans with rows of 2 to 448 terms, 183 pass; their error here is 0.95 of that there or less.
+    // 5e-8 to 6e-8).  Those in the list aside, 5026 rows of 36 layers that pass have 0.99 of the tile kernel's error or less,
+    // 0.43 in the mean.
     auto rows_as_exact = [&](const MatrixPlan& p, double steps) {
-        if ((0.81 + 0.047 * 3 * steps + 0.04 * p.nchunks) * 1.1 <= 0.0335 * shortest * inside / parts) return true;   // the least they can be
+        if (0.81 + 0.047 * 3 * steps + 0.04 * p.nchunks <= 0.0335 * shortest * inside / parts) return true;   // the least they can be
         if (before.empty()) {
             before.assign((size_t)csr.K * (C + 1), 0);
             for (int k = 0; k < csr.K; ++k) {
@@ -384,12 +425,14 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
         const int own = p.CG / 2 / p.KS * 16, part = (C + parts - 1) / parts;
         for (int k = 0; k < csr.K; ++k) {
             const int n = before[(size_t)(k + 1) * (C + 1) - 1];
-            if (!n) continue;
+            if (!n || in_list[k]) continue;
             const double met = steps * (1.0 - std::exp(-company(k, own) / steps)), chunks = p.nchunks * (1.0 - std::exp(-n * inside / p.nchunks));
-            if ((0.81 + 0.047 * 3 * met + 0.04 * chunks) * 1.1 > 0.0335 * company(k, part)) return false;
+            if (0.81 + 0.047 * 3 * met + 0.04 * chunks > 0.0335 * company(k, part)) return false;
         }
         return true;
     };
+    // (a row in the list is one sum of its terms, as in the tile kernel where that does not deal the channels over parts)
+    if (lists && parts > 1) return false;
     double best_us = -1.0;
     for (const auto& sh : split ? kShapes32 : kShapes16)
         for (int CG = 2; CG <= 2 * kMatrixGroups; CG *= 2) {
@@ -403,7 +446,13 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
                 const double steps = RS * (CG / 2.0 / sh[3]);
                 if ((0.81 + 0.047 * 3 * steps + 0.04 * p.nchunks) * 1.3 > 0.0335 * terms / parts) continue;
             }
-            const double t = estimate_matrix(p, RS, split);
+            int turns = 0;                 // of the wavefront with most of the list
+            for (int b = 0; b < (int)trips.size(); b += sh[0]) {
+                int mine = 0;
+                for (int q = b; q < std::min((int)trips.size(), b + sh[0]); ++q) mine += trips[q];
+                turns = std::max(turns, mine);
+            }
+            const double t = estimate_matrix(p, RS, split, 4700.0 * turns);
             if ((best_us < 0 || t < best_us) && (!split || rows_as_exact(p, RS * (CG / 2.0 / sh[3])))) {
                 best_us = t;
                 best = p;

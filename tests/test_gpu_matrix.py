@@ -279,6 +279,51 @@ def test_matrix_kernel_fp32_images_do_not_depend_on_their_neighbours(shape, rati
     layer.close()
 
 
+# Rows of few weights, by their number, and the split they are multiplied in (MK, KS, chunks).  Both of them in a block's first
+# places in the list, in its first row and its last, and behind those places.
+SHORT = [((96, 64, 64, 3, 3, 14, 14, 1, 1), {0: 1, 1: 3, 31: 0}, (2, 4, 1)), ((200, 192, 100, 3, 3, 8, 8, 1, 1), {0: 1, 1: 5}, (2, 4, 3)),
+         ((80, 240, 130, 1, 1, 15, 14, 1, 0), {0: 1, 1: 5, 31: 0, 40: 20, 129: 3}, (1, 1, 8)),
+         ((120, 240, 130, 1, 1, 15, 15, 1, 0), {0: 1, 1: 5, 31: 4, 40: 20, 129: 3}, (2, 1, 4))]
+
+
+@pytest.mark.parametrize("how", ["normal", "spread", "far apart", "tiny", "not finite"])
+@pytest.mark.parametrize("shape,short,split", SHORT, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else "")
+def test_matrix_kernel_rows_of_few_weights_are_fp32_sums(shape, short, split, how):
+    """Rows of few weights are multiplied as fp32: each term is rounded once as it joins the sum, 2^-24 of at most the sum of the
+    terms' magnitudes.  (Two binary16 pieces hold a single product to some 2^-22 only.)"""
+    from paper_2011_06295_amd import binding as B
+    N, C, K, R, S, H, W, st, p = shape
+    rng = np.random.default_rng(105)
+    w, m, x = rand_layer(rng, N, C, K, R, S, H, W, density=0.9)
+    for k, n in short.items():
+        m[k] = 0
+        m[k].reshape(-1)[rng.permutation(C * R * S)[:n]] = 1
+    if how == "spread":
+        x *= np.exp2(rng.uniform(-25, 25, x.shape)).astype(np.float32)
+    elif how == "far apart":
+        x *= np.where(rng.random(x.shape) < 0.02, 1e20, 1e-15).astype(np.float32)
+    elif how == "tiny":
+        x *= np.float32(1e-30)
+    elif how == "not finite":
+        x[1, ::7, H // 2, W // 2] = np.inf
+        x[2, 3] = np.nan
+    layer = B.SparseConv(w, m, dtype="f32")
+    plan = layer.get_matrix_plan(N, H, W, st, p)
+    assert (plan["MK"], plan["KS"], plan["nchunks"]) == split, "the sizes no longer take the split under test"
+    assert layer.check_plan(N, H, W, st, p) == 0
+    got = run_gpu(layer, x, st, p, "f32")
+    rows = list(short)
+    rowptr, colidx, values = oracle.csr_encode(w[rows], m[rows])
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref, size = (v.astype(np.float64) for v in oracle.sparse_conv((rowptr, colidx, values), x, len(rows), R, S, st, p, want_abs=True))
+    fin = np.isfinite(ref)
+    assert np.array_equal(np.isfinite(got[:, rows]), fin)
+    for i, k in enumerate(rows):
+        err, f = np.abs(got[:, k] - ref[:, i])[fin[:, i]], fin[:, i]
+        assert (err <= size[:, i][f] * short[k] * 2.0 ** -24 + max(1, short[k]) * 2.0 ** -149).all(), (how, k, float((err / np.maximum(size[:, i][f], 1e-300)).max()))
+    layer.close()
+
+
 @pytest.mark.parametrize("how", ["corner", "channel", "spread", "far apart", "tiny", "subnormal", "late", "late and quiet", "dead first", "one pixel",
                                  "few and quiet"])
 @pytest.mark.parametrize("shape", RANGES, ids=lambda s: "x".join(map(str, s)))

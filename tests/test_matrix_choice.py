@@ -22,13 +22,17 @@ def _masked(K, C, density):
 
 
 @pytest.mark.parametrize("unify", [False, True])
-@pytest.mark.parametrize("short,kernel", [(9, "tile"), (1, "tile"), (40, "tile"), (200, "matrix"), (0, "matrix")])
-def test_short_rows_keep_the_precision_of_fp32_products(short, kernel, unify):
+@pytest.mark.parametrize("kept,kernel", [([460] * 255 + [9], "matrix"), ([460] * 255 + [1], "matrix"), ([460] * 255 + [60], "matrix"),
+                                         ([460] * 255 + [0], "matrix"), ([460] * 31 + [60], "matrix"), ([460] * 3 + [3], "matrix"),
+                                         ([460] * 3 + [20], "tile"), ([460] * 3 + [40], "tile")])
+def test_short_rows_keep_the_precision_of_fp32_products(kept, kernel, unify):
     """256 -> 256, 14 x 14, 80 %: the matrix kernel holds a weight and an input in two binary16 pieces each, 1.0e-7 of a sum of
-    10 terms, where fp32 products leave 0.6e-7 (0.9e-7 and 0.5e-7 of 5 terms; from some 60 terms on it is the more exact one).
-    One such row keeps the layer on the tile kernel, with or without zero weights that fill it up; an empty row has no error."""
-    layer = _fp32_layer([460] * 255 + [short], unify=unify)
+    10 terms, where fp32 products leave 0.6e-7 (0.9e-7 and 0.5e-7 of 5 terms; from some 65 terms on it is the more exact one).
+    So it multiplies rows of up to 68 as fp32, with or without zero weights that fill them up.  Eight such rows among 32 take
+    it too long (160 weights), or are more than it does so (320): the tile kernel's."""
+    layer = _fp32_layer(kept, unify=unify)
     assert layer.get_kernel(256, 14, 14, 1, 1) == kernel
+    assert layer.check_plan(256, 14, 14, 1, 1) == 0
     layer.close()
 
 
