@@ -5,14 +5,14 @@
 // matrix instructions take them: v_mfma_f32_32x32x16_f16 multiplies 32 output channels x 16 input channels of one tap with
 // 16 input channels x 32 outputs.  At 90 % sparsity nine tenths of the products are with zeros, yet it is the faster way:
 // the tile kernel is bound by its LDS reads (16 bytes for 4 to 8 multiply-adds a lane) at 30 to 40 TFLOP/s of stored
-// weights, where this kernel does 600 to 1000 TFLOP/s of all weights in binary16 (256 -> 512 channels, 28 x 28, batch 128,
-// 90 %: 555 us by the tile kernel, 219 us here) and 200 to 340 in fp32 (256 -> 256, 14 x 14, batch 256, 70 %: 440 -> 178 us).
+// weights, where this kernel does 600 to 1100 TFLOP/s of all weights in binary16 (256 -> 512 channels, 28 x 28, batch 128,
+// 90 %: 569 us by the tile kernel, 220 us here) and 200 to 330 in fp32 (256 -> 256, 14 x 14, batch 256, 70 %: 430 and 182 us).
 //
 // Tile.  A workgroup of four wavefronts owns consecutive outputs of the batch and keeps, chunk by chunk of channels, the
 // lattice elements they touch in LDS, 8 channels of one position to a 16-byte element: a tap is an LDS offset, so the
 // tile is loaded once for all R * S taps, and a fragment of inputs is one ds_read_b128 a lane, 32 consecutive elements
-// for 32 consecutive outputs (outputs alone: no lane works on padding; a row's end costs a bank conflict, 20 to 40 % of the
-// LDS cycles, which are a quarter of the time).  A wavefront's MK x NP fragments share MK weight and NP input fragments per
+// for 32 consecutive outputs (outputs alone: no lane works on padding; a row's end costs a bank conflict, up to half of the
+// LDS cycles, which are a third to a half of the time).  A wavefront's MK x NP fragments share MK weight and NP input fragments per
 // step: 2 x 4 is what 256 registers hold.  Weight fragments come straight from L2 (each is used by one wavefront of the
 // workgroup, or few), AHEAD steps before their use.
 //
@@ -28,8 +28,9 @@
 // multiplied (the fourth is 2^-22 of the result or less), smallest first.  binary16 has few exponents, so the weights of an
 // output channel are scaled by a power of two of their own (those below 2^-16 of the largest, which two pieces do not hold, are
 // few: they stand in a list and are multiplied as fp32; so are all weights of rows of few, which are more exact so), and the
-// inputs by one for each image of the tile, taken from the image's largest magnitude in the first chunk.  The low piece of an input is kept times 2^12 and meets the high piece of the
-// weight times 2^-12: so 29 binary orders of magnitude hold every value to 2^-23 (kWindow; without that factor 17).
+// inputs by one for each image of the tile, taken from the image's largest magnitude in the first chunk.  The low piece of an
+// input is kept times 2^12 and meets the high piece of the weight times 2^-12: so 29 binary orders of magnitude hold every value
+// to 2^-23 (kWindow; without that factor 17).
 //  * An input above its image's window is left out, and its chunk is multiplied once more with only what was left out, under
 //    a scale that fits it, as often as something is left.
 //  * An input below the window takes part with 11 bits.  Its place is marked, and if an output that sees a marked place has a
@@ -37,8 +38,8 @@
 //    multiplied in the same way.  (Normally distributed inputs: one tile in two thousand has such an input, and one in some
 //    ten thousand repeats a chunk for it.)
 // So every output has fp32's precision whatever else is in its tile, and no image's sums depend on another image.  Measured
-// (256 -> 256, 14 x 14, batch 256, 70 %): 172 us with one scale for the tile and no such care, 177 with it; 779 us for inputs
-// spread evenly over 50 binary orders of magnitude, 320 if the second half of the channels is a million times the first.
+// (256 -> 256, 14 x 14, batch 256, 70 %): this care is 3 % of the 180 us; 620 us for inputs spread evenly over 50 binary orders of
+// magnitude, 275 if the second half of the channels is a million times the first.
 // The sum of a chunk is added to that of the chunks before it, which keeps the
 // rounding below that of a sum over all terms: 1.6e-7 of the result (2-norm, against 64 bits) for the layer above, 4.6e-7
 // by the tile kernel.
@@ -46,7 +47,7 @@
 // Non-finite inputs.  The table's zeros meet every input of the receptive field, so exactly the outputs with an input that
 // is not finite have a sum that is not: those are summed again over the stored weights alone (a mask says which), one after
 // the other, a lane a row, about 50 us each for 2304 columns.  Measured on the layer above (430 us by the tile kernel): 180 us,
-// with one NaN (nine outputs of four wavefronts) 600, with nothing but NaN 3600.
+// with one NaN (nine outputs of four wavefronts) 610, with nothing but NaN 5000.
 #pragma once
 #include <hip/hip_runtime.h>
 

@@ -266,7 +266,7 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
 namespace {
 
 // Rough time of one launch in microseconds.  Structure and constants are fitted to the measured times of every split (3278 of
-// them) of 187 layers (the 32-pixel VGG-16's, those of larger networks, and random ones: 1 x 1, 1-D, 3 x 3, 5 x 5, stride 2,
+// them) of 186 layers (the 32-pixel VGG-16's, those of larger networks, and random ones: 1 x 1, 1-D, 3 x 3, 5 x 5, stride 2,
 // batches of 1 to 256): 10 % rms of the logarithm, the cheapest by estimate 2 % slower than the fastest measured in the mean.
 // In clocks of 2.1 GHz:
 //  * A step costs its matrix instructions (39 to 41 clocks each over the workgroups resident on the CU; 32 at the nominal rate)
@@ -466,10 +466,12 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
 // binary16: taken where it is estimated 0.7 us faster.  Of 504 layers of every size timed in turn, four that take it so are 4 to
 // 8 % slower, and the mean loses 2.2 % to the better kernel of each.  (The 0.7 us are for launches of 8 to 10 us, most of which
 // both kernels have alike: without, 16 are slower, by up to 20 %.  Below 0.95 of the tile kernel's estimate instead: six, by up
-// to 14 %, the mean loses 2.3 %, and VGG-16's last layer takes 26 us by the tile kernel for 18.7.)
+// to 14 %, the mean loses 2.3 %, and VGG-16's last layer takes 26 us by the tile kernel for 18.7.  Of 95 others whose kernel
+// or split this and the one estimate for all sizes changed, the mean is 13 % faster, and three of 8 to 9 us are 8 to 21 % slower.)
 // fp32: taken below 0.85 of the tile kernel's estimate.  Of 71 layers, timed over blocks of a tenth of a second, which heat the
 // chip as a pass does, all below gain 6 % or more; between 0.85 and 0.9 lie 256 -> 256, 14 x 14, batch 256 at 90 % (169 us, tile
-// kernel 167) and its like, and from 0.9 to 1.0 six of twelve lose 5 to 19 %.
+// kernel 167) and its like, and from 0.9 to 1.0 six of twelve lose 5 to 19 %.  (Of 36 others with ragged rows, all below, two are
+// slower, by 1 and 8 %; the mean takes 0.53 of the tile kernel's time.)
 bool matrix_pays(double us, double tile_us, bool split) { return us < (split ? 0.85 * tile_us : tile_us - 0.7); }
 
 void fill_matrix_args(const MatrixWeights& m, const MatrixPlan& p, int K, int C, int R, int S, const Geometry& g, MatrixArgs& a)
