@@ -39,11 +39,12 @@ bool small_weight(float scaled) { return scaled != 0.f && std::fabs(scaled) < 0.
 // Normally distributed weights have 4 in a block of 147456.
 constexpr int kMaxSmall = 32;
 
-// Weights of a row but zeros, which add no rounding.
-int row_weights(const Csr& csr, int k)
+// Weights of the rows but zeros, which add no rounding.
+std::vector<int> row_weights(const Csr& csr)
 {
-    int n = 0;
-    for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) n += csr.val32[i] != 0.f;
+    std::vector<int> n(csr.K, 0);
+    for (int k = 0; k < csr.K; ++k)
+        for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) n[k] += csr.val32[i] != 0.f;
     return n;
 }
 
@@ -56,19 +57,19 @@ int short_row(int RS) { return 32 + 4 * RS; }
 // has none in the list: one whose rows are mostly short is the tile kernel's.
 constexpr int kMaxShort = 160;
 
-// [K] whether the row's weights stand in the list.
-std::vector<char> listed_rows(const Csr& csr, int RS)
+// Whether the rows' weights stand in the list, by their numbers.
+std::vector<char> listed_rows(const std::vector<int>& n, int RS)
 {
-    std::vector<char> listed(csr.K, 0);
-    for (int k0 = 0; k0 < csr.K; k0 += 32) {
+    const int K = (int)n.size();
+    std::vector<char> listed(K, 0);
+    for (int k0 = 0; k0 < K; k0 += 32) {
         int weights = 0;
-        for (int k = k0; k < std::min(csr.K, k0 + 32); ++k) {
-            const int n = row_weights(csr, k);
-            if (n > short_row(RS)) continue;
+        for (int k = k0; k < std::min(K, k0 + 32); ++k) {
+            if (n[k] > short_row(RS)) continue;
             listed[k] = 1;
-            weights += n;
+            weights += n[k];
         }
-        if (weights > kMaxShort) return std::vector<char>(csr.K, 0);
+        if (weights > kMaxShort) return std::vector<char>(K, 0);
     }
     return listed;
 }
@@ -115,7 +116,7 @@ void pack_matrix_weights(const Csr& csr, int C, int R, int S, bool split, Matrix
     m.row_exp.assign((size_t)m.KF * 32, 0);
     m.small_first.assign(split ? (size_t)m.KF + 1 : 0, 0);
     m.slots.assign(split ? (size_t)m.KF * m.kSlots : 0, {-1, 0, 0, 0.f});
-    const std::vector<char> listed = split ? listed_rows(csr, RS) : std::vector<char>();
+    const std::vector<char> listed = split ? listed_rows(row_weights(csr), RS) : std::vector<char>();
     for (int k = 0; k < K; ++k) {
         m.longest = std::max(m.longest, csr.rowptr[k + 1] - csr.rowptr[k]);
         if (split) m.row_exp[k] = row_exponent(csr, k);
@@ -153,7 +154,7 @@ int check_matrix(const Csr& csr, int C, int R, int S, const MatrixWeights& m)
     for (const auto& s : m.slots) listed += s.row >= 0;
     std::vector<int> used(m.KF, 0);
     std::vector<uint16_t> rest = m.image;
-    const std::vector<char> in_list = m.pieces == 2 ? listed_rows(csr, RS) : std::vector<char>();
+    const std::vector<char> in_list = m.pieces == 2 ? listed_rows(row_weights(csr), RS) : std::vector<char>();
     for (int k = 0; k < csr.K; ++k)
         for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) {
             const int col = csr.colidx[i];
@@ -388,10 +389,11 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
             for (int s = 0; s < S; ++s) cols += (unsigned)(j * g.stride + s - g.pad) < (unsigned)g.W;
         inside = rows * cols / ((double)E * F * RS);
         terms = (double)csr.colidx.size() / csr.K * inside;
-        in_list = listed_rows(csr, RS);
+        const std::vector<int> weights = row_weights(csr);
+        in_list = listed_rows(weights, RS);
         for (int k = 0; k < csr.K; ++k) {
             if (k % 32 == 0) trips.push_back(0);
-            const int n = row_weights(csr, k);
+            const int n = weights[k];
             if (in_list[k]) trips.back() += n, lists |= n > 0;
             else if (n) shortest = std::min(shortest, n);
         }
