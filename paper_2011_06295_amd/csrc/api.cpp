@@ -347,6 +347,7 @@ int forward_matrix(sparse_conv_s* h, const MatrixPlan& p, const void* input, voi
     a.relu = (h->epilogue & SC_EPILOGUE_RELU) ? 1 : 0;
     a.pool = (h->epilogue & SC_EPILOGUE_MAXPOOL2) ? 1 : 0;
     fill_matrix_args(m, p, h->K, h->C, h->R, h->S, g, a);
+    a.out_runs = reinterpret_cast<uintptr_t>(output) % 16 ? 0 : p.out_runs;   // (an output that starts elsewhere: one by one)
     const int e = h->dtype == SC_F32 ? launch_matrix_f32(p, a, stream) : launch_matrix_f16(p, a, stream);
     if (e != 0) {
         h->last_hip = e;

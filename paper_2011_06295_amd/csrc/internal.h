@@ -287,6 +287,7 @@ struct MatrixPlan {
     int fly;         // staging blocks a wavefront has in flight: fp32 1, 2 or 3, binary16 2, 4 or 6
     // Wide staging: a lane takes 8 bytes of each of 8 channels, four (fp32: two) consecutive pixels of one plane.
     int quads;       // such runs of pixels of one channel group a tile holds at most; 0: the planes are not whole runs
+    int out_runs;    // bytes of the runs that outputs are stored in (16 or 8: a plane is whole runs); 0: one by one
     int wide_fly;    // blocks of 64 of them a wavefront has in flight: 1 or 2
 };
 constexpr int kImageWindowBytes = 24;   // fp32: LDS bytes for each of them
@@ -333,6 +334,7 @@ struct MatrixArgs {
     int block_major;       // order of the (tile, channel block) pairs
     int quads, plane_quads;   // wide staging: runs of pixels of a tile (at most) and of a plane
     int padded;               // ... the lattice has elements that are no pixel
+    int out_runs;             // bytes of the runs that outputs are stored in; 0: one by one
     FastDiv fd_EF, fd_F, fd_Wp, fd_Hs, fd_EB, fd_W, fd_quads, fd_plane_quads;
 };
 void fill_matrix_args(const MatrixWeights& m, const MatrixPlan& p, int K, int C, int R, int S, const Geometry& g, MatrixArgs& a);

@@ -82,6 +82,10 @@ __device__ __forceinline__ const MatrixArgs& late_arguments()
 }
 __device__ __forceinline__ half8 lds_read(unsigned address) { return *(const SC_LDS half8*)(address); }
 __device__ __forceinline__ void lds_write(unsigned address, half8 v) { *(SC_LDS half8*)(address) = v; }
+template <typename V>
+__device__ __forceinline__ void lds_put(unsigned address, V v) { *(SC_LDS V*)(address) = v; }
+template <typename V>
+__device__ __forceinline__ V lds_get(unsigned address) { return *(const SC_LDS V*)(address); }
 #pragma clang diagnostic pop
 
 // n / d for 0 <= n < 2^31 with the multiplier prepared on the host.
@@ -921,17 +925,24 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
         if constexpr (kSplit) return late_arguments();
         return a;
     }();
+    // (kSplit: the lane's number is asked for anew: kept since the kernel's start it would be spilled)
+    int late_lane = lane;
+    if constexpr (kSplit) {
+        late_lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        asm volatile("" : "+v"(late_lane));
+    }
+    const int late_half = late_lane >> 5;
     T* __restrict__ y = static_cast<T*>(la.y);
     const int kfirst = (kf0 + (KS > 1 ? wave / NP : 0)) * 32;                  // first output channel and
     const int ofirst = o0 + (wp * NP + (KS > 1 ? wave % NP : 0)) * 32;         // first output of the wavefront's sums
-    const int krow0 = kfirst + half * 4;
+    const int krow0 = kfirst + late_half * 4;
     auto finish = [&](float v, float b) __attribute__((always_inline)) {       // section 3: bias, then activation
         v += b;
         return la.relu ? (v > 0.f ? v : 0.f) : v;
     };
     // What the table holds for the lane's 16 rows of a fragment, in registers before the fragment's first store (read
     // inside the branches below, each of them would wait for its own).
-    const int table_row = kfirst - kb * rows + half * 4;
+    const int table_row = kfirst - kb * rows + late_half * 4;
     float4 bias[4];
     int4 rexp[4];
     auto take_rows = [&](int mk) __attribute__((always_inline)) {
@@ -954,13 +965,68 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
         if constexpr (kSplit) v = ldexpf(v, exponent - at4(rexp[i >> 2], i & 3));
         return finish(v, at4(bias[i >> 2], i & 3));
     };
+    // Outputs in runs.  A store of 64 lanes takes the address unit some 20 clocks, 2 bytes each or 16, and 32 binary16 outputs of a
+    // row are half a cache line.  So where planes are whole runs of 16 (8) bytes, a block of 32 rows goes through the tile's
+    // place in LDS, and a lane stores a run of one row, past the caches: the launch does not read it again.  (64 -> 256 channels,
+    // 56 x 56, binary16, batch 128, 257 MB: 90 -> 83 us with runs, 61 with runs past the caches; 256 -> 512, 28 x 28: 254 -> 244 and
+    // 240; 256 -> 256, 14 x 14, fp32, batch 256: 200 -> 200 and 194.)
+    constexpr int kPitch = kNP * 32 * (int)sizeof(T) + 16;
+    auto put_runs = [&](int mk, auto run) __attribute__((always_inline)) {
+        using Run = decltype(run);
+        constexpr int kRun = (int)(sizeof(Run) / sizeof(T)), kRuns = kNP * 32 / kRun;           // outputs of a run, runs of a row
+        const MatrixArgs& la = late_arguments();
+        int own = late_lane;
+        asm volatile("" : "+v"(own));            // (what follows is not worked out before, nor for both kinds of runs)
+        const int row = own / kRuns, o = ofirst + own % kRuns * kRun;
+        const unsigned from = lds0 + (unsigned)((wave * 32 + row) * kPitch) + (unsigned)(own % kRuns) * (unsigned)sizeof(Run);
+        Run v[32 * kRuns / 64];
+#pragma unroll
+        for (int r = 0; r < 32 * kRuns / 64; ++r) v[r] = lds_get<Run>(from + (unsigned)(r * (64 / kRuns) * kPitch));
+#pragma unroll
+        for (int r = 0; r < 32 * kRuns / 64; ++r) asm volatile("" : "+v"(v[r]));                 // (not each in its branch, where it would be waited for)
+        const int u = fdiv(o, la.fd_EF), k = kfirst + mk * 32 + row;
+        Run* to = reinterpret_cast<Run*>(static_cast<T*>(la.y) + ((size_t)u * la.K + k) * la.EF + (o - u * la.EF));
+        const int rows_left = o < la.nout ? la.K - k : 0;
+        const size_t step = (size_t)(64 / kRuns) * la.EF / kRun;
+#pragma unroll
+        for (int r = 0; r < 32 * kRuns / 64; ++r) {
+            if (r * (64 / kRuns) < rows_left) {
+                if constexpr (sizeof(Run) == 16) __builtin_nontemporal_store(v[r], to + r * step);
+                else to[r * step] = v[r];
+            }
+        }
+    };
+    const bool in_runs = late_arguments().out_runs && __ballot(bad != 0) == 0;
+    // (the sums as they are: else the compiler copies them apart before the branch, and the smallest variant spills)
+#pragma unroll
+    for (int mk = 0; mk < kMK; ++mk)
+#pragma unroll
+        for (int np = 0; np < kNP; ++np) asm volatile("" : "+v"(acc[mk][np]));
+    if (in_runs) {
+#pragma unroll
+        for (int mk = 0; mk < kMK; ++mk) {
+            take_rows(mk);
+            const unsigned to = lds0 + (unsigned)((wave * 32 + late_half * 4) * kPitch) + (unsigned)(late_lane & 31) * (unsigned)sizeof(T);
+#pragma unroll
+            for (int np = 0; np < kNP; ++np) {
+                const int exponent = unscale(ofirst + np * 32 + (late_lane & 31));
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    lds_put(to + (unsigned)(((i >> 2) * 8 + (i & 3)) * kPitch + np * 32 * (int)sizeof(T)), (T)scaled(acc[mk][np][i], i, exponent));
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (late_arguments().out_runs == 16) put_runs(mk, uint4v{});
+            else put_runs(mk, uint2v{});
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+    } else
 #pragma unroll
     for (int mk = 0; mk < kMK; ++mk) {
         take_rows(mk);
         if (!la.pool) {
 #pragma unroll
             for (int np = 0; np < kNP; ++np) {
-                const int o = ofirst + np * 32 + (lane & 31);
+                const int o = ofirst + np * 32 + (late_lane & 31);
                 const int u = fdiv(o, la.fd_EF);
                 const bool valid = o < la.nout && !((bad >> np) & 1u);
                 const int exponent = unscale(o);
@@ -986,7 +1052,7 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
                 wrong &= 1u;
                 if (!apart) wrong |= (unsigned)__shfl_xor((int)wrong, F);
                 wrong |= (unsigned)__shfl_xor((int)wrong, 1);
-                const int o = ofirst + np * 32 + (lane & 31);
+                const int o = ofirst + np * 32 + (late_lane & 31);
                 const int u = fdiv(o, la.fd_EF);
                 const int rem = o - u * la.EF, i0 = fdiv(rem, la.fd_F), j0 = rem - i0 * F;
                 const bool valid = o < la.nout && !wrong && !((i0 | j0) & 1);

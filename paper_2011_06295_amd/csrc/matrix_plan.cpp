@@ -188,6 +188,9 @@ int matrix_extra_lds(const MatrixPlan& p)
     return p.MK * p.WK * MatrixWeights::kSlots * (int)sizeof(MatrixWeights::Small) + p.images * kImageWindowBytes + p.EB * 8;
 }
 
+// What the wavefronts' rows of outputs take on their way to memory.
+int out_runs_lds(const MatrixPlan& p, int elem_bytes) { return 4 * 32 * ((p.KS > 1 ? 1 : p.NP) * 32 * elem_bytes + 16); }
+
 // Whether the kernel stages runs.  Where a wavefront has but one block of single
 // pixels to stage (binary16: two), runs would leave wavefronts without one: of 506 splits of 27 layers those with one are 2 to
 // 4 % slower with runs in the mean, up to 24 % (64 -> 256, 56 x 56, binary16: 65 -> 80 us); with two (three) and more, 6 to 40 %
@@ -253,6 +256,9 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     p.wide_fly = (CG * p.quads + 255) / 256 > 1 && MK * NP * pieces < 8 ? 2 : 1;
     long long lds = (long long)(p.nchunks > 1 ? 2 : 1) * CG * p.EB * 64 * 16 * pieces;
     if (KS > 1) lds = std::max(lds, (long long)KS * MK * NP * 16 * 64 * 4);   // where the four sums of a pair meet
+    // outputs in runs, where a plane is whole ones: 32 rows of a wavefront's outputs at a time go through LDS
+    p.out_runs = pool || EF * elem_bytes % 8 ? 0 : EF * elem_bytes % 16 ? 8 : 16;
+    if (p.out_runs) lds = std::max(lds, (long long)out_runs_lds(p, elem_bytes));
     lds += 64 + 8 * 32 * MK * WK;             // what the wavefronts tell each other, bias and scale of the rows
     if (pieces == 2) lds += matrix_extra_lds(p);
     if (lds > kMaxLds) return false;
@@ -325,6 +331,7 @@ int check_matrix_plan(int K, int C, int R, int S, int elem_bytes, const Geometry
     const long long buffers = (long long)(p.nchunks > 1 ? 2 : 1) * p.CG * p.EB * 1024 * pieces, rows = 32ll * p.MK * p.WK;
     const long long behind = 64 + 8 * rows + (pieces == 2 ? matrix_extra_lds(p) : 0);
     if (p.lds_bytes > kMaxLds || buffers + behind > p.lds_bytes || (p.KS > 1 && p.KS * p.MK * p.NP * 4096ll + behind > p.lds_bytes)) return 15;
+    if (p.out_runs && (out_runs_lds(p, elem_bytes) + behind > p.lds_bytes || (long long)p.E * p.F * elem_bytes % p.out_runs)) return 15;
     if (p.kblocks * rows < K || (long long)p.ntiles * p.PT < p.nout || p.WK * p.WP * p.KS != 4 || p.PT != 32 * p.NP * p.WP) return 15;
     if (p.grid % 8 || p.grid < (long long)p.ntiles * p.kblocks) return 15;
     // 17: (wide staging) the tile's runs of pixels hold every input that its taps read

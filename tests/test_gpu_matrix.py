@@ -125,6 +125,31 @@ def test_the_variants_are_all_that_is_built():
     assert {(d, s[0], s[1], s[3], s[4], "any" if s[6] else s[5], s[6]) for d, s, _ in VARIANTS} == built
 
 
+# Planes that are whole runs of 16 bytes, of 8 (binary16 14 x 14, fp32 15 x 14) and of neither; rows off their
+# blocks of 32, a last tile that is not full, wavefronts that share the tile's outputs or its channels.
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("shape", [(41, 64, 65, 3, 3, 14, 14, 1, 1), (33, 48, 130, 3, 3, 16, 12, 1, 1), (61, 240, 250, 1, 1, 15, 14, 1, 0),
+                                   (131, 256, 70, 3, 3, 4, 4, 1, 1), (1201, 256, 70, 3, 3, 2, 2, 1, 1), (45, 64, 100, 3, 3, 9, 13, 1, 1)], ids=lambda s: "x".join(map(str, s)))
+def test_matrix_kernel_stores_runs(dtype, shape):
+    """Every output is written and nothing beside them, with the bits that an output off the runs' alignment gets one by one."""
+    import torch
+    layer, w, m, x = _layer(dtype, shape, 97, 0.9)
+    N, C, K, R, S, H, W, st, p = shape
+    layer.set_epilogue(np.random.default_rng(8).standard_normal(K).astype(np.float32), relu=True)
+    assert layer.get_kernel(N, H, W, st, p) == "matrix" and layer.check_plan(N, H, W, st, p) == 0
+    xt = torch.from_numpy(x).cuda().to(torch.float16 if dtype == "f16" else torch.float32)
+    size = torch.Size((N, K, *layer.output_shape(H, W, st, p)))
+    got = []
+    for first in (32, 33):                # (a tensor starts at 256 bytes or more)
+        room = torch.full((size.numel() + 64,), float("nan"), dtype=xt.dtype, device="cuda")
+        y = layer.forward(xt, st, p, out=room[first:first + size.numel()].view(size))
+        assert torch.isnan(room[:first]).all() and torch.isnan(room[first + size.numel():]).all()
+        assert torch.isfinite(y).all()
+        got.append(y.clone())
+    assert torch.equal(*got)
+    layer.close()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
 @pytest.mark.parametrize("H,N,C,K", [(2, 1200, 256, 64), (4, 400, 256, 40), (8, 64, 128, 64), (16, 33, 64, 96), (32, 9, 48, 64), (64, 5, 40, 64)])
 def test_matrix_kernel_pooled_store(dtype, H, N, C, K):
