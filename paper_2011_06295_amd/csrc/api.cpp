@@ -196,6 +196,15 @@ void build_image(Plan& p)
         }
         return;
     }
+    if (p.indexed) {   // the weight, then the offset in 16 bytes and the first of its row's accumulators
+        if (!p.image4.empty()) return;
+        p.image4.resize(p.entries.size() * 2);
+        for (size_t i = 0; i < p.entries.size(); ++i) {
+            p.image4[2 * i] = p.entries[i].wbits;
+            p.image4[2 * i + 1] = (uint32_t)(p.entries[i].off >> 4) << 16 | (uint32_t)(p.entries[i].off & 15) * 4u;
+        }
+        return;
+    }
     if (!p.image.empty() || p.entries.empty()) return;
     p.image.resize(p.entries.size() / kBatch);
     for (size_t b = 0; b < p.image.size(); ++b)
@@ -397,7 +406,7 @@ int forward_impl(sparse_conv_s* h, const void* input, void* output, int N, int H
         if (!use_static) {
             if (!p->uploaded) {
                 build_image(*p);
-                if ((rc = p->compact ? upload(h, p->image4, &p->d_entries) : upload(h, p->image, &p->d_entries)) != SC_OK)
+                if ((rc = p->compact || p->indexed ? upload(h, p->image4, &p->d_entries) : upload(h, p->image, &p->d_entries)) != SC_OK)
                     return rc;
                 if ((rc = upload(h, p->seg, &p->d_seg)) != SC_OK) return rc;
                 if ((rc = upload(h, p->krow, &p->d_krow)) != SC_OK) return rc;
@@ -428,9 +437,9 @@ int forward_impl(sparse_conv_s* h, const void* input, void* output, int N, int H
             a.counters = static_cast<unsigned*>(p->d_counters);
         } else {
             build_image(*p);
-            const size_t b_entries = p->compact ? p->image4.size() * sizeof(uint32_t) : p->image.size() * sizeof(Batch),
+            const size_t b_entries = p->compact || p->indexed ? p->image4.size() * sizeof(uint32_t) : p->image.size() * sizeof(Batch),
                          b_seg = p->seg.size() * sizeof(int), b_krow = p->krow.size() * sizeof(int);
-            const void* entries_at = p->compact ? static_cast<const void*>(p->image4.data()) : static_cast<const void*>(p->image.data());
+            const void* entries_at = p->compact || p->indexed ? static_cast<const void*>(p->image4.data()) : static_cast<const void*>(p->image.data());
             const size_t at_seg = round256(b_entries), at_krow = at_seg + round256(b_seg);
             const size_t b_units = p->units.size() * sizeof(Plan::Unit);
             const size_t at_units = at_krow + round256(b_krow), at_counters = at_units + round256(b_units),

@@ -89,6 +89,14 @@ struct Batch {
 };
 static_assert(sizeof(Batch) == kBatch * sizeof(Entry), "same bytes as the entries it holds");
 
+// Whether a wavefront's weights of a chunk are one stream for all its rows ("indexed", see kernels.hip): four fp32 images an
+// element, one position a lane, four rows or more, ordinary entries.
+constexpr bool tile_indexed(int elem_bytes, int V, int KW, int LP, bool compact)
+{
+    return elem_bytes == 4 && V == 4 && LP == 1 && KW >= 4 && !compact;
+}
+constexpr int kAhead = 24;   // entries behind the table's last that an indexed stream may ask for ahead
+
 // Everything a forward call needs for one geometry.
 //
 // The batch is laid out (virtually) as one tall zero-padded image per channel:
@@ -141,10 +149,13 @@ struct Plan {
     // host tables
     bool compact = false;         // binary16 weights (binary16 layers, cluster-quantised layers): one word per device entry
     int off_shift = 0;            // compact: LDS byte offset = (entry >> 16) << off_shift
-    std::vector<uint32_t> image4; // compact: the entry table as the device reads it, (offset >> off_shift) << 16 | binary16 weight
-    std::vector<Entry> entries;   // segments padded to kBatch
-    std::vector<int> seg;         // [kblocks][nchunks][WK][1 + KW] = first entry, batches of each row; then one
-                                  // terminal descriptor whose first entry is the end of the last segment
+    std::vector<uint32_t> image4; // the entry table as the device reads it, compact: (offset >> off_shift) << 16 | binary16 weight,
+                                  // indexed: fp32 weight, offset / 16 << 16 | 4 * slot
+    bool indexed = false;         // a wavefront's weights of a chunk are one stream: pairs that share their input, then single ones
+    std::vector<Entry> entries;   // segments padded to kBatch (indexed: off holds the row's slot in its low four bits)
+    std::vector<int> seg;         // [kblocks][nchunks][WK][1 + KW] = first entry, batches of each row (indexed: [1 + 2], eights of
+                                  // pairs and fours of single ones); then one terminal descriptor whose first entry is the end of
+                                  // the last segment
     std::vector<int> krow;        // [kblocks][WK][KW] output channel or -1
     // Output-lane plans: what every thread stages per chunk, worked out here instead of in every workgroup.
     // Tiles whose first output has the same place within a super-group stage the same pattern; there are

@@ -153,6 +153,115 @@ struct Vec<T, 1> {
     } while (0)
 #endif
 
+// The multiply loop of the kernels with four fp32 images an element and four or more rows a wavefront ("indexed").  A wavefront's
+// stored weights of a chunk are one stream, whatever their rows: an entry names the row's accumulators (in words, bits 0-7 of its
+// second word, LDS offset / 16 in bits 16-31), which the multiply-adds reach through the VGPR index (s_set_gpr_idx).  So rows are not
+// padded one by one, and weights of two rows under the same input share its read: the stream begins with pairs (entries 2i and 2i + 1
+// have the offset of entry 2i), n2 times eight entries, then come single ones, n1 times four.
+// What bounds it: a multiply-add of 64 lanes takes 4 clocks of the vector unit, 16 an entry, and an LDS read's return takes
+// the registers' write port from it for some 5.  Bare loops, 16 wavefronts a CU: 49.9 TFLOP/s with a read an entry, 55.4 with a
+// read for two, 65.6 without reads (the clock falls to 2.0 GHz); the loop by rows 50.8, and its padding to whole batches of a row is
+// 10 % of the entries at 90 % sparsity and half at 99 %.
+// Two sets of eight entries in scalar registers take turns (s[36:51], s[52:67]); while one is multiplied the next is fetched.
+// Two LDS reads are in flight while the two before them are multiplied; one wait a group serves reads and fetches alike (scalar
+// loads return out of order).
+// Everything that is asked for is waited for before the block ends.  Reads and fetches that run ahead of the stream's end touch the
+// next stream's entries (the table ends in slack) and are dropped.
+#define SC_RD(at, set, e, x) \
+    "v_mad_u32_u16 %[" at "], s[" set "+2*" e "+1], 16, %[base] op_sel:[1,0,0,0]\n\t" \
+    "ds_read_b128 v[%[x]+" x ":%[x]+" x "+3], %[" at "]\n\t"
+#define SC_FMA(set, e, x) \
+    "v_fma_f32 v[%[acc]+0], s[" set "+2*" e "], v[%[x]+" x "+0], v[%[acc]+0]\n\t" \
+    "v_fma_f32 v[%[acc]+1], s[" set "+2*" e "], v[%[x]+" x "+1], v[%[acc]+1]\n\t" \
+    "v_fma_f32 v[%[acc]+2], s[" set "+2*" e "], v[%[x]+" x "+2], v[%[acc]+2]\n\t" \
+    "v_fma_f32 v[%[acc]+3], s[" set "+2*" e "], v[%[x]+" x "+3], v[%[acc]+3]\n\t"
+#define SC_FIRST(set, e, x) "s_set_gpr_idx_on s[" set "+2*" e "+1], 0xc\n\t" SC_FMA(set, e, x)   /* third operand and result are indexed */
+#define SC_NEXT(set, e, x) "s_set_gpr_idx_idx s[" set "+2*" e "+1]\n\t" SC_FMA(set, e, x)
+#define SC_OFF "s_set_gpr_idx_off\n\t"
+#define SC_WAIT "s_waitcnt lgkmcnt(0)\n\t"
+#define SC_FETCH(to) "s_load_dwordx16 s[" to ":" to "+15], %[ptr], %[off]\n\ts_add_u32 %[off], %[off], 64\n\t"
+#define SC_TWO(set, a, b, x) SC_FIRST(set, a, x) SC_NEXT(set, b, x "+4") SC_OFF
+#define SC_FOUR(set, a, b, c, d, x) SC_FIRST(set, a, x) SC_NEXT(set, b, x) SC_NEXT(set, c, x "+4") SC_NEXT(set, d, x "+4") SC_OFF
+#define SC_PAIRS(cur, nxt) \
+    SC_WAIT SC_RD("at0", cur, "4", "8") SC_RD("at1", cur, "6", "12") SC_FETCH(nxt) SC_FOUR(cur, "0", "1", "2", "3", "0") \
+    SC_WAIT SC_RD("at0", nxt, "0", "0") SC_RD("at1", nxt, "2", "4") SC_FOUR(cur, "4", "5", "6", "7", "8") \
+    "s_sub_u32 %[n2], %[n2], 1\n\ts_cmp_eq_u32 %[n2], 0\n\t"
+// (The issue priority falls as the stream is worked off, see yield_to_slower: 3 for pairs, 2 for the first half of the single ones,
+// 1 for a quarter, then 0.)
+#define SC_LESS(back, done) \
+    "s_sub_u32 %[n1], %[n1], 1\n\ts_cmp_eq_u32 %[n1], 0\n\ts_cbranch_scc1 " done "f\n\t" back ":\n\t"
+#define SC_REST(back, done, last) \
+    done ":\n\ts_setprio 1\n\ts_cmp_lg_u32 %[n3], 0\n\ts_cbranch_scc1 " last "f\n\ts_setprio 0\n\t" last ":\n\t" \
+    "s_mov_b32 %[n1], %[n0]\n\ts_mov_b32 %[n0], %[n3]\n\ts_mov_b32 %[n3], 0\n\ts_cmp_eq_u32 %[n1], 0\n\ts_cbranch_scc0 " back "b\n\ts_branch 9f\n\t"
+#define SC_EACH(set, a, b, c, d, x) SC_FIRST(set, a, x) SC_NEXT(set, b, x "+4") SC_NEXT(set, c, x "+8") SC_NEXT(set, d, x "+12") SC_OFF
+#define SC_SINGLES2(cur, nxt, back1, done1, back2, done2) \
+    SC_WAIT SC_RD("at0", cur, "2", "8") SC_RD("at1", cur, "3", "12") SC_FETCH(nxt) SC_TWO(cur, "0", "1", "0") \
+    SC_WAIT SC_RD("at0", cur, "4", "0") SC_RD("at1", cur, "5", "4") SC_TWO(cur, "2", "3", "8") SC_LESS(back1, done1) \
+    SC_WAIT SC_RD("at0", cur, "6", "8") SC_RD("at1", cur, "7", "12") SC_TWO(cur, "4", "5", "0") \
+    SC_WAIT SC_RD("at0", nxt, "0", "0") SC_RD("at1", nxt, "1", "4") SC_TWO(cur, "6", "7", "8") SC_LESS(back2, done2)
+#define SC_SINGLES4(cur, nxt, back1, done1, back2, done2) \
+    SC_WAIT SC_RD("at0", cur, "4", "16") SC_RD("at1", cur, "5", "20") SC_RD("at0", cur, "6", "24") SC_RD("at1", cur, "7", "28") SC_FETCH(nxt) \
+    SC_EACH(cur, "0", "1", "2", "3", "0") SC_LESS(back1, done1) \
+    SC_WAIT SC_RD("at0", nxt, "0", "0") SC_RD("at1", nxt, "1", "4") SC_RD("at0", nxt, "2", "8") SC_RD("at1", nxt, "3", "12") \
+    SC_EACH(cur, "4", "5", "6", "7", "16") SC_LESS(back2, done2)
+#define SC_ENTER2(set) SC_RD("at0", set, "0", "0") SC_RD("at1", set, "1", "4")
+#define SC_ENTER4(set) SC_ENTER2(set) SC_RD("at0", set, "2", "8") SC_RD("at1", set, "3", "12")
+#define SC_STREAM(R) \
+    "s_cmp_eq_u32 %[n2], 0\n\ts_cbranch_scc1 3f\n\t" \
+    SC_RD("at0", "36", "0", "0") SC_RD("at1", "36", "2", "4") \
+    "1:\n\t" SC_PAIRS("36", "52") "s_cbranch_scc1 5f\n\t" \
+    SC_PAIRS("52", "36") "s_cbranch_scc0 1b\n\t" \
+    "3:\n\ts_setprio 2\n\ts_cmp_eq_u32 %[n1], 0\n\ts_cbranch_scc1 9f\n\t" SC_ENTER##R("36") \
+    "4:\n\t" SC_SINGLES##R("36", "52", "11", "21", "12", "22") "s_branch 6f\n\t" \
+    "5:\n\ts_setprio 2\n\ts_cmp_eq_u32 %[n1], 0\n\ts_cbranch_scc1 9f\n\t" SC_ENTER##R("52") \
+    "6:\n\t" SC_SINGLES##R("52", "36", "13", "23", "14", "24") "s_branch 4b\n\t" \
+    SC_REST("11", "21", "31") SC_REST("12", "22", "32") SC_REST("13", "23", "33") SC_REST("14", "24", "34") \
+    "9:\n\t" SC_WAIT
+
+typedef float float16v __attribute__((ext_vector_type(16)));
+typedef float float32v __attribute__((ext_vector_type(32)));
+typedef unsigned uint16v __attribute__((ext_vector_type(16)));
+
+// (m0 holds the index; the compiler notes that it keeps m0 for itself, which it does not across an operation that needs it.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+// Accumulators of KW rows of four images each, row by row in consecutive registers (the block names them by number).
+template <int KW>
+struct Indexed;
+#define SC_INDEXED(KW, R, ACCS, OPERANDS, ACC, X, ...) \
+    template <> \
+    struct Indexed<KW> { \
+        ACCS; \
+        __device__ __forceinline__ void multiply(const SC_CONSTANT uint32_t* from, uint16v first, int pairs, int singles, unsigned base) \
+        { \
+            unsigned off = 64, at0, at1; \
+            int last = singles >> 2, rest = (singles >> 1) - last; \
+            singles -= rest + last; \
+            asm volatile(SC_STREAM(R) \
+                         : OPERANDS, "+{s[36:51]}"(first), [n2] "+s"(pairs), [n1] "+s"(singles), [n0] "+s"(rest), [n3] "+s"(last), [off] "+s"(off), \
+                           [at0] "=&v"(at0), [at1] "=&v"(at1) \
+                         : [ptr] "s"(from), [base] "v"(base), [acc] "i"(ACC), [x] "i"(X) \
+                         : "s52", "s53", "s54", "s55", "s56", "s57", "s58", "s59", "s60", "s61", "s62", "s63", "s64", "s65", "s66", "s67", \
+                           "m0", "scc", "memory", __VA_ARGS__); \
+        } \
+    };
+SC_INDEXED(4, 4, float16v a, "+{v[32:47]}"(a), 32, 48,
+           "v48", "v49", "v50", "v51", "v52", "v53", "v54", "v55", "v56", "v57", "v58", "v59", "v60", "v61", "v62", "v63", "v64", "v65",
+           "v66", "v67", "v68", "v69", "v70", "v71", "v72", "v73", "v74", "v75", "v76", "v77", "v78", "v79")
+SC_INDEXED(8, 4, float32v a, "+{v[32:63]}"(a), 32, 64,
+           "v64", "v65", "v66", "v67", "v68", "v69", "v70", "v71", "v72", "v73", "v74", "v75", "v76", "v77", "v78", "v79", "v80", "v81",
+           "v82", "v83", "v84", "v85", "v86", "v87", "v88", "v89", "v90", "v91", "v92", "v93", "v94", "v95")
+#define SC_COMMA ,
+SC_INDEXED(16, 2, float32v a; float32v b, "+{v[64:95]}"(a) SC_COMMA "+{v[96:127]}"(b), 64, 48,
+           "v48", "v49", "v50", "v51", "v52", "v53", "v54", "v55", "v56", "v57", "v58", "v59", "v60", "v61", "v62", "v63")
+#pragma clang diagnostic pop
+template <int KW>
+__device__ __forceinline__ float indexed_sum(const Indexed<KW>& s, int i)
+{
+    if constexpr (KW == 16) return i < 32 ? s.a[i & 31] : s.b[i & 31];
+    else return s.a[i];
+}
+
 template <typename T, int V, int KW, int LP, bool COMPACT, bool REAL>
 __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
 {
@@ -222,6 +331,8 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
     }
     const int lposb = lpos * (int)sizeof(vec);
 
+    constexpr bool kIndexed = tile_indexed(sizeof(T), V, KW, LP, COMPACT);
+    Indexed<kIndexed ? KW : 4> sums;
     float acc[KW][LP][V];
 #pragma unroll
     for (int kk = 0; kk < KW; ++kk)
@@ -229,6 +340,10 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
         for (int p = 0; p < LP; ++p)
 #pragma unroll
             for (int v = 0; v < V; ++v) acc[kk][p][v] = 0.f;
+    if constexpr (kIndexed) {
+        sums.a = 0.f;
+        if constexpr (KW == 16) sums.b = 0.f;
+    }
 
     const T* __restrict__ x = static_cast<const T*>(a.x);
     const int chan_stride = a.H * a.W;
@@ -252,13 +367,15 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
     // batch count of each of the KW rows; the KW segments are contiguous in the
     // entry table.  The descriptor of the next chunk and the first batch of this
     // chunk are requested a phase ahead, so their latency is hidden.
-    const SC_CONSTANT int* sg = as_constant(a.seg) + (((size_t)kb * a.nchunks + ch_first) * a.WK + wk) * (KW + 1);
-    const size_t sg_step = (size_t)a.WK * (KW + 1);
+    // (Indexed: how many times eight entries are pairs, and four are single ones, in the place of the counts of rows.)
+    constexpr int kCounts = kIndexed ? 2 : KW;
+    const SC_CONSTANT int* sg = as_constant(a.seg) + (((size_t)kb * a.nchunks + ch_first) * a.WK + wk) * (kCounts + 1);
+    const size_t sg_step = (size_t)a.WK * (kCounts + 1);
     int d_start = sg[0];
-    int d_end = sg[KW + 1];  // the next descriptor's first entry: segments are laid out in descriptor order
-    int d_nb[KW];
+    int d_end = sg[kCounts + 1];  // the next descriptor's first entry: segments are laid out in descriptor order
+    int d_nb[kCounts];
 #pragma unroll
-    for (int kk = 0; kk < KW; ++kk) d_nb[kk] = sg[1 + kk];
+    for (int kk = 0; kk < kCounts; ++kk) d_nb[kk] = sg[1 + kk];
     // Compact entries (binary16 layers, and cluster-quantised layers, whose weights are binary16 centroids:
     // sections 6 and 9): an entry is one word, (LDS offset in units of 2 or 4 bytes) << 16 | binary16 weight,
     // half the bytes of the (fp32 weight, offset) pair.  A batch is decoded once, when it has arrived, on the
@@ -269,10 +386,11 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
     constexpr bool compact = COMPACT;
     constexpr int epd = compact ? 1 : 2;       // 32-bit words per entry
     const SC_CONSTANT uint32_t* e = nullptr;   // epd * kBatch dwords per batch
-    int nb[KW];
+    int nb[kCounts];
+    uint16v eight;   // indexed: the stream's first entries
     Batch cur;
     Batch ahead;   // the batch after cur (deep pipeline only)
-    constexpr bool kDeep = REAL && LP == 1 && sizeof(T) == 4;   // whole batches of reads in flight (see compute)
+    constexpr bool kDeep = REAL && LP == 1 && sizeof(T) == 4 && !kIndexed;   // whole batches of reads in flight (see compute)
     auto fetch_batch = [&](Batch& b, const SC_CONSTANT uint32_t* p) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) b.w[u] = p[u];
@@ -303,8 +421,9 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
     auto begin_chunk = [&](int ch) __attribute__((always_inline)) {
         e = as_constant(a.entries) + (size_t)epd * (size_t)d_start;
 #pragma unroll
-        for (int kk = 0; kk < KW; ++kk) nb[kk] = d_nb[kk];
-        fetch_batch(cur, e);  // the table ends in 2 * kBatch slack entries
+        for (int kk = 0; kk < kCounts; ++kk) nb[kk] = d_nb[kk];
+        if constexpr (kIndexed) eight = *reinterpret_cast<const SC_CONSTANT uint16v*>(e);   // (and here in what an indexed stream runs ahead)
+        else fetch_batch(cur, e);  // the table ends in 2 * kBatch slack entries
         if constexpr (kDeep) {
             e += epd * kBatch;
             fetch_batch(ahead, e);
@@ -312,9 +431,9 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
         if (ch + 1 < ch_end) {
             sg += sg_step;
             d_start = sg[0];
-            d_end = sg[KW + 1];
+            d_end = sg[kCounts + 1];
 #pragma unroll
-            for (int kk = 0; kk < KW; ++kk) d_nb[kk] = sg[1 + kk];
+            for (int kk = 0; kk < kCounts; ++kk) d_nb[kk] = sg[1 + kk];
         }
     };
     // The entries of a wavefront's segment are read once, batch by batch, through the scalar
@@ -394,7 +513,7 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
     // channels load whatever follows in memory (or zero past the end) into tile channels
     // that no plan entry refers to.
     vec st_val[kStage];
-    unsigned st_dst[kStage];       // where the unit in flight goes: LDS address in the first tile buffer
+    unsigned st_dst[kStage];       // later passes: where the unit in flight goes, LDS address in the first tile buffer
     unsigned u_off[kStage];        // first pass: source offset (0x80000000: none) ...
     unsigned u_dst[kStage];        // ... and LDS address in the first buffer (the spare element if none)
     int gi = 0, c = 0, sp = 0;     // later passes: the thread's next unit
@@ -445,7 +564,6 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
         f_rs = chunk_rsrc(c0);
     };
     auto fetch_unit = [&](int t) __attribute__((always_inline)) {  // first pass; t is a constant after unrolling
-        st_dst[t] = u_dst[t];
         unsigned ib = img_bytes;
         // with many accumulators, keep the V offsets of all units from being worked out once and held in registers
         if constexpr (KW * LP * V > 16 || LP * V > 8) asm volatile("" : "+s"(ib));
@@ -482,11 +600,11 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
             next_unit();
         }
     };
-    auto deposit = [&](int buf) __attribute__((always_inline)) {
+    auto deposit = [&](int buf, const unsigned(&dst)[kStage]) __attribute__((always_inline)) {
         const unsigned base = (unsigned)(buf * a.tile_elems) * (unsigned)sizeof(vec);
 #pragma unroll
         for (int t = 0; t < kStage; ++t)  // unconditional (units without an element go to the buffer's spare one): one add a write
-            lds_write<vec>(st_dst[t] + base, st_val[t]);
+            lds_write<vec>(dst[t] + base, st_val[t]);
     };
 
     // Gather-FMA over this wavefront's KW rows of one chunk whose tile starts at
@@ -528,6 +646,15 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
         }
     };
     auto compute = [&](int base, bool prefetch) __attribute__((always_inline)) {
+        if constexpr (kIndexed) {
+            if (prefetch) {
+#pragma unroll
+                for (int t = 0; t < kStage; ++t) fetch_unit(t);
+            }
+            __builtin_amdgcn_s_setprio(3);
+            sums.multiply(reinterpret_cast<const SC_CONSTANT uint32_t*>(e), eight, nb[0], nb[1], lds_address(smem) + (unsigned)base);
+            return;
+        } else {
         vec xs[2][kGroup][LP];
         static_assert(kGroup == 2, "a group is the two entries whose offsets share a 64-bit scalar");
         // the lane's LDS address (of the tile element under its first position), in both halves
@@ -689,6 +816,7 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
                 cur = nxt;
             }
         }
+        }
     };
 
     if constexpr (!REAL) __syncthreads();  // slot table complete
@@ -703,10 +831,10 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
     // once and stay zero for the whole kernel (staging writes real elements only)
     for (int u = tid; u < a.nbuf * a.tile_elems + a.zero_elems; u += nthreads) tile[u] = VT::zero();   // and the zero region behind them
     __syncthreads();  // zero fill complete
-    deposit(0);
+    deposit(0, u_dst);
     for (int p = 1; p < a.npass; ++p) {
         fetch_more(p);
-        deposit(0);
+        deposit(0, st_dst);
     }
     retire(warm);
     __syncthreads();  // chunk 0 is in LDS
@@ -724,15 +852,22 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
         SC_PHASE(2);
         if (more) {
             begin_chunk(ch + 1);
-            deposit((ch + 1 - ch_first) & (a.nbuf - 1));
+            deposit((ch + 1 - ch_first) & (a.nbuf - 1), u_dst);
             retire(warm);
             for (int p = 1; p < a.npass; ++p) {
                 fetch_more(p);
-                deposit((ch + 1 - ch_first) & (a.nbuf - 1));
+                deposit((ch + 1 - ch_first) & (a.nbuf - 1), st_dst);
             }
             __syncthreads();  // chunk ch+1 is in LDS; everyone is done with chunk ch's buffer
             SC_PHASE(3);
         }
+    }
+
+    if constexpr (kIndexed) {
+#pragma unroll
+        for (int kk = 0; kk < KW; ++kk)
+#pragma unroll
+            for (int v = 0; v < V; ++v) acc[kk][0][v] = indexed_sum(sums, kk * V + v);
     }
 
     // What follows needs launch constants that nothing before it uses (output pointer, channel slots, bias, the

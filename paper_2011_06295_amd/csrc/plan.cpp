@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <climits>
 #include <cmath>
+#include <map>
 #include <utility>
 #include <vector>
 
@@ -501,6 +502,12 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
     // ---- tables
     const int RS = R * S;
     const int nchunks = p.nchunks;
+    // Weights that are binary16 values (binary16 layers; cluster-quantised layers, whose centroids are binary16)
+    // go to the device as one word per entry, with the LDS offset in 16 bits: in units of 4 bytes (2 for
+    // 2-byte elements, whose tile must then stay below 128 KB; otherwise the ordinary 8-byte entries are kept).
+    p.off_shift = s.ub >= 4 ? 2 : 1;
+    p.compact = (csr.coded || elem_bytes == 2) && ((long long)p.nbuf * ((long long)p.Cc * p.CS + 1) * s.ub >> p.off_shift) < 65536;
+    p.indexed = tile_indexed(elem_bytes, p.V, p.KW, p.LP, p.compact);
     // Output channel of every accumulator slot (kb, wk, kk).  The wavefronts of a workgroup meet
     // at a barrier after every channel chunk, so what should be equal among them is the number
     // of batches per chunk, not only per layer (a row's weights are spread unevenly over the
@@ -511,7 +518,7 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
     //     so far overlaps least with the row's own chunk profile (smallest dot product).
     p.krow.assign((size_t)p.kblocks * KB, -1);
     {
-        std::vector<int> batches((size_t)K * nchunks);   // batches of row k in chunk ch
+        std::vector<int> batches((size_t)K * nchunks);   // batches (indexed: weights) of row k in chunk ch
         std::vector<long long> total(K, 0);
         for (int k = 0; k < K; ++k) {
             const int* cb = csr.colidx.data() + csr.rowptr[k];
@@ -520,7 +527,7 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
             for (int ch = 0; ch < nchunks; ++ch) {
                 const int c1 = std::min(C, (ch + 1) * p.Cc);
                 const int* hi = std::lower_bound(lo, ce, c1 * RS);
-                batches[(size_t)k * nchunks + ch] = cdiv(hi - lo, kBatch);
+                batches[(size_t)k * nchunks + ch] = p.indexed ? (int)(hi - lo) : cdiv(hi - lo, kBatch);
                 total[k] += batches[(size_t)k * nchunks + ch];
                 lo = hi;
             }
@@ -559,20 +566,60 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
     }
 
     const int ge = p.G ? p.G : 1;   // elements per lattice position
-    const int SW = p.KW + 1;  // descriptor: first entry, then batches of each of the KW rows
+    const int SW = (p.indexed ? 2 : p.KW) + 1;  // descriptor: first entry, then batches of each of the KW rows (indexed: the two counts)
     p.seg.assign(((size_t)p.kblocks * nchunks * p.WK + 1) * SW, 0);   // one terminal descriptor
     p.entries.clear();
-    // Weights that are binary16 values (binary16 layers; cluster-quantised layers, whose centroids are binary16)
-    // go to the device as one word per entry, with the LDS offset in 16 bits: in units of 4 bytes (2 for
-    // 2-byte elements, whose tile must then stay below 128 KB; otherwise the ordinary 8-byte entries are kept).
-    p.off_shift = s.ub >= 4 ? 2 : 1;
-    p.compact = (csr.coded || elem_bytes == 2) && ((long long)p.nbuf * ((long long)p.Cc * p.CS + 1) * s.ub >> p.off_shift) < 65536;
+    struct Stored {
+        int col, kk;
+        uint32_t wbits;
+    };
+    std::vector<Stored> stored;      // indexed: a wavefront's weights of a chunk, by column
+    std::vector<Entry> pairs, singles;
     for (int kb = 0; kb < p.kblocks; ++kb)
         for (int ch = 0; ch < nchunks; ++ch) {
             const int c0 = ch * p.Cc, c1 = std::min(C, c0 + p.Cc);
             for (int wk = 0; wk < p.WK; ++wk) {
                 int* sg = &p.seg[(((size_t)kb * nchunks + ch) * p.WK + wk) * SW];
                 sg[0] = (int)p.entries.size();
+                if (p.indexed) {
+                    stored.clear();
+                    for (int kk = 0; kk < p.KW; ++kk) {
+                        const int k = p.krow[(size_t)kb * KB + wk * p.KW + kk];
+                        if (k < 0) continue;
+                        const int* ce = csr.colidx.data() + csr.rowptr[k + 1];
+                        for (const int* q = std::lower_bound(csr.colidx.data() + csr.rowptr[k], ce, c0 * RS); q < ce && *q < c1 * RS; ++q) {
+                            uint32_t wb;
+                            __builtin_memcpy(&wb, &csr.val32[(size_t)(q - csr.colidx.data())], 4);
+                            stored.push_back({*q, kk, wb});
+                        }
+                    }
+                    std::stable_sort(stored.begin(), stored.end(), [](const Stored& x, const Stored& y) { return x.col < y.col; });
+                    pairs.clear();
+                    singles.clear();
+                    auto entry = [&](const Stored& w) {
+                        const int c = w.col / RS, r = (w.col / S) % R, sx = w.col % S;
+                        return Entry{w.wbits, ((c - c0) * p.CS + (r * p.pitch + sx) * ge) * s.ub + w.kk};
+                    };
+                    for (size_t i = 0; i < stored.size();) {      // weights under the same input go in twos, of different rows
+                        const bool two = i + 1 < stored.size() && stored[i + 1].col == stored[i].col;
+                        (two ? pairs : singles).push_back(entry(stored[i]));
+                        if (two) pairs.push_back(entry(stored[i + 1]));
+                        i += two ? 2 : 1;
+                    }
+                    while (pairs.size() % 8) {                    // pairs come in eights: the rest are single ones
+                        singles.push_back(pairs.back());
+                        pairs.pop_back();
+                    }
+                    // filled up to whole batches with weights of zero in the zero region, as the segments below
+                    const int buf = (ch % p.cpp) & (p.nbuf - 1);
+                    while (singles.size() % kBatch) singles.push_back(Entry{0u, (int)((long long)(p.nbuf - buf) * (p.Cc * p.CS + 1) * s.ub)});
+                    sg[1] = (int)(pairs.size() / 8);
+                    sg[2] = (int)(singles.size() / kBatch);
+                    p.entries.insert(p.entries.end(), pairs.begin(), pairs.end());
+                    p.entries.insert(p.entries.end(), singles.begin(), singles.end());
+                    if (p.entries.size() > (size_t)INT_MAX / 2) return SC_EUNSUPPORTED;
+                    continue;
+                }
                 for (int kk = 0; kk < p.KW; ++kk) {
                     const int k = p.krow[(size_t)kb * KB + wk * p.KW + kk];
                     sg[1 + kk] = 0;
@@ -605,7 +652,7 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
             }
         }
     p.seg[(size_t)p.kblocks * nchunks * p.WK * SW] = (int)p.entries.size();  // where the last segment ends
-    for (int t = 0; t < 2 * kBatch; ++t) p.entries.push_back(Entry{0u, 0});  // slack for look-ahead fetches (two batches)
+    for (int t = 0; t < (p.indexed ? kAhead : 2 * kBatch); ++t) p.entries.push_back(Entry{0u, 0});  // slack for look-ahead fetches
 
     // ---- output lanes: the staging units of every thread, per pattern
     p.units.clear();
@@ -672,7 +719,7 @@ int check_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Plan& 
 {
     const int K = csr.K, RS = R * S;
     const int ub = p.V * elem_bytes;
-    const int KB = p.WK * p.KW, SW = p.KW + 1;
+    const int KB = p.WK * p.KW, SW = (p.indexed ? 2 : p.KW) + 1;
     // 1: launch shape within the hardware's limits
     if (p.threads != kWave * p.WP * p.WK || p.threads > kWave * kMaxWaves || p.lds_bytes > kMaxLds) return 1;
     if (p.nchunks != cdiv(C, p.Cc) || (p.nbuf != 1 && p.nbuf != 2) || (p.nchunks > 1 && p.nbuf != 2)) return 1;
@@ -716,6 +763,44 @@ int check_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Plan& 
             for (int wk = 0; wk < p.WK; ++wk) {
                 const int* sg = &p.seg[(((size_t)kb * p.nchunks + ch) * p.WK + wk) * SW];
                 if ((size_t)sg[0] != pos) return 3;                       // segments are contiguous
+                if (p.indexed) {
+                    // pairs and single ones together are the rows' weights of the chunk, each once, at its tap's offset
+                    if (!tile_indexed(elem_bytes, p.V, p.KW, p.LP, p.compact) || sg[1] < 0 || sg[2] < 0) return 4;
+                    const size_t paired = (size_t)sg[1] * 8, n = paired + (size_t)sg[2] * kBatch;
+                    if (pos + n + kAhead > p.entries.size()) return 4;
+                    std::map<std::pair<int, long long>, uint32_t> found;  // (slot, offset): weight
+                    size_t padding = 0;
+                    for (size_t t = 0; t < n; ++t) {
+                        const Entry& e = p.entries[pos + t];
+                        const long long off = e.off & ~15;
+                        if (t < paired && t % 2 && off != (p.entries[pos + t - 1].off & ~15)) return 5;
+                        if (off == (long long)(p.nbuf - ((ch % p.cpp) & (p.nbuf - 1))) * ((long long)p.Cc * p.CS + 1) * ub) {
+                            if (e.wbits != 0u || (e.off & 15) || t + kBatch <= n) return 5;      // padding: in the last batch only
+                            ++padding;
+                            continue;
+                        }
+                        if (off < 0 || off >> 4 >= 65536 || off / ub + lane_reach >= (long long)(c1 - c0) * p.CS) return 6;
+                        if (!found.emplace(std::make_pair(e.off & 15, off), e.wbits).second) return 5;
+                    }
+                    if (padding >= kBatch) return 4;
+                    for (int kk = 0; kk < p.KW; ++kk) {
+                        const int k = p.krow[(size_t)kb * KB + wk * p.KW + kk];
+                        if (k < 0) continue;
+                        for (int i = csr.rowptr[k]; i < csr.rowptr[k + 1]; ++i) {
+                            const int col = csr.colidx[i], c = col / RS, r = (col / S) % R, sx = col % S;
+                            if (c < c0 || c >= c1) continue;
+                            const auto it = found.find({kk, ((long long)(c - c0) * p.CS + ((long long)r * p.pitch + sx) * ge) * ub});
+                            uint32_t wb;
+                            __builtin_memcpy(&wb, &csr.val32[i], 4);
+                            if (it == found.end() || it->second != wb) return 5;
+                            found.erase(it);
+                            ++real;
+                        }
+                    }
+                    if (!found.empty()) return 5;
+                    pos += n;
+                    continue;
+                }
                 for (int kk = 0; kk < p.KW; ++kk) {
                     const int k = p.krow[(size_t)kb * KB + wk * p.KW + kk];
                     const int nb = sg[1 + kk];

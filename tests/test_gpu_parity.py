@@ -535,3 +535,38 @@ def test_pooled_store_refuses_what_it_cannot_do():
         layer.get_launch(4, 8, 8, 1, 1)
     assert e.value.code == B.SC_EUNSUPPORTED
     layer.close()
+
+
+# Weights of rows that share a wavefront: under the same inputs (pairs alone), under different ones (single ones alone), both, and rows
+# without any; with 4, 8 and 16 rows a wavefront, lattice positions and outputs as lanes, parts of the channels.
+# V, WP, WK, KW, Cc, LDS, LP, channel blocks, store, lanes, parts
+INDEXED = [(4, 1, 2, 4, 3, 0, 1, 0, 0, 1, 1), (4, 2, 1, 8, 0, 0, 1, 0, 0, 1, 1), (4, 1, 2, 16, 2, 0, 1, 0, 0, 1, 1), (4, 1, 4, 4, 2, 0, 1, 0, 0, 3, 1),
+           (4, 1, 1, 8, 3, 0, 1, 0, 0, 3, 2), (4, 1, 3, 16, 1, 0, 1, 0, 0, 3, 4)]
+
+
+@pytest.mark.parametrize("launch", INDEXED, ids=lambda v: "x".join(map(str, v)))
+@pytest.mark.parametrize("rows", ["same", "apart", "mixed", "few", "dense"])
+def test_rows_of_a_wavefront_in_one_stream(rows, launch):
+    rng = np.random.default_rng(61)
+    N, C, K, H = 9, 7, 37, 16
+    w, m, x = rand_layer(rng, N, C, K, 3, 3, H, H, density=0.3)
+    flat = m.reshape(K, -1)
+    if rows == "same":                     # every row the same 24 columns
+        flat[:] = 0
+        flat[:, rng.permutation(C * 9)[:24]] = 1
+    elif rows == "apart":                  # no column twice in a wavefront's rows: 63 columns for 16 rows
+        flat[:] = 0
+        for k in range(K):
+            flat[k, (k % 16) * 3:(k % 16) * 3 + 3] = 1
+    elif rows == "few":                    # rows of 0 to 3 weights
+        flat[:] = 0
+        for k in range(K):
+            flat[k, rng.permutation(C * 9)[:k % 4]] = 1
+    elif rows == "dense":
+        flat[:] = 1
+    from paper_2011_06295_amd import binding as B
+    layer = B.SparseConv(w, m)
+    layer.set_launch(launch)
+    assert layer.check_plan(N, H, H, 1, 1) == 0
+    layer.close()
+    check(w, m, x, 1, 1, "f32", launch=launch, what=f"{rows} {launch}")
