@@ -214,6 +214,7 @@ struct KernelArgs {
     int pool;            // 1: store the maximum over 2 x 2 windows of the (biased, clamped) sums: [N][K][E/2][F/2]
     int pool_rows;       // pooled store: output channels per wavefront that go through LDS together (1..KW, as LDS allows)
     int nt_store;        // non-temporal output stores
+    int out_32;          // the outputs of a tile's image groups span less than 2^31 bytes
     int N, C, H, W, K, E, F, stride, pad;
     int WP, WK, Cc, Wp, Hs, Hb, CS, span;
     int nchunks, ngroups, ntiles, kblocks;
