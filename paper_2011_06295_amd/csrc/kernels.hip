@@ -197,8 +197,8 @@ struct Vec<T, 1> {
     SC_WAIT SC_RD("at0", cur, "4", "8") SC_RD("at1", cur, "6", "12") SC_FETCH(nxt) SC_FOUR(cur, "0", "1", "2", "3", "0") \
     SC_WAIT SC_RD("at0", nxt, "0", "0") SC_RD("at1", nxt, "2", "4") SC_FOUR(cur, "4", "5", "6", "7", "8") \
     "s_sub_u32 %[n2], %[n2], 1\n\ts_cmp_eq_u32 %[n2], 0\n\t"
-// (The issue priority falls as the stream is worked off, see yield_to_slower: 3 for pairs, 2 for the first half of the single ones,
-// 1 for a quarter, then 0.)
+// (The issue priority falls as the stream is worked off, see yield_to_slower: 3 for pairs up to half the stream, 2 for the others, 1 for
+// three quarters of the single ones, then 0; without pairs 3 for the first half.)
 #define SC_LESS(back, done) \
     "s_sub_u32 %[n1], %[n1], 1\n\ts_cmp_eq_u32 %[n1], 0\n\ts_cbranch_scc1 " done "f\n\t" back ":\n\t"
 #define SC_REST(back, done, last) \
@@ -217,14 +217,17 @@ struct Vec<T, 1> {
     SC_EACH(cur, "4", "5", "6", "7", "16") SC_LESS(back2, done2)
 #define SC_ENTER2(set) SC_RD("at0", set, "0", "0") SC_RD("at1", set, "1", "4")
 #define SC_ENTER4(set) SC_ENTER2(set) SC_RD("at0", set, "2", "8") SC_RD("at1", set, "3", "12")
+#define SC_MORE_PAIRS "s_setprio 2\n\ts_mov_b32 %[n2], %[n4]\n\ts_mov_b32 %[n4], 0\n\ts_cmp_eq_u32 %[n2], 0\n\ts_cbranch_scc0 "
 #define SC_STREAM(R) \
-    "s_cmp_eq_u32 %[n2], 0\n\ts_cbranch_scc1 3f\n\t" \
+    "s_cmp_eq_u32 %[n2], 0\n\ts_cbranch_scc1 8f\n\t" \
     SC_RD("at0", "36", "0", "0") SC_RD("at1", "36", "2", "4") \
-    "1:\n\t" SC_PAIRS("36", "52") "s_cbranch_scc1 5f\n\t" \
-    SC_PAIRS("52", "36") "s_cbranch_scc0 1b\n\t" \
-    "3:\n\ts_setprio 2\n\ts_cmp_eq_u32 %[n1], 0\n\ts_cbranch_scc1 9f\n\t" SC_ENTER##R("36") \
+    "1:\n\t" SC_PAIRS("36", "52") "s_cbranch_scc1 7f\n\t" \
+    "2:\n\t" SC_PAIRS("52", "36") "s_cbranch_scc0 1b\n\t" SC_MORE_PAIRS "1b\n\t" \
+    "s_setprio 1\n\t" \
+    "8:\n\ts_cmp_eq_u32 %[n1], 0\n\ts_cbranch_scc1 9f\n\t" SC_ENTER##R("36") \
     "4:\n\t" SC_SINGLES##R("36", "52", "11", "21", "12", "22") "s_branch 6f\n\t" \
-    "5:\n\ts_setprio 2\n\ts_cmp_eq_u32 %[n1], 0\n\ts_cbranch_scc1 9f\n\t" SC_ENTER##R("52") \
+    "7:\n\t" SC_MORE_PAIRS "2b\n\t" \
+    "s_setprio 1\n\ts_cmp_eq_u32 %[n1], 0\n\ts_cbranch_scc1 9f\n\t" SC_ENTER##R("52") \
     "6:\n\t" SC_SINGLES##R("52", "36", "13", "23", "14", "24") "s_branch 4b\n\t" \
     SC_REST("11", "21", "31") SC_REST("12", "22", "32") SC_REST("13", "23", "33") SC_REST("14", "24", "34") \
     "9:\n\t" SC_WAIT
@@ -246,10 +249,12 @@ struct Indexed;
         __device__ __forceinline__ void multiply(const SC_CONSTANT uint32_t* from, uint16v first, int pairs, int singles, unsigned base) \
         { \
             unsigned off = 64, at0, at1; \
-            int last = singles >> 2, rest = (singles >> 1) - last; \
+            int last = singles >> 2, rest = (singles >> 1) - last, more = (2 * pairs + singles + 3) >> 2; \
+            more = pairs > more ? pairs - more : 0; \
+            pairs -= more; \
             singles -= rest + last; \
             asm volatile(SC_STREAM(R) \
-                         : OPERANDS, "+{s[36:51]}"(first), [n2] "+s"(pairs), [n1] "+s"(singles), [n0] "+s"(rest), [n3] "+s"(last), [off] "+s"(off), \
+                         : OPERANDS, "+{s[36:51]}"(first), [n2] "+s"(pairs), [n1] "+s"(singles), [n0] "+s"(rest), [n3] "+s"(last), [n4] "+s"(more), [off] "+s"(off), \
                            [at0] "=&v"(at0), [at1] "=&v"(at1) \
                          : [ptr] "s"(from), [base] "v"(base), [acc] "i"(ACC), [x] "i"(X) \
                          : "s52", "s53", "s54", "s55", "s56", "s57", "s58", "s59", "s60", "s61", "s62", "s63", "s64", "s65", "s66", "s67", \
@@ -448,11 +453,12 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
         }
     };
     // The entries of a wavefront's segment are read once, batch by batch, through the scalar
-    // cache; coming from HBM each batch would cost a full memory latency.  One vector load per
-    // 64 bytes of the coming segment (d_start..d_end), issued a chunk ahead, brings the lines
-    // into L2 first.  The loaded value is only kept until the next wait for staged data.
-    auto touch = [&]() __attribute__((always_inline)) -> unsigned {
-        const size_t first = (size_t)epd * (size_t)d_start + (size_t)lane * 16;  // 16 words = 64 bytes
+    // cache; coming from beyond L2 each batch would cost a full memory latency.  Two vector loads a lane, one
+    // per 128-byte line of the coming segment (d_start..d_end), issued a chunk ahead, bring its first 16 KB
+    // into L2 first (tables of more than an L2: 382 -> 393 channels, 5 x 5, 32 x 32, 70 %, 9 KB a wavefront and chunk: 506 us with
+    // 4 KB touched, 428 so).  The loaded values are only kept until the next wait for staged data.
+    auto touch = [&](int part) __attribute__((always_inline)) -> unsigned {
+        const size_t first = (size_t)epd * (size_t)d_start + (size_t)(part * 64 + lane) * 32;  // 32 words = 128 bytes
         return first < (size_t)epd * (size_t)d_end ? a.entries[first] : 0u;
     };
     auto retire = [](unsigned t) __attribute__((always_inline)) { asm volatile("" ::"v"(t)); };
@@ -836,7 +842,7 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
 #pragma unroll
     for (int t = 0; t < kStage; ++t) fetch_unit(t);
     // the input loads do not wait for the descriptor (requested at the top); what needs it comes after them
-    unsigned warm = touch();  // the first chunk's entries
+    unsigned warm = touch(0), warm2 = touch(1);  // the first chunk's entries
     begin_chunk(ch_first);
     // while the first loads are in flight: padding rows/columns and absent images are zeroed
     // once and stay zero for the whole kernel (staging writes real elements only)
@@ -848,13 +854,15 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
         deposit(0, st_dst);
     }
     retire(warm);
+    retire(warm2);
     __syncthreads();  // chunk 0 is in LDS
     SC_PHASE(0);
     const int tile_bytes = a.tile_elems * (int)sizeof(vec);
     for (int ch = ch_first; ch < ch_end; ++ch) {
         const bool more = ch + 1 < ch_end;
         if (more) {
-            warm = touch();           // chunk ch+1's entries (its descriptor was requested a chunk ago)
+            warm = touch(0);          // chunk ch+1's entries (its descriptor was requested a chunk ago)
+            warm2 = touch(1);
             fetch_begin(ch + 1);
         }
         SC_PHASE(1);
@@ -865,6 +873,7 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
             begin_chunk(ch + 1);
             deposit((ch + 1 - ch_first) & (a.nbuf - 1), u_dst);
             retire(warm);
+            retire(warm2);
             for (int p = 1; p < a.npass; ++p) {
                 fetch_more(p);
                 deposit((ch + 1 - ch_first) & (a.nbuf - 1), st_dst);
