@@ -94,7 +94,53 @@ void rows_per_wavefront(int nrows, int WP, int WK, int KW, std::vector<int>& roo
     }
 }
 
-// Rough time of one launch in CU clocks.  The structure follows measurements on
+// Rough time of one fp32 launch in CU clocks.  Structure and constants are fitted to the measured times of 10000 launch
+// configurations (up to 64 that differ, of each of 150 layers: 3x3 and 5x5, 1x1, 1-D, stride 2, batches of 2 to 256, 50 to 99 %
+// sparse): 11 % rms of the logarithm; the cheapest by estimate takes 5 % longer than the fastest measured in the mean, and 12 % or less
+// in nine of ten layers.  (By the estimate below, fitted before rows shared a stream: 9 %, and 23 %.)
+//  * A weight costs its SIMD the multiply-adds of its positions and images, some 4 clocks each (16 where rows share a stream), and 8
+//    for its address and read; with two positions a lane and elements of less than four images a quarter more, with one or two rows a
+//    wavefront and several workgroups a CU half as much again.
+//  * Padding: 8 weights a wavefront and chunk where rows share a stream, else 3.3 a row and chunk.
+//  * A lone wavefront cannot hide its own LDS and scalar-fetch latency: 45 to 48 clocks a weight.
+//  * A chunk costs 1430 clocks and 7 a wavefront; its staging a clock for 80 bytes (33 with four image groups or more an element, where
+//    its writes meet in the banks), half of which the arithmetic does not hide.
+//  * A workgroup costs 10000 clocks and 15 for each of its wavefronts' stores; as a part of the channels 1170, 1030 a part, and 28 for
+//    each of its wavefronts' sums, which the last part reads back.
+//  * Registers bound the wavefronts resident on a SIMD: 4 of the kernels with 16 rows or, with lattice lanes, 4 or 8, else 5.
+//  * Workgroups run in rounds of (CUs * resident workgroups); what does not multiply takes 1.1 to 1.2 times as long beside others.
+double estimate_f32(const Shape& s, const Cand& c)
+{
+    const int J = std::max(1, c.J), waves = c.WP * c.WK, acc = c.KW * c.LP * c.V;
+    const bool indexed = tile_indexed(s.elem_bytes, c.V, c.KW, c.LP, false);
+    const double regs = std::min(128.0, 56.0 + acc + 4.0 * c.LP * c.V);
+    const int per_simd = indexed ? (c.KW == 16 || s.G == 0 ? 4 : 5) : std::min(8, 512 / (8 * (int)std::ceil(regs / 8.0)));
+    const int conc_max = std::min(kMaxLds / c.lds, 4 * per_simd / waves);
+    if (conc_max < 1) return -1.0;
+    const int nchunks = cdiv(cdiv(s.C, c.Cc), J);          // chunks a workgroup walks
+    const double seg = s.row_nnz * c.Cc / s.C, rows = std::max(1.0, std::min((double)c.KW, (double)cdiv(s.K, c.kblocks) / c.WK));
+    // weights of a wavefront and chunk, padded, and what each costs its SIMD
+    const double padding = nchunks == 1 ? std::ceil(seg / kBatch) * kBatch - seg : 3.34;
+    const double weights = rows * seg + (indexed ? 8.0 : rows * padding);
+    const double each = ((indexed ? 16.0 : 4.12 * c.LP * c.V) + 8.0) * (c.LP == 2 && c.V < 4 ? 1.265 : 1.0);
+    const double alone = weights * (each + (indexed ? 44.6 : 48.3));
+    const double bytes = (double)s.C / J * c.CS * s.ub * ((double)s.W / s.Wp) * std::min(1.0, (double)s.H / s.Hs);
+    auto round = [&](double conc) {
+        const double on_simd = waves < 8 ? std::ceil(conc * waves / 4.0) : conc * waves / 4.0;
+        const double multiply = nchunks * std::max(on_simd * weights * each / 1.05 * (!indexed && c.KW <= 2 && conc > 1 ? 1.463 : 1.0), alone);
+        const double stage = conc * bytes / 80.0 * (s.G >= 4 ? 2.41 : 1.0);
+        const double beside = nchunks * (1432.0 + 7.2 * waves) + 1.153 * stage + 15.3 * waves * acc * conc;
+        const double crowd = conc >= 3 ? 1.2 : conc >= 2 ? 1.11 : 1.0;
+        return std::max(multiply, stage) + (beside + stage / nchunks) * crowd + 10000.0 +
+               (J > 1 ? 1173.0 + 1031.0 * J + 27.8 * waves * acc * conc : 0.0);
+    };
+    const long long wgs = (long long)cdiv(s.npos, (long long)kWave * c.WP * c.LP) * c.kblocks * J, slots = (long long)kCUs * conc_max;
+    const long long rest = wgs % slots;
+    return (double)(wgs / slots) * round(conc_max) + (rest ? round((double)cdiv(rest, kCUs)) : 0.0);
+}
+
+// The same for binary16 layers, and for fp32 ones as their kernels were when each row was a stream of its own (what the choice of
+// the matrix kernel also looks at).  The structure follows measurements on
 // MI355X; the constants were fitted to the measured times of ~41000 launch
 // configurations (every shape the candidate loops below produce) of the 13
 // VGG-16 layers at 32 px (batch 128, fp32), four of its layers at 224 px
@@ -130,11 +176,8 @@ double estimate(const Shape& s, const Cand& c)
     if (conc_max < 1) return -1.0;
     const int kblocks = c.kblocks;
     const long long wgs = (long long)cdiv(s.npos, (long long)kWave * c.WP * c.LP) * kblocks * J;
-    // rows on the fullest SIMD and wavefront-rows in all of a typical channel block
-    std::vector<int> room;
-    rows_per_wavefront(cdiv(s.K, kblocks), c.WP, c.WK, c.KW, room);
-    long long rows_all = 0;
-    for (int w = 0; w < c.WK; ++w) rows_all += (long long)room[w] * c.WP;
+    // wavefront-rows in all of a typical channel block
+    const long long rows_all = (long long)std::min(cdiv(s.K, kblocks), c.WK * c.KW) * c.WP;
     // with the empty slots spread as they are the SIMDs differ by a row at most: the mean fits as well as the maximum
     const double rows_simd = (double)rows_all / 4.0;
     const double fma_clk = s.elem_bytes == 2 ? 4.4 : 4.0;
@@ -201,7 +244,8 @@ FastDiv make_fastdiv(int d)
 }
 
 int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geometry& g,
-               const Launch& over, Plan& p, std::vector<std::pair<double, Launch>>* ranked, std::pair<double, Launch>* cheapest)
+               const Launch& over, Plan& p, std::vector<std::pair<double, Launch>>* ranked, std::pair<double, Launch>* cheapest,
+               double* cheapest_by_rows)
 {
     const int K = csr.K;
     const int st = g.stride, pad = g.pad;
@@ -226,6 +270,12 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
     Cand best{};
     Shape bs{};
     double best_t = -1.0;
+    // fp32: the cheapest of each number of channel parts (1, 2, 4, 8), and the one that the estimate for kernels by rows would take.  A
+    // sum dealt over parts is the more exact one, so no fewer parts are taken than that.
+    Cand best_of[4];
+    Shape bs_of[4];
+    double best_t_of[4] = {-1.0, -1.0, -1.0, -1.0}, rows_t = -1.0;
+    int rows_parts = 0;
     bool too_many_positions = false;
     // images interleaved per LDS element: an element of up to 16 bytes, not wider than the batch can fill
     const int EF = p.E * p.F;
@@ -390,7 +440,7 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
                             const int nch = cdiv(C, Cc);
                             if (J > 1 && (J > nch || (long long)(J - 1) * cdiv(nch, J) >= nch)) continue;   // every part needs a chunk
                             Cand c{V, wp, wk, kw, Cc, LP, kblocks, Hb, (int)CS, (int)lds, (int)SL, banded ? 2 : rows_mode ? 1 : 0, rows_mode ? 1 : (int)GC, nbuf, pitch, J, (int)ZE};
-                            double t = estimate(s, c);
+                            double t = elem_bytes == 4 ? estimate_f32(s, c) : estimate(s, c);
                             if (t < 0) {
                                 if (!(over.WP || over.WK || over.KW || over.Cc || over.lds_budget || over.LP || over.kblocks)) continue;
                                 t = 1e30;   // an explicit request is honoured even where the estimate expects no residency
@@ -402,6 +452,16 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
                                 l.lanes = 1 + G;
                                 l.csplit = J;
                                 ranked->emplace_back(t, l);
+                            }
+                            if (elem_bytes == 4 && !ranked) {
+                                const int parts = J == 1 ? 0 : J == 2 ? 1 : J == 4 ? 2 : 3;
+                                const double rows = estimate(s, c);
+                                if (rows >= 0 && (rows_t < 0 || rows < rows_t)) rows_t = rows, rows_parts = parts;
+                                if (best_t_of[parts] < 0 || t < best_t_of[parts]) {
+                                    best_t_of[parts] = t;
+                                    best_of[parts] = c;
+                                    bs_of[parts] = s;
+                                }
                             }
                             if (best_t < 0 || t < best_t) {
                                 best_t = t;
@@ -416,6 +476,16 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
         }
         }
     }
+    if (rows_t >= 0) {
+        best_t = -1.0;
+        for (int parts = rows_parts; parts < 4; ++parts)
+            if (best_t_of[parts] >= 0 && (best_t < 0 || best_t_of[parts] < best_t)) {
+                best_t = best_t_of[parts];
+                best = best_of[parts];
+                bs = bs_of[parts];
+            }
+    }
+    if (cheapest_by_rows) *cheapest_by_rows = rows_t;
     if (best_t < 0 && too_many_positions) return SC_EUNSUPPORTED;
     if (best_t < 0) return SC_EUNSUPPORTED;
     if (ranked) {   // the caller only wants the candidates, cheapest estimate first, each once
@@ -574,6 +644,7 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
         uint32_t wbits;
     };
     std::vector<Stored> stored;      // indexed: a wavefront's weights of a chunk, by column
+    std::vector<int> first_of;       // ... and how many of them, then which, are a column's first
     std::vector<Entry> pairs, singles;
     for (int kb = 0; kb < p.kblocks; ++kb)
         for (int ch = 0; ch < nchunks; ++ch) {
@@ -582,18 +653,31 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
                 int* sg = &p.seg[(((size_t)kb * nchunks + ch) * p.WK + wk) * SW];
                 sg[0] = (int)p.entries.size();
                 if (p.indexed) {
-                    stored.clear();
-                    for (int kk = 0; kk < p.KW; ++kk) {
-                        const int k = p.krow[(size_t)kb * KB + wk * p.KW + kk];
-                        if (k < 0) continue;
-                        const int* ce = csr.colidx.data() + csr.rowptr[k + 1];
-                        for (const int* q = std::lower_bound(csr.colidx.data() + csr.rowptr[k], ce, c0 * RS); q < ce && *q < c1 * RS; ++q) {
-                            uint32_t wb;
-                            __builtin_memcpy(&wb, &csr.val32[(size_t)(q - csr.colidx.data())], 4);
-                            stored.push_back({*q, kk, wb});
+                    // by column, a column's by row: counted, then dealt out
+                    first_of.assign((size_t)(c1 - c0) * RS + 1, 0);
+                    for (int turn = 0; turn < 2; ++turn) {
+                        for (int kk = 0; kk < p.KW; ++kk) {
+                            const int k = p.krow[(size_t)kb * KB + wk * p.KW + kk];
+                            if (k < 0) continue;
+                            const int* ce = csr.colidx.data() + csr.rowptr[k + 1];
+                            for (const int* q = std::lower_bound(csr.colidx.data() + csr.rowptr[k], ce, c0 * RS); q < ce && *q < c1 * RS; ++q) {
+                                int& at = first_of[(size_t)(*q - c0 * RS)];
+                                if (turn == 0) {
+                                    ++at;
+                                } else {
+                                    Stored& to = stored[(size_t)at++];
+                                    to.col = *q;
+                                    to.kk = kk;
+                                    __builtin_memcpy(&to.wbits, &csr.val32[(size_t)(q - csr.colidx.data())], 4);
+                                }
+                            }
+                        }
+                        if (turn == 0) {
+                            int sum = 0;
+                            for (int& n : first_of) sum += n, n = sum - n;
+                            stored.resize((size_t)sum);
                         }
                     }
-                    std::stable_sort(stored.begin(), stored.end(), [](const Stored& x, const Stored& y) { return x.col < y.col; });
                     pairs.clear();
                     singles.clear();
                     auto entry = [&](const Stored& w) {
