@@ -6,7 +6,7 @@
 // 16 input channels x 32 outputs.  At 90 % sparsity nine tenths of the products are with zeros, yet it is the faster way:
 // the tile kernel is bound by its LDS reads (16 bytes for 4 to 8 multiply-adds a lane) at 30 to 40 TFLOP/s of stored
 // weights, where this kernel does 600 to 1100 TFLOP/s of all weights in binary16 (256 -> 512 channels, 28 x 28, batch 128,
-// 90 %: 569 us by the tile kernel, 220 us here) and 200 to 330 in fp32 (256 -> 256, 14 x 14, batch 256, 70 %: 430 and 182 us).
+// 90 %: 569 us by the tile kernel, 208 us here) and 200 to 330 in fp32 (256 -> 256, 14 x 14, batch 256, 70 %: 430 and 172 us).
 //
 // Tile.  A workgroup of four wavefronts owns consecutive outputs of the batch and keeps, chunk by chunk of channels, the
 // lattice elements they touch in LDS, 8 channels of one position to a 16-byte element: a tap is an LDS offset, so the

@@ -8,7 +8,8 @@
 // which a lane only adds the tile-local index of its own position.
 // The paper's unified per-row count (one trip count for every output channel)
 // reappears at segment granularity: each (row, channel-chunk) segment is padded
-// with zero-weight entries to a multiple of the scalar fetch batch.
+// with zero-weight entries to a multiple of the scalar fetch batch (fp32 rows of a wavefront that share a stream:
+// each (wavefront, channel-chunk) stream).
 // The launch configuration (positions, channels and wavefronts per workgroup,
 // channels per LDS pass) plays the role of the per-layer thread-block count the
 // paper tunes by hand (section 8, subBatchSize); it is chosen here by a cost
@@ -272,10 +273,12 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
     double best_t = -1.0;
     // fp32: the cheapest of each number of channel parts (1, 2, 4, 8), and the one that the estimate for kernels by rows would take.  A
     // sum dealt over parts is the more exact one, so no fewer parts are taken than that.
-    Cand best_of[4];
-    Shape bs_of[4];
-    double best_t_of[4] = {-1.0, -1.0, -1.0, -1.0}, rows_t = -1.0;
+    // Nor a launch whose tables and partial sums may be more than the static scratch, where those of that one are not.
+    Cand best_of[2][4];
+    Shape bs_of[2][4];
+    double best_t_of[2][4] = {{-1.0, -1.0, -1.0, -1.0}, {-1.0, -1.0, -1.0, -1.0}}, rows_t = -1.0;
     int rows_parts = 0;
+    bool rows_fit = false;
     bool too_many_positions = false;
     // images interleaved per LDS element: an element of up to 16 bytes, not wider than the batch can fill
     const int EF = p.E * p.F;
@@ -421,12 +424,14 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
                         // (the pooled store stages one sum per thread and image in LDS)
                         if (over.pool) lds = std::max<long long>(lds, (long long)kWave * wp * wk * V * 4);
                         if (lds > kMaxLds) continue;
+                        long long units = 0;   // bytes
                         if (G) {   // the staging patterns of output-lane tiles must stay a small table (build below)
                             int ga = (span / G) % EF, gb = EF;
                             while (ga) { const int r = gb % ga; gb = ga; ga = r; }
                             const long long per = (SL * Cc + (long long)kStage * kWave * wp * wk - 1) / ((long long)kStage * kWave * wp * wk) *
                                                   ((long long)kStage * kWave * wp * wk);
-                            if (per * (EF / gb) * 8 > (8ll << 20)) continue;
+                            units = per * (EF / gb) * 8;
+                            if (units > (8ll << 20)) continue;
                         }
                         // More channel blocks than the rows need leave slots empty, which relieves the
                         // last wavefronts of the fullest SIMDs (rows_per_wavefront): up to two extra.
@@ -456,12 +461,21 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
                             if (elem_bytes == 4 && !ranked) {
                                 const int parts = J == 1 ? 0 : J == 2 ? 1 : J == 4 ? 2 : 3;
                                 const double rows = estimate(s, c);
-                                if (rows >= 0 && (rows_t < 0 || rows < rows_t)) rows_t = rows, rows_parts = parts;
-                                if (best_t_of[parts] < 0 || t < best_t_of[parts]) {
-                                    best_t_of[parts] = t;
-                                    best_of[parts] = c;
-                                    bs_of[parts] = s;
+                                // what sparse_conv_forward_static copies: entries, without and with padding, descriptors, patterns, sums
+                                const double sums = J > 1 ? (double)cdiv(s.npos, (long long)kWave * wp * LP) * kblocks * (J * (kw * LP * V) * 64.0 * wp * wk + 1) * 4.0 : 0.0;
+                                const double tables = units + sums + 4.0 * kblocks * nch * wk * (kw + 1.0) + 4096.0, scratch = (double)kStaticScratchBytes;
+                                const bool fits = tables + 8.0 * K * nch * (s.row_nnz * Cc / C + 3.0) <= scratch;
+                                if (rows >= 0 && (rows_t < 0 || rows < rows_t)) {
+                                    rows_t = rows;
+                                    rows_parts = parts;
+                                    rows_fit = tables + 4.0 * csr.colidx.size() <= scratch;
                                 }
+                                for (int any = fits ? 0 : 1; any < 2; ++any)
+                                    if (best_t_of[any][parts] < 0 || t < best_t_of[any][parts]) {
+                                        best_t_of[any][parts] = t;
+                                        best_of[any][parts] = c;
+                                        bs_of[any][parts] = s;
+                                    }
                             }
                             if (best_t < 0 || t < best_t) {
                                 best_t = t;
@@ -477,13 +491,14 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
         }
     }
     if (rows_t >= 0) {
-        best_t = -1.0;
-        for (int parts = rows_parts; parts < 4; ++parts)
-            if (best_t_of[parts] >= 0 && (best_t < 0 || best_t_of[parts] < best_t)) {
-                best_t = best_t_of[parts];
-                best = best_of[parts];
-                bs = bs_of[parts];
-            }
+        double least = -1.0;
+        for (int any = rows_fit ? 0 : 1; any < 2 && least < 0; ++any)
+            for (int parts = rows_parts; parts < 4; ++parts)
+                if (best_t_of[any][parts] >= 0 && (least < 0 || best_t_of[any][parts] < least)) {
+                    least = best_t = best_t_of[any][parts];
+                    best = best_of[any][parts];
+                    bs = bs_of[any][parts];
+                }
     }
     if (cheapest_by_rows) *cheapest_by_rows = rows_t;
     if (best_t < 0 && too_many_positions) return SC_EUNSUPPORTED;

@@ -59,3 +59,23 @@ def test_binary16_layers_take_the_kernel_that_was_measured_faster():
     layer = B.SparseConv(*_masked(512, 512, 0.05), dtype="f16")
     assert layer.get_kernel(256, 2, 2, 1, 1) == "matrix"
     layer.close()
+
+
+# Layers whose fastest launch by estimate deals the channels over fewer parts than before (4, 2, 2 and 1), or over two, with 40 MB of
+# partial sums, where the whole tables were less than the static scratch.  N, C, K, taps, H = W, stride, density, parts at least
+CHOICES = [(241, 136, 16, 5, 6, 1, 0.3, 8), (15, 62, 59, 3, 4, 1, 0.2, 4), (4, 44, 19, 5, 108, 1, 0.2, 4), (2, 274, 403, 1, 31, 1, 0.125, 2),
+           (14, 487, 192, 3, 40, 1, 0.01, 1)]
+
+
+@pytest.mark.parametrize("N,C,K,R,H,stride,density,parts", CHOICES)
+def test_the_launch_keeps_its_parts_and_fits_the_static_scratch(N, C, K, R, H, stride, density, parts):
+    """A sum dealt over parts is the more exact one, and what sparse_conv_forward_static took it still takes."""
+    rng = np.random.default_rng(23)
+    w = rng.standard_normal((K, C, R, R), dtype=np.float32)
+    layer = B.SparseConv(w, (rng.random(w.shape, dtype=np.float32) < density).astype(np.uint8))
+    plan = layer.get_launch(N, H, H, stride, R // 2)
+    assert layer.check_plan(N, H, H, stride, R // 2) == 0
+    assert plan["csplit"] >= parts
+    sums = plan["grid"] * plan["threads"] * plan["KW"] * plan["LP"] * plan["V"] * 4 if plan["csplit"] > 1 else 0
+    assert plan["entries"] * plan["entry_bytes"] + sums <= 16 << 20
+    layer.close()
