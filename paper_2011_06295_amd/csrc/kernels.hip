@@ -26,6 +26,9 @@
 // next chunk are issued into registers during the arithmetic of the current
 // one and written to the other buffer after it (one barrier per chunk).
 //
+// fp32 wavefronts with four rows or more have one stream of weights for all their rows, whose multiply-adds reach the
+// accumulators through the VGPR index ("indexed", below).
+//
 // Second kind of tile (REAL = true): lanes are output elements, G image groups
 // interleaved element by element, so small maps spend no lanes on padding; the
 // staging units of a thread then come from a per-plan table.  Further down:

@@ -983,7 +983,7 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
 #pragma unroll
         for (int r = 0; r < 32 * kRuns / 64; ++r) v[r] = lds_get<Run>(from + (unsigned)(r * (64 / kRuns) * kPitch));
 #pragma unroll
-        for (int r = 0; r < 32 * kRuns / 64; ++r) asm volatile("" : "+v"(v[r]));                 // (not each in its branch, where it would be waited for)
+        for (int r = 0; r < 32 * kRuns / 64; ++r) asm volatile("" : "+v"(v[r]));       // (not read in the branches, one wait each)
         const int u = fdiv(o, la.fd_EF), k = kfirst + mk * 32 + row;
         Run* to = reinterpret_cast<Run*>(static_cast<T*>(la.y) + ((size_t)u * la.K + k) * la.EF + (o - u * la.EF));
         const int rows_left = o < la.nout ? la.K - k : 0;

@@ -462,8 +462,10 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
                                 const int parts = J == 1 ? 0 : J == 2 ? 1 : J == 4 ? 2 : 3;
                                 const double rows = estimate(s, c);
                                 // what sparse_conv_forward_static copies: entries, without and with padding, descriptors, patterns, sums
-                                const double sums = J > 1 ? (double)cdiv(s.npos, (long long)kWave * wp * LP) * kblocks * (J * (kw * LP * V) * 64.0 * wp * wk + 1) * 4.0 : 0.0;
-                                const double tables = units + sums + 4.0 * kblocks * nch * wk * (kw + 1.0) + 4096.0, scratch = (double)kStaticScratchBytes;
+                                const double pairs = (double)cdiv(s.npos, (long long)kWave * wp * LP) * kblocks;
+                                const double sums = J > 1 ? pairs * (J * (kw * LP * V) * 64.0 * wp * wk + 1) * 4.0 : 0.0;
+                                const double tables = units + sums + 4.0 * kblocks * nch * wk * (kw + 1.0) + 4096.0;
+                                const double scratch = (double)kStaticScratchBytes;
                                 const bool fits = tables + 8.0 * K * nch * (s.row_nnz * Cc / C + 3.0) <= scratch;
                                 if (rows >= 0 && (rows_t < 0 || rows < rows_t)) {
                                     rows_t = rows;
