@@ -273,7 +273,7 @@ int sparse_conv_set_epilogue(sparse_conv_t h, const float* bias, unsigned flags)
  * host against the CSR: every stored weight appears exactly once, with the LDS
  * offset of its tap (section 7's pre-computed input offsets) inside the staged
  * tile, every output channel has one accumulator slot, the tables have the sizes
- * the kernel walks, and the launch fits the hardware; and, with nothing pinned, every way the matrix kernel could share the
+ * the kernel walks, the launch fits the hardware and no output is stored outside the tensor; and, with nothing pinned, every way the matrix kernel could share the
  * geometry out, and its weight table where it is taken.  *failed_check receives 0,
  * or the number of the first check that failed.  Needs no GPU.  Returns SC_OK
  * when the check ran (whatever it found), else as sparse_conv_get_launch. */

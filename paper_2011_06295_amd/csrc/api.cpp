@@ -231,12 +231,7 @@ void fill_args(const sparse_conv_s* h, const Plan* p, const void* input, void* o
     a.pool = p->pool;
     a.pool_rows = std::max(1, std::min(p->KW, p->lds_bytes / std::max(1, p->threads * p->V * 4)));
     a.nt_store = p->store == 2 ? 1 : 0;
-    {
-        // image groups that a tile's outputs belong to, at most (lattice rows of its positions, or super-groups of its outputs)
-        const long long EF = (long long)p->E * p->F, rows = (p->span + p->Wp - 2) / p->Wp + 1;
-        const long long groups = p->G ? ((p->PT - 1) / EF + 2) * p->G : (rows - 1) / p->Hs + 2;
-        a.out_32 = groups * p->V * h->K * EF * elem_bytes(h) < (1ll << 31) ? 1 : 0;
-    }
+    a.out_32 = tile_out_groups(*p) * p->V * h->K * p->E * p->F * elem_bytes(h) < (1ll << 31) ? 1 : 0;
     a.N = N; a.C = h->C; a.H = H; a.W = W; a.K = h->K; a.E = p->E; a.F = p->F;
     a.stride = stride; a.pad = pad;
     a.WP = p->WP; a.WK = p->WK; a.Cc = p->Cc;
@@ -880,7 +875,7 @@ int sparse_conv_check_plan(sparse_conv_t h, int N, int H, int W, int stride, int
         sc::Plan* p = nullptr;
         int rc = sc::get_plan(h, sc::Geometry{N, H, W, stride, pad}, &p);
         if (rc != SC_OK) return rc;
-        int bad = sc::check_plan(h->csr, h->C, h->R, h->S, h->dtype == SC_F16 ? 2 : 4, *p);
+        int bad = sc::check_plan(h->csr, N, h->C, h->R, h->S, h->dtype == SC_F16 ? 2 : 4, *p);
         const sc::Geometry g{N, H, W, stride, pad};
         const sc::Route* route = nullptr;
         if (!bad && N > 0 && sc::automatic(h->over) && sc::get_route(h, g, &route) == SC_OK) {

@@ -189,10 +189,25 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
                const Launch& over, Plan& plan, std::vector<std::pair<double, Launch>>* ranked = nullptr,
                std::pair<double, Launch>* cheapest = nullptr, double* cheapest_by_rows = nullptr);
 
-// Checks a built plan against its CSR on the host (every stored weight exactly once, with its
+// Image groups that a tile's outputs belong to, at most.
+long long tile_out_groups(const Plan& p);
+
+// The tile kernel's store through a descriptor that begins with the tile's first image and ends with the output, at most 2^31 bytes
+// on: an output's place behind it is the lane's offset, which ranges over images and pixels, and a scalar one, its row's.  The compiler
+// leaves it open whether the scalar one takes part in the range check, so the lane's alone is out of range where there is no output
+// (of the lane, or no such image), and the scalar one is always less than an image, which the range holds: dropped or
+// stored is then the same whether it is left out, added, or taken from the range.
+constexpr unsigned kNoOutput = 0x80000000u;
+constexpr unsigned out_lane(bool output, int image, int images, unsigned image_bytes, unsigned pixel_bytes)
+{
+    return output && image < images ? (unsigned)image * image_bytes + pixel_bytes : kNoOutput;
+}
+constexpr unsigned out_scalar(int k, unsigned plane_bytes) { return (unsigned)k * plane_bytes; }
+
+// Checks a built plan of N images against its CSR on the host (every stored weight exactly once, with its
 // tap's LDS offset, inside the tile; every output channel in one slot; table sizes; launch
-// limits).  Returns 0, or the number of the first failed check.
-int check_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Plan& plan);
+// limits; where outputs are stored).  Returns 0, or the number of the first failed check.
+int check_plan(const Csr& csr, int N, int C, int R, int S, int elem_bytes, const Plan& plan);
 
 // ---------------------------------------------------------------- kernels
 

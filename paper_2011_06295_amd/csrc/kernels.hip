@@ -1037,14 +1037,17 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
             valid = g < la.ngroups && oi * la.stride == yy && oj * la.stride == X && oi < la.E && oj < la.F;
         }
         if (la.out_32) {
-            // Through a descriptor that begins with the tile's first image group and ends with the output: a lane's offset is worked
-            // out once, a row's and an image's are scalar, and lanes without an output and images past the batch are out of range.
+            // Through a descriptor that begins with the tile's first image group and ends with the output: a lane's offsets, one an
+            // image, are worked out once, a row's is scalar, and lanes without an output and images past the batch are out of range (out_lane).
             // (With an address, a test and a branch for each store the 64 stores of a lane took 13 of 50 us on the 14 x 14 layer at 99 %.)
             const unsigned image = (unsigned)la.K * (unsigned)plane * (unsigned)sizeof(T);
             const size_t first = (size_t)g_first * V * image, total = (size_t)la.N * image, left = total > first ? total - first : 0;
             const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>(y) + first, 0,
                                                                                  left > 0x80000000ull ? 0x80000000u : (unsigned)left, 0x00020000);
-            const unsigned off = valid ? (unsigned)((g - g_first) * V) * image + (unsigned)(oi * la.F + oj) * (unsigned)sizeof(T) : 0x80000000u;
+            const unsigned plane_bytes = (unsigned)plane * (unsigned)sizeof(T), pixel = (unsigned)(oi * la.F + oj) * (unsigned)sizeof(T);
+            unsigned at[V];
+#pragma unroll
+            for (int v = 0; v < V; ++v) at[v] = out_lane(valid, (g - g_first) * V + v, la.N - g_first * V, image, pixel);
             int k[KW];                  // all rows' channels and biases first: each row would wait for its own
             float bias[KW];
 #pragma unroll
@@ -1058,7 +1061,7 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
 #pragma unroll
             for (int kk = 0; kk < KW; ++kk) {
                 if (k[kk] < 0) continue;
-                const unsigned row = (unsigned)k[kk] * (unsigned)plane * (unsigned)sizeof(T);
+                const unsigned row = out_scalar(k[kk], plane_bytes);
                 float r[V];
 #pragma unroll
                 for (int v = 0; v < V; ++v) r[v] = acc[kk][p][v] + bias[kk];    // section 3: bias, then activation
@@ -1068,10 +1071,10 @@ __global__ __launch_bounds__(1024) void tile_kernel(const KernelArgs a)
                 }
                 if (la.nt_store) {
 #pragma unroll
-                    for (int v = 0; v < V; ++v) store_elem<T, 2>(out, (T)r[v], off, row + (unsigned)v * image);
+                    for (int v = 0; v < V; ++v) store_elem<T, 2>(out, (T)r[v], at[v], row);
                 } else {
 #pragma unroll
-                    for (int v = 0; v < V; ++v) store_elem<T, 0>(out, (T)r[v], off, row + (unsigned)v * image);
+                    for (int v = 0; v < V; ++v) store_elem<T, 0>(out, (T)r[v], at[v], row);
                 }
             }
             continue;

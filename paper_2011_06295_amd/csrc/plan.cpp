@@ -814,9 +814,49 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
     return SC_OK;
 }
 
+// (Lattice rows of its positions, or super-groups of its outputs.)
+long long tile_out_groups(const Plan& p)
+{
+    const long long EF = (long long)p.E * p.F, rows = (p.span + p.Wp - 2) / p.Wp + 1;
+    return p.G ? ((p.PT - 1) / EF + 2) * p.G : (rows - 1) / p.Hs + 2;
+}
+
+namespace {
+
+// Whether tiles' stores reach their outputs and nothing else, whichever way the range check takes the scalar offset.
+bool stores_in_range(const Plan& p, int N, int K, int elem_bytes)
+{
+    const long long EF = (long long)p.E * p.F, plane = EF * elem_bytes, image = plane * K, limit = 1ll << 31;
+    const long long most = tile_out_groups(p);
+    for (long long t = 0; t < p.ntiles; ++t) {
+        const long long a = t * p.span, b = std::min<long long>(a + p.span, p.npos) - 1;
+        const long long first = p.G ? a / p.G / EF * p.G : a / p.Wp / p.Hs, last = p.G ? b / p.G / EF * p.G + p.G - 1 : b / p.Wp / p.Hs;
+        if (last - first + 1 > most) return false;
+        if (most * p.V * image >= limit) continue;       // through addresses
+        const long long images = N - first * p.V, records = std::min(images * image, limit);
+        if (images < 1) return false;
+        for (long long i = std::max(0ll, images - 1); i < most * p.V; ++i)
+            for (int k = 0; k < K; k += std::max(1, K - 1))
+                for (long long pix = 0; pix < EF; pix += std::max(1ll, EF - 1))
+                    for (int output = 0; output < 2; ++output) {
+                        const uint32_t lane = out_lane(output != 0, (int)i, (int)images, (unsigned)image, (unsigned)(pix * elem_bytes));
+                        const uint32_t scalar = out_scalar(k, (unsigned)plane);
+                        const bool there = output && i < images;
+                        const bool kept[] = {lane < records, (long long)lane + scalar < records, (uint32_t)(lane + scalar) < records,
+                                             lane < (uint32_t)(records - scalar)};
+                        for (bool is : kept)
+                            if (is != there) return false;
+                        if (there && (long long)lane + scalar != i * image + k * plane + pix * elem_bytes) return false;
+                    }
+    }
+    return true;
+}
+
+}  // namespace
+
 // Host-side consistency check of a built plan against the CSR it was made from.
 // 0 = consistent; otherwise the number of the first check that failed.
-int check_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Plan& p)
+int check_plan(const Csr& csr, int N, int C, int R, int S, int elem_bytes, const Plan& p)
 {
     const int K = csr.K, RS = R * S;
     const int ub = p.V * elem_bytes;
@@ -961,6 +1001,7 @@ int check_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Plan& 
         }
     }
     if (real != csr.colidx.size()) return 7;                              // 7: every stored weight exactly once
+    if (N > 0 && !p.pool && !stores_in_range(p, N, K, elem_bytes)) return 10;   // 10: outputs are stored in their places, and nothing else is
     return 0;
 }
 

@@ -10,7 +10,7 @@ import pytest
 
 import oracle
 from paper_2011_06295_amd import binding as B
-from helpers import rand_layer
+from helpers import PARTIAL_GROUPS, rand_layer
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -233,6 +233,20 @@ def test_sizes_beyond_the_kernels_index_range_are_refused():
 def _plan_ok(layer, N, H, W, st, p, what):
     bad = layer.check_plan(N, H, W, st, p)
     assert bad == 0, f"{what}: plan check {bad} failed, launch {layer.get_launch(N, H, W, st, p)}"
+
+
+@pytest.mark.parametrize("case", PARTIAL_GROUPS, ids=lambda c: "x".join(map(str, c)))
+def test_stores_of_a_group_that_is_not_full_stay_in_the_output(case):
+    """An image past the batch is out of the store's range by the lane's own offset: the compiler does not say that a buffer store's
+    scalar offset takes part in the range check, and a check against the range less that offset would wrap round where it is larger."""
+    dtype, N, H, *launch = case
+    rng = np.random.default_rng(62)
+    w, m, _ = rand_layer(rng, 1, 5, 37, 3, 3, 1, 1)
+    layer = B.SparseConv(w, m, dtype=dtype)
+    layer.set_launch(launch)
+    assert N % launch[0] and layer.get_launch(N, H, H, 1, 1)["V"] == launch[0]
+    _plan_ok(layer, N, H, H, 1, 1, f"{case}")
+    layer.close()
 
 
 def test_plans_hold_every_stored_weight_once_random_shapes_and_launches():

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import oracle
-from helpers import TOL, assert_close, rand_layer
+from helpers import PARTIAL_GROUPS, TOL, assert_close, rand_layer
 
 pytestmark = pytest.mark.gpu
 
@@ -570,3 +570,27 @@ def test_rows_of_a_wavefront_in_one_stream(rows, launch):
     assert layer.check_plan(N, H, H, 1, 1) == 0
     layer.close()
     check(w, m, x, 1, 1, "f32", launch=launch, what=f"{rows} {launch}")
+
+
+@pytest.mark.parametrize("case", PARTIAL_GROUPS, ids=lambda c: "x".join(map(str, c)))
+def test_nothing_is_stored_beside_the_output(case):
+    """Room before and after the output, more than the images that the last group lacks, keeps what it held."""
+    from paper_2011_06295_amd import binding as B
+    torch = _torch()
+    dtype, N, H, *launch = case
+    rng = np.random.default_rng(63)
+    K = 37
+    w, m, x = rand_layer(rng, N, 5, K, 3, 3, H, H)
+    bias = rng.standard_normal(K).astype(np.float32)
+    layer = B.SparseConv(w, m, dtype=dtype)
+    layer.set_launch(launch)
+    layer.set_epilogue(bias)
+    assert layer.check_plan(N, H, H, 1, 1) == 0
+    xt = torch.from_numpy(x).cuda().to(torch.float16 if dtype == "f16" else torch.float32)
+    size = torch.Size((N, K, H, H))
+    beside = 8 * K * H * H
+    room = torch.full((size.numel() + 2 * beside,), float("nan"), dtype=xt.dtype, device="cuda")
+    y = layer.forward(xt, 1, 1, out=room[beside:beside + size.numel()].view(size))
+    assert torch.isnan(room[:beside]).all() and torch.isnan(room[beside + size.numel():]).all()
+    assert_close(y.float().cpu().numpy(), oracle_ref(w, m, x, 1, 1, dtype) + bias[None, :, None, None], TOL[dtype], f"{case}")
+    layer.close()
