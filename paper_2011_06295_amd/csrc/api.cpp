@@ -65,13 +65,13 @@ int find_tile(sparse_conv_s* h, const Geometry& g, Route** out)
         within.pool = (h->epilogue & SC_EPILOGUE_MAXPOOL2) ? 1 : 0;
         Plan none;
         std::pair<double, Launch> tile;
-        double by_rows = 0.0;
+        std::pair<double, int> by_rows{0.0, 1};
         const int rc = build_plan(h->csr, h->C, h->R, h->S, elem_bytes(h), g, within, none, nullptr, &tile, h->dtype == SC_F32 ? &by_rows : nullptr);
         if (rc != SC_OK) return rc;
         Route r;
         r.tile = tile.second;
         r.tile_clocks = tile.first;
-        r.tile_clocks_by_rows = by_rows;
+        r.by_rows = by_rows;
         it = h->routes.emplace(g, r).first;
     }
     *out = &it->second;
@@ -94,13 +94,15 @@ int get_route(sparse_conv_s* h, const Geometry& g, const Route** out)
     if (h->matrix_holds < 0)
         h->matrix_holds = matrix_bytes_at_least(h->K, h->C, h->R, h->S, !half) <= kStaticScratchBytes && matrix_holds(h->csr, !half) ? 1 : 0;
     double us = 0.0;
-    if (h->matrix_holds && choose_matrix(h->csr, h->C, h->R, h->S, elem_bytes(h), g, r->tile.pool != 0, r->tile.csplit, r->plan, &us)) {
+    // (fp32: beside the tile launch that the measurements of both kernels were compared with)
+    const double tile_clocks = half ? r->tile_clocks : r->by_rows.first;
+    const int tile_parts = half ? r->tile.csplit : r->by_rows.second;
+    if (h->matrix_holds && choose_matrix(h->csr, h->C, h->R, h->S, elem_bytes(h), g, r->tile.pool != 0, tile_parts, r->plan, &us)) {
         // stores are not hidden behind short rows: the estimate for kernels by rows leaves them out
         const double terms = (double)h->csr.colidx.size() / h->K;
         const double mbytes = (double)g.N * ((double)h->C * g.H * g.W + (double)h->K * r->plan.E * r->plan.F) * elem_bytes(h) * 1e-6;
-        const double stores = terms < 32.0 ? 0.2 * mbytes : 0.0;
-        const double tile_us = r->tile_clocks / 2400.0 + (half ? stores : 0.0);
-        if (matrix_pays(us, tile_us, r->tile_clocks_by_rows / 2400.0 + stores, !half)) {
+        const double tile_us = tile_clocks / 2400.0 + (terms < 32.0 ? 0.2 * mbytes : 0.0);
+        if (matrix_pays(us, tile_us, !half)) {
             if (!h->matrix) {
                 std::unique_ptr<MatrixWeights> m(new MatrixWeights());
                 pack_matrix_weights(h->csr, h->C, h->R, h->S, !half, *m);

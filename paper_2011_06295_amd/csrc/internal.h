@@ -183,11 +183,11 @@ struct Plan {
 // Chooses the configuration (honouring overrides) and builds the host tables.
 // With `ranked` it only lists the candidate configurations (estimated clocks,
 // full override), cheapest first, and builds nothing.  Returns an SC_* status.
-// With `cheapest` it stops after the search and reports the cheapest configuration and its estimate; cheapest_by_rows: the
-// cheapest by the estimate for kernels by rows.
+// With `cheapest` it stops after the search and reports the cheapest configuration and its estimate; cheapest_by_rows: estimate and
+// channel parts of the cheapest by the estimate for kernels by rows.
 int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geometry& g,
                const Launch& over, Plan& plan, std::vector<std::pair<double, Launch>>* ranked = nullptr,
-               std::pair<double, Launch>* cheapest = nullptr, double* cheapest_by_rows = nullptr);
+               std::pair<double, Launch>* cheapest = nullptr, std::pair<double, int>* cheapest_by_rows = nullptr);
 
 // Image groups that a tile's outputs belong to, at most.
 long long tile_out_groups(const Plan& p);
@@ -327,8 +327,8 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
 // kernel's plan (they decide how exact its fp32 sums are, and the matrix kernel's must not be less so).
 bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, int tile_parts,
                    MatrixPlan& p, double* us);
-// Whether that is worth taking beside the tile kernel's estimate (fp32: and that for kernels by rows).
-bool matrix_pays(double us, double tile_us, double tile_us_by_rows, bool split);
+// Whether that is worth taking beside the tile kernel's estimate (fp32: the one for kernels by rows).
+bool matrix_pays(double us, double tile_us, bool split);
 // Host check of the weight table against the CSR; 0, or the number of the first check that failed.
 int check_matrix(const Csr& csr, int C, int R, int S, const MatrixWeights& m);
 // Host check of every split that plan_matrix accepts for the geometry, as the kernel walks it: each tap of each output in the
@@ -388,7 +388,7 @@ int launch_copy_probe(void* dst, const void* src, long long bytes, void* stream)
 struct Route {
     Launch tile;
     double tile_clocks = 0.0;      // its estimate
-    double tile_clocks_by_rows = 0.0;   // fp32: the cheapest by the estimate for kernels by rows
+    std::pair<double, int> by_rows{0.0, 1};   // fp32: estimate and channel parts of the cheapest by the estimate for kernels by rows
     bool decided = false;
     bool matrix = false;
     MatrixPlan plan{};             // matrix: the kernel's tiles

@@ -477,15 +477,13 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
 // both kernels have alike: without, 16 are slower, by up to 20 %.  Below 0.95 of the tile kernel's estimate instead: six, by up
 // to 14 %, the mean loses 2.3 %, and VGG-16's last layer takes 26 us by the tile kernel for 18.7.  Of 95 others whose kernel
 // or split this and the one estimate for all sizes changed, the mean is 13 % faster, and three of 8 to 9 us are 8 to 21 % slower.)
-// fp32: taken below the tile kernel's estimate, or below 0.85 of what the estimate for kernels by rows makes of it.  Of 49 layers, drawn over
-// the range of the cases, whose estimates lie between 0.80 and 1.12 of each other, timed by both kernels: of 26 below 1.0 one is 6 % slower
-// by the matrix kernel, one 1 %, the others gain 1 to 67 %; of 23 above, nine gain and the mean loses 6 %.  The second bound is for
-// launches of some 10 us of dense rows, where the first estimate is 10 to 20 % low: of twelve that it adds eight gain 17 to 60 % and
-// four, of 7 to 11 us, lose 3 to 9 %.
-bool matrix_pays(double us, double tile_us, double tile_us_by_rows, bool split)
-{
-    return split ? us < std::max(tile_us, 0.85 * tile_us_by_rows) : us < tile_us - 0.7;
-}
+// fp32: taken below 0.85 of the cheapest tile launch by the estimate for kernels by rows.  Of 71 layers, timed over blocks of a tenth of a
+// second, which heat the chip as a pass does, all below gain 6 % or more; between 0.85 and 0.9 lie 256 -> 256, 14 x 14, batch 256 at 90 %
+// (169 us; tile kernel 167 then, 153 since its rows share a stream) and its like.  (Of 36 others with ragged rows, all below, two are slower, by 1 and 8 %; the mean takes
+// 0.53 of the tile kernel's time.)  Not below all of the estimate that tile launches are chosen by (estimate_f32): of 113 drawn layers that
+// it adds, 25 are 3 to 31 % slower by the matrix kernel, and its products hold 21 bits where the tile kernel's hold 24: with inputs that
+// went through a ReLU, whose sums cancel less, 13 of 48 are less exact by it, up to 1.15 of the tile kernel's error against 64 bits.
+bool matrix_pays(double us, double tile_us, bool split) { return us < (split ? 0.85 * tile_us : tile_us - 0.7); }
 
 void fill_matrix_args(const MatrixWeights& m, const MatrixPlan& p, int K, int C, int R, int S, const Geometry& g, MatrixArgs& a)
 {

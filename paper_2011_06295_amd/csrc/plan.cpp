@@ -246,7 +246,7 @@ FastDiv make_fastdiv(int d)
 
 int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geometry& g,
                const Launch& over, Plan& p, std::vector<std::pair<double, Launch>>* ranked, std::pair<double, Launch>* cheapest,
-               double* cheapest_by_rows)
+               std::pair<double, int>* cheapest_by_rows)
 {
     const int K = csr.K;
     const int st = g.stride, pad = g.pad;
@@ -502,7 +502,7 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
                     bs = bs_of[any][parts];
                 }
     }
-    if (cheapest_by_rows) *cheapest_by_rows = rows_t;
+    if (cheapest_by_rows) *cheapest_by_rows = {rows_t, 1 << rows_parts};
     if (best_t < 0 && too_many_positions) return SC_EUNSUPPORTED;
     if (best_t < 0) return SC_EUNSUPPORTED;
     if (ranked) {   // the caller only wants the candidates, cheapest estimate first, each once
