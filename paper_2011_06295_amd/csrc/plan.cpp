@@ -43,6 +43,7 @@ struct Shape {
     int G;               // 0: lanes are lattice positions; else image groups interleaved per element (lanes are outputs)
     long long npos;      // lanes of the whole batch: lattice positions, or outputs * G
     double row_nnz;      // mean stored weights per output channel
+    bool coded;          // the weights are binary16 centroids
 };
 
 struct Cand {
@@ -51,6 +52,15 @@ struct Cand {
     int J;
     int ZE;   // elements of the zero region behind the tile buffers
 };
+
+// Weights that are binary16 values (binary16 layers; cluster-quantised layers, whose centroids are binary16)
+// go to the device as one word per entry, with the LDS offset in 16 bits: in units of 4 bytes (2 for
+// 2-byte elements, whose tile must then stay below 128 KB; otherwise the ordinary 8-byte entries are kept).
+int compact_shift(int ub) { return ub >= 4 ? 2 : 1; }
+bool tile_compact(bool coded, int elem_bytes, int ub, int nbuf, int Cc, int CS)
+{
+    return (coded || elem_bytes == 2) && ((long long)nbuf * ((long long)Cc * CS + 1) * ub >> compact_shift(ub)) < 65536;
+}
 
 // Output-lane tiles: the most lattice rows between the first and the last of PT consecutive outputs
 // (outputs are numbered super-group, row, column; super-group u starts at lattice row u * Hs).
@@ -97,7 +107,7 @@ void rows_per_wavefront(int nrows, int WP, int WK, int KW, std::vector<int>& roo
 
 // Rough time of one fp32 launch in CU clocks.  Structure and constants are fitted to the measured times of 10000 launch
 // configurations (up to 64 that differ, of each of 150 layers: 3x3 and 5x5, 1x1, 1-D, stride 2, batches of 2 to 256, 50 to 99 %
-// sparse): 11 % rms of the logarithm; the cheapest by estimate takes 5 % longer than the fastest measured in the mean, and 12 % or less
+// sparse, none of them cluster-quantised): 11 % rms of the logarithm; the cheapest by estimate takes 5 % longer than the fastest measured in the mean, and 12 % or less
 // in nine of ten layers.  (By the estimate below, fitted before rows shared a stream: 9 %, and 23 %.)
 //  * A weight costs its SIMD the multiply-adds of its positions and images, some 4 clocks each (16 where rows share a stream), and 8
 //    for its address and read; with two positions a lane and elements of less than four images a quarter more, with one or two rows a
@@ -113,7 +123,7 @@ void rows_per_wavefront(int nrows, int WP, int WK, int KW, std::vector<int>& roo
 double estimate_f32(const Shape& s, const Cand& c)
 {
     const int J = std::max(1, c.J), waves = c.WP * c.WK, acc = c.KW * c.LP * c.V;
-    const bool indexed = tile_indexed(s.elem_bytes, c.V, c.KW, c.LP, false);
+    const bool indexed = tile_indexed(s.elem_bytes, c.V, c.KW, c.LP, tile_compact(s.coded, s.elem_bytes, s.ub, c.nbuf, c.Cc, c.CS));
     const double regs = std::min(128.0, 56.0 + acc + 4.0 * c.LP * c.V);
     const int per_simd = indexed ? (c.KW == 16 || s.G == 0 ? 4 : 5) : std::min(8, 512 / (8 * (int)std::ceil(regs / 8.0)));
     const int conc_max = std::min(kMaxLds / c.lds, 4 * per_simd / waves);
@@ -319,6 +329,7 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
         s.V = V;
         s.G = G;
         s.elem_bytes = elem_bytes;
+        s.coded = csr.coded;
         s.ub = V * elem_bytes;
         s.H = g.H; s.W = g.W;
         // pitch and group height: the padding below/right of an image is shared with the
@@ -589,11 +600,8 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
     // ---- tables
     const int RS = R * S;
     const int nchunks = p.nchunks;
-    // Weights that are binary16 values (binary16 layers; cluster-quantised layers, whose centroids are binary16)
-    // go to the device as one word per entry, with the LDS offset in 16 bits: in units of 4 bytes (2 for
-    // 2-byte elements, whose tile must then stay below 128 KB; otherwise the ordinary 8-byte entries are kept).
-    p.off_shift = s.ub >= 4 ? 2 : 1;
-    p.compact = (csr.coded || elem_bytes == 2) && ((long long)p.nbuf * ((long long)p.Cc * p.CS + 1) * s.ub >> p.off_shift) < 65536;
+    p.off_shift = compact_shift(s.ub);
+    p.compact = tile_compact(csr.coded, elem_bytes, s.ub, p.nbuf, p.Cc, p.CS);
     p.indexed = tile_indexed(elem_bytes, p.V, p.KW, p.LP, p.compact);
     // Output channel of every accumulator slot (kb, wk, kk).  The wavefronts of a workgroup meet
     // at a barrier after every channel chunk, so what should be equal among them is the number

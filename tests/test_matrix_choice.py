@@ -94,3 +94,28 @@ def test_the_launch_keeps_its_parts_and_fits_the_static_scratch(N, C, K, R, H, s
     sums = plan["grid"] * plan["threads"] * plan["KW"] * plan["LP"] * plan["V"] * 4 if plan["csplit"] > 1 else 0
     assert plan["entries"] * plan["entry_bytes"] + sums <= 16 << 20
     layer.close()
+
+
+def _choice(N, C, K, R, H, stride, density, coded=False):
+    rng = np.random.default_rng(25)
+    order = rng.random((K, C * R * R), dtype=np.float32)
+    kept = max(1, int(C * R * R * density))
+    m = (order <= np.partition(order, kept - 1, axis=1)[:, kept - 1:kept]).astype(np.uint8).reshape(K, C, R, R)
+    if coded:
+        layer = B.SparseConv.from_codebook(rng.integers(0, 16, m.shape, dtype=np.uint8), np.sort(rng.standard_normal(16)).astype(np.float32), m)
+    else:
+        layer = B.SparseConv(rng.standard_normal(m.shape, dtype=np.float32), m)
+    plan = layer.get_launch(N, H, H, stride, R // 2)
+    assert layer.get_kernel(N, H, H, stride, R // 2) == "tile" and layer.check_plan(N, H, H, stride, R // 2) == 0
+    layer.close()
+    return plan
+
+
+# N, C, K, taps, H = W, density
+@pytest.mark.parametrize("layer", [(158, 301, 45, 3, 71, 0.1), (58, 160, 17, 5, 105, 0.1), (5, 22, 449, 3, 74, 0.125)])
+def test_coded_layers_are_ranked_by_the_kernel_they_run(layer):
+    """Weights that are binary16 centroids have a stream a row, whatever the launch: 789 us by two positions a lane and 995 by 16 rows
+    a wavefront, 421 and 460, 48 and 56."""
+    N, C, K, R, H, density = layer
+    plan = _choice(N, C, K, R, H, 1, density, coded=True)
+    assert plan["entry_bytes"] == 4 and plan["LP"] == 2 and plan["KW"] <= 4
