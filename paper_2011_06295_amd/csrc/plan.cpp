@@ -105,10 +105,21 @@ void rows_per_wavefront(int nrows, int WP, int WK, int KW, std::vector<int>& roo
     }
 }
 
+// fp32 wavefronts that a SIMD holds, as the compiler reports it for the kernels that are chosen among: with one image an element scalar
+// registers bound them, else vector registers (gfx950 has 512 a lane, in eights).
+int resident_f32(int V, int LP, int KW)
+{
+    if (V == 1) return 7;
+    if (V == 2) return LP == 1 ? (KW <= 4 ? 7 : KW == 8 ? 6 : 5) : KW <= 4 ? 6 : 4;
+    return LP == 1 && KW <= 2 ? 5 : 4;
+}
+
 // Rough time of one fp32 launch in CU clocks.  Structure and constants are fitted to the measured times of 10000 launch
 // configurations (up to 64 that differ, of each of 150 layers: 3x3 and 5x5, 1x1, 1-D, stride 2, batches of 2 to 256, 50 to 99 %
-// sparse, none of them cluster-quantised): 11 % rms of the logarithm; the cheapest by estimate takes 5 % longer than the fastest measured in the mean, and 12 % or less
-// in nine of ten layers.  (By the estimate below, fitted before rows shared a stream: 9 %, and 23 %.)
+// sparse, none of them cluster-quantised); the room of a SIMD and the cost of two positions a lane to those of 7300 others, up to 14 that
+// one of the estimates ranks first, of each of 1200 layers drawn over the range of the cases (a quarter of them of one image, a third
+// cluster-quantised): 10 % rms of the logarithm, and the cheapest by estimate takes 3 % longer than the fastest measured in the mean.
+// (With the whole CU's room and without that cost 13 %, and 4 %; by the estimate below, fitted before rows shared a stream, 8 %.)
 //  * A weight costs its SIMD the multiply-adds of its positions and images, some 4 clocks each (16 where rows share a stream), and 8
 //    for its address and read; with two positions a lane and elements of less than four images a quarter more, with one or two rows a
 //    wavefront and several workgroups a CU half as much again.
@@ -116,17 +127,18 @@ void rows_per_wavefront(int nrows, int WP, int WK, int KW, std::vector<int>& roo
 //  * A lone wavefront cannot hide its own LDS and scalar-fetch latency: 45 to 48 clocks a weight.
 //  * A chunk costs 1430 clocks and 7 a wavefront; its staging a clock for 80 bytes (33 with four image groups or more an element, where
 //    its writes meet in the banks), half of which the arithmetic does not hide.
-//  * A workgroup costs 10000 clocks and 15 for each of its wavefronts' stores; as a part of the channels 1170, 1030 a part, and 28 for
-//    each of its wavefronts' sums, which the last part reads back.
-//  * Registers bound the wavefronts resident on a SIMD: 4 of the kernels with 16 rows or, with lattice lanes, 4 or 8, else 5.
+//  * A workgroup costs 10000 clocks, 1000 more with two positions a lane, and 15 for each of its wavefronts' stores; as a part of the
+//    channels 1170, 1030 a part, and 28 for each of its wavefronts' sums, which the last part reads back.
+//  * A workgroup's wavefronts go round the four SIMDs from the same one on, so with 13 of them a SIMD needs room for four of each
+//    resident workgroup, and with 5 for two.  (Counted by the whole CU's room instead, launches of 300 workgroups and more of 13 to 15
+//    wavefronts took 1.28 times the estimate, and the choice 28 us where another takes 20: one image, 44 -> 91, 5x5, 96x96, 90 %.)
 //  * Workgroups run in rounds of (CUs * resident workgroups); what does not multiply takes 1.1 to 1.2 times as long beside others.
 double estimate_f32(const Shape& s, const Cand& c)
 {
     const int J = std::max(1, c.J), waves = c.WP * c.WK, acc = c.KW * c.LP * c.V;
     const bool indexed = tile_indexed(s.elem_bytes, c.V, c.KW, c.LP, tile_compact(s.coded, s.elem_bytes, s.ub, c.nbuf, c.Cc, c.CS));
-    const double regs = std::min(128.0, 56.0 + acc + 4.0 * c.LP * c.V);
-    const int per_simd = indexed ? (c.KW == 16 || s.G == 0 ? 4 : 5) : std::min(8, 512 / (8 * (int)std::ceil(regs / 8.0)));
-    const int conc_max = std::min(kMaxLds / c.lds, 4 * per_simd / waves);
+    const int per_simd = resident_f32(c.V, c.LP, c.KW);
+    const int conc_max = std::min(kMaxLds / c.lds, waves < 4 ? 4 * per_simd / waves : per_simd / cdiv(waves, 4));
     if (conc_max < 1) return -1.0;
     const int nchunks = cdiv(cdiv(s.C, c.Cc), J);          // chunks a workgroup walks
     const double seg = s.row_nnz * c.Cc / s.C, rows = std::max(1.0, std::min((double)c.KW, (double)cdiv(s.K, c.kblocks) / c.WK));
@@ -142,7 +154,7 @@ double estimate_f32(const Shape& s, const Cand& c)
         const double stage = conc * bytes / 80.0 * (s.G >= 4 ? 2.41 : 1.0);
         const double beside = nchunks * (1432.0 + 7.2 * waves) + 1.153 * stage + 15.3 * waves * acc * conc;
         const double crowd = conc >= 3 ? 1.2 : conc >= 2 ? 1.11 : 1.0;
-        return std::max(multiply, stage) + (beside + stage / nchunks) * crowd + 10000.0 +
+        return std::max(multiply, stage) + (beside + stage / nchunks) * crowd + 10000.0 + (c.LP == 2 ? 1000.0 : 0.0) +
                (J > 1 ? 1173.0 + 1031.0 * J + 27.8 * waves * acc * conc : 0.0);
     };
     const long long wgs = (long long)cdiv(s.npos, (long long)kWave * c.WP * c.LP) * c.kblocks * J, slots = (long long)kCUs * conc_max;
