@@ -295,10 +295,12 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
     double best_t = -1.0;
     // fp32: the cheapest of each number of channel parts (1, 2, 4, 8), and the one that the estimate for kernels by rows would take.  A
     // sum dealt over parts is the more exact one, so no fewer parts are taken than that.
-    // Nor a launch whose tables and partial sums may be more than the static scratch, where those of that one are not.
+    // Nor another launch whose tables and partial sums may be more than the static scratch, where those of that one may be less.
     Cand best_of[2][4];
     Shape bs_of[2][4];
-    double best_t_of[2][4] = {{-1.0, -1.0, -1.0, -1.0}, {-1.0, -1.0, -1.0, -1.0}}, rows_t = -1.0;
+    double best_t_of[2][4] = {{-1.0, -1.0, -1.0, -1.0}, {-1.0, -1.0, -1.0, -1.0}}, rows_t = -1.0, rows_own = 0.0;
+    Cand rows_c{};
+    Shape rows_s{};
     int rows_parts = 0;
     bool rows_fit = false;
     bool too_many_positions = false;
@@ -484,16 +486,22 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
                             if (elem_bytes == 4 && !ranked) {
                                 const int parts = J == 1 ? 0 : J == 2 ? 1 : J == 4 ? 2 : 3;
                                 const double rows = estimate(s, c);
-                                // what sparse_conv_forward_static copies: entries, without and with padding, descriptors, patterns, sums
+                                // what sparse_conv_forward_static copies: entries, without and with the most padding, descriptors, patterns, sums
                                 const double pairs = (double)cdiv(s.npos, (long long)kWave * wp * LP) * kblocks;
                                 const double sums = J > 1 ? pairs * (J * (kw * LP * V) * 64.0 * wp * wk + 1) * 4.0 : 0.0;
-                                const double tables = units + sums + 4.0 * kblocks * nch * wk * (kw + 1.0) + 4096.0;
+                                const double least = sums + 4.0 * kblocks * nch * wk * (kw + 1.0), most = least + units + 4096.0;
+                                const bool compact = tile_compact(csr.coded, elem_bytes, s.ub, nbuf, Cc, (int)CS);
+                                const double entry = compact ? 4.0 : 8.0, stored = (double)csr.colidx.size();
+                                const double padded = stored + (kBatch - 1.0) * nch * (tile_indexed(elem_bytes, V, kw, LP, compact) ? (double)kblocks * wk : K);
                                 const double scratch = (double)kStaticScratchBytes;
-                                const bool fits = tables + 8.0 * K * nch * (s.row_nnz * Cc / C + 3.0) <= scratch;
+                                const bool fits = most + entry * padded <= scratch;
                                 if (rows >= 0 && (rows_t < 0 || rows < rows_t)) {
                                     rows_t = rows;
                                     rows_parts = parts;
-                                    rows_fit = tables + 4.0 * csr.colidx.size() <= scratch;
+                                    rows_fit = least + entry * stored <= scratch;
+                                    rows_own = t;
+                                    rows_c = c;
+                                    rows_s = s;
                                 }
                                 for (int any = fits ? 0 : 1; any < 2; ++any)
                                     if (best_t_of[any][parts] < 0 || t < best_t_of[any][parts]) {
@@ -516,14 +524,16 @@ int build_plan(const Csr& csr, int C, int R, int S, int elem_bytes, const Geomet
         }
     }
     if (rows_t >= 0) {
-        double least = -1.0;
-        for (int any = rows_fit ? 0 : 1; any < 2 && least < 0; ++any)
-            for (int parts = rows_parts; parts < 4; ++parts)
-                if (best_t_of[any][parts] >= 0 && (least < 0 || best_t_of[any][parts] < least)) {
-                    least = best_t = best_t_of[any][parts];
-                    best = best_of[any][parts];
-                    bs = bs_of[any][parts];
-                }
+        best_t = rows_own;      // it is one of them, whether it surely fits or not
+        best = rows_c;
+        bs = rows_s;
+        const int any = rows_fit ? 0 : 1;
+        for (int parts = rows_parts; parts < 4; ++parts)
+            if (best_t_of[any][parts] >= 0 && best_t_of[any][parts] < best_t) {
+                best_t = best_t_of[any][parts];
+                best = best_of[any][parts];
+                bs = bs_of[any][parts];
+            }
     }
     if (cheapest_by_rows) *cheapest_by_rows = {rows_t, 1 << rows_parts};
     if (best_t < 0 && too_many_positions) return SC_EUNSUPPORTED;
