@@ -594,3 +594,45 @@ def test_nothing_is_stored_beside_the_output(case):
     assert torch.isnan(room[:beside]).all() and torch.isnan(room[beside + size.numel():]).all()
     assert_close(y.float().cpu().numpy(), oracle_ref(w, m, x, 1, 1, dtype) + bias[None, :, None, None], TOL[dtype], f"{case}")
     layer.close()
+
+
+# dtype, N, H = W, K and the launch: V, WP, WK, KW, Cc, LDS, LP, channel blocks, store, lanes
+WIDE_STORES = [("f32", 1, 2048, 64, (1, 1, 2, 4, 2, 0, 1, 0, 1, 1)), ("f32", 5, 1024, 67, (4, 1, 2, 8, 2, 0, 1, 0, 1, 1)),
+               ("f32", 3, 1024, 130, (2, 1, 2, 4, 2, 0, 2, 0, 2, 1)), ("f32", 5, 64, 16389, (4, 1, 2, 4, 2, 0, 1, 0, 1, 2)),
+               ("f16", 9, 1024, 65, (8, 1, 2, 4, 2, 0, 1, 0, 2, 1))]
+
+
+@pytest.mark.parametrize("case", WIDE_STORES, ids=lambda c: "x".join(map(str, c[:4] + c[4])))
+def test_outputs_of_two_gigabytes_a_tile(case):
+    """Where the outputs of a tile's images span 2^31 bytes or more, each is stored through an address of its own: every output against
+    its taps, and nothing beside them, the last group not full."""
+    from paper_2011_06295_amd import binding as B
+    torch = _torch()
+    dtype, N, H, K, launch = case
+    want = torch.float16 if dtype == "f16" else torch.float32
+    assert 2 * launch[0] * K * H * H * (2 if dtype == "f16" else 4) >= 2 ** 31     # (a tile's positions lie in one group or two)
+    rng = np.random.default_rng(64)
+    w, m, _ = rand_layer(rng, 1, 2, K, 3, 3, 1, 1)
+    bias = rng.standard_normal(K).astype(np.float32)
+    layer = B.SparseConv(w, m, dtype=dtype)
+    layer.set_launch(launch)
+    layer.set_epilogue(bias, relu=True)
+    assert layer.check_plan(N, H, H, 1, 1) == 0
+    x = torch.randn((N, 2, H, H), generator=torch.Generator(device="cuda").manual_seed(64), device="cuda").to(want)
+    size, beside = torch.Size((N, K, H, H)), 8 * K * H
+    room = torch.full((size.numel() + 2 * beside,), float("nan"), dtype=want, device="cuda")
+    y = layer.forward(x, 1, 1, out=room[beside:beside + size.numel()].view(size))
+    assert torch.isnan(room[:beside]).all() and torch.isnan(room[beside + size.numel():]).all()
+    around = torch.nn.functional.pad(x.float(), (1, 1, 1, 1))
+    weights = torch.from_numpy(w * m).cuda().to(want).float()
+    # (18 taps at most, in fp32 in any order: 18 roundings of 2^-24 of their magnitudes' sum; binary16: half a unit of the result)
+    for k in range(K):
+        ref, magnitude = torch.zeros_like(x[:, 0], dtype=torch.float32), torch.zeros_like(x[:, 0], dtype=torch.float32)
+        for c, r, s in np.argwhere(m[k]):
+            term = around[:, c, r:r + H, s:s + H] * weights[k, c, r, s]
+            ref += term
+            magnitude += term.abs()
+        ref = torch.relu(ref + float(bias[k]))
+        bound = (magnitude + abs(float(bias[k]))) * (40 * 2.0 ** -24) + (ref * 2.0 ** -11 + 2.0 ** -25 if dtype == "f16" else 0.0)
+        assert ((y[:, k].float() - ref).abs() <= bound).all(), f"{case} channel {k}"
+    layer.close()
