@@ -300,6 +300,10 @@ int sparse_conv_get_matrix_plan(sparse_conv_t h, int N, int H, int W, int stride
  * it stages single pixels ([8] above).  Returns as sparse_conv_get_matrix_plan.  Needs no GPU. */
 int sparse_conv_get_matrix_runs(sparse_conv_t h, int N, int H, int W, int stride, int pad, int* in_flight);
 
+/* How it stores its output there: *bytes receives 16 or 8, the runs of one plane in which outputs leave where the output starts at a
+ * multiple of 16 bytes, 0 where each leaves by itself.  Returns as sparse_conv_get_matrix_plan.  Needs no GPU. */
+int sparse_conv_get_matrix_out_runs(sparse_conv_t h, int N, int H, int W, int stride, int pad, int* bytes);
+
 /* The tile kernel's launch configuration for a geometry (in force unless sparse_conv_get_kernel says 1): [0] V .. [4] Cc, [5] the LDS
  * budget in force, [6] workgroups launched, [7] LDS bytes
  * per workgroup, [8] threads per workgroup, [9] stored plan entries

@@ -28,7 +28,7 @@ EXPORTS = (
     "sparse_conv_create", "sparse_conv_output_shape", "sparse_conv_forward", "sparse_conv_forward_static",
     "sparse_conv_get_csr", "sparse_conv_set_launch", "sparse_conv_get_launch", "sparse_conv_set_epilogue", "sparse_conv_autotune",
     "sparse_conv_create_codebook", "sparse_conv_get_codebook", "sparse_conv_check_plan", "sparse_conv_rank_launches", "sparse_conv_get_kernel",
-    "sparse_conv_get_matrix_plan", "sparse_conv_get_matrix_runs",
+    "sparse_conv_get_matrix_plan", "sparse_conv_get_matrix_runs", "sparse_conv_get_matrix_out_runs",
     "sparse_conv_probe_lds_read", "sparse_conv_probe_copy",
     "sparse_conv_last_hip_error", "sparse_conv_strerror", "sparse_conv_destroy",
 )
@@ -68,6 +68,7 @@ def _load():
     lib.sparse_conv_get_kernel.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip]
     lib.sparse_conv_get_matrix_plan.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip]
     lib.sparse_conv_get_matrix_runs.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip]
+    lib.sparse_conv_get_matrix_out_runs.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip]
     lib.sparse_conv_rank_launches.argtypes = [vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, ip, ip]
     lib.sparse_conv_autotune.argtypes = [vp, vp, vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, vp, C.c_int,
                                          C.POINTER(C.c_float)]
@@ -234,6 +235,13 @@ def sparse_conv_get_matrix_plan(handle: int, N: int, H: int, W: int, stride: int
     return dict(zip(MATRIX_PLAN_KEYS, arr), runs=runs.value)
 
 
+def sparse_conv_get_matrix_out_runs(handle: int, N: int, H: int, W: int, stride: int, pad: int) -> int:
+    """Bytes of the runs that the matrix kernel stores its outputs in (16 or 8), 0 where it stores them one by one."""
+    n = C.c_int(0)
+    _check(_lib.sparse_conv_get_matrix_out_runs(handle, N, H, W, stride, pad, C.byref(n)), "sparse_conv_get_matrix_out_runs", handle)
+    return n.value
+
+
 def sparse_conv_check_plan(handle: int, N: int, H: int, W: int, stride: int, pad: int) -> int:
     """Host-side consistency check of the geometry's plan: 0, or the number of the first failed check."""
     bad = C.c_int(-1)
@@ -310,6 +318,9 @@ class SparseConv:
 
     def get_matrix_plan(self, N: int, H: int, W: int, stride: int = 1, pad: int = 0) -> dict:
         return sparse_conv_get_matrix_plan(self.handle, N, H, W, stride, pad)
+
+    def get_matrix_out_runs(self, N: int, H: int, W: int, stride: int = 1, pad: int = 0) -> int:
+        return sparse_conv_get_matrix_out_runs(self.handle, N, H, W, stride, pad)
 
     def check_plan(self, N: int, H: int, W: int, stride: int = 1, pad: int = 0) -> int:
         return sparse_conv_check_plan(self.handle, N, H, W, stride, pad)

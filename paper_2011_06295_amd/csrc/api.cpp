@@ -869,6 +869,17 @@ int sparse_conv_get_matrix_runs(sparse_conv_t h, int N, int H, int W, int stride
     return SC_OK;
 }
 
+int sparse_conv_get_matrix_out_runs(sparse_conv_t h, int N, int H, int W, int stride, int pad, int* bytes)
+{
+    if (!bytes) return SC_EINVAL;
+    int kernel = 0;
+    const int rc = sparse_conv_get_kernel(h, N, H, W, stride, pad, &kernel);
+    if (rc != SC_OK) return rc;
+    if (!kernel) return SC_EUNSUPPORTED;
+    *bytes = h->routes.at(sc::Geometry{N, H, W, stride, pad}).plan.out_runs;
+    return SC_OK;
+}
+
 int sparse_conv_check_plan(sparse_conv_t h, int N, int H, int W, int stride, int pad, int* failed_check)
 {
     if (!h || N < 0) return SC_EINVAL;

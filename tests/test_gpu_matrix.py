@@ -127,16 +127,23 @@ def test_the_variants_are_all_that_is_built():
 
 # Planes that are whole runs of 16 bytes, of 8 (binary16 14 x 14, fp32 15 x 14) and of neither; rows off their
 # blocks of 32, a last tile that is not full, wavefronts that share the tile's outputs or its channels.
+# Bytes of a run in fp32 and in binary16, and the layer.
+STORED_RUNS = [(16, 8, (41, 64, 65, 3, 3, 14, 14, 1, 1)), (16, 16, (33, 48, 130, 3, 3, 16, 12, 1, 1)), (8, 0, (61, 240, 250, 1, 1, 15, 14, 1, 0)),
+               (16, 16, (131, 256, 70, 3, 3, 4, 4, 1, 1)), (16, 8, (1201, 256, 70, 3, 3, 2, 2, 1, 1)), (0, 0, (45, 64, 100, 3, 3, 9, 13, 1, 1))]
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
-@pytest.mark.parametrize("shape", [(41, 64, 65, 3, 3, 14, 14, 1, 1), (33, 48, 130, 3, 3, 16, 12, 1, 1), (61, 240, 250, 1, 1, 15, 14, 1, 0),
-                                   (131, 256, 70, 3, 3, 4, 4, 1, 1), (1201, 256, 70, 3, 3, 2, 2, 1, 1), (45, 64, 100, 3, 3, 9, 13, 1, 1)], ids=lambda s: "x".join(map(str, s)))
-def test_matrix_kernel_stores_runs(dtype, shape):
-    """Every output is written and nothing beside them, with the bits that an output off the runs' alignment gets one by one."""
+@pytest.mark.parametrize("runs32,runs16,shape", STORED_RUNS, ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else str(s))
+def test_matrix_kernel_stores_runs(dtype, runs32, runs16, shape):
+    """Every output is written and nothing beside them, with the bits that an output off the runs' alignment gets one by one; the first and
+    the last images' are the oracle's."""
     import torch
     layer, w, m, x = _layer(dtype, shape, 97, 0.9)
     N, C, K, R, S, H, W, st, p = shape
-    layer.set_epilogue(np.random.default_rng(8).standard_normal(K).astype(np.float32), relu=True)
+    bias = np.random.default_rng(8).standard_normal(K).astype(np.float32)
+    layer.set_epilogue(bias, relu=True)
     assert layer.get_kernel(N, H, W, st, p) == "matrix" and layer.check_plan(N, H, W, st, p) == 0
+    assert layer.get_matrix_out_runs(N, H, W, st, p) == (runs32 if dtype == "f32" else runs16)
     xt = torch.from_numpy(x).cuda().to(torch.float16 if dtype == "f16" else torch.float32)
     size = torch.Size((N, K, *layer.output_shape(H, W, st, p)))
     got = []
@@ -147,6 +154,9 @@ def test_matrix_kernel_stores_runs(dtype, shape):
         assert torch.isfinite(y).all()
         got.append(y.clone())
     assert torch.equal(*got)
+    some = [0, 1, N - 2, N - 1]
+    ref = np.maximum(oracle_ref(w, m, x[some], st, p, dtype) + bias[None, :, None, None], 0.0)
+    assert_close(got[0][some].float().cpu().numpy(), ref, TOL[dtype], f"{dtype} {shape}")
     layer.close()
 
 
