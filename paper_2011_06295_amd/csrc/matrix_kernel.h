@@ -969,7 +969,8 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
     // row are half a cache line.  So where planes are whole runs of 16 (8) bytes, a block of 32 rows goes through the tile's
     // place in LDS, and a lane stores a run of one row, past the caches: the launch does not read it again.  (64 -> 256 channels,
     // 56 x 56, binary16, batch 128, 257 MB: 90 -> 83 us with runs, 61 with runs past the caches; 256 -> 512, 28 x 28: 254 -> 244 and
-    // 240; 256 -> 256, 14 x 14, fp32, batch 256: 200 -> 200 and 194.)
+    // 240; 256 -> 256, 14 x 14, fp32, batch 256: 200 -> 200 and 194; all by launches repeated on the same buffers.  With inputs that
+    // change from launch to launch the first takes 87 us one by one and 56 so.)
     constexpr int kPitch = kNP * 32 * (int)sizeof(T) + 16;
     auto put_runs = [&](int mk, auto run) __attribute__((always_inline)) {
         using Run = decltype(run);

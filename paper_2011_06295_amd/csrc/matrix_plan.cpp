@@ -275,7 +275,8 @@ namespace {
 // Rough time of one launch in microseconds.  Structure and constants are fitted to the measured times of every split (3278 of
 // them) of 186 layers (the 32-pixel VGG-16's, those of larger networks, and random ones: 1 x 1, 1-D, 3 x 3, 5 x 5, stride 2,
 // batches of 1 to 256): 10 % rms of the logarithm, the cheapest by estimate 2 % slower than the fastest measured in the mean.
-// In clocks of 2.1 GHz:
+// (The fit is from before outputs left in runs, which it does not price: it is high where stores bound a layer, most for wide 1 x 1 layers in
+// binary16, of which 64 -> 256, 56 x 56 takes two thirds of what it did.)  In clocks of 2.1 GHz:
 //  * A step costs its matrix instructions (39 to 41 clocks each over the workgroups resident on the CU; 32 at the nominal rate)
 //    and its reads, but never less than a wavefront's own chain of loads and instructions.
 //  * A chunk's staging blocks cost 59 to 299 clocks each by kind (single pixels or runs, half or two pieces); multiplying and
@@ -479,8 +480,8 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
 // or split this and the one estimate for all sizes changed, the mean is 13 % faster, and three of 8 to 9 us are 8 to 21 % slower.)
 // fp32: taken below 0.85 of the cheapest tile launch by the estimate for kernels by rows.  Of 71 layers, timed over blocks of a tenth of a
 // second, which heat the chip as a pass does, all below gain 6 % or more; between 0.85 and 0.9 lie 256 -> 256, 14 x 14, batch 256 at 90 %
-// (169 us; tile kernel 167 then, 153 since its rows share a stream) and its like.  (Of 36 others with ragged rows, all below, two are slower, by 1 and 8 %; the mean takes
-// 0.53 of the tile kernel's time.)  Not below all of the estimate that tile launches are chosen by (estimate_f32): of 113 drawn layers that
+// (169 us; tile kernel 167 then, 153 since its rows share a stream) and its like.  (Of 36 others with ragged rows, all below, two are
+// slower, by 1 and 8 %; the mean takes 0.53 of the tile kernel's time.)  Not below all of the estimate that tile launches are chosen by (estimate_f32): of 113 drawn layers that
 // it adds, 25 are 3 to 31 % slower by the matrix kernel, and its products hold 21 bits where the tile kernel's hold 24: with inputs that
 // went through a ReLU, whose sums cancel less, 13 of 48 are less exact by it, up to 1.15 of the tile kernel's error against 64 bits.
 bool matrix_pays(double us, double tile_us, bool split) { return us < (split ? 0.85 * tile_us : tile_us - 0.7); }

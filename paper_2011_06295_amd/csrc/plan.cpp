@@ -162,8 +162,8 @@ double estimate_f32(const Shape& s, const Cand& c)
     return (double)(wgs / slots) * round(conc_max) + (rest ? round((double)cdiv(rest, kCUs)) : 0.0);
 }
 
-// The same for binary16 layers, and for fp32 ones as their kernels were when each row was a stream of its own (what the choice of
-// the matrix kernel also looks at).  The structure follows measurements on
+// The same for binary16 layers, and for fp32 ones as their kernels were when each row was a stream of its own (what their choice of
+// the matrix kernel and the least number of channel parts go by).  The structure follows measurements on
 // MI355X; the constants were fitted to the measured times of ~41000 launch
 // configurations (every shape the candidate loops below produce) of the 13
 // VGG-16 layers at 32 px (batch 128, fp32), four of its layers at 224 px
