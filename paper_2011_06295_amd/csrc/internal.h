@@ -361,6 +361,7 @@ struct MatrixArgs {
     int stream_steps, KF;
     int block_major;       // order of the (tile, channel block) pairs
     int quads, plane_quads;   // wide staging: runs of pixels of a tile (at most) and of a plane
+    int last_run;             // ... the pixel that a plane's last run begins at
     int padded;               // ... the lattice has elements that are no pixel
     int out_runs;             // bytes of the runs that outputs are stored in; 0: one by one
     FastDiv fd_EF, fd_F, fd_Wp, fd_Hs, fd_EB, fd_W, fd_quads, fd_plane_quads;

@@ -385,6 +385,8 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
     // run holds, is cleared once.  (That layer's best split: 37.5 -> 26.4 us; in fp32, batch 128: 51.3 -> 37.1.)  A block is 64
     // runs, those of all channel groups one behind the other.  Inputs start at any element, as vector memory loads 8 bytes from
     // any address: 2 bytes off a word that layer takes 24.8 us for 23.6 (single pixels: 33.3), 2 x 2 maps 21.4 for 18.0.
+    // Planes that are not whole runs end in one that overlaps the run before it (ragged_runs: 173 -> 354 channels, 25 x 25, binary16,
+    // 91 %, batch 5: 17.2 -> 13.8 us).
     const int nwide = WIDE ? (a.CG * a.quads + 63) >> 6 : 0;
     int quad0 = 0;                              // the tile's first run
     if constexpr (WIDE) {
@@ -397,19 +399,21 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
     }
     const int blocks = WIDE ? nwide : nblk;     // what the wavefronts share
     staged st[FLY][8];
-    // run b * 64 + lane: its channel group, image and place in the plane
+    // run b * 64 + lane: its channel group, image and first pixel.  (The last run of a plane that is not whole ones begins
+    // before the one before it ends: both write the same there.)
     auto run_of = [&](int b, int& cg, int& u, int& at, const MatrixArgs& a) __attribute__((always_inline)) {
         const int n = b * 64 + lane;
         cg = fdiv(n, a.fd_quads);
         const int quad = quad0 + n - cg * a.quads;
         u = fdiv(quad, a.fd_plane_quads);
-        at = quad - u * a.plane_quads;
+        at = (quad - u * a.plane_quads) * kPx;
+        at = at < a.last_run ? at : a.last_run;
     };
     auto load_runs = [&](uint2v(&dst)[8], int ch, int b, const MatrixArgs& a) __attribute__((always_inline)) {
         int cg, u, at;
         run_of(b, cg, u, at, a);
         const bool ok = (u < a.N) & (cg < a.CG) & (ch < a.nchunks);
-        const unsigned off = (unsigned)(u - u0) * (unsigned)img_bytes + (unsigned)(cg * 8) * chan_bytes + (unsigned)at * 8u;
+        const unsigned off = (unsigned)(u - u0) * (unsigned)img_bytes + (unsigned)(cg * 8) * chan_bytes + (unsigned)at * (unsigned)sizeof(T);
         const int left = ok ? a.C - (ch * a.CG + cg) * 8 : 0;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -472,7 +476,7 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
     auto store_runs = [&](const uint2v(&src)[8], float scale, int buf, int b) __attribute__((always_inline)) {
         int cg, u, at;
         run_of(b, cg, u, at, a);
-        const int y = fdiv(at * kPx, a.fd_W), x = at * kPx - y * a.W;
+        const int y = fdiv(at, a.fd_W), x = at - y * a.W;
         const int e0 = (u * a.Hs + a.pad + y) * a.Wp + a.pad + x - q0;
         const unsigned to = lds0 + (unsigned)buf * buffer + (unsigned)cg * plane;
 #pragma unroll
@@ -537,7 +541,7 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
                 load_runs(src, ch, b, a);
                 int cg, u, at;
                 run_of(b, cg, u, at, a);
-                const int y = fdiv(at * kPx, a.fd_W), x = at * kPx - y * a.W;
+                const int y = fdiv(at, a.fd_W), x = at - y * a.W;
                 const int e0 = (u * a.Hs + a.pad + y) * a.Wp + a.pad + x - q0;
 #pragma unroll 1
                 for (int p = 0; p < kPx; ++p) {

@@ -197,6 +197,14 @@ int out_runs_lds(const MatrixPlan& p, int elem_bytes) { return 4 * 32 * ((p.KS >
 // faster, two in a hundred of them slower, by 5 % at most.
 bool stages_runs(const MatrixPlan& p, int elem_bytes) { return p.quads && p.fly > (elem_bytes == 4 ? 1 : 2); }
 
+// Whether planes that are not whole runs are staged in runs, the last of a plane overlapping the one before it; `blocks`: of single
+// pixels, a wavefront and chunk.  Of 4400 splits of 145 layers with such planes, those with more than four blocks are 15 % faster so in the
+// mean, none slower by more than 3 % (173 -> 354 channels, 25 x 25, binary16: 17.2 -> 13.8 us).  With four or fewer, all in flight as single
+// pixels, binary16 under 3 x 3 and 5 x 5 taps still gains 10 %; under 1 x 1 taps up to 31 % is lost, in fp32 up to 43 %, 5 % under
+// 3 x 3 taps.  Layers of fewer than 64 channels would gain 7 % and stay as they are: they are what the kernels that stage single pixels
+// are tested by.
+bool ragged_runs(int C, int RS, int blocks, int elem_bytes) { return C >= 64 && blocks > (RS == 1 || elem_bytes == 4 ? 4 : 2); }
+
 bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, int MK, int NP, int WK, int KS,
                  int CG, MatrixPlan& p)
 {
@@ -222,18 +230,19 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     long long gcd = EF;
     for (long long r = p.PT % EF; r;) { const long long t = gcd % r; gcd = r; r = t; }
     auto lattice = [&](long long o) { return (o / EF * p.Hs + o % EF / p.F * g.stride) * (long long)p.Wp + o % p.F * g.stride; };
-    // The pixels before a lattice element, images one behind the other: those a tile needs are consecutive.
-    auto pixels_before = [&](long long L) {
-        const long long Y = L / p.Wp, u = Y / p.Hs, y = Y % p.Hs - g.pad, x = L % p.Wp - g.pad;
-        const long long before = y < 0 ? 0 : y >= g.H ? (long long)g.H * g.W : y * g.W + std::min<long long>(std::max<long long>(x, 0), g.W);
-        return u * g.H * g.W + before;
-    };
+    // The runs of pixels before a lattice element, images one behind the other: those a tile needs are consecutive.
     const int px = 8 / elem_bytes;
+    const long long plane = (long long)g.H * g.W, plane_quads = (plane + px - 1) / px;
+    auto runs_before = [&](long long L, int begun) {       // begun: px - 1 to count one that it is in the middle of
+        const long long Y = L / p.Wp, u = Y / p.Hs, y = Y % p.Hs - g.pad, x = L % p.Wp - g.pad;
+        const long long before = y < 0 ? 0 : y >= g.H ? plane : y * g.W + std::min<long long>(std::max<long long>(x, 0), g.W);
+        return u * plane_quads + (before + begun) / px;
+    };
     long long span = 0, quads = 0;
     for (long long t = 0; t < std::min<long long>(p.ntiles, EF / gcd); ++t) {
         const long long a = t * p.PT, b = std::min<long long>(nout, a + p.PT) - 1;
         span = std::max(span, lattice(b) - lattice(a));
-        quads = std::max(quads, (pixels_before(lattice(b) + (long long)(R - 1) * p.Wp + S) + px - 1) / px - pixels_before(lattice(a)) / px);
+        quads = std::max(quads, runs_before(lattice(b) + (long long)(R - 1) * p.Wp + S, px - 1) - runs_before(lattice(a), 0));
     }
     const long long elems = span + (long long)(R - 1) * p.Wp + S;
     if (elems > kMaxLds / 16) return false;
@@ -252,7 +261,7 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     p.ahead = own % 3 == 0 && !(pieces == 2 && own % 2 == 0) ? 3 : 2;
     const int unit = pieces == 2 ? 1 : 2, blocks = (CG * p.EB + 3) / 4;   // a chunk's staging blocks of a wavefront
     p.fly = blocks <= unit ? unit : blocks < 3 * unit ? 2 * unit : 3 * unit;
-    p.quads = (long long)g.H * g.W % px == 0 && g.W >= 2 && quads > 0 ? (int)quads : 0;
+    p.quads = (plane % px == 0 || (plane > px && ragged_runs(C, R * S, blocks, elem_bytes))) && g.W >= 2 && quads > 0 ? (int)quads : 0;
     p.wide_fly = (CG * p.quads + 255) / 256 > 1 && MK * NP * pieces < 8 ? 2 : 1;
     long long lds = (long long)(p.nchunks > 1 ? 2 : 1) * CG * p.EB * 64 * 16 * pieces;
     if (KS > 1) lds = std::max(lds, (long long)KS * MK * NP * 16 * 64 * 4);   // where the four sums of a pair meet
@@ -336,8 +345,8 @@ int check_matrix_plan(int K, int C, int R, int S, int elem_bytes, const Geometry
     if (p.kblocks * rows < K || (long long)p.ntiles * p.PT < p.nout || p.WK * p.WP * p.KS != 4 || p.PT != 32 * p.NP * p.WP) return 15;
     if (p.grid % 8 || p.grid < (long long)p.ntiles * p.kblocks) return 15;
     // 17: (wide staging) the tile's runs of pixels hold every input that its taps read
-    const int px = 8 / elem_bytes, run = g.H * g.W / px;
-    if (p.quads && (g.H * g.W % px || g.W < 2)) return 17;
+    const int px = 8 / elem_bytes, plane = g.H * g.W, run = (plane + px - 1) / px;
+    if (p.quads && (plane < px || g.W < 2)) return 17;
     // 16: each tap of each output of a tile is inside the tile, at the element of its input or at one that reads as zero
     const int EF = p.E * p.F, look = std::min(p.ntiles, 48);
     auto lattice = [&](int o) { return (o / EF * p.Hs + o % EF / p.F * g.stride) * p.Wp + o % p.F * g.stride; };
@@ -345,7 +354,7 @@ int check_matrix_plan(int K, int C, int R, int S, int elem_bytes, const Geometry
         const int tile = t == look - 1 ? p.ntiles - 1 : t, o0 = tile * p.PT, q0 = lattice(o0), u0 = o0 / EF;
         if ((q0 + p.EB * 64 - 1) / p.Wp / p.Hs - u0 >= p.images) return 16;
         const int Y0 = q0 / p.Wp % p.Hs - g.pad, X0 = q0 % p.Wp - g.pad;      // as the kernel finds the first run
-        const int first = p.quads ? (u0 * run * px + (Y0 < 0 ? 0 : std::min(Y0 * g.W + std::min(std::max(X0, 0), g.W), run * px))) / px : 0;
+        const int first = p.quads ? u0 * run + (Y0 < 0 ? 0 : std::min(Y0 * g.W + std::min(std::max(X0, 0), g.W), plane)) / px : 0;
         for (int o = o0; o < std::min(p.nout, o0 + p.PT); ++o)
             for (int r = 0; r < R; ++r)
                 for (int s = 0; s < S; ++s) {
@@ -355,7 +364,7 @@ int check_matrix_plan(int K, int C, int R, int S, int elem_bytes, const Geometry
                     const bool reads = u < g.N && y >= 0 && y < g.H && X >= 0 && X < g.W;
                     const bool wants = yy >= 0 && yy < g.H && xx >= 0 && xx < g.W;
                     if (reads != wants || (wants && (u != o / EF || y != yy || X != xx))) return 16;
-                    const int quad = p.quads && wants ? (u * run * px + y * g.W + X) / px - first : 0;
+                    const int quad = p.quads && wants ? u * run + (y * g.W + X) / px - first : 0;
                     if (quad < 0 || (p.quads && quad >= p.quads)) return 17;
                 }
     }
@@ -510,8 +519,9 @@ void fill_matrix_args(const MatrixWeights& m, const MatrixPlan& p, int K, int C,
     a.fd_EB = make_fastdiv(p.EB);
     const int px = m.pieces == 2 ? 2 : 4;
     a.quads = p.quads;
+    a.last_run = g.H * g.W - px;
     a.padded = p.Wp != g.W || p.Hs != g.H;
-    a.plane_quads = g.H * g.W / px;
+    a.plane_quads = (g.H * g.W + px - 1) / px;
     a.fd_W = make_fastdiv(g.W);
     a.fd_quads = make_fastdiv(std::max(1, a.quads));
     a.fd_plane_quads = make_fastdiv(std::max(1, a.plane_quads));
