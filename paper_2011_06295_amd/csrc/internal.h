@@ -303,7 +303,7 @@ void pack_matrix_weights(const Csr& csr, int C, int R, int S, bool split, Matrix
 // Tiles of the matrix kernel for one geometry.  A workgroup of four wavefronts owns PT consecutive outputs of the batch
 // (numbered image, row, column) and 32 * MK * WK output channels; a wavefront multiplies MK fragments of weights with NP
 // fragments of 32 outputs.  KS = 1: WK * WP wavefronts share the tile out; KS = 4: each takes the whole tile for a quarter
-// of a chunk's channels.  The lattice (zero-padded rows of all images, one below the other) is the tile kernel's, with 8
+// of a chunk's channels; KS = 8: so do eight wavefronts for an eighth.  The lattice (zero-padded rows of all images, one below the other) is the tile kernel's, with 8
 // channels of one image to an element instead of V images.
 struct MatrixPlan {
     int MK, NP, WK, WP, KS;
@@ -360,6 +360,7 @@ struct MatrixArgs {
     int own_steps;         // ... times taps
     int stream_steps, KF;
     int block_major;       // order of the (tile, channel block) pairs
+    int groups;               // of 16 input channels
     int quads, plane_quads;   // wide staging: runs of pixels of a tile (at most) and of a plane
     int last_run;             // ... the pixel that a plane's last run begins at
     int padded;               // ... the lattice has elements that are no pixel

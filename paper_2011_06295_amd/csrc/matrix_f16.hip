@@ -10,6 +10,8 @@ int launch_matrix_f16(const MatrixPlan& p, const MatrixArgs& a, void* stream)
         case 221: return launch_fly<_Float16, 2, 2, 1>(a, p, s);
         case 241: return launch_fly<_Float16, 2, 4, 1>(a, p, s);
         case 224: return launch_fly<_Float16, 2, 2, 4>(a, p, s);
+        case 118: return launch_fly<_Float16, 1, 1, 8>(a, p, s);
+        case 128: return launch_fly<_Float16, 1, 2, 8>(a, p, s);
     }
     return (int)hipErrorInvalidValue;
 }

@@ -16,6 +16,12 @@
 // step: 2 x 4 is what 256 registers hold.  Weight fragments come straight from L2 (each is used by one wavefront of the
 // workgroup, or few), AHEAD steps before their use.
 //
+// Few outputs (a batch of one to some ten images, small maps) leave most CUs without a tile, and a wavefront alone on its SIMD takes some
+// 240 clocks a step, the latencies of its weights and inputs, for 32 to 128 of products.  So there (binary16) eight wavefronts share the channels of a
+// tile of 32 x 32 or 32 x 64: up to four times the workgroups, two wavefronts a SIMD, and chunks of twice the channels, a memory
+// latency each.  1381 -> 385 channels, 14 x 14, one image, 70 %: 25.2 us by the tile kernel, 18.4 by four wavefronts, 9.5 so; 205 -> 100,
+// 8 x 8, 5 x 5 taps, batch 26: 16.4 by four, 9.9; VGG-16's 512 -> 512 on 2 x 2, batch 256: 18.1 and 14.3.
+//
 // Order of the loads.  Vector loads return in order, so a weight fragment that is asked for after the loads of the next
 // chunk's inputs waits for those.  All of a chunk's input loads are therefore issued together at its start, behind the
 // weights of its first AHEAD steps, and those steps stand outside the loop: there the compiler can count exactly which
@@ -263,19 +269,24 @@ __device__ __forceinline__ bool finite(float v) { return __builtin_fabsf(v) <= 3
 
 }  // namespace
 
+// Wavefronts of a workgroup.
+template <int KS>
+constexpr int kWaves = KS > 4 ? KS : 4;
+
 // Wavefronts a SIMD holds at least: the smallest variant (1 x 1 layers mostly, which load and store more than they multiply)
 // fits 128 registers but for one, and four of it are faster than three (64 -> 256 channels, 56 x 56, binary16: 71 and 79 us).
 template <typename T, int MK, int NP, int AHEAD, int FLY, int KS, bool WIDE>
 constexpr int kResident = sizeof(T) == 2 && MK * NP == 4 && AHEAD == 2 && FLY <= 2 && KS == 1 && !WIDE ? 4 : 2;
 
 template <typename T, int MK, int NP, int AHEAD, int FLY, int KS, bool WIDE>
-__global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) void matrix_kernel(const MatrixArgs a)
+__global__ __launch_bounds__(64 * kWaves<KS>, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) void matrix_kernel(const MatrixArgs a)
 {
     using raw = typename Raw<T>::type;
     constexpr int kPx = WIDE ? 8 / (int)sizeof(T) : 1;          // pixels of a channel a lane stages
     using staged = std::conditional_t<WIDE, uint2v, raw>;
     constexpr bool kSplit = sizeof(T) == 4;
     constexpr int kParts = kSplit ? 2 : 1;      // binary16 pieces a value is held in
+    constexpr int kW = kWaves<KS>, kThreads = 64 * kW;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
     const int tid = threadIdx.x;
@@ -290,8 +301,8 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
     const int major = a.block_major ? a.ntiles : a.kblocks;
     const int outer = item / major, inner = item - outer * major;
     const int tile = a.block_major ? inner : outer, kb = a.block_major ? outer : inner;
-    // KS = 1: the wavefronts share the tile's output channels and outputs out among them; KS = 4: each works on the
-    // whole tile for a quarter of every chunk's channels
+    // KS = 1: the wavefronts share the tile's output channels and outputs out among them; KS = 4 (8): each works on the
+    // whole tile for a quarter (an eighth) of every chunk's channels
     const int wk = KS == 1 ? wave & (a.WK - 1) : 0, wp = KS == 1 ? wave >> a.logWK : 0;
     const int ks = KS == 1 ? 0 : wave;
     const int kf0 = (kb * a.WK + wk) * MK;      // first block of 32 output channels of this wavefront
@@ -320,8 +331,8 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
             const int at = kb * rows / 32 * MatrixWeights::kSlots + tid;
             slots[tid] = at < a.KF * MatrixWeights::kSlots ? a.slots[at] : MatrixWeights::Small{-1, 0, 0, 0.f};
         }
-        for (int i = tid; i < a.images; i += 256) images[i].above = 0u;
-        for (int i = tid; i < a.EB * 2; i += 256) marks[i] = 0u;
+        for (int i = tid; i < a.images; i += kThreads) images[i].above = 0u;
+        for (int i = tid; i < a.EB * 2; i += kThreads) marks[i] = 0u;
         if (tid < 4) meet[tid] = 0u;
     }
 
@@ -351,15 +362,22 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
     constexpr size_t frag = 64 * 8;                              // halves of one fragment
     const size_t stream = (size_t)a.stream_steps * kParts * frag;
     const _Float16* wa[MK];
+    // the wavefront's first group of 16 channels of a chunk.  (Eight wavefronts: past the last one, the first of those that the
+    // table holds behind it, whatever the chunk lacks: they meet zeros of the input.)
+    auto group_of = [&](int ch, const MatrixArgs& a) __attribute__((always_inline)) {
+        const int g = ch * (a.CG / 2) + ks * a.own_groups;
+        if constexpr (KS > 4) return g < a.groups ? g : a.groups;
+        return g;
+    };
     auto weights_of = [&](int ch, const MatrixArgs& a) __attribute__((always_inline)) {
 #pragma unroll
         for (int mk = 0; mk < MK; ++mk)                          // blocks past the last repeat it (never stored)
             wa[mk] = static_cast<const _Float16*>(a.weights) + (size_t)(kf0 + mk < a.KF ? kf0 + mk : a.KF - 1) * stream +
-                     (size_t)((ch * (a.CG / 2) + ks * a.own_groups) * a.RS) * kParts * frag;
+                     (size_t)(group_of(ch, a) * a.RS) * kParts * frag;
     };
     weights_of(0, a);
     // from the end of a chunk's steps of this wavefront to the next chunk's first
-    const size_t skip = KS == 1 ? 0 : (size_t)((a.CG / 2 - a.own_groups) * a.RS) * kParts * frag;
+    const ptrdiff_t skip = KS == 1 ? 0 : (ptrdiff_t)((a.CG / 2 - a.own_groups) * a.RS) * (ptrdiff_t)(kParts * frag);
     const unsigned lane8 = (unsigned)lane * 8u;
     half8 A[AHEAD][MK][kParts];
     auto load_a = [&](half8(&dst)[MK][kParts]) __attribute__((always_inline)) {
@@ -395,7 +413,7 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
         quad0 = u0 * a.plane_quads + (inside < a.H * a.W ? inside : a.H * a.W) / kPx;
         const half8 zero = {};
         const unsigned all = a.padded ? (a.nchunks > 1 ? 2u : 1u) * buffer : 0u;
-        for (unsigned i = (unsigned)tid * 16u; i < all; i += 256u * 16u) lds_write(lds0 + i, zero);
+        for (unsigned i = (unsigned)tid * 16u; i < all; i += (unsigned)kThreads * 16u) lds_write(lds0 + i, zero);
     }
     const int blocks = WIDE ? nwide : nblk;     // what the wavefronts share
     staged st[FLY][8];
@@ -535,7 +553,7 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
             }
         };
 #pragma unroll 1
-        for (int b = wave; b < blocks; b += 4) {
+        for (int b = wave; b < blocks; b += kW) {
             if constexpr (WIDE) {
                 uint2v src[8];
                 load_runs(src, ch, b, a);
@@ -579,14 +597,14 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
     };
     auto fetch = [&](int ch) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < FLY; ++i) load(st[i], ch, wave + 4 * i);
+        for (int i = 0; i < FLY; ++i) load(st[i], ch, wave + kW * i);
     };
     float scale[kSplit ? FLY : 1];              // kSplit: of the blocks in flight
     auto take_scales = [&]() __attribute__((always_inline)) {
         if constexpr (kSplit) {
 #pragma unroll
             for (int i = 0; i < FLY; ++i)
-                if (wave + 4 * i < blocks) scale[i] = staged_scale(wave + 4 * i);
+                if (wave + kW * i < blocks) scale[i] = staged_scale(wave + kW * i);
         }
     };
     auto deposit = [&](int ch, int buf) __attribute__((always_inline)) {
@@ -596,8 +614,8 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
         };
 #pragma unroll
         for (int i = 0; i < FLY; ++i)
-            if (wave + 4 * i < blocks) store(st[i], scale[kSplit ? i : 0], wave + 4 * i);
-        for (int b = wave + 4 * FLY; b < blocks; b += 4) {      // what does not fit in flight
+            if (wave + kW * i < blocks) store(st[i], scale[kSplit ? i : 0], wave + kW * i);
+        for (int b = wave + kW * FLY; b < blocks; b += kW) {      // what does not fit in flight
             staged more[8];
             load(more, ch, b);
             store(more, kSplit ? staged_scale(b) : 0.f, b);
@@ -625,11 +643,11 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
                 if constexpr (WIDE) see(st[i][j][0]), see(st[i][j][1]);
                 else see((unsigned)st[i][j]);
             }
-            const int image = staged_image(wave + 4 * i);
+            const int image = staged_image(wave + kW * i);
             if (top && (!WIDE || image < a.images)) atomicMax(&images[image].above, top);           // (absent blocks hold zeros)
         }
         __syncthreads();
-        for (int i = tid; i < a.images; i += 256) {
+        for (int i = tid; i < a.images; i += kThreads) {
             const unsigned top = images[i].above;
             const int last = top ? (int)(top >> 23) + kRoom : kDefaultTop - 1;
             const int base = window_ending(last < 254 ? last : 254);
@@ -638,9 +656,10 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
         __syncthreads();
     };
 
-    auto for_steps = [&](auto& step, int t, bool more) __attribute__((always_inline)) {
+    auto for_steps = [&](auto& step, int t, int ch, bool more) __attribute__((always_inline)) {
         if constexpr (KS > 1) {   // the weights asked for during a chunk's last steps are the next chunk's
-            const size_t jump = more && t + AHEAD >= a.own_steps ? skip : 0;
+            ptrdiff_t jump = 0;
+            if (more && t + AHEAD >= a.own_steps) jump = KS > 4 ? (ptrdiff_t)((group_of(ch + 1, a) - group_of(ch, a) - a.own_groups) * a.RS) * (ptrdiff_t)(kParts * frag) : skip;
 #pragma unroll
             for (int mk = 0; mk < MK; ++mk) wa[mk] += jump;
         }
@@ -722,8 +741,8 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
             load_a(W);
         };
         // the first steps stand by themselves: their weights were asked for before the loads of the next chunk
-        for_steps(step, 0, kMore);
-        for (int t = AHEAD; t < a.own_steps; t += AHEAD) for_steps(step, t, kMore);
+        for_steps(step, 0, ch, kMore);
+        for (int t = AHEAD; t < a.own_steps; t += AHEAD) for_steps(step, t, ch, kMore);
         if constexpr (kSplit) {
 #pragma unroll
             for (int mk = 0; mk < MK; ++mk)
@@ -826,7 +845,7 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
                 const MatrixArgs& a = late_arguments();
                 const bool some = anything_left(a);
                 if (!some && !short_of) break;
-                for (int i = tid; i < a.images; i += 256) {
+                for (int i = tid; i < a.images; i += kThreads) {
                     if (some) {
                         next_window(images[i]);
                     } else {                                      // those below: out of the sums
@@ -891,25 +910,29 @@ __global__ __launch_bounds__(256, (kResident<T, MK, NP, AHEAD, FLY, KS, WIDE>)) 
             for (int np = 0; np < NP; ++np) acc[mk][np] = sum[mk][np];
     }
     if constexpr (KS > 1) {
-        // the four wavefronts' sums of a (mk, np) pair meet at the wavefront with the pair's number, always added in
+        // the wavefronts' sums of a (mk, np) pair meet at the wavefront with the pair's number, always added in
         // the same order (nobody reads the tile any more: its place is free)
-        static_assert(MK * NP == KS, "one pair a wavefront");
+        constexpr int kPairs = MK * NP;
+        static_assert(kPairs <= KS, "a pair a wavefront at most");
         float* meeting = reinterpret_cast<float*>(smem);
 #pragma unroll
         for (int mk = 0; mk < MK; ++mk)
 #pragma unroll
             for (int np = 0; np < NP; ++np)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) meeting[(((ks * MK + mk) * NP + np) * 16 + i) * 64 + lane] = acc[mk][np][i];
+                for (int i = 0; i < 16; ++i) meeting[((ks * kPairs + mk * NP + np) * 16 + i) * 64 + lane] = acc[mk][np][i];
         __syncthreads();
+        if (wave < kPairs) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            float v = meeting[((size_t)wave * 16 + i) * 64 + lane];
+            for (int i = 0; i < 16; ++i) {
+                float v = meeting[((size_t)wave * 16 + i) * 64 + lane];
 #pragma unroll
-            for (int q = 1; q < KS; ++q) v += meeting[(((size_t)q * KS + wave) * 16 + i) * 64 + lane];
-            acc[0][0][i] = v;
+                for (int q = 1; q < KS; ++q) v += meeting[(((size_t)q * kPairs + wave) * 16 + i) * 64 + lane];
+                acc[0][0][i] = v;
+            }
         }
         __syncthreads();
+        if (kPairs < KS && wave >= kPairs) return;
         bad = bad >> (wave % NP) & 1u;
     }
 #pragma unroll
@@ -1128,7 +1151,7 @@ int launch_one(const MatrixArgs& a, int grid, int lds, hipStream_t s)
             allowed.fetch_or(bit, std::memory_order_relaxed);
         }
     }
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(256), lds, s, a);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(64 * kWaves<KS>), lds, s, a);
     return (int)hipGetLastError();
 }
 

@@ -10,7 +10,11 @@ namespace sc {
 
 namespace {
 
-constexpr int kMatrixGroups = 8;      // groups of 16 channels a chunk holds at most
+constexpr int kMatrixGroups = 8;      // groups of 16 channels a chunk holds at most (eight wavefronts that share them: twice as many)
+int waves(int KS) { return std::max(4, KS); }
+int most_groups(int KS) { return KS > 4 ? 2 * kMatrixGroups : kMatrixGroups; }
+// Bytes where the sums of wavefronts that share the channels meet.
+int meeting_bytes(int MK, int NP, int KS) { return KS * MK * NP * 4096; }
 constexpr int kMaxLds = 160 * 1024;   // LDS per CU
 constexpr int kCUs = 256;
 
@@ -209,7 +213,7 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
                  int CG, MatrixPlan& p)
 {
     p = MatrixPlan{};
-    p.MK = MK; p.NP = NP; p.WK = WK; p.KS = KS; p.WP = 4 / (WK * KS);
+    p.MK = MK; p.NP = NP; p.WK = WK; p.KS = KS; p.WP = waves(KS) / (WK * KS);
     p.E = (g.H + 2 * g.pad - R) / g.stride + 1;
     p.F = (g.W + 2 * g.pad - S) / g.stride + 1;
     const long long EF = (long long)p.E * p.F, nout = g.N * EF;
@@ -251,7 +255,10 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     const long long images = ((long long)p.EB * 64 / p.Wp + 1) / p.Hs + 2;
     p.images = (int)images;
     if (images * C * g.H * g.W * elem_bytes >= (1ll << 31)) return false;
-    if (CG / 2 > kMatrixGroups || CG / 2 % KS) return false;
+    if (CG / 2 > most_groups(KS) || CG / 2 % KS) return false;
+    // Eight wavefronts: from 64 channels on, a group of 16 for every other of them, and where there is more than one tile of theirs.  (One
+    // tile or less is a launch of 6 us, bound by its issue, and up to 1 us faster so; below 64 channels most wavefronts have none.)
+    if (KS > 4 && (C < 64 || nout <= 32)) return false;
     p.CG = CG;
     const int own = CG / 2 / KS * R * S;
     if (own % 3 && own % 2) return false;           // the kernel walks a chunk two or three steps at a time
@@ -259,12 +266,12 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     p.nchunks = (groups + CG - 1) / CG;
     // (two binary16 pieces: three steps of weights ahead are more registers than there are, unless it has to be three)
     p.ahead = own % 3 == 0 && !(pieces == 2 && own % 2 == 0) ? 3 : 2;
-    const int unit = pieces == 2 ? 1 : 2, blocks = (CG * p.EB + 3) / 4;   // a chunk's staging blocks of a wavefront
+    const int unit = pieces == 2 ? 1 : 2, blocks = (CG * p.EB + waves(KS) - 1) / waves(KS);   // a chunk's staging blocks of a wavefront
     p.fly = blocks <= unit ? unit : blocks < 3 * unit ? 2 * unit : 3 * unit;
     p.quads = (plane % px == 0 || (plane > px && ragged_runs(C, R * S, blocks, elem_bytes))) && g.W >= 2 && quads > 0 ? (int)quads : 0;
-    p.wide_fly = (CG * p.quads + 255) / 256 > 1 && MK * NP * pieces < 8 ? 2 : 1;
+    p.wide_fly = (CG * p.quads + 64 * waves(KS) - 1) / (64 * waves(KS)) > 1 && MK * NP * pieces < 8 ? 2 : 1;
     long long lds = (long long)(p.nchunks > 1 ? 2 : 1) * CG * p.EB * 64 * 16 * pieces;
-    if (KS > 1) lds = std::max(lds, (long long)KS * MK * NP * 16 * 64 * 4);   // where the four sums of a pair meet
+    if (KS > 1) lds = std::max(lds, (long long)meeting_bytes(MK, NP, KS));   // where the sums of a pair meet
     // outputs in runs, where a plane is whole ones: 32 rows of a wavefront's outputs at a time go through LDS
     p.out_runs = pool || EF * elem_bytes % 8 ? 0 : EF * elem_bytes % 16 ? 8 : 16;
     if (p.out_runs) lds = std::max(lds, (long long)out_runs_lds(p, elem_bytes));
@@ -293,27 +300,33 @@ namespace {
 //  * Workgroups run in rounds of what is resident.
 // (A launch of few products is mostly the fixed part: 51 fp32 and 44 binary16 layers of fewer than 4e8, zeros counted, are
 // within 2.4 and 1.4 % of their fastest split in the mean as well.)
+//  * Eight wavefronts that share the channels have constants of their own: 864 splits of 429 layers, 9 % rms beside the 1.06 of their
+//    time that the others' estimate has on those layers.  By it the fastest split of all is missed by 2.4 % in the mean; what was
+//    taken without them by 16 %, and no layer is more than 1 % slower than by that.
 //  * Weights in the list (but for a block's first ones) take 4700 clocks for eight, in a wavefront's own chain: `listed`.
 double estimate_matrix(const MatrixPlan& p, int RS, bool split, double listed)
 {
     struct Clocks { double fixed, chain, chain_mf, mf, read, chunk, stage_chunk, stage, run_chunk, run, both, late, pair, tail; };
     static const Clocks k16 = {11300, 172, 17.2, 40.9, 9.2, 482, 13, 58.5, 2, 197, 1.24, 659, 993, 1.0},
-                        k32 = {11800, 7, 49.0, 38.9, 1.5, 306, 45, 139, 6, 290, 1.19, 676, 2110, 1.09};
-    const Clocks& k = split ? k32 : k16;
+                        k32 = {11800, 7, 49.0, 38.9, 1.5, 306, 45, 139, 6, 290, 1.19, 676, 2110, 1.09},
+                        k16_8 = {7190, 230, 0, 28, 0, 1100, 0, 56.4, 0, 190, 1.77, 0, 4700, 1.05};
+    const Clocks& k = split ? k32 : p.KS > 4 ? k16_8 : k16;
     const int unit = split ? 1 : 2, pieces = split ? 2 : 1;
     const bool runs = stages_runs(p, split ? 4 : 2);
     const int blocks = runs ? (p.CG * p.quads + 63) / 64 : p.CG * p.EB, fly = runs ? p.wide_fly : p.fly;
-    // workgroups a CU holds: registers allow two, three of the small variants, four of the smallest
-    const int room = p.MK * p.NP * pieces > 4 ? 2 : !split && p.ahead == 2 && p.fly == unit && p.KS == 1 && !runs ? 4 :
+    // workgroups a CU holds: registers allow two, three of the small variants, four of the smallest; of eight wavefronts, two, three
+    // of the smallest variant
+    const int room = p.KS > 4 ? (p.MK * p.NP == 1 && fly <= 2 ? 3 : 2) : p.MK * p.NP * pieces > 4 ? 2 : !split && p.ahead == 2 && p.fly == unit && p.KS == 1 && !runs ? 4 :
                      fly == (runs ? (split ? 2 : 0) : 3 * unit) ? 2 : 3;
     const int conc_max = std::min(room, kMaxLds / p.lds_bytes);
     const double mf = p.MK * p.NP * (split ? 3 : 1), own = (double)(p.CG / 2 / p.KS) * RS;
-    const double late = std::max(0, (blocks + 3) / 4 - fly) * k.late, begin = runs ? k.run_chunk : k.stage_chunk;
+    const double late = std::max(0, (blocks + waves(p.KS) - 1) / waves(p.KS) - fly) * k.late, begin = runs ? k.run_chunk : k.stage_chunk;
+    const double pair = p.KS > 4 && !p.out_runs ? 1.35 * k.pair : k.pair;
     auto round = [&](double conc) {
-        const double multiply = own * std::max(k.chain + k.chain_mf * mf, conc * (mf * k.mf + p.NP * pieces * k.read));
+        const double multiply = own * std::max(k.chain + k.chain_mf * mf, conc * waves(p.KS) / 4 * (mf * k.mf + p.NP * pieces * k.read));
         const double stage = conc * blocks * (runs ? k.run : k.stage);
         return p.nchunks * (std::max(multiply, stage + begin) + k.both * std::min(multiply, stage) + k.chunk + late) + 0.6 * stage + begin +
-               conc * k.pair * p.MK * p.NP / (p.KS > 1 ? 4 : 1) + listed;
+               conc * pair * p.MK * p.NP / (p.KS > 1 ? 4 : 1) + listed;
     };
     const long long slots = (long long)kCUs * conc_max, wgs = (long long)p.ntiles * p.kblocks;
     const long long full = wgs / slots, rest = wgs % slots;
@@ -327,22 +340,32 @@ double estimate_matrix(const MatrixPlan& p, int RS, bool split, double listed)
 namespace {
 
 // The splits an automatic choice looks at: MK, NP, WK, KS.
-constexpr int kShapes16[][4] = {{2, 4, 1, 1}, {2, 4, 2, 1}, {2, 4, 4, 1}, {2, 2, 1, 1}, {2, 2, 2, 1}, {2, 2, 4, 1}, {2, 2, 1, 4}};
+constexpr int kShapes16[][4] = {{2, 4, 1, 1}, {2, 4, 2, 1}, {2, 4, 4, 1}, {2, 2, 1, 1}, {2, 2, 2, 1}, {2, 2, 4, 1}, {2, 2, 1, 4}, {1, 2, 1, 8}, {1, 1, 1, 8}};
 constexpr int kShapes32[][4] = {{2, 2, 1, 1}, {2, 2, 2, 1}, {2, 2, 4, 1}, {1, 2, 1, 1}, {1, 2, 2, 1}, {1, 2, 4, 1}, {2, 2, 1, 4}};
+struct Shapes {
+    const int (*first)[4], (*last)[4];
+    const int (*begin() const)[4] { return first; }
+    const int (*end() const)[4] { return last; }
+};
+Shapes shapes(bool split)
+{
+    return split ? Shapes{std::begin(kShapes32), std::end(kShapes32)} : Shapes{std::begin(kShapes16), std::end(kShapes16)};
+}
 
 int check_matrix_plan(int K, int C, int R, int S, int elem_bytes, const Geometry& g, const MatrixPlan& p)
 {
     const int pieces = elem_bytes == 4 ? 2 : 1, RS = R * S, own = p.CG / 2 / p.KS * RS;
     // 14: the channels are covered, the steps come out, the table holds what the last block asks for (last steps' weights ahead)
-    const long long steps = (C + 15) / 16 * RS, last = (long long)p.nchunks * (p.CG / 2) * RS + p.ahead;
+    // (eight wavefronts: one whose groups are past the last starts right behind it)
+    const long long steps = (C + 15) / 16 * RS, last = (p.KS > 4 ? steps + own : (long long)p.nchunks * (p.CG / 2) * RS) + p.ahead;
     if ((long long)p.nchunks * p.CG * 8 < C || own % p.ahead || p.CG / 2 % p.KS) return 14;
     if (((long long)(K + 31) / 32 - 1) * steps + last > (long long)image_halves(K, C, RS, 1) / 512) return 14;
     // 15: LDS holds the buffers (and the sums that meet there) and what lies behind them; every block of rows and outputs is there
     const long long buffers = (long long)(p.nchunks > 1 ? 2 : 1) * p.CG * p.EB * 1024 * pieces, rows = 32ll * p.MK * p.WK;
     const long long behind = 64 + 8 * rows + (pieces == 2 ? matrix_extra_lds(p) : 0);
-    if (p.lds_bytes > kMaxLds || buffers + behind > p.lds_bytes || (p.KS > 1 && p.KS * p.MK * p.NP * 4096ll + behind > p.lds_bytes)) return 15;
+    if (p.lds_bytes > kMaxLds || buffers + behind > p.lds_bytes || (p.KS > 1 && meeting_bytes(p.MK, p.NP, p.KS) + behind > p.lds_bytes)) return 15;
     if (p.out_runs && (out_runs_lds(p, elem_bytes) + behind > p.lds_bytes || (long long)p.E * p.F * elem_bytes % p.out_runs)) return 15;
-    if (p.kblocks * rows < K || (long long)p.ntiles * p.PT < p.nout || p.WK * p.WP * p.KS != 4 || p.PT != 32 * p.NP * p.WP) return 15;
+    if (p.kblocks * rows < K || (long long)p.ntiles * p.PT < p.nout || p.WK * p.WP * p.KS != waves(p.KS) || p.PT != 32 * p.NP * p.WP) return 15;
     if (p.grid % 8 || p.grid < (long long)p.ntiles * p.kblocks) return 15;
     // 17: (wide staging) the tile's runs of pixels hold every input that its taps read
     const int px = 8 / elem_bytes, plane = g.H * g.W, run = (plane + px - 1) / px;
@@ -375,8 +398,8 @@ int check_matrix_plan(int K, int C, int R, int S, int elem_bytes, const Geometry
 
 int check_matrix_plans(int K, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool)
 {
-    for (const auto& sh : elem_bytes == 4 ? kShapes32 : kShapes16)
-        for (int CG = 2; CG <= 2 * kMatrixGroups; CG *= 2) {
+    for (const auto& sh : shapes(elem_bytes == 4))
+        for (int CG = 2; CG <= 2 * most_groups(sh[3]); CG *= 2) {
             MatrixPlan p;
             if (!plan_matrix(K, C, R, S, elem_bytes, g, pool, sh[0], sh[1], sh[2], sh[3], CG, p)) continue;
             const int bad = check_matrix_plan(K, C, R, S, elem_bytes, g, p);
@@ -453,8 +476,8 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
     // (a row in the list is one sum of its terms, as in the tile kernel where that does not deal the channels over parts)
     if (lists && parts > 1) return false;
     double best_us = -1.0;
-    for (const auto& sh : split ? kShapes32 : kShapes16)
-        for (int CG = 2; CG <= 2 * kMatrixGroups; CG *= 2) {
+    for (const auto& sh : shapes(split))
+        for (int CG = 2; CG <= 2 * most_groups(sh[3]); CG *= 2) {
             MatrixPlan p;
             if (CG > 2 && CG / 2 >= 2 * ((C + 15) / 16)) break;   // a smaller chunk holds them all
             if (!plan_matrix(csr.K, C, R, S, elem_bytes, g, pool, sh[0], sh[1], sh[2], sh[3], CG, p)) continue;
@@ -518,6 +541,7 @@ void fill_matrix_args(const MatrixWeights& m, const MatrixPlan& p, int K, int C,
     a.fd_Hs = make_fastdiv(p.Hs);
     a.fd_EB = make_fastdiv(p.EB);
     const int px = m.pieces == 2 ? 2 : 4;
+    a.groups = (C + 15) / 16;
     a.quads = p.quads;
     a.last_run = g.H * g.W - px;
     a.padded = p.Wp != g.W || p.Hs != g.H;
