@@ -66,7 +66,10 @@ namespace sc {
 
 namespace {
 
+typedef _Float16 half2 __attribute__((ext_vector_type(2)));
+typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float float4v __attribute__((ext_vector_type(4)));
 typedef float float16v __attribute__((ext_vector_type(16)));
 typedef unsigned uint2v __attribute__((ext_vector_type(2)));
 typedef unsigned uint4v __attribute__((ext_vector_type(4)));
@@ -1024,6 +1027,56 @@ __global__ __launch_bounds__(64 * kWaves<KS>, (kResident<T, MK, NP, AHEAD, FLY, 
             }
         }
     };
+    // Pooled outputs in runs.  A wavefront's outputs are whole pairs of rows, so its maxima are consecutive too.  One by one each of
+    // a fragment's 16 registers takes a store of which a quarter of the lanes hold something, and on rows of 16 or fewer a trip through
+    // LDS for the row below: 14.4 us of 36 (128 -> 128 channels, 16 x 16, binary16, batch 256; 64 -> 64, 32 x 32: 7.1 of 31), 3.0
+    // (2.6) so.  So all outputs go to LDS as above and a lane reads the windows of a run.  (Rows of two have windows of half
+    // a word in two rows; they stay one by one.)
+    auto put_pooled = [&](int mk, auto run) {
+        using Run = decltype(run);
+        constexpr int kRun = (int)(sizeof(Run) / sizeof(T)), kRuns = kNP * 8 / kRun, kAll = 32 * kRuns;
+        constexpr int kPasses = kAll > 64 ? kAll / 64 : 1;
+        using Pair = std::conditional_t<kSplit, uint2v, unsigned>;             // two maxima
+        const MatrixArgs& la = late_arguments();
+        int own = late_lane;
+        asm volatile("" : "+v"(own));
+        const int row = own / kRuns & 31, F = la.F, logQ = __builtin_ctz((unsigned)F) - 2;     // F / 4 windows of two in a row
+        const unsigned from = lds0 + (unsigned)((wave * 32 + row) * kPitch), below = (unsigned)F * (unsigned)sizeof(T);
+        auto two = [&](unsigned at) __attribute__((always_inline)) -> Pair {
+            if constexpr (kSplit) {
+                const float4v a = lds_get<float4v>(at), b = lds_get<float4v>(at + below);
+                const float p = a.x > b.x ? a.x : b.x, q = a.y > b.y ? a.y : b.y, r = a.z > b.z ? a.z : b.z, s = a.w > b.w ? a.w : b.w;
+                return Pair{__float_as_uint(p > q ? p : q), __float_as_uint(r > s ? r : s)};
+            } else {
+                const half4 a = lds_get<half4>(at), b = lds_get<half4>(at + below), m = __builtin_elementwise_max(a, b);
+                return __builtin_bit_cast(unsigned, __builtin_elementwise_max(half2{m[0], m[2]}, half2{m[1], m[3]}));
+            }
+        };
+        Run v[kPasses];
+#pragma unroll
+        for (int r = 0; r < kPasses; ++r)
+#pragma unroll
+            for (int t = 0; t < kRun / 2; ++t) {
+                const int n = (own % kRuns * kRun >> 1) + t, p = n >> logQ, q = n & ((1 << logQ) - 1);
+                const Pair pair = two(from + (unsigned)(r * (64 / kRuns) * kPitch) + (unsigned)(p * 2 * F + q * 4) * (unsigned)sizeof(T));
+                if constexpr (kSplit) v[r][2 * t] = pair[0], v[r][2 * t + 1] = pair[1];
+                else v[r][t] = pair;
+            }
+#pragma unroll
+        for (int r = 0; r < kPasses; ++r) asm volatile("" : "+v"(v[r]));
+        const int o = ofirst + own % kRuns * kRun * 4, u = fdiv(o, la.fd_EF), k = kfirst + mk * 32 + row;
+        const int plane_out = la.EF >> 2;
+        Run* to = reinterpret_cast<Run*>(static_cast<T*>(la.y) + ((size_t)u * la.K + k) * plane_out + ((o - u * la.EF) >> 2));
+        const int rows_left = o < la.nout && (kAll >= 64 || own < kAll) ? la.K - k : 0;
+        const size_t step = (size_t)(64 / kRuns) * plane_out / kRun;
+#pragma unroll
+        for (int r = 0; r < kPasses; ++r) {
+            if (r * (64 / kRuns) < rows_left) {
+                if constexpr (sizeof(Run) == 16) __builtin_nontemporal_store(v[r], to + r * step);
+                else to[r * step] = v[r];
+            }
+        }
+    };
     const bool in_runs = late_arguments().out_runs && __ballot(bad != 0) == 0;
     // (the sums as they are: else the compiler copies them apart before the branch, and the smallest variant spills)
 #pragma unroll
@@ -1043,8 +1096,13 @@ __global__ __launch_bounds__(64 * kWaves<KS>, (kResident<T, MK, NP, AHEAD, FLY, 
                     lds_put(to + (unsigned)(((i >> 2) * 8 + (i & 3)) * kPitch + np * 32 * (int)sizeof(T)), (T)scaled(acc[mk][np][i], i, exponent));
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            if (late_arguments().out_runs == 16) put_runs(mk, uint4v{});
-            else put_runs(mk, uint2v{});
+            if (late_arguments().pool) {
+                if (late_arguments().out_runs == 16) put_pooled(mk, uint4v{});
+                else put_pooled(mk, uint2v{});
+            } else {
+                if (late_arguments().out_runs == 16) put_runs(mk, uint4v{});
+                else put_runs(mk, uint2v{});
+            }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
     } else

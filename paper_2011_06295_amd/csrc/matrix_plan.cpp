@@ -272,8 +272,10 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     p.wide_fly = (CG * p.quads + 64 * waves(KS) - 1) / (64 * waves(KS)) > 1 && MK * NP * pieces < 8 ? 2 : 1;
     long long lds = (long long)(p.nchunks > 1 ? 2 : 1) * CG * p.EB * 64 * 16 * pieces;
     if (KS > 1) lds = std::max(lds, (long long)meeting_bytes(MK, NP, KS));   // where the sums of a pair meet
-    // outputs in runs, where a plane is whole ones: 32 rows of a wavefront's outputs at a time go through LDS
-    p.out_runs = pool || EF * elem_bytes % 8 ? 0 : EF * elem_bytes % 16 ? 8 : 16;
+    // outputs in runs, where a plane is whole ones: 32 rows of a wavefront's outputs at a time go through LDS (pooled: rows of
+    // four at least, whose windows begin at whole words)
+    const long long plane_bytes = (pool ? EF / 4 : EF) * elem_bytes;
+    p.out_runs = (pool && p.F < 4) || plane_bytes % 8 ? 0 : plane_bytes % 16 ? 8 : 16;
     if (p.out_runs) lds = std::max(lds, (long long)out_runs_lds(p, elem_bytes));
     lds += 64 + 8 * 32 * MK * WK;             // what the wavefronts tell each other, bias and scale of the rows
     if (pieces == 2) lds += matrix_extra_lds(p);
@@ -352,7 +354,7 @@ Shapes shapes(bool split)
     return split ? Shapes{std::begin(kShapes32), std::end(kShapes32)} : Shapes{std::begin(kShapes16), std::end(kShapes16)};
 }
 
-int check_matrix_plan(int K, int C, int R, int S, int elem_bytes, const Geometry& g, const MatrixPlan& p)
+int check_matrix_plan(int K, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, const MatrixPlan& p)
 {
     const int pieces = elem_bytes == 4 ? 2 : 1, RS = R * S, own = p.CG / 2 / p.KS * RS;
     // 14: the channels are covered, the steps come out, the table holds what the last block asks for (last steps' weights ahead)
@@ -364,7 +366,7 @@ int check_matrix_plan(int K, int C, int R, int S, int elem_bytes, const Geometry
     const long long buffers = (long long)(p.nchunks > 1 ? 2 : 1) * p.CG * p.EB * 1024 * pieces, rows = 32ll * p.MK * p.WK;
     const long long behind = 64 + 8 * rows + (pieces == 2 ? matrix_extra_lds(p) : 0);
     if (p.lds_bytes > kMaxLds || buffers + behind > p.lds_bytes || (p.KS > 1 && meeting_bytes(p.MK, p.NP, p.KS) + behind > p.lds_bytes)) return 15;
-    if (p.out_runs && (out_runs_lds(p, elem_bytes) + behind > p.lds_bytes || (long long)p.E * p.F * elem_bytes % p.out_runs)) return 15;
+    if (p.out_runs && (out_runs_lds(p, elem_bytes) + behind > p.lds_bytes || (long long)p.E * p.F / (pool ? 4 : 1) * elem_bytes % p.out_runs)) return 15;
     if (p.kblocks * rows < K || (long long)p.ntiles * p.PT < p.nout || p.WK * p.WP * p.KS != waves(p.KS) || p.PT != 32 * p.NP * p.WP) return 15;
     if (p.grid % 8 || p.grid < (long long)p.ntiles * p.kblocks) return 15;
     // 17: (wide staging) the tile's runs of pixels hold every input that its taps read
@@ -402,7 +404,7 @@ int check_matrix_plans(int K, int C, int R, int S, int elem_bytes, const Geometr
         for (int CG = 2; CG <= 2 * most_groups(sh[3]); CG *= 2) {
             MatrixPlan p;
             if (!plan_matrix(K, C, R, S, elem_bytes, g, pool, sh[0], sh[1], sh[2], sh[3], CG, p)) continue;
-            const int bad = check_matrix_plan(K, C, R, S, elem_bytes, g, p);
+            const int bad = check_matrix_plan(K, C, R, S, elem_bytes, g, pool, p);
             if (bad) return bad;
         }
     return 0;
