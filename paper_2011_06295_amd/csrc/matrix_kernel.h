@@ -268,8 +268,6 @@ __device__ __forceinline__ bool summable(const ImageWindow& w)
     return by >= -kMaxApart && by <= kMaxApart && w.high > window_low(1);
 }
 
-__device__ __forceinline__ bool finite(float v) { return __builtin_fabsf(v) <= 3.402823466e38f; }
-
 }  // namespace
 
 // Wavefronts of a workgroup.
@@ -414,9 +412,6 @@ __global__ __launch_bounds__(64 * kWaves<KS>, (kResident<T, MK, NP, AHEAD, FLY, 
         const int Y = fdiv(q0, a.fd_Wp), X = q0 - Y * a.Wp - a.pad, y = Y - fdiv(Y, a.fd_Hs) * a.Hs - a.pad;
         const int inside = y < 0 ? 0 : y * a.W + (X < 0 ? 0 : X < a.W ? X : a.W);
         quad0 = u0 * a.plane_quads + (inside < a.H * a.W ? inside : a.H * a.W) / kPx;
-        const half8 zero = {};
-        const unsigned all = a.padded ? (a.nchunks > 1 ? 2u : 1u) * buffer : 0u;
-        for (unsigned i = (unsigned)tid * 16u; i < all; i += (unsigned)kThreads * 16u) lds_write(lds0 + i, zero);
     }
     const int blocks = WIDE ? nwide : nblk;     // what the wavefronts share
     staged st[FLY][8];
@@ -690,6 +685,11 @@ __global__ __launch_bounds__(64 * kWaves<KS>, (kResident<T, MK, NP, AHEAD, FLY, 
     fetch(0);
 #pragma unroll
     for (int i = 0; i < AHEAD; ++i) load_a(A[i]);
+    if constexpr (WIDE) {                                // the padding is cleared while the first loads are on their way
+        const half8 zero = {};
+        const unsigned all = a.padded ? (a.nchunks > 1 ? 2u : 1u) * buffer : 0u;
+        for (unsigned i = (unsigned)tid * 16u; i < all; i += (unsigned)kThreads * 16u) lds_write(lds0 + i, zero);
+    }
     if constexpr (kSplit) first_windows();
     take_scales();
     if constexpr (WIDE && !kSplit)
@@ -940,12 +940,15 @@ __global__ __launch_bounds__(64 * kWaves<KS>, (kResident<T, MK, NP, AHEAD, FLY, 
     }
 #pragma unroll
     for (int np = 0; np < kNP; ++np) {
-        bool ok = true;
+        // (a value that is not finite makes 0 * value, and every sum with it, a NaN: one instruction a value, in two chains; 128 values
+        // compared one by one took 1.3 to 1.6 us, 0.4 so)
+        float none[2] = {0.f, 0.f};
 #pragma unroll
         for (int mk = 0; mk < kMK; ++mk)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) ok = ok & finite(acc[mk][np][i]);
-        bad |= ok ? 0u : 1u << np;
+            for (int i = 0; i < 16; ++i) none[i & 1] = __builtin_fmaf(acc[mk][np][i], 0.f, none[i & 1]);
+        const float all = none[0] + none[1];
+        bad |= all == all ? 0u : 1u << np;
     }
     bad |= (unsigned)__shfl_xor((int)bad, 32);           // the lane that holds the other rows of the same outputs
 
@@ -966,10 +969,10 @@ __global__ __launch_bounds__(64 * kWaves<KS>, (kResident<T, MK, NP, AHEAD, FLY, 
     const int kfirst = (kf0 + (KS > 1 ? wave / NP : 0)) * 32;                  // first output channel and
     const int ofirst = o0 + (wp * NP + (KS > 1 ? wave % NP : 0)) * 32;         // first output of the wavefront's sums
     const int krow0 = kfirst + late_half * 4;
-    auto finish = [&](float v, float b) __attribute__((always_inline)) {       // section 3: bias, then activation
-        v += b;
-        return la.relu ? (v > 0.f ? v : 0.f) : v;
-    };
+    // section 3: bias, then activation.  (The larger of a number and a NaN is the number: one instruction with ReLU and without, and
+    // a NaN becomes 0 under ReLU, as where it is compared with 0.)
+    const float least = la.relu ? 0.f : __builtin_nanf("");
+    auto finish = [&](float v, float b) __attribute__((always_inline)) { return __builtin_fmaxf(v + b, least); };
     // What the table holds for the lane's 16 rows of a fragment, in registers before the fragment's first store (read
     // inside the branches below, each of them would wait for its own).
     const int table_row = kfirst - kb * rows + late_half * 4;
@@ -1029,8 +1032,8 @@ __global__ __launch_bounds__(64 * kWaves<KS>, (kResident<T, MK, NP, AHEAD, FLY, 
     };
     // Pooled outputs in runs.  A wavefront's outputs are whole pairs of rows, so its maxima are consecutive too.  One by one each of
     // a fragment's 16 registers takes a store of which a quarter of the lanes hold something, and on rows of 16 or fewer a trip through
-    // LDS for the row below: 14.4 us of 36 (128 -> 128 channels, 16 x 16, binary16, batch 256; 64 -> 64, 32 x 32: 7.1 of 31), 3.0
-    // (2.6) so.  So all outputs go to LDS as above and a lane reads the windows of a run.  (Rows of two have windows of half
+    // LDS for the row below: 14.4 us of 36 (128 -> 128 channels, 16 x 16, binary16, batch 256; 64 -> 64, 32 x 32: 7.1 of 31), 3.2
+    // (3.5) so.  So all outputs go to LDS as above and a lane reads the windows of a run.  (Rows of two have windows of half
     // a word in two rows; they stay one by one.)
     auto put_pooled = [&](int mk, auto run) {
         using Run = decltype(run);
@@ -1087,7 +1090,9 @@ __global__ __launch_bounds__(64 * kWaves<KS>, (kResident<T, MK, NP, AHEAD, FLY, 
 #pragma unroll
         for (int mk = 0; mk < kMK; ++mk) {
             take_rows(mk);
-            const unsigned to = lds0 + (unsigned)((wave * 32 + late_half * 4) * kPitch) + (unsigned)(late_lane & 31) * (unsigned)sizeof(T);
+            unsigned to = lds0 + (unsigned)((wave * 32 + late_half * 4) * kPitch) + (unsigned)(late_lane & 31) * (unsigned)sizeof(T);
+            asm volatile("" : "+v"(to));         // (the rest of an address is the instruction's offset, not two additions a value:
+                                                 // with ReLU by one instruction 4.7 -> 3.3 us for 2 x 4 fragments)
 #pragma unroll
             for (int np = 0; np < kNP; ++np) {
                 const int exponent = unscale(ofirst + np * 32 + (late_lane & 31));
