@@ -213,7 +213,7 @@ int check_plan(const Csr& csr, int N, int C, int R, int S, int elem_bytes, const
 
 // Division by a run-time constant: q = n / d for 0 <= n < 2^31.
 struct FastDiv {
-    uint32_t mul, shift, d;
+    uint32_t mul, shift;
 };
 FastDiv make_fastdiv(int d);
 

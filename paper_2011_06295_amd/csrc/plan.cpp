@@ -253,16 +253,16 @@ int output_tile_groups(long long nout, int PT, int EF, int F, int Hs, int st, in
 
 }  // namespace
 
-// floor(n / d) = (n * mul) >> (32 + shift) for every 0 <= n < 2^31, where
-// mul = floor(2^(31+s) / d) + 1 and shift = s - 1 with 2^(s-1) < d <= 2^s.
+// floor(n / d) = (n * mul) >> (31 + shift) for every 0 <= n < 2^31, the upper half of 2 n * mul shifted, where
+// mul = floor(2^(31+shift) / d) + 1 and 2^(shift-1) < d <= 2^shift (d = 1: mul = 2^31 + 1, shift = 0).
 FastDiv make_fastdiv(int d)
 {
-    FastDiv f{0u, 0u, (uint32_t)d};
-    if (d <= 1) return f;
+    FastDiv f{0u, 0u};
+    d = std::max(d, 1);
     int s = 0;
     while ((1ll << s) < d) ++s;
     f.mul = (uint32_t)((1ull << (31 + s)) / (uint64_t)d + 1ull);
-    f.shift = (uint32_t)(s - 1);
+    f.shift = (uint32_t)s;
     return f;
 }
 
