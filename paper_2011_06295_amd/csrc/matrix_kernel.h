@@ -277,7 +277,8 @@ template <int KS>
 constexpr int kWaves = KS > 4 ? KS : 4;
 
 // Wavefronts a SIMD holds at least: the smallest variant (1 x 1 layers mostly, which load and store more than they multiply)
-// fits 128 registers but for one, and four of it are faster than three (64 -> 256 channels, 56 x 56, binary16: 71 and 79 us).
+// would take 130 registers, fits 128 without scratch, and four of it are faster than three (64 -> 256 channels, 56 x 56, binary16: 47 and
+// 55 us; 40 layers 1.5 % in the mean, one 2 % slower).
 template <typename T, int MK, int NP, int AHEAD, int FLY, int KS, bool WIDE>
 constexpr int kResident = sizeof(T) == 2 && MK * NP == 4 && AHEAD == 2 && FLY <= 2 && KS == 1 && !WIDE ? 4 : 2;
 
@@ -960,9 +961,9 @@ __global__ __launch_bounds__(64 * kWaves<KS>, (kResident<T, MK, NP, AHEAD, FLY, 
         if constexpr (kSplit) return late_arguments();
         return a;
     }();
-    // (kSplit: the lane's number is asked for anew: kept since the kernel's start it would be spilled)
+    // (kSplit, and the variant of 128 registers: the lane's number is asked for anew: kept since the kernel's start it would be spilled)
     int late_lane = lane;
-    if constexpr (kSplit) {
+    if constexpr (kSplit || kResident<T, MK, NP, AHEAD, FLY, KS, WIDE> == 4) {
         late_lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
         asm volatile("" : "+v"(late_lane));
     }

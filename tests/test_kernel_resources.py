@@ -1,0 +1,68 @@
+"""Registers and scratch of the built kernels, as their code objects state them.  Needs no GPU."""
+import re
+import struct
+
+import msgpack
+import pytest
+
+from paper_2011_06295_amd import build
+
+_MATRIX = re.compile(r"matrix_kernelI(DF16_|f)Li(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb(\d)EEE")
+
+
+def _code_objects(data):
+    """The gfx950 ELF images of the library's offload bundles."""
+    magic, at = b"__CLANG_OFFLOAD_BUNDLE__", 0
+    while (at := data.find(magic, at)) >= 0:
+        p = at + len(magic) + 8
+        for _ in range(struct.unpack_from("<Q", data, p - 8)[0]):
+            offset, size, length = struct.unpack_from("<QQQ", data, p)
+            if b"gfx950" in data[p + 24:p + 24 + length]:
+                yield data[at + offset:at + offset + size]
+            p += 24 + length
+        at += len(magic)
+
+
+def _metadata(elf):
+    """The kernels' entries of an image's AMDGPU metadata note (type 32)."""
+    table, = struct.unpack_from("<Q", elf, 40)
+    entry, count = struct.unpack_from("<HH", elf, 58)
+    for i in range(count):
+        kind, = struct.unpack_from("<I", elf, table + i * entry + 4)
+        offset, size = struct.unpack_from("<QQ", elf, table + i * entry + 24)
+        p, end = offset, offset + size
+        while kind == 7 and p + 12 <= end:
+            namesz, descsz, note = struct.unpack_from("<III", elf, p)
+            desc = p + 12 + (namesz + 3) // 4 * 4
+            if note == 32:
+                yield from msgpack.unpackb(elf[desc:desc + descsz])["amdhsa.kernels"]
+            p = desc + (descsz + 3) // 4 * 4
+
+
+@pytest.fixture(scope="module")
+def matrix_kernels():
+    """(type, MK, NP, steps ahead, blocks in flight, KS, runs) of every matrix kernel -> its metadata."""
+    found = {}
+    with open(build.LIB, "rb") as f:
+        data = f.read()
+    for elf in _code_objects(data):
+        for kernel in _metadata(elf):
+            m = _MATRIX.search(kernel[".name"])
+            if m:
+                found[("f32" if m[1] == "f" else "f16", *map(int, m.groups()[1:]))] = kernel
+    assert found
+    return found
+
+
+def _wavefronts(kernel):
+    """That a SIMD's 512 registers a lane hold."""
+    return min(8, 512 // ((kernel[".vgpr_count"] + 7) // 8 * 8))
+
+
+def test_binary16_matrix_kernels_use_no_scratch(matrix_kernels):
+    kept = {v: k[".private_segment_fixed_size"] for v, k in matrix_kernels.items() if v[0] == "f16" and k[".private_segment_fixed_size"]}
+    assert not kept, kept
+
+
+def test_the_smallest_variant_has_four_wavefronts_a_simd(matrix_kernels):
+    assert _wavefronts(matrix_kernels[("f16", 2, 2, 2, 2, 1, 0)]) == 4
