@@ -320,6 +320,8 @@ struct MatrixPlan {
 };
 constexpr int kImageWindowBytes = 24;   // fp32: LDS bytes for each of them
 bool stages_runs(const MatrixPlan& p, int elem_bytes);
+// Workgroups of a variant that the registers of a CU hold (fly: of single pixels; runs: blocks of runs in flight, 0 for single pixels).
+int matrix_resident(int MK, int NP, int KS, int ahead, int fly, int runs, bool split);
 // Fills p for the given split; false if the kernel cannot run it.
 bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, int MK, int NP, int WK, int KS,
                  int CG, MatrixPlan& p);

@@ -288,6 +288,22 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     return true;
 }
 
+int matrix_resident(int MK, int NP, int KS, int ahead, int fly, int runs, bool split)
+{
+    const int unit = split ? 1 : 2, pieces = split ? 2 : 1;
+    // eight wavefronts are two a SIMD: 71 to 80 registers hold three such workgroups, 86 to 128 two, 133 one
+    if (KS > 4) {
+        if (MK * NP == 1) return runs == 1 || (!runs && fly == unit) ? 3 : 2;
+        return !runs && ahead == 3 && fly == 3 * unit ? 1 : 2;
+    }
+    // four are one: two, three of the small variants (fp32 with three steps of weights ahead and two blocks in flight: 169 registers, two),
+    // four of the smallest
+    if (MK * NP * pieces > 4) return 2;
+    if (runs) return split && runs == 2 ? 2 : 3;
+    if (!split && ahead == 2 && fly == unit && KS == 1) return 4;
+    return fly == 3 * unit || (split && ahead == 3 && fly == 2) ? 2 : 3;
+}
+
 namespace {
 
 // Rough time of one launch in microseconds.  Structure and constants are fitted to the measured times of every split (3278 of
@@ -313,14 +329,10 @@ double estimate_matrix(const MatrixPlan& p, int RS, bool split, double listed)
                         k32 = {11800, 7, 49.0, 38.9, 1.5, 306, 45, 139, 6, 290, 1.19, 676, 2110, 1.09},
                         k16_8 = {7190, 230, 0, 28, 0, 1100, 0, 56.4, 0, 190, 1.77, 0, 4700, 1.05};
     const Clocks& k = split ? k32 : p.KS > 4 ? k16_8 : k16;
-    const int unit = split ? 1 : 2, pieces = split ? 2 : 1;
+    const int pieces = split ? 2 : 1;
     const bool runs = stages_runs(p, split ? 4 : 2);
     const int blocks = runs ? (p.CG * p.quads + 63) / 64 : p.CG * p.EB, fly = runs ? p.wide_fly : p.fly;
-    // workgroups a CU holds: registers allow two, three of the small variants, four of the smallest; of eight wavefronts, two, three
-    // of the smallest variant
-    const int room = p.KS > 4 ? (p.MK * p.NP == 1 && fly <= 2 ? 3 : 2) : p.MK * p.NP * pieces > 4 ? 2 : !split && p.ahead == 2 && p.fly == unit && p.KS == 1 && !runs ? 4 :
-                     fly == (runs ? (split ? 2 : 0) : 3 * unit) ? 2 : 3;
-    const int conc_max = std::min(room, kMaxLds / p.lds_bytes);
+    const int conc_max = std::min(matrix_resident(p.MK, p.NP, p.KS, p.ahead, p.fly, runs ? p.wide_fly : 0, split), kMaxLds / p.lds_bytes);
     const double mf = p.MK * p.NP * (split ? 3 : 1), own = (double)(p.CG / 2 / p.KS) * RS;
     const double late = std::max(0, (blocks + waves(p.KS) - 1) / waves(p.KS) - fly) * k.late, begin = runs ? k.run_chunk : k.stage_chunk;
     const double pair = p.KS > 4 && !p.out_runs ? 1.35 * k.pair : k.pair;

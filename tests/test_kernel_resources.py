@@ -1,11 +1,12 @@
 """Registers and scratch of the built kernels, as their code objects state them.  Needs no GPU."""
+import ctypes as C
 import re
 import struct
 
 import msgpack
 import pytest
 
-from paper_2011_06295_amd import build
+from paper_2011_06295_amd import binding as B, build
 
 _MATRIX = re.compile(r"matrix_kernelI(DF16_|f)Li(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb(\d)EEE")
 
@@ -66,3 +67,15 @@ def test_binary16_matrix_kernels_use_no_scratch(matrix_kernels):
 
 def test_the_smallest_variant_has_four_wavefronts_a_simd(matrix_kernels):
     assert _wavefronts(matrix_kernels[("f16", 2, 2, 2, 2, 1, 0)]) == 4
+
+
+def test_the_estimate_counts_the_workgroups_that_registers_hold(matrix_kernels):
+    resident = B.raw_library()["_ZN2sc15matrix_residentEiiiiiib"]   # sc::matrix_resident(MK, NP, KS, ahead, fly, runs, split)
+    resident.argtypes = [C.c_int] * 6 + [C.c_bool]
+    wrong = {}
+    for (dtype, MK, NP, ahead, fly, KS, wide), kernel in matrix_kernels.items():
+        counted = resident(MK, NP, KS, ahead, 0 if wide else fly, fly if wide else 0, dtype == "f32")
+        held = _wavefronts(kernel) // (2 if KS == 8 else 1)
+        if counted != held:
+            wrong[dtype, MK, NP, ahead, fly, KS, wide] = counted, held
+    assert not wrong, wrong
