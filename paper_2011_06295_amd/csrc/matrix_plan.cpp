@@ -256,9 +256,10 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     p.images = (int)images;
     if (images * C * g.H * g.W * elem_bytes >= (1ll << 31)) return false;
     if (CG / 2 > most_groups(KS) || CG / 2 % KS) return false;
-    // Eight wavefronts: from 64 channels on, a group of 16 for every other of them, and where there is more than one tile of theirs.  (One
-    // tile or less is a launch of 6 us, bound by its issue, and up to 1 us faster so; below 64 channels most wavefronts have none.)
-    if (KS > 4 && (C < 64 || nout <= 32)) return false;
+    // Eight wavefronts: above 64 channels, and where there are more than 32 outputs.  (A launch of 32 or fewer takes 6 us, bound by its
+    // issue, and up to 1 us less so.  With 64 channels or fewer half of the wavefronts and more have none to multiply: 163 layers of 33 to 64
+    // channels that would take it, of 6 to 12 us, gain 3 % in the mean, where those above gain 20, and 17 of them lose 3 to 24 %.)
+    if (KS > 4 && (C <= 64 || nout <= 32)) return false;
     p.CG = CG;
     const int own = CG / 2 / KS * R * S;
     if (own % 3 && own % 2) return false;           // the kernel walks a chunk two or three steps at a time
@@ -306,6 +307,13 @@ int matrix_resident(int MK, int NP, int KS, int ahead, int fly, int runs, bool s
 
 namespace {
 
+// Workgroups of a plan that a CU holds.
+int resident_workgroups(const MatrixPlan& p, bool split)
+{
+    const int runs = stages_runs(p, split ? 4 : 2) ? p.wide_fly : 0;
+    return std::min(matrix_resident(p.MK, p.NP, p.KS, p.ahead, p.fly, runs, split), kMaxLds / p.lds_bytes);
+}
+
 // Rough time of one launch in microseconds.  Structure and constants are fitted to the measured times of every split (3278 of
 // them) of 186 layers (the 32-pixel VGG-16's, those of larger networks, and random ones: 1 x 1, 1-D, 3 x 3, 5 x 5, stride 2,
 // batches of 1 to 256): 10 % rms of the logarithm, the cheapest by estimate 2 % slower than the fastest measured in the mean.
@@ -332,7 +340,7 @@ double estimate_matrix(const MatrixPlan& p, int RS, bool split, double listed)
     const int pieces = split ? 2 : 1;
     const bool runs = stages_runs(p, split ? 4 : 2);
     const int blocks = runs ? (p.CG * p.quads + 63) / 64 : p.CG * p.EB, fly = runs ? p.wide_fly : p.fly;
-    const int conc_max = std::min(matrix_resident(p.MK, p.NP, p.KS, p.ahead, p.fly, runs ? p.wide_fly : 0, split), kMaxLds / p.lds_bytes);
+    const int conc_max = resident_workgroups(p, split);
     const double mf = p.MK * p.NP * (split ? 3 : 1), own = (double)(p.CG / 2 / p.KS) * RS;
     const double late = std::max(0, (blocks + waves(p.KS) - 1) / waves(p.KS) - fly) * k.late, begin = runs ? k.run_chunk : k.stage_chunk;
     const double pair = p.KS > 4 && !p.out_runs ? 1.35 * k.pair : k.pair;
@@ -493,8 +501,12 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
     for (const auto& sh : shapes(split))
         for (int CG = 2; CG <= 2 * most_groups(sh[3]); CG *= 2) {
             MatrixPlan p;
-            if (CG > 2 && CG / 2 >= 2 * ((C + 15) / 16)) break;   // a smaller chunk holds them all
+            if (CG > 2 && CG / 2 >= 2 * ((C + 15) / 16)) break;   // a smaller chunk holds them all (eight wavefronts': 128 of more than 64 channels)
             if (!plan_matrix(csr.K, C, R, S, elem_bytes, g, pool, sh[0], sh[1], sh[2], sh[3], CG, p)) continue;
+            // Eight wavefronts are for launches that leave CUs without a tile.  In more than two rounds of workgroups, where the estimate
+            // knows them less well, the best such split of 163 layers is slower than the one of four wavefronts, by 8 % at least (127 -> 29,
+            // 54 x 54, batch 45: 31.0 and 33.4 us); up to one round 288 of 315 are faster, by 19 % in the mean.
+            if (p.KS > 4 && (long long)p.ntiles * p.kblocks > 2ll * kCUs * resident_workgroups(p, split)) continue;
             if (split) {
                 // Squared relative error of an output, in units of 1e-14, fitted to the measured ones: the tile kernel rounds
                 // its sum at every term (1.8e-7 at 100); here the pieces' own error, three roundings a step of a chunk's

@@ -137,3 +137,25 @@ def test_a_launch_that_may_fit_the_static_scratch_is_not_given_up(layer, want):
     N, C, K, R, H, density = layer
     plan = _choice(N, C, K, R, H, 1, density)
     assert {k: plan[k] for k in want} == want
+
+
+def _split(N, C, K, R, H, density):
+    rng = np.random.default_rng(26)
+    w = rng.standard_normal((K, C, R, R), dtype=np.float32)
+    layer = B.SparseConv(w, (rng.random(w.shape, dtype=np.float32) < density).astype(np.uint8), dtype="f16")
+    plan = layer.get_matrix_plan(N, H, H, 1, R // 2) if layer.get_kernel(N, H, H, 1, R // 2) == "matrix" else None
+    assert layer.check_plan(N, H, H, 1, R // 2) == 0
+    layer.close()
+    return plan
+
+
+@pytest.mark.parametrize("C,KS", [(48, 4), (64, 4), (65, 8), (128, 8)])
+def test_eight_wavefronts_share_more_than_64_channels(C, KS):
+    """With 64 or fewer, half of them have none to multiply."""
+    assert _split(1, C, 128, 3, 14, 0.1)["KS"] == KS
+
+
+def test_eight_wavefronts_are_for_launches_of_few_workgroups():
+    """127 -> 29, 54 x 54, batch 45, 80 %: 33.4 us by eight wavefronts in 2056 workgroups, 31.0 by four in 520; batch 1: by eight."""
+    assert _split(45, 127, 29, 3, 54, 0.2)["KS"] == 1
+    assert _split(1, 127, 29, 3, 54, 0.2)["KS"] == 8
