@@ -202,12 +202,11 @@ int out_runs_lds(const MatrixPlan& p, int elem_bytes) { return 4 * 32 * ((p.KS >
 bool stages_runs(const MatrixPlan& p, int elem_bytes) { return p.quads && p.fly > (elem_bytes == 4 ? 1 : 2); }
 
 // Whether planes that are not whole runs are staged in runs, the last of a plane overlapping the one before it; `blocks`: of single
-// pixels, a wavefront and chunk.  Of 4400 splits of 145 layers with such planes, those with more than four blocks are 15 % faster so in the
-// mean, none slower by more than 3 % (173 -> 354 channels, 25 x 25, binary16: 17.2 -> 13.8 us).  With four or fewer, all in flight as single
-// pixels, binary16 under 3 x 3 and 5 x 5 taps still gains 10 %; under 1 x 1 taps up to 31 % is lost, in fp32 up to 43 %, 5 % under
-// 3 x 3 taps.  Layers of fewer than 64 channels would gain 7 % and stay as they are: they are what the kernels that stage single pixels
-// are tested by.
-bool ragged_runs(int C, int RS, int blocks, int elem_bytes) { return C >= 64 && blocks > (RS == 1 || elem_bytes == 4 ? 4 : 2); }
+// pixels, a wavefront and chunk.  Every split of 1693 layers with such planes timed both ways, those within 30 % of their layer's best:
+// binary16 4613 that stage runs by this rule, 0.87 of the time in the mean, 20 slower by 3 to 9 % (173 -> 354 channels, 25 x 25: 17.2 ->
+// 13.8 us); fp32 1199, 0.92, two slower.  With four blocks or fewer under 1 x 1 taps half of binary16 splits lose, up to 36 %, and three
+// quarters of fp32 ones, up to 59 %; under larger taps fp32 would gain 5 %, but one in 27 loses, up to 11 %.
+bool ragged_runs(int RS, int blocks, int elem_bytes) { return blocks > (RS == 1 || elem_bytes == 4 ? 4 : 2); }
 
 bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, int MK, int NP, int WK, int KS,
                  int CG, MatrixPlan& p)
@@ -269,7 +268,7 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     p.ahead = own % 3 == 0 && !(pieces == 2 && own % 2 == 0) ? 3 : 2;
     const int unit = pieces == 2 ? 1 : 2, blocks = (CG * p.EB + waves(KS) - 1) / waves(KS);   // a chunk's staging blocks of a wavefront
     p.fly = blocks <= unit ? unit : blocks < 3 * unit ? 2 * unit : 3 * unit;
-    p.quads = (plane % px == 0 || (plane > px && ragged_runs(C, R * S, blocks, elem_bytes))) && g.W >= 2 && quads > 0 ? (int)quads : 0;
+    p.quads = (plane % px == 0 || (plane > px && ragged_runs(R * S, blocks, elem_bytes))) && g.W >= 2 && quads > 0 ? (int)quads : 0;
     p.wide_fly = (CG * p.quads + 64 * waves(KS) - 1) / (64 * waves(KS)) > 1 && MK * NP * pieces < 8 ? 2 : 1;
     long long lds = (long long)(p.nchunks > 1 ? 2 : 1) * CG * p.EB * 64 * 16 * pieces;
     if (KS > 1) lds = std::max(lds, (long long)meeting_bytes(MK, NP, KS));   // where the sums of a pair meet

@@ -17,7 +17,9 @@ SHAPES = [("f16", (70, 65, 130, 3, 3, 25, 13, 1, 0)), ("f16", (70, 70, 130, 3, 3
           ("f16", (3, 64, 130, 2, 2, 13, 2, 1, 1)), ("f16", (150, 64, 64, 3, 3, 1, 5, 1, 1)), ("f16", (150, 300, 130, 1, 3, 9, 6, 1, 0)),
           ("f16", (30, 64, 64, 3, 3, 21, 2, 2, 1)),
           ("f32", (150, 64, 130, 5, 5, 13, 13, 1, 1)), ("f32", (150, 64, 130, 3, 3, 13, 5, 1, 0)), ("f32", (30, 96, 130, 3, 3, 15, 3, 1, 1)),
-          ("f32", (150, 200, 130, 1, 1, 5, 9, 2, 1)), ("f32", (150, 64, 130, 2, 2, 15, 3, 1, 1))]
+          ("f32", (150, 200, 130, 1, 1, 5, 9, 2, 1)), ("f32", (150, 64, 130, 2, 2, 15, 3, 1, 1)),
+          ("f16", (150, 40, 64, 3, 3, 7, 7, 1, 1)), ("f16", (30, 17, 130, 5, 5, 9, 11, 1, 2)), ("f16", (3, 48, 33, 2, 2, 13, 3, 2, 1)),
+          ("f32", (24, 62, 73, 3, 3, 19, 11, 2, 1)), ("f32", (169, 33, 56, 1, 2, 17, 17, 2, 1))]
 
 
 @pytest.mark.parametrize("dtype,shape", SHAPES, ids=lambda v: v if isinstance(v, str) else "x".join(map(str, v)))

@@ -139,12 +139,12 @@ def test_a_launch_that_may_fit_the_static_scratch_is_not_given_up(layer, want):
     assert {k: plan[k] for k in want} == want
 
 
-def _split(N, C, K, R, H, density):
+def _split(N, C, K, R, H, density, stride=1):
     rng = np.random.default_rng(26)
     w = rng.standard_normal((K, C, R, R), dtype=np.float32)
     layer = B.SparseConv(w, (rng.random(w.shape, dtype=np.float32) < density).astype(np.uint8), dtype="f16")
-    plan = layer.get_matrix_plan(N, H, H, 1, R // 2) if layer.get_kernel(N, H, H, 1, R // 2) == "matrix" else None
-    assert layer.check_plan(N, H, H, 1, R // 2) == 0
+    plan = layer.get_matrix_plan(N, H, H, stride, R // 2) if layer.get_kernel(N, H, H, stride, R // 2) == "matrix" else None
+    assert layer.check_plan(N, H, H, stride, R // 2) == 0
     layer.close()
     return plan
 
@@ -159,3 +159,9 @@ def test_eight_wavefronts_are_for_launches_of_few_workgroups():
     """127 -> 29, 54 x 54, batch 45, 80 %: 33.4 us by eight wavefronts in 2056 workgroups, 31.0 by four in 520; batch 1: by eight."""
     assert _split(45, 127, 29, 3, 54, 0.2)["KS"] == 1
     assert _split(1, 127, 29, 3, 54, 0.2)["KS"] == 8
+
+
+@pytest.mark.parametrize("C", [24, 40, 63, 64])
+def test_odd_planes_are_staged_in_runs_whatever_their_channels(C):
+    """Of 2051 splits of layers with fewer than 64 channels the mean is 11 % faster so."""
+    assert _split(150, C, 64, 3, 17, 0.1)["runs"] > 0
