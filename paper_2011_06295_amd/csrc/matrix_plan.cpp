@@ -306,13 +306,6 @@ int matrix_resident(int MK, int NP, int KS, int ahead, int fly, int runs, bool s
 
 namespace {
 
-// Workgroups of a plan that a CU holds.
-int resident_workgroups(const MatrixPlan& p, bool split)
-{
-    const int runs = stages_runs(p, split ? 4 : 2) ? p.wide_fly : 0;
-    return std::min(matrix_resident(p.MK, p.NP, p.KS, p.ahead, p.fly, runs, split), kMaxLds / p.lds_bytes);
-}
-
 // Rough time of one launch in microseconds.  Structure and constants are fitted to the measured times of every split (3278 of
 // them) of 186 layers (the 32-pixel VGG-16's, those of larger networks, and random ones: 1 x 1, 1-D, 3 x 3, 5 x 5, stride 2,
 // batches of 1 to 256): 10 % rms of the logarithm, the cheapest by estimate 2 % slower than the fastest measured in the mean.
@@ -327,7 +320,9 @@ int resident_workgroups(const MatrixPlan& p, bool split)
 // within 2.4 and 1.4 % of their fastest split in the mean as well.)
 //  * Eight wavefronts that share the channels have constants of their own: 864 splits of 429 layers, 9 % rms beside the 1.06 of their
 //    time that the others' estimate has on those layers.  By it the fastest split of all is missed by 2.4 % in the mean; what was
-//    taken without them by 16 %, and no layer is more than 1 % slower than by that.
+//    taken without them by 16 %.  (Of 296 others that take them the mean is 20 % faster than by four, two are slower, by 3 and 16 %.  In more
+//    than two rounds of workgroups only rows of 32 channels or fewer take them: seven of 126 such layers, six 3 to 25 % faster, one
+//    8 % slower, as 127 -> 29, 54 x 54, batch 45, is: 31.0 -> 33.4 us.)
 //  * Weights in the list (but for a block's first ones) take 4700 clocks for eight, in a wavefront's own chain: `listed`.
 double estimate_matrix(const MatrixPlan& p, int RS, bool split, double listed)
 {
@@ -339,7 +334,7 @@ double estimate_matrix(const MatrixPlan& p, int RS, bool split, double listed)
     const int pieces = split ? 2 : 1;
     const bool runs = stages_runs(p, split ? 4 : 2);
     const int blocks = runs ? (p.CG * p.quads + 63) / 64 : p.CG * p.EB, fly = runs ? p.wide_fly : p.fly;
-    const int conc_max = resident_workgroups(p, split);
+    const int conc_max = std::min(matrix_resident(p.MK, p.NP, p.KS, p.ahead, p.fly, runs ? p.wide_fly : 0, split), kMaxLds / p.lds_bytes);
     const double mf = p.MK * p.NP * (split ? 3 : 1), own = (double)(p.CG / 2 / p.KS) * RS;
     const double late = std::max(0, (blocks + waves(p.KS) - 1) / waves(p.KS) - fly) * k.late, begin = runs ? k.run_chunk : k.stage_chunk;
     const double pair = p.KS > 4 && !p.out_runs ? 1.35 * k.pair : k.pair;
@@ -502,10 +497,6 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
             MatrixPlan p;
             if (CG > 2 && CG / 2 >= 2 * ((C + 15) / 16)) break;   // a smaller chunk holds them all (eight wavefronts': 128 of more than 64 channels)
             if (!plan_matrix(csr.K, C, R, S, elem_bytes, g, pool, sh[0], sh[1], sh[2], sh[3], CG, p)) continue;
-            // Eight wavefronts are for launches that leave CUs without a tile.  In more than two rounds of workgroups, where the estimate
-            // knows them less well, the best such split of 163 layers is slower than the one of four wavefronts, by 8 % at least (127 -> 29,
-            // 54 x 54, batch 45: 31.0 and 33.4 us); up to one round 288 of 315 are faster, by 19 % in the mean.
-            if (p.KS > 4 && (long long)p.ntiles * p.kblocks > 2ll * kCUs * resident_workgroups(p, split)) continue;
             if (split) {
                 // Squared relative error of an output, in units of 1e-14, fitted to the measured ones: the tile kernel rounds
                 // its sum at every term (1.8e-7 at 100); here the pieces' own error, three roundings a step of a chunk's
