@@ -206,7 +206,9 @@ bool stages_runs(const MatrixPlan& p, int elem_bytes) { return p.quads && p.fly 
 // binary16 4613 that stage runs by this rule, 0.87 of the time in the mean, 20 slower by 3 to 9 % (173 -> 354 channels, 25 x 25: 17.2 ->
 // 13.8 us); fp32 1199, 0.92, two slower.  With four blocks or fewer under 1 x 1 taps half of binary16 splits lose, up to 36 %, and three
 // quarters of fp32 ones, up to 59 %; under larger taps fp32 would gain 5 %, but one in 27 loses, up to 11 %.
-bool ragged_runs(int RS, int blocks, int elem_bytes) { return blocks > (RS == 1 || elem_bytes == 4 ? 4 : 2); }
+// (Fewer than 16 channels, a network's first layers: 83 that take the matrix kernel anyway gain 10 %, but by its lower estimate 11 others leave
+// the tile kernel for it, six of which lose 6 to 43 %: 1 -> 217, 207 x 207, batch 8: 44.4 and 63.4 us.)
+bool ragged_runs(int C, int RS, int blocks, int elem_bytes) { return C >= 16 && blocks > (RS == 1 || elem_bytes == 4 ? 4 : 2); }
 
 bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, int MK, int NP, int WK, int KS,
                  int CG, MatrixPlan& p)
@@ -268,7 +270,7 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     p.ahead = own % 3 == 0 && !(pieces == 2 && own % 2 == 0) ? 3 : 2;
     const int unit = pieces == 2 ? 1 : 2, blocks = (CG * p.EB + waves(KS) - 1) / waves(KS);   // a chunk's staging blocks of a wavefront
     p.fly = blocks <= unit ? unit : blocks < 3 * unit ? 2 * unit : 3 * unit;
-    p.quads = (plane % px == 0 || (plane > px && ragged_runs(R * S, blocks, elem_bytes))) && g.W >= 2 && quads > 0 ? (int)quads : 0;
+    p.quads = (plane % px == 0 || (plane > px && ragged_runs(C, R * S, blocks, elem_bytes))) && g.W >= 2 && quads > 0 ? (int)quads : 0;
     p.wide_fly = (CG * p.quads + 64 * waves(KS) - 1) / (64 * waves(KS)) > 1 && MK * NP * pieces < 8 ? 2 : 1;
     long long lds = (long long)(p.nchunks > 1 ? 2 : 1) * CG * p.EB * 64 * 16 * pieces;
     if (KS > 1) lds = std::max(lds, (long long)meeting_bytes(MK, NP, KS));   // where the sums of a pair meet
