@@ -314,7 +314,8 @@ struct MatrixPlan {
     int ahead;       // steps the weights are asked for ahead: 2 or 3, the chunk's steps of a wavefront being a multiple
     int fly;         // staging blocks a wavefront has in flight: fp32 1, 2 or 3, binary16 2, 4 or 6
     // Wide staging: a lane takes 8 bytes of each of 8 channels, four (fp32: two) consecutive pixels of one plane.
-    int quads;       // such runs of pixels of one channel group a tile holds at most; 0: the planes are not whole runs
+    int quads;       // such runs of pixels of one channel group a tile holds at most; 0: it stages single pixels
+    int odd_planes;  // ... the planes are not whole runs: the last one overlaps the run before it
     int out_runs;    // bytes of the runs that outputs are stored in (16 or 8: a plane is whole runs); 0: one by one
     int wide_fly;    // blocks of 64 of them a wavefront has in flight: 1 or 2
 };

@@ -203,12 +203,19 @@ bool stages_runs(const MatrixPlan& p, int elem_bytes) { return p.quads && p.fly 
 
 // Whether planes that are not whole runs are staged in runs, the last of a plane overlapping the one before it; `blocks`: of single
 // pixels, a wavefront and chunk.  Every split of 1693 layers with such planes timed both ways, those within 30 % of their layer's best:
-// binary16 4613 that stage runs by this rule, 0.87 of the time in the mean, 20 slower by 3 to 9 % (173 -> 354 channels, 25 x 25: 17.2 ->
+// binary16 4573 that stage runs by this rule, 0.87 of the time in the mean, five slower by 3 to 7 % (173 -> 354 channels, 25 x 25: 17.2 ->
 // 13.8 us); fp32 1199, 0.92, two slower.  With four blocks or fewer under 1 x 1 taps half of binary16 splits lose, up to 36 %, and three
 // quarters of fp32 ones, up to 59 %; under larger taps fp32 would gain 5 %, but one in 27 loses, up to 11 %.
+// (`late`: binary16 variants of 2 x 4 fragments have one block of runs in flight and six of single pixels.  Where that is all of the single
+// pixels and not all of the runs, and the layer's tensors exceed the 256 MB of the last cache, 15 of 40 splits lose 3 to 9 % by runs and the
+// mean 1 %; below 256 MB 167 gain 4 %.)
 // (Fewer than 16 channels, a network's first layers: 83 that take the matrix kernel anyway gain 10 %, but by its lower estimate 11 others leave
 // the tile kernel for it, six of which lose 6 to 43 %: 1 -> 217, 207 x 207, batch 8: 44.4 and 63.4 us.)
-bool ragged_runs(int C, int RS, int blocks, int elem_bytes) { return C >= 16 && blocks > (RS == 1 || elem_bytes == 4 ? 4 : 2); }
+bool ragged_runs(int C, int RS, int blocks, bool late, long long bytes, int elem_bytes)
+{
+    if (C < 16 || (late && blocks <= 6 && bytes > 256ll << 20)) return false;
+    return blocks > (RS == 1 || elem_bytes == 4 ? 4 : 2);
+}
 
 bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, bool pool, int MK, int NP, int WK, int KS,
                  int CG, MatrixPlan& p)
@@ -270,8 +277,18 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     p.ahead = own % 3 == 0 && !(pieces == 2 && own % 2 == 0) ? 3 : 2;
     const int unit = pieces == 2 ? 1 : 2, blocks = (CG * p.EB + waves(KS) - 1) / waves(KS);   // a chunk's staging blocks of a wavefront
     p.fly = blocks <= unit ? unit : blocks < 3 * unit ? 2 * unit : 3 * unit;
-    p.quads = (plane % px == 0 || (plane > px && ragged_runs(C, R * S, blocks, elem_bytes))) && g.W >= 2 && quads > 0 ? (int)quads : 0;
-    p.wide_fly = (CG * p.quads + 64 * waves(KS) - 1) / (64 * waves(KS)) > 1 && MK * NP * pieces < 8 ? 2 : 1;
+    p.odd_planes = plane % px != 0;
+    p.wide_fly = 1;
+    if (g.W >= 2 && quads > 0) {
+        const long long run_blocks = (CG * quads + 64 * waves(KS) - 1) / (64 * waves(KS));
+        const int wide_fly = run_blocks > 1 && MK * NP * pieces < 8 ? 2 : 1;
+        const bool late = pieces == 1 && MK * NP == 8 && run_blocks > wide_fly;
+        const long long bytes = g.N * (C * plane + K * EF / (pool ? 4 : 1)) * elem_bytes;
+        if (!p.odd_planes || (plane > px && ragged_runs(C, R * S, blocks, late, bytes, elem_bytes))) {
+            p.quads = (int)quads;
+            p.wide_fly = wide_fly;
+        }
+    }
     long long lds = (long long)(p.nchunks > 1 ? 2 : 1) * CG * p.EB * 64 * 16 * pieces;
     if (KS > 1) lds = std::max(lds, (long long)meeting_bytes(MK, NP, KS));   // where the sums of a pair meet
     // outputs in runs, where a plane is whole ones: 32 rows of a wavefront's outputs at a time go through LDS (pooled: rows of
@@ -326,7 +343,7 @@ namespace {
 //    than two rounds of workgroups only rows of 32 channels or fewer take them: seven of 126 such layers, six 3 to 25 % faster, one
 //    8 % slower, as 127 -> 29, 54 x 54, batch 45, is: 31.0 -> 33.4 us.)
 //  * Weights in the list (but for a block's first ones) take 4700 clocks for eight, in a wavefront's own chain: `listed`.
-double estimate_matrix(const MatrixPlan& p, int RS, bool split, double listed)
+double estimate_matrix(const MatrixPlan& p, int RS, bool split, double listed, double lone = 1.0)
 {
     struct Clocks { double fixed, chain, chain_mf, mf, read, chunk, stage_chunk, stage, run_chunk, run, both, late, pair, tail; };
     static const Clocks k16 = {11300, 172, 17.2, 40.9, 9.2, 482, 13, 58.5, 2, 197, 1.24, 659, 993, 1.0},
@@ -348,9 +365,23 @@ double estimate_matrix(const MatrixPlan& p, int RS, bool split, double listed)
     };
     const long long slots = (long long)kCUs * conc_max, wgs = (long long)p.ntiles * p.kblocks;
     const long long full = wgs / slots, rest = wgs % slots;
-    double t = k.fixed + (double)full * round(conc_max);
-    if (rest) t += round((double)((rest + kCUs - 1) / kCUs)) * (full ? k.tail : 1.0);
+    double t = k.fixed + (double)full * round(conc_max) * lone;
+    if (rest) t += round((double)((rest + kCUs - 1) / kCUs)) * (full ? k.tail * lone : 1.0);
     return t / 2100.0;
+}
+
+// Splits whose wavefronts share the tile out are ranked with a full round of a launch taking so much longer than the estimate says.  Runs of
+// odd planes start off a word, and where few workgroups of a CU hide their loads from one another the estimate, fitted to whole planes, is
+// low: of 1142 binary16 layers with such planes 19 are 3 to 18 % slower with this than by the split that was taken when odd planes were
+// staged pixel by pixel, the mean is 13 % faster; without, 28, by up to 20 % (301 -> 45, 71 x 71, batch 158: 296 us by single pixels, 354
+// and, with this, 319).  In fp32 (150 layers, 8 % faster in the mean, nine 3 to 19 % slower) it picks wrong as often as right, and so it does
+// beside splits whose wavefronts share the channels (102 -> 24, 47 x 47, stride 2, batch 246: 53.7 and 68.0 us).  There and beside the tile
+// kernel, which was compared with the estimate as it is, it does not count.
+double lone_rounds(const MatrixPlan& p, bool split)
+{
+    if (split || p.KS > 1 || !p.odd_planes || !stages_runs(p, 2)) return 1.0;
+    const int resident = std::min(matrix_resident(p.MK, p.NP, p.KS, p.ahead, p.fly, p.wide_fly, split), kMaxLds / p.lds_bytes);
+    return resident == 1 ? 1.25 : resident == 2 && p.MK * p.NP == 4 ? 1.1 : 1.0;
 }
 
 }  // namespace
@@ -493,7 +524,10 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
     };
     // (a row in the list is one sum of its terms, as in the tile kernel where that does not deal the channels over parts)
     if (lists && parts > 1) return false;
-    double best_us = -1.0;
+    struct Choice {
+        double rank = -1.0, us = 0.0;
+        MatrixPlan plan{};
+    } choices[2];                  // the wavefronts share the tile out, or the channels
     for (const auto& sh : shapes(split))
         for (int CG = 2; CG <= 2 * most_groups(sh[3]); CG *= 2) {
             MatrixPlan p;
@@ -512,14 +546,15 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
                 for (int q = b; q < std::min((int)trips.size(), b + sh[0]); ++q) mine += trips[q];
                 turns = std::max(turns, mine);
             }
-            const double t = estimate_matrix(p, RS, split, 4700.0 * turns);
-            if ((best_us < 0 || t < best_us) && (!split || rows_as_exact(p, RS * (CG / 2.0 / sh[3])))) {
-                best_us = t;
-                best = p;
-            }
+            const double t = estimate_matrix(p, RS, split, 4700.0 * turns, lone_rounds(p, split));
+            Choice& of_kind = choices[p.KS > 1];
+            if ((of_kind.rank < 0 || t < of_kind.rank) && (!split || rows_as_exact(p, RS * (CG / 2.0 / sh[3]))))
+                of_kind = {t, estimate_matrix(p, RS, split, 4700.0 * turns), p};
         }
-    if (best_us < 0) return false;
-    *us = best_us;
+    const Choice& choice = choices[choices[0].rank < 0 || (choices[1].rank >= 0 && choices[1].us < choices[0].us)];
+    if (choice.rank < 0) return false;
+    best = choice.plan;
+    *us = choice.us;
     return true;
 }
 

@@ -171,3 +171,16 @@ def test_odd_planes_are_staged_in_runs_from_16_channels_on(C):
 def test_first_layers_on_odd_planes_stay_with_the_tile_kernel(N, C, K, H, density):
     """us by the tile kernel and by the matrix kernel with runs: 44 and 63, 62 and 72, 22 and 23."""
     assert _split(N, C, K, 3, H, density) is None
+
+
+def test_runs_of_odd_planes_are_priced_as_they_load():
+    """301 -> 45, 71 x 71, batch 158: 354 us in chunks of 32 channels, which leave a CU two workgroups, 319 in chunks of 16."""
+    plan = _split(158, 301, 45, 3, 71, 0.1)
+    assert plan["runs"] == 1 and plan["CG"] == 2
+
+
+def test_layers_beyond_the_last_cache_hold_all_loads_in_flight():
+    """239 -> 134, 73 x 73, stride 2, fragments of 2 x 4, which have one block of runs in flight and six of single pixels: 397 us by runs
+    at batch 247 (650 MB), 382 pixel by pixel; at batch 60 it is staged in runs."""
+    plans = [_split(N, 239, 134, 3, 73, 0.1, stride=2) for N in (247, 60)]
+    assert [(p["MK"], p["NP"], p["fly"], p["runs"]) for p in plans] == [(2, 4, 6, 0), (2, 4, 6, 1)]
