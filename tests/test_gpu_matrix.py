@@ -115,7 +115,7 @@ def test_every_variant_against_the_oracle(dtype, split, shape):
 
 
 def test_the_variants_are_all_that_is_built():
-    """Two or three steps ahead; single pixels one, two or three blocks at a time (binary16: twice as many; not one in fp32 where
+    """Of four wavefronts (test_kernel_resources.py holds those of eight too against the built library).  Two or three steps ahead; single pixels one, two or three blocks at a time (binary16: twice as many; not one in fp32 where
     wavefronts share the channels) or runs, one block or, where registers allow it, two."""
     built = set()
     for dtype, MK, NP, KS in (("f16", 2, 2, 1), ("f16", 2, 4, 1), ("f16", 2, 2, 4), ("f32", 1, 2, 1), ("f32", 2, 2, 1), ("f32", 2, 2, 4)):

@@ -20,7 +20,9 @@ VARIANTS = [((1, 1, 2, 2, 0, 5), (9, 530, 33, 2, 2, 1, 3, 1, 1)), ((1, 1, 2, 4, 
             ((1, 2, 2, 4, 0, 2), (30, 300, 70, 1, 1, 13, 7, 1, 0)), ((1, 2, 2, None, 1, 2), (70, 200, 70, 2, 2, 8, 13, 1, 1)),
             ((1, 2, 2, None, 2, 1), (150, 200, 40, 1, 2, 5, 9, 1, 0)), ((1, 2, 3, 6, 0, 1), (300, 100, 130, 3, 3, 6, 1, 1, 1)),
             ((1, 2, 3, None, 1, 2), (150, 130, 70, 1, 3, 4, 16, 1, 0)), ((1, 2, 3, None, 2, 2), (70, 130, 130, 3, 3, 5, 16, 1, 0)),
-            ((1, 2, 3, None, 1, 4), (230, 512, 513, 3, 3, 2, 2, 1, 1))]
+            ((1, 2, 3, None, 1, 4), (230, 512, 513, 3, 3, 2, 2, 1, 1)), ((1, 2, 2, 6, 0, 1), (234, 111, 279, 2, 2, 10, 1, 2, 1)),
+            ((1, 2, 3, 4, 0, 3), (176, 364, 108, 3, 1, 15, 1, 1, 0)), ((1, 2, 2, 2, 0, 1), (2, 65, 4770, 1, 2, 1, 32, 1, 0)),
+            ((1, 2, 3, 2, 0, 1), (4, 83, 4837, 1, 3, 1, 14, 1, 0))]
 
 
 @pytest.mark.parametrize("split,shape", VARIANTS, ids=lambda v: "x".join(map(str, v)))

@@ -79,3 +79,11 @@ def test_the_estimate_counts_the_workgroups_that_registers_hold(matrix_kernels):
         if counted != held:
             wrong[dtype, MK, NP, ahead, fly, KS, wide] = counted, held
     assert not wrong, wrong
+
+
+def test_every_matrix_kernel_that_is_built_has_a_layer_in_the_tests(matrix_kernels):
+    from test_gpu_matrix import VARIANTS
+    from test_gpu_matrix_eight import VARIANTS as EIGHT
+    tested = {(d, MK, NP, ahead, runs or fly, KS, int(runs > 0)) for d, (MK, NP, _, KS, ahead, fly, runs), _ in VARIANTS}
+    tested |= {("f16", MK, NP, ahead, runs or fly, 8, int(runs > 0)) for (MK, NP, ahead, fly, runs, _), _ in EIGHT}
+    assert tested == set(matrix_kernels)
