@@ -203,12 +203,12 @@ bool stages_runs(const MatrixPlan& p, int elem_bytes) { return p.quads && p.fly 
 
 // Whether planes that are not whole runs are staged in runs, the last of a plane overlapping the one before it; `blocks`: of single
 // pixels, a wavefront and chunk.  Every split of 1693 layers with such planes timed both ways, those within 30 % of their layer's best:
-// binary16 4573 that stage runs by this rule, 0.87 of the time in the mean, five slower by 3 to 7 % (173 -> 354 channels, 25 x 25: 17.2 ->
-// 13.8 us); fp32 1199, 0.92, two slower.  With four blocks or fewer under 1 x 1 taps half of binary16 splits lose, up to 36 %, and three
-// quarters of fp32 ones, up to 59 %; under larger taps fp32 would gain 5 %, but one in 27 loses, up to 11 %.
+// binary16 4463 that stage runs by this rule, 0.87 of the time in the mean, two slower by 3 % (173 -> 354 channels, 25 x 25: 17.2 ->
+// 13.8 us); fp32 904, 0.89, none slower by 3 %.  With four blocks or fewer under 1 x 1 taps half of binary16 splits lose, up to 37 %, and three
+// quarters of fp32 ones, up to 59 %; under larger taps fp32 would gain 7 %, but one in 23 loses 3 to 11 %.
 // (`late`: binary16 variants of 2 x 4 fragments have one block of runs in flight and six of single pixels.  Where that is all of the single
-// pixels and not all of the runs, and the layer's tensors exceed the 256 MB of the last cache, 15 of 40 splits lose 3 to 9 % by runs and the
-// mean 1 %; below 256 MB 167 gain 4 %.)
+// pixels and not all of the runs, and the layer's tensors exceed the 256 MB of the last cache, 16 of 40 splits lose 3 to 9 % by runs and the
+// mean 1 %; below 256 MB 166 gain 4 %.)
 // (Fewer than 16 channels, a network's first layers: 83 that take the matrix kernel anyway gain 10 %, but by its lower estimate 11 others leave
 // the tile kernel for it, six of which lose 6 to 43 %: 1 -> 217, 207 x 207, batch 8: 44.4 and 63.4 us.)
 bool ragged_runs(int C, int RS, int blocks, bool late, long long bytes, int elem_bytes)
@@ -266,7 +266,7 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     if (CG / 2 > most_groups(KS) || CG / 2 % KS) return false;
     // Eight wavefronts: above 64 channels, and where there are more than 32 outputs.  (A launch of 32 or fewer takes 6 us, bound by its
     // issue, and up to 1 us less so.  With 64 channels or fewer half of the wavefronts and more have none to multiply: 163 layers of 33 to 64
-    // channels that would take it, of 6 to 12 us, gain 3 % in the mean, where those above gain 20, and 17 of them lose 3 to 24 %.)
+    // channels that would take it, of 6 to 12 us, gain 5 % in the mean, where those above gain 20, and 11 of them lose 3 to 24 %.)
     if (KS > 4 && (C <= 64 || nout <= 32)) return false;
     p.CG = CG;
     const int own = CG / 2 / KS * R * S;
@@ -339,7 +339,7 @@ namespace {
 // within 2.4 and 1.4 % of their fastest split in the mean as well.)
 //  * Eight wavefronts that share the channels have constants of their own: 864 splits of 429 layers, 9 % rms beside the 1.06 of their
 //    time that the others' estimate has on those layers.  By it the fastest split of all is missed by 2.4 % in the mean; what was
-//    taken without them by 16 %.  (Of 296 others that take them the mean is 20 % faster than by four, two are slower, by 3 and 16 %.  In more
+//    taken without them by 16 %.  (Of 296 others that take them the mean is 20 % faster than by four, one is slower, by 16 %.  In more
 //    than two rounds of workgroups only rows of 32 channels or fewer take them: seven of 126 such layers, six 3 to 25 % faster, one
 //    8 % slower, as 127 -> 29, 54 x 54, batch 45, is: 31.0 -> 33.4 us.)
 //  * Weights in the list (but for a block's first ones) take 4700 clocks for eight, in a wavefront's own chain: `listed`.
@@ -372,9 +372,9 @@ double estimate_matrix(const MatrixPlan& p, int RS, bool split, double listed, d
 
 // Splits whose wavefronts share the tile out are ranked with a full round of a launch taking so much longer than the estimate says.  Runs of
 // odd planes start off a word, and where few workgroups of a CU hide their loads from one another the estimate, fitted to whole planes, is
-// low: of 1142 binary16 layers with such planes 19 are 3 to 18 % slower with this than by the split that was taken when odd planes were
-// staged pixel by pixel, the mean is 13 % faster; without, 28, by up to 20 % (301 -> 45, 71 x 71, batch 158: 296 us by single pixels, 354
-// and, with this, 319).  In fp32 (150 layers, 8 % faster in the mean, nine 3 to 19 % slower) it picks wrong as often as right, and so it does
+// low: of 1142 binary16 layers with such planes 16 are 3 to 9 % slower with this than by the split that was taken when odd planes were
+// staged pixel by pixel, the mean is 13 % faster; without, 26, by up to 20 % (301 -> 45, 71 x 71, batch 158: 296 us by single pixels, 354
+// and, with this, 319).  In fp32 (150 layers, 12 % faster in the mean, 15 3 to 20 % slower) it picks wrong as often as right, and so it does
 // beside splits whose wavefronts share the channels (102 -> 24, 47 x 47, stride 2, batch 246: 53.7 and 68.0 us).  There and beside the tile
 // kernel, which was compared with the estimate as it is, it does not count.
 double lone_rounds(const MatrixPlan& p, bool split)
