@@ -528,6 +528,7 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
         double rank = -1.0, us = 0.0;
         MatrixPlan plan{};
     } choices[2];                  // the wavefronts share the tile out, or the channels
+    double cheapest = -1.0;        // of all, by the estimate as it is
     for (const auto& sh : shapes(split))
         for (int CG = 2; CG <= 2 * most_groups(sh[3]); CG *= 2) {
             MatrixPlan p;
@@ -546,15 +547,18 @@ bool choose_matrix(const Csr& csr, int C, int R, int S, int elem_bytes, const Ge
                 for (int q = b; q < std::min((int)trips.size(), b + sh[0]); ++q) mine += trips[q];
                 turns = std::max(turns, mine);
             }
-            const double t = estimate_matrix(p, RS, split, 4700.0 * turns, lone_rounds(p, split));
+            const double t = estimate_matrix(p, RS, split, 4700.0 * turns), rank = estimate_matrix(p, RS, split, 4700.0 * turns, lone_rounds(p, split));
             Choice& of_kind = choices[p.KS > 1];
-            if ((of_kind.rank < 0 || t < of_kind.rank) && (!split || rows_as_exact(p, RS * (CG / 2.0 / sh[3]))))
-                of_kind = {t, estimate_matrix(p, RS, split, 4700.0 * turns), p};
+            const bool first = of_kind.rank < 0 || rank < of_kind.rank;
+            if ((first || t < cheapest) && (!split || rows_as_exact(p, RS * (CG / 2.0 / sh[3])))) {
+                if (first) of_kind = {rank, t, p};
+                cheapest = cheapest < 0 ? t : std::min(cheapest, t);
+            }
         }
     const Choice& choice = choices[choices[0].rank < 0 || (choices[1].rank >= 0 && choices[1].us < choices[0].us)];
     if (choice.rank < 0) return false;
     best = choice.plan;
-    *us = choice.us;
+    *us = cheapest;
     return true;
 }
 
