@@ -264,9 +264,10 @@ bool plan_matrix(int K, int C, int R, int S, int elem_bytes, const Geometry& g, 
     p.images = (int)images;
     if (images * C * g.H * g.W * elem_bytes >= (1ll << 31)) return false;
     if (CG / 2 > most_groups(KS) || CG / 2 % KS) return false;
-    // Eight wavefronts: above 64 channels, and where there are more than 32 outputs.  (A launch of 32 or fewer takes 6 us, bound by its
-    // issue, and up to 1 us less so.  With 64 channels or fewer half of the wavefronts and more have none to multiply: 163 layers of 33 to 64
-    // channels that would take it, of 6 to 12 us, gain 5 % in the mean, where those above gain 20, and 11 of them lose 3 to 24 %.)
+    // Eight wavefronts: above 64 channels, and where there are more than 32 outputs.  (With 64 channels or fewer half of the wavefronts and
+    // more have none to multiply: 163 layers of 33 to 64 channels that would take it, of 6 to 12 us, gain 5 % in the mean, where those above
+    // gain 20, and 11 of them lose 3 to 24 %.  Launches of 32 outputs or fewer are bound by their issue where their sums are short: 17 of 276 that
+    // would take it, of 6 to 10 us, lose 3 to 13 %; where they are long they would halve, 941 -> 621, 3 x 3, one output: 31.7 and 13.5 us.)
     if (KS > 4 && (C <= 64 || nout <= 32)) return false;
     p.CG = CG;
     const int own = CG / 2 / KS * R * S;
